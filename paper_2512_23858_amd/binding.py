@@ -1,12 +1,14 @@
-"""ctypes binding of include/ygg.h: argument marshalling only.
+"""Python binding of include/ygg.h: argument marshalling only.
 
 Every function takes torch tensors that already live on the GPU, checks dtypes/contiguity,
 passes raw device pointers and the current HIP stream to the C ABI, and raises on a non-zero
-status.  There is no CPU or PyTorch fallback: if libygg.so is missing, loading fails.
+status.  The launching calls are marshalled by a small native module (csrc/python_calls.cpp), the
+queries through ctypes.  There is no CPU or PyTorch fallback: if libygg.so is missing, loading fails.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from dataclasses import dataclass
 
@@ -100,6 +102,18 @@ def load_library() -> ctypes.CDLL:
     return _lib
 
 
+_native = None
+
+
+def _calls():
+    """The native marshalling module (linked against libygg.so, so that library is looked for first)."""
+    global _native
+    if _native is None:
+        load_library()
+        _native = importlib.import_module(__package__ + "._calls")
+    return _native
+
+
 def status_string(code: int) -> str:
     return load_library().ygg_status_string(code).decode()
 
@@ -129,10 +143,6 @@ def _dev(t, dtype=None, name="tensor"):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-
-
 def _check(rc: int, what: str):
     if rc != 0:
         raise RuntimeError(f"{what} failed: {status_string(rc)} (status {rc})")
@@ -143,64 +153,68 @@ def _kv_torch_dtype(shape: Shape):
     return {F32: torch.float32, BF16: torch.bfloat16, FP8_E4M3: torch.uint8}[shape.kv_dtype]
 
 
-def _ws(workspace):
-    if workspace is None:
-        return None, 0
-    return _dev(workspace, None, "workspace"), workspace.numel() * workspace.element_size()
+def _explain(shape: Shape, *checks):
+    """The native module refused an argument: run the same checks here, which raise what the caller should see.
+    checks: (tensor or None, wanted dtype or None, name)."""
+    shape.c()
+    for t, dtype, name in checks:
+        _dev(t, dtype, name)
+    raise TypeError("an argument is neither a tensor nor None, or a number is out of range")
 
 
 def tree_attention(shape: Shape, q, k_cache, v_cache, seq_lens, k_tree, v_tree, parent_idx, out, lse=None,
                    workspace=None, main_kernel_only=False):
     """ygg_tree_attention: writes `out` (and `lse` if given) on the current stream.
     main_kernel_only: the measurement hook ygg_debug_tree_attention_main (no merge of the key splits)."""
-    dt = _kv_torch_dtype(shape)
-    cs = shape.c()
-    wsp, wsn = _ws(workspace)
-    fn = load_library().ygg_debug_tree_attention_main if main_kernel_only else load_library().ygg_tree_attention
-    rc = fn(
-        ctypes.byref(cs), _dev(q, dt, "q"), _dev(k_cache, dt, "k_cache"), _dev(v_cache, dt, "v_cache"),
-        _dev(seq_lens, torch.int32, "seq_lens"), _dev(k_tree, dt, "k_tree"), _dev(v_tree, dt, "v_tree"),
-        _dev(parent_idx, torch.int32, "parent_idx"), _dev(out, dt, "out"), _dev(lse, torch.float32, "lse"),
-        wsp, wsn, _stream())
-    _check(rc, "ygg_tree_attention")
+    rc = (_native or _calls()).tree_attention(shape, q, k_cache, v_cache, seq_lens, k_tree, v_tree, parent_idx, out, lse,
+                                              workspace, True if main_kernel_only else False)
+    if rc:
+        if rc < 0:
+            dt, i32 = _kv_torch_dtype(shape), torch.int32
+            _explain(shape, (q, dt, "q"), (k_cache, dt, "k_cache"), (v_cache, dt, "v_cache"), (seq_lens, i32, "seq_lens"),
+                     (k_tree, dt, "k_tree"), (v_tree, dt, "v_tree"), (parent_idx, i32, "parent_idx"), (out, dt, "out"),
+                     (lse, torch.float32, "lse"), (workspace, None, "workspace"))
+        _check(rc, "ygg_tree_attention")
     return out
 
 
 def tree_attention_fp8kv(shape: Shape, q, k_cache, v_cache, seq_lens, k_tree, v_tree, k_scale, v_scale, parent_idx,
                          out, lse=None, workspace=None):
     """ygg_tree_attention_fp8kv: K/V as uint8 E4M3 codes with per-kv-head fp32 scales, Q and out bf16."""
-    cs = shape.c()
-    wsp, wsn = _ws(workspace)
-    u8, bf = torch.uint8, torch.bfloat16
-    rc = load_library().ygg_tree_attention_fp8kv(
-        ctypes.byref(cs), _dev(q, bf, "q"), _dev(k_cache, u8, "k_cache"), _dev(v_cache, u8, "v_cache"),
-        _dev(seq_lens, torch.int32, "seq_lens"), _dev(k_tree, u8, "k_tree"), _dev(v_tree, u8, "v_tree"),
-        _dev(k_scale, torch.float32, "k_scale"), _dev(v_scale, torch.float32, "v_scale"),
-        _dev(parent_idx, torch.int32, "parent_idx"), _dev(out, bf, "out"), _dev(lse, torch.float32, "lse"),
-        wsp, wsn, _stream())
-    _check(rc, "ygg_tree_attention_fp8kv")
+    rc = (_native or _calls()).tree_attention_fp8kv(shape, q, k_cache, v_cache, seq_lens, k_tree, v_tree, k_scale, v_scale,
+                                                    parent_idx, out, lse, workspace)
+    if rc:
+        if rc < 0:
+            u8, bf, f32, i32 = torch.uint8, torch.bfloat16, torch.float32, torch.int32
+            _explain(shape, (q, bf, "q"), (k_cache, u8, "k_cache"), (v_cache, u8, "v_cache"), (seq_lens, i32, "seq_lens"),
+                     (k_tree, u8, "k_tree"), (v_tree, u8, "v_tree"), (k_scale, f32, "k_scale"), (v_scale, f32, "v_scale"),
+                     (parent_idx, i32, "parent_idx"), (out, bf, "out"), (lse, f32, "lse"), (workspace, None, "workspace"))
+        _check(rc, "ygg_tree_attention_fp8kv")
     return out
+
+
+def _explain_growth(shape, draft_logits, parent_idx, token_ids, cum_logprob, *scratch):
+    _explain(shape, (draft_logits, torch.float32, "draft_logits"), (parent_idx, torch.int32, "parent_idx"),
+             (token_ids, torch.int32, "token_ids"), (cum_logprob, torch.float32, "cum_logprob"),
+             *((t, None, "workspace") for t in scratch))
 
 
 def equal_growth_expand(shape: Shape, d: int, draft_logits, parent_idx, token_ids, cum_logprob, workspace=None):
     """ygg_equal_growth_expand: fills the depth-d slots of parent_idx/token_ids/cum_logprob."""
-    cs = shape.c()
-    wsp, wsn = _ws(workspace)
-    rc = load_library().ygg_equal_growth_expand(
-        ctypes.byref(cs), d, _dev(draft_logits, torch.float32, "draft_logits"),
-        _dev(parent_idx, torch.int32, "parent_idx"), _dev(token_ids, torch.int32, "token_ids"),
-        _dev(cum_logprob, torch.float32, "cum_logprob"), wsp, wsn, _stream())
-    _check(rc, "ygg_equal_growth_expand")
+    rc = (_native or _calls()).equal_growth_expand(shape, d, draft_logits, parent_idx, token_ids, cum_logprob, workspace)
+    if rc:
+        if rc < 0:
+            _explain_growth(shape, draft_logits, parent_idx, token_ids, cum_logprob, workspace)
+        _check(rc, "ygg_equal_growth_expand")
 
 
 def equal_growth_expand_static(shape: Shape, d: int, draft_logits, parent_idx, token_ids, cum_logprob):
     """ygg_equal_growth_expand_static: the same draft step on the library's built-in scratch (no workspace)."""
-    cs = shape.c()
-    rc = load_library().ygg_equal_growth_expand_static(
-        ctypes.byref(cs), d, _dev(draft_logits, torch.float32, "draft_logits"),
-        _dev(parent_idx, torch.int32, "parent_idx"), _dev(token_ids, torch.int32, "token_ids"),
-        _dev(cum_logprob, torch.float32, "cum_logprob"), _stream())
-    _check(rc, "ygg_equal_growth_expand_static")
+    rc = (_native or _calls()).equal_growth_expand_static(shape, d, draft_logits, parent_idx, token_ids, cum_logprob)
+    if rc:
+        if rc < 0:
+            _explain_growth(shape, draft_logits, parent_idx, token_ids, cum_logprob)
+        _check(rc, "ygg_equal_growth_expand_static")
 
 
 def attach_pool_bytes(shape: Shape) -> int:
@@ -210,28 +224,25 @@ def attach_pool_bytes(shape: Shape) -> int:
 
 def equal_growth_attach(shape: Shape, t: int, draft_logits, parent_idx, token_ids, cum_logprob, pool, workspace=None):
     """ygg_equal_growth_attach: draft step t with free attachment; fills nodes 1+(t-1)W .. tW and updates `pool`."""
-    cs = shape.c()
-    wsp, wsn = _ws(workspace)
-    pp, pn = _ws(pool)
-    rc = load_library().ygg_equal_growth_attach(
-        ctypes.byref(cs), t, _dev(draft_logits, torch.float32, "draft_logits"),
-        _dev(parent_idx, torch.int32, "parent_idx"), _dev(token_ids, torch.int32, "token_ids"),
-        _dev(cum_logprob, torch.float32, "cum_logprob"), pp, pn, wsp, wsn, _stream())
-    _check(rc, "ygg_equal_growth_attach")
+    rc = (_native or _calls()).equal_growth_attach(shape, t, draft_logits, parent_idx, token_ids, cum_logprob, pool, workspace)
+    if rc:
+        if rc < 0:
+            _explain_growth(shape, draft_logits, parent_idx, token_ids, cum_logprob, workspace, pool)
+        _check(rc, "ygg_equal_growth_attach")
 
 
 def prune_for_verification(shape: Shape, w_verify: int, parent_idx, token_ids, cum_logprob, kept_nodes, new_parent,
                            new_token, expected_len=None, best_width=None, t_verifier=None, t_draft: float = 0.0):
     """ygg_prune_for_verification: keeps the w_verify most valuable nodes as a renumbered tree."""
-    cs = shape.c()
-    i32t = torch.int32
-    rc = load_library().ygg_prune_for_verification(
-        ctypes.byref(cs), w_verify, _dev(parent_idx, i32t, "parent_idx"), _dev(token_ids, i32t, "token_ids"),
-        _dev(cum_logprob, torch.float32, "cum_logprob"), _dev(t_verifier, torch.float32, "t_verifier"),
-        ctypes.c_float(t_draft), _dev(kept_nodes, i32t, "kept_nodes"), _dev(new_parent, i32t, "new_parent"),
-        _dev(new_token, i32t, "new_token"), _dev(expected_len, torch.float32, "expected_len"),
-        _dev(best_width, i32t, "best_width"), _stream())
-    _check(rc, "ygg_prune_for_verification")
+    rc = (_native or _calls()).prune_for_verification(shape, w_verify, parent_idx, token_ids, cum_logprob, kept_nodes,
+                                                      new_parent, new_token, expected_len, best_width, t_verifier, t_draft)
+    if rc:
+        if rc < 0:
+            f32, i32 = torch.float32, torch.int32
+            _explain(shape, (parent_idx, i32, "parent_idx"), (token_ids, i32, "token_ids"), (cum_logprob, f32, "cum_logprob"),
+                     (t_verifier, f32, "t_verifier"), (kept_nodes, i32, "kept_nodes"), (new_parent, i32, "new_parent"),
+                     (new_token, i32, "new_token"), (expected_len, f32, "expected_len"), (best_width, i32, "best_width"))
+        _check(rc, "ygg_prune_for_verification")
 
 
 def debug_validate(shape: Shape, flags, parent_idx=None, seq_lens=None, token_ids=None, logits=None):
@@ -241,7 +252,7 @@ def debug_validate(shape: Shape, flags, parent_idx=None, seq_lens=None, token_id
     rc = load_library().ygg_debug_validate(
         ctypes.byref(cs), _dev(parent_idx, torch.int32, "parent_idx"), _dev(seq_lens, torch.int32, "seq_lens"),
         _dev(token_ids, torch.int32, "token_ids"), _dev(logits, torch.float32, "logits"), rows,
-        _dev(flags, torch.int32, "flags"), _stream())
+        _dev(flags, torch.int32, "flags"), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     _check(rc, "ygg_debug_validate")
 
 
@@ -249,17 +260,18 @@ def accept_and_compact(shape: Shape, n_layers: int, parent_idx, token_ids, k_tre
                        seq_lens, accept_len, accept_path, bonus_token, target_logits=None, target_tokens=None,
                        workspace=None):
     """ygg_accept_and_compact: updates the caches and seq_lens in place, fills the three outputs."""
-    dt = _kv_torch_dtype(shape)
-    cs = shape.c()
-    wsp, wsn = _ws(workspace)
-    rc = load_library().ygg_accept_and_compact(
-        ctypes.byref(cs), n_layers, _dev(target_logits, torch.float32, "target_logits"),
-        _dev(target_tokens, torch.int32, "target_tokens"), _dev(parent_idx, torch.int32, "parent_idx"),
-        _dev(token_ids, torch.int32, "token_ids"), _dev(k_tree, dt, "k_tree"), _dev(v_tree, dt, "v_tree"),
-        _dev(k_cache, dt, "k_cache"), _dev(v_cache, dt, "v_cache"), _dev(seq_lens, torch.int32, "seq_lens"),
-        _dev(accept_len, torch.int32, "accept_len"), _dev(accept_path, torch.int32, "accept_path"),
-        _dev(bonus_token, torch.int32, "bonus_token"), wsp, wsn, _stream())
-    _check(rc, "ygg_accept_and_compact")
+    rc = (_native or _calls()).accept_and_compact(shape, n_layers, parent_idx, token_ids, k_tree, v_tree, k_cache, v_cache,
+                                                  seq_lens, accept_len, accept_path, bonus_token, target_logits, target_tokens,
+                                                  workspace)
+    if rc:
+        if rc < 0:
+            dt, i32 = _kv_torch_dtype(shape), torch.int32
+            _explain(shape, (target_logits, torch.float32, "target_logits"), (target_tokens, i32, "target_tokens"),
+                     (parent_idx, i32, "parent_idx"), (token_ids, i32, "token_ids"), (k_tree, dt, "k_tree"),
+                     (v_tree, dt, "v_tree"), (k_cache, dt, "k_cache"), (v_cache, dt, "v_cache"), (seq_lens, i32, "seq_lens"),
+                     (accept_len, i32, "accept_len"), (accept_path, i32, "accept_path"), (bonus_token, i32, "bonus_token"),
+                     (workspace, None, "workspace"))
+        _check(rc, "ygg_accept_and_compact")
 
 
 def attention_plan(shape: Shape) -> dict:

@@ -3,43 +3,323 @@
 // Width Selection").
 //
 // Two kernels:
-//   expand_scan   grid (frontier row, vocab chunk of 4096): streams the fp32 logits once,
-//                 coalesced, and leaves per chunk {max, sum exp(x - max) in fp64, the chunk's W
-//                 largest logits, best first}.  Inside one row the candidate order is the order
-//                 of the raw logits, so the chunk lists are exact whatever the row's normaliser
-//                 turns out to be.
-//   expand_merge  one workgroup per sequence: per-row log-sum-exp from the chunk statistics, the
-//                 fp64 score cum[p] + (x - lse_p) of every list head, the W lists with the best
-//                 heads (no entry of any other list can be among the W best), and finally the W
-//                 best of those lists' W*W entries; ties go to the lower flat index p*V + v.
+//   scan     one workgroup per chunk of a logits row: streams the fp32 logits once and leaves the chunk's list: its sum of
+//            exponentials in fp64 and its W largest logits, best first.  Inside one row the candidate order is the order
+//            of the raw logits, so the lists are exact whatever the row's normaliser turns out to be.
+//   finish   one workgroup per sequence, one list per thread: per-row log-sum-exp, fp64 scores cum[p] + (x - lse_p), and
+//            the W best of all lists; ties go to the lower flat index p*V + v.  With free attachment the rows' W best
+//            join the carried pool instead (below).
 //
-// Selection of "the W best of a workgroup's candidates" (used three times) never sorts and has no
-// serial per-element rounds on its main path: each wavefront bisects, with ballots, for the W-th
-// largest of its lanes' maxima (a lower bound of its W-th best candidate), pools the few candidates
-// at or above that threshold in LDS, ranks them against each other, and the four sorted wavefront
-// lists are merged by rank (binary search).  Candidates are ordered by an order-preserving integer
-// key of the value, then by the lower index.
+// Both are chains of dependent steps on little data: what counts is how many instructions, branches (a taken one costs
+// about 50 cycles), barriers and memory trips follow each other.  Hence
+//   - few candidates per thread (four at the small sizes), so that a chain is short and all compute units have work;
+//   - "the W best" is never sorted out of all candidates: a threshold that at least W and few more candidates reach comes
+//     from lane maxima, the candidates above it are pooled in LDS and ranked against each other;
+//   - the sum of exponentials needs no maximum first (fp64 holds exp of any logit up to 500; a reference other than 0 is
+//     kept only beyond that), and the row sums are plain sums of the chunks';
+//   - a list's four best entries sit beside its sum, in one 48-byte record: they decide almost every step, so that the
+//     finish kernel makes one trip to memory (the rest of a list is read only if all four reach the threshold).
+// Measured per step, back to back (16 logits per thread, four list merges by binary search and a bitonic pool sort in LDS
+// -> this): 8 rows of 32000 logits 12.8 -> 7.3 us, 128 rows of 32000 (batch 16) 18.4 -> 12.7, free attachment with 16 rows
+// of 128256 24.6 -> 14.8.  Left at the small size: 1.5 us of launch per kernel, memory latency once per kernel, and about
+// 1.5 us of dependent steps in each; at the large one the fp64 exponentials (23 instructions per logit).
 #include "ygg_internal.h"
 #include "ygg_device.h"
+
+#include <algorithm>
+#include <type_traits>
 
 namespace ygg {
 namespace {
 
-constexpr int kScanThreads = 256;
-constexpr int kScanElems = 16;  // logits per thread; chunk = 4096, 1024 consecutive logits per wavefront
 constexpr uint32_t kNone = 0xffffffffu;
+constexpr int kFront = 4;        // list entries kept beside the sum
+constexpr int kMaxLists = 1024;  // lists of one sequence, padded to a power of two per row: one per thread of the finish kernel
+constexpr float kPlainRange = 500.f;  // logits whose exponential is summed as it is
 
-struct ChunkStat {
-    double sumexp;
-    float maxv;
-    int32_t count;
-};
 struct Cand {
     float val;
     int32_t idx;
 };
+struct __align__(16) ListHead {
+    double sumexp;          // sum exp(x - ref) over the chunk
+    float ref;              // 0, or the chunk's maximum where that lies outside +-kPlainRange
+    int32_t count;          // entries of the list: min(W, logits in the chunk)
+    Cand front[kFront];     // the best ones; entries 4 .. W-1 are in the `rest` array
+};
+static_assert(sizeof(ListHead) == 48, "three 16-byte loads");
 
-// ---- the W best of a workgroup's candidates ---------------------------------------------------------
+// Largest found t with at least `want` (and not many more) of the wavefront's NK*64 keys >= t; key 0 = no candidate.
+// Returns 1, which every candidate reaches, if there are fewer than `want`.  Bisection in rounds of four steps: a step is
+// a chain of about 60 cycles, a branch as much again.
+template <int NK>
+__device__ __forceinline__ uint32_t wave_threshold(const uint32_t (&g)[NK], int want) {
+    auto count = [&](uint32_t t) {
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < NK; ++i) n += (int)__popcll(__ballot(g[i] >= t));
+        return n;
+    };
+    uint32_t top = g[0];
+#pragma unroll
+    for (int i = 1; i < NK; ++i) top = max(top, g[i]);
+    uint32_t hi = wave_max_u32(top);
+    uint32_t lo = max(wave_min_u32(top), 1u);   // if no lane is empty, 64 keys reach the smallest lane maximum
+    int n = count(lo);
+    if (n < want) return 1u;
+    const int enough = want + (want >> 3);
+    while (lo < hi && n > enough) {              // n = count(lo) >= want; no key exceeds hi
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t mid = lo + ((hi - lo + 1) >> 1);
+            const int m = count(mid);
+            const bool ok = m >= want;
+            lo = ok ? mid : lo;
+            n = ok ? m : n;
+            hi = ok ? hi : mid - 1;
+        }
+        hi = max(hi, lo);
+    }
+    return lo;
+}
+
+// Threshold over a workgroup's keys, one per thread, published in keys[64 * wave + lane] (barrier before): every wavefront
+// works it out for itself from the 64 lane-wise maxima.  LOOSE and W <= 8: the lanes form eight groups, and W keys reach
+// the smallest group maximum -- about 22 candidates are pooled instead of 9, which costs less time than a bisection (but
+// more instructions: not where many workgroups share a compute unit).  W > 32: four maxima per lane, or too many candidates
+// would lie above the threshold.
+template <bool LOOSE>
+__device__ __forceinline__ uint32_t group_threshold(const uint32_t* keys, int nwaves, int lane, int want) {
+    uint32_t g[4] = {0, 0, 0, 0};
+    for (int w = 0; w < nwaves; w += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (w + u < nwaves) g[u] = max(g[u], keys[64 * (w + u) + lane]);
+    if (want > 32) return wave_threshold<4>(g, want);
+    const uint32_t one[1] = {max(max(g[0], g[1]), max(g[2], g[3]))};
+    if (LOOSE && want <= 8) {
+        uint32_t v = max(one[0], row_xor<8>(one[0]));
+        auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = max(p[0], p[1]);
+        p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = max(p[0], p[1]);
+        v = min(v, row_xor<1>(v));
+        v = min(v, row_xor<2>(v));
+        v = min(v, row_xor<7>(v));
+        const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+        if (t) return t;
+    }
+    return wave_threshold<1>(one, want);
+}
+
+// ---- scan ---------------------------------------------------------------------------------------
+constexpr int kScanThreads = 256;
+constexpr int kScanPool = 512;   // pooled candidates per chunk
+
+struct ScanArgs {
+    const float* logits;
+    ListHead* heads;     // [rows][nchunk]
+    Cand* rest;          // [rows][nchunk][W - 4]
+    int32_t V, W, chunk, nchunk;
+};
+
+__device__ __forceinline__ uint64_t order_of(uint32_t key, uint32_t idx) {   // larger = better: value, then lower index
+    return ((uint64_t)key << 32) | (uint32_t)~idx;
+}
+
+// Exact but slow: used when more candidates tie than the pool holds.  Each round finds the best candidate after the last.
+__device__ __noinline__ void scan_ties(const float* x, int c0, int c1, int want, int lane, ListHead* head, Cand* rest) {
+    uint64_t last = ~0ull;
+    for (int r = 0; r < want; ++r) {
+        uint64_t best = 0;
+        for (int i = c0 + lane; i < c1; i += 64) {
+            const uint64_t o = order_of(key_of(x[i]), (uint32_t)i);
+            if (o < last && o > best) best = o;
+        }
+        const uint32_t bh = wave_max_u32((uint32_t)(best >> 32));
+        const uint32_t bl = wave_max_u32((uint32_t)(best >> 32) == bh ? (uint32_t)best : 0u);
+        last = ((uint64_t)bh << 32) | bl;
+        if (lane == 0) {
+            const Cand cd = {float_of(bh), (int32_t)~bl};
+            if (r < kFront) head->front[r] = cd; else rest[r - kFront] = cd;
+        }
+    }
+}
+
+// Appends the wavefront's selected candidates to a pool: the positions follow from ballots and one count per wavefront.
+// Few candidates are selected, so what(i), the candidate's pool entry, is formed only where some lane has it.
+template <int N, typename T, typename What>
+__device__ __forceinline__ void pool_put(const bool (&sel)[N], What what, T* pool, int cap, int* counter, int lane) {
+    uint64_t m[N];
+    int total = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        m[i] = __ballot(sel[i]);
+        total += (int)__popcll(m[i]);
+    }
+    if (total == 0) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(counter, total);
+    base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (__builtin_expect(m[i] != 0, 0)) {
+            const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[i], 0));
+            pool[sel[i] && pos < cap ? pos : cap + lane] = what(i);   // (a slot of the lane's own behind the pool: no branch)
+            base += (int)__popcll(m[i]);
+        }
+    }
+}
+
+// Number of pool entries better than the lane's own, for pools of up to 64 entries followed by zeros.  Up to 32 entries the
+// two halves of the wavefront share the comparisons (lane j and lane j + 32 get the rank of entry j).
+__device__ __forceinline__ int rank_in_wave(const uint64_t* pool, int n, int lane, uint64_t& mine) {
+    const bool halves = n <= 32;
+    mine = pool[halves ? lane & 31 : lane];
+    uint32_t r = 0;
+    const int step = halves ? 8 : 4;
+    const uint64_t* q = pool + (halves ? (lane >> 5) * 4 : 0);
+    for (int i = 0; i < n; i += step) {
+        uint64_t x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = q[i + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r += x[u] > mine;
+    }
+    if (halves) {
+        const auto p = __builtin_amdgcn_permlane32_swap(r, r, false, false);
+        r = p[0] + p[1];
+    }
+    return (int)r;
+}
+
+// E logits per thread and pass; a chunk is one pass (256 E logits) or, with ONE = false, several.  VEC: 16-byte loads (row
+// starts and V are multiples of four logits).
+template <int E, bool VEC, bool ONE>
+__global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
+    constexpr int PASS = kScanThreads * E;
+    __shared__ __align__(16) uint64_t pool[kScanPool + 64];
+    __shared__ uint32_t keys[kScanThreads];
+    __shared__ double sums[4];
+    __shared__ int pooled;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = blockIdx.y;
+    const int64_t row = blockIdx.x, list = row * a.nchunk + c;
+    const int c0 = c * a.chunk, c1 = min(a.V, c0 + a.chunk);
+    const float* __restrict__ x = a.logits + row * a.V;
+    const int want = min(a.W, c1 - c0);
+    uint32_t best = 0;      // key of the thread's largest logit
+    float ref = 0.f;
+    double sum = 0.0;       // this thread's share of sum exp(x - ref)
+    int base = c0;
+    do {
+        float v[E];
+        const int w0 = base + wave * (64 * E);
+        const bool full = base + PASS <= c1;
+        auto index = [&](int i) { return VEC ? w0 + 256 * (i >> 2) + 4 * lane + (i & 3) : w0 + 64 * i + lane; };
+        auto load = [&](auto whole) {   // places past the end hold NaN: it loses every comparison and adds nothing to the sum
+            constexpr float none = __builtin_nanf("");
+#pragma unroll
+            for (int k = 0; k < E / 4; ++k) {
+                if constexpr (VEC) {
+                    float4 q = make_float4(none, none, none, none);
+                    if (whole || index(4 * k) < c1) q = *reinterpret_cast<const float4*>(x + index(4 * k));
+                    v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[4 * k + e] = whole || index(4 * k + e) < c1 ? x[index(4 * k + e)] : none;
+                }
+            }
+        };
+        if (full) load(std::true_type{}); else load(std::false_type{});
+        if (base == c0) {   // while the loads are out
+#pragma unroll
+            for (int i = tid; i < kScanPool; i += kScanThreads) pool[i] = 0;
+            if (tid == 0) pooled = 0;
+        }
+        float vmax = v[0];
+#pragma unroll
+        for (int i = 1; i < E; ++i) vmax = fmaxf(vmax, v[i]);
+        best = index(0) < c1 ? max(best, key_of(vmax)) : best;
+        keys[tid] = best;
+        __syncthreads();
+        const uint32_t t = group_threshold<E == 4>(keys, 4, lane, want);
+        const float tf = t <= 1u ? -INFINITY : float_of(t);
+        bool sel[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) sel[i] = v[i] >= tf;
+        pool_put(sel, [&](int i) { return order_of(key_of(v[i]), (uint32_t)index(i)); }, pool, kScanPool, &pooled, lane);
+        // sum of exponentials
+        const uint32_t top = max(max(keys[lane], keys[64 + lane]), max(keys[128 + lane], keys[192 + lane]));
+        const float cmax = float_of(wave_max_u32(top));   // of the chunk so far
+        const float r = fabsf(cmax) <= kPlainRange || cmax == -INFINITY ? 0.f : cmax;
+        if (r != ref) {   // a first pass has nothing to rescale; later the reference only moves so that the sum shrinks
+            sum = sum == 0.0 ? 0.0 : sum * exp_nonpos((double)ref - (double)r);
+            ref = r;
+        }
+        constexpr int NE = E < 8 ? E : 8;   // independent series in step: a dependent fp64 operation takes 20 cycles
+#pragma unroll
+        for (int i0 = 0; i0 < E; i0 += NE) {
+            double t[NE], e[NE];
+#pragma unroll
+            for (int i = 0; i < NE; ++i) t[i] = (double)v[i0 + i] - (double)ref;
+            exp_below_n(t, e);
+#pragma unroll
+            for (int i = 0; i < NE; i += 4) sum += (e[i] + e[i + 1]) + (e[i + 2] + e[i + 3]);
+        }
+        base += PASS;
+        if (ONE || base >= c1) break;
+        __syncthreads();   // the next pass writes keys again
+    } while (true);
+    sum = group_sum(sum, 64);
+    if (lane == 0) sums[wave] = sum;
+    __syncthreads();
+    ListHead* head = a.heads + list;
+    Cand* rest = a.rest + list * max(a.W - kFront, 0);
+    if (tid == 0) {
+        head->sumexp = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+        head->ref = ref;
+        head->count = want;
+    }
+    auto store = [&](int rank, uint64_t o) {
+        const Cand cd = {float_of((uint32_t)(o >> 32)), (int32_t)~(uint32_t)o};
+        Cand* dst = rank < kFront ? head->front + rank : rest + (rank - kFront);
+        if (rank < want) *dst = cd;
+    };
+    const int n = __builtin_amdgcn_readfirstlane(pooled);
+    if (n <= 64) {
+        if (wave > 0) return;
+        uint64_t mine;
+        const int rank = rank_in_wave(pool, n, lane, mine);
+        if (lane < n) store(rank, mine);
+    } else if (n <= kScanPool) {
+        for (int j = tid; j < n; j += kScanThreads) {
+            const uint64_t mine = pool[j];
+            int rank = 0;
+            for (int i = 0; i < n; i += 8) {   // (zeros follow the pooled entries)
+                uint64_t x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = pool[i + u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) rank += x[u] > mine;
+            }
+            store(rank, mine);
+        }
+    } else if (wave == 0) {
+        scan_ties(x, c0, c1, want, lane, head, rest);
+    }
+}
+
+// Log-sum-exp of a row from its lists, which sit in an aligned group of `width` lanes (fixed order of summation).
+__device__ __forceinline__ double row_lse(const ListHead& h, int width) {
+    if (!__any(h.ref != 0.f)) return log(group_sum(h.sumexp, width));
+    const float ref = h.sumexp > 0.0 ? h.ref : -INFINITY;
+    const float mx = group_reduce(ref, width, [](float x, float y) { return fmaxf(x, y); });
+    const double s = ref > -INFINITY ? h.sumexp * exp_nonpos((double)ref - (double)mx) : 0.0;
+    return (double)mx + log(group_sum(s, width));
+}
+
+// ---- finish, frontier rule ------------------------------------------------------------------------
 // A candidate: larger key first, then lower tie; key == 0 means "no candidate" (real keys are > 0).
 struct __align__(16) Entry {
     uint64_t key;
@@ -50,348 +330,190 @@ __device__ __forceinline__ bool beats(const Entry& a, const Entry& b) {
     return a.key > b.key || (a.key == b.key && a.tie < b.tie);
 }
 
-constexpr int kPoolCap = 256;  // pooled candidates per wavefront on the fast path
-
-struct TopWShared {
-    Entry pool[4][kPoolCap];
-    Entry list[4][kMaxWidth];  // per-wavefront result, best first
-    int count[4];
+struct FinishArgs {
+    const ListHead* heads;
+    const Cand* rest;
+    int32_t* parent_idx;
+    int32_t* token_ids;
+    float* cum_logprob;
+    unsigned char* pool;   // free attachment only: per sequence {int32 count, pad to 16 B, pool_cap offers}
+    int32_t pool_cap;
+    int32_t D, W, V, N, d, F, nchunk, shift;   // 1 << shift: lists of a row padded to a power of two
 };
 
-// Wave-wide best candidate; lanes without one pass key 0.
-__device__ __forceinline__ Entry wave_best(const Entry& e) {
-    const uint32_t hi = (uint32_t)(e.key >> 32);
-    const uint32_t mh = wave_max_u32(hi);
-    const bool in1 = e.key != 0 && hi == mh;
-    const uint32_t ml = wave_max_u32(in1 ? (uint32_t)e.key : 0u);
-    const bool in2 = in1 && (uint32_t)e.key == ml;
-    const uint32_t mt = wave_min_u32(in2 ? e.tie : kNone);
-    const bool win = in2 && e.tie == mt;
-    const int src = __ffsll((unsigned long long)__ballot(win)) - 1;
-    Entry r;
-    r.key = ((uint64_t)mh << 32) | ml;
-    r.tie = mt;
-    r.tag = src >= 0 ? (uint32_t)__builtin_amdgcn_readlane((int)e.tag, src) : 0u;
-    return r;
-}
+constexpr int kMergePool = 1024;   // pooled candidates of one sequence
 
-// Every lane holds N candidate slots, read through get(k) (key 0 = empty).  Leaves the wavefront's best
-// min(W, #candidates) in sh.list[wave], best first, and their number in sh.count[wave].
-template <int N, typename Get>
-__device__ __forceinline__ void wave_top_w(Get get, int W, int wave, int lane, TopWShared& sh) {
-    uint32_t cmax = 0;   // largest coarse key (top 32 bits) of this lane
-    int tot = 0;         // candidates of the wavefront
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const Entry e = get(k);
-        cmax = max(cmax, (uint32_t)(e.key >> 32));
-        tot += (int)__popcll(__ballot(e.key != 0));
-    }
-    const int want = min(W, tot);
-    const int wn = min(W, (int)__popcll(__ballot(cmax != 0)));
-    // threshold: at most the wn-th largest lane maximum, so at least wn candidates lie at or above it.  Its low
-    // twelve bits stay zero: a slightly lower threshold only pools a few more candidates.
-    uint32_t t = 0;
-    if (wn > 0) {
-        for (int bit = 31; bit >= 12; --bit) {
-            const uint32_t c = t | (1u << bit);
-            if ((int)__popcll(__ballot(cmax >= c)) >= wn) t = c;
-        }
-    }
-    // pool the candidates at or above the threshold
-    int base = 0;
-    const unsigned long long below = __lanemask_lt();
-    bool fits = true;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const Entry e = get(k);
-        const bool sel = wn > 0 && e.key != 0 && (uint32_t)(e.key >> 32) >= t;
-        const unsigned long long m = __ballot(sel);
-        const int pos = base + (int)__popcll(m & below);
-        if (sel && pos < kPoolCap) sh.pool[wave][pos] = e;
-        base += (int)__popcll(m);
-    }
-    fits = base <= kPoolCap && base >= want;
-    // the ranking below reads pool entries written by other lanes of this wavefront
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (fits) {
-        // rank the pooled candidates against each other; the best `want` go out in order
-        const int C = base;
-        for (int j0 = 0; j0 < C; j0 += 64) {
-            const int j = j0 + lane;
-            const Entry mine = sh.pool[wave][min(j, C - 1)];
-            int rank = 0;
-            const int C8 = C & ~7;
-            for (int i = 0; i < C8; i += 8) {  // eight independent LDS reads in flight
-#pragma unroll
-                for (int u = 0; u < 8; ++u) rank += beats(sh.pool[wave][i + u], mine);
-            }
-            for (int i = C8; i < C; ++i) rank += beats(sh.pool[wave][i], mine);
-            if (j < C && rank < want) sh.list[wave][rank] = mine;
-        }
-    } else {
-        // Rare (more ties than the pool holds, or too few lanes hold candidates): one candidate per round.
-        uint64_t gone = 0;  // bit k: slot k already emitted
-        for (int r = 0; r < want; ++r) {
-            Entry best = {0, kNone, 0};
-            int bk = -1;
-#pragma unroll
-            for (int k = 0; k < N; ++k) {
-                const Entry e = get(k);
-                if (e.key != 0 && !((gone >> k) & 1ull) && (bk < 0 || beats(e, best))) { best = e; bk = k; }
-            }
-            const Entry w = wave_best(best);
-            if (bk >= 0 && best.key == w.key && best.tie == w.tie) gone |= 1ull << bk;
-            if (lane == 0) sh.list[wave][r] = w;
-        }
-    }
-    if (lane == 0) sh.count[wave] = want;
-}
-
-// After wave_top_w in all four wavefronts and a barrier: rank of entry `lane` of this wavefront's list among
-// the four lists (-1 if this lane holds none); ranks below W are the workgroup's best W, in order.
-__device__ __forceinline__ int merged_rank(const TopWShared& sh, int wave, int lane, Entry& mine) {
-    if (lane >= sh.count[wave]) return -1;
-    mine = sh.list[wave][lane];
-    // first position of each other list whose entry does not beat `mine`: three binary searches in step, so the
-    // three LDS reads of a round are in flight together
-    int lo[3], hi[3], cnt[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int w = i + (i >= wave);
-        lo[i] = 0;
-        hi[i] = cnt[i] = sh.count[w];
-    }
-    for (int span = max(cnt[0], max(cnt[1], cnt[2])); span > 0; span >>= 1) {  // enough rounds for the longest list
-        Entry e[3];
-        int mid[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int w = i + (i >= wave);
-            mid[i] = (lo[i] + hi[i]) >> 1;
-            e[i] = sh.list[w][min(mid[i], kMaxWidth - 1)];
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const bool open = lo[i] < hi[i];
-            const bool b = beats(e[i], mine);
-            lo[i] = open && b ? mid[i] + 1 : lo[i];
-            hi[i] = open && !b ? mid[i] : hi[i];
-        }
-    }
-    return lane + lo[0] + lo[1] + lo[2];
-}
-
-// ---- scan ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ExpandArgs a) {
-    __shared__ double red_d[4];
-    __shared__ float red_f[4];
-    __shared__ TopWShared sh;
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t row = blockIdx.x;  // b*F + p
-    const int c = blockIdx.y;
-    const int c0 = c * a.chunk;
-    const int c1 = min(a.V, c0 + a.chunk);
-    const float* x = a.logits + row * a.V;
-    const int w0 = c0 + wave * (kScanElems * 64);  // this wavefront's 1024 consecutive logits
-
-    float xv[kScanElems];
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < kScanElems; ++k) {
-        const int idx = w0 + k * 64 + lane;
-        xv[k] = idx < c1 ? x[idx] : -INFINITY;
-        tmax = fmaxf(tmax, xv[k]);
-    }
-    // chunk maximum and sum of exponentials (fp64)
-    const float wmax = float_of(wave_max_u32(key_of(tmax)));
-    if (lane == 0) red_f[wave] = wmax;
-    __syncthreads();
-    const float cmax = fmaxf(fmaxf(red_f[0], red_f[1]), fmaxf(red_f[2], red_f[3]));
-    double sum = 0.0;
-    if (cmax > -INFINITY) {
-        // logits past the end of the chunk are -inf and add exactly 0; no branch, so the sixteen series interleave
-#pragma unroll
-        for (int k = 0; k < kScanElems; ++k) sum += exp_nonpos((double)xv[k] - (double)cmax);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if (lane == 0) red_d[wave] = sum;
-
-    // the chunk's W largest logits: value key in the upper half of the key, vocabulary index as the tie-break
-    auto get = [&](int k) {
-        const int idx = w0 + k * 64 + lane;
-        Entry e;
-        e.key = idx < c1 ? (uint64_t)key_of(xv[k]) << 32 : 0ull;
-        e.tie = (uint32_t)idx;
-        e.tag = 0;
-        return e;
+// Best candidate of the workgroup per round, every thread offering the entry at the cursor of its list (count 0: none);
+// used when more candidates tie than the pool holds.
+__device__ __noinline__ void merge_serially(int32_t* parent, int32_t* token, float* cum_out, int W, int V, int base_prev, int nwaves,
+                                            const ListHead* h, const Cand* rest, int count, int p, double cum, double lse, Entry* best_s) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto entry = [&](int i) {
+        if (i >= count) return Entry{0, kNone, 0};
+        const Cand cd = i < kFront ? h->front[i] : rest[i - kFront];
+        return Entry{key_of(cum + ((double)cd.val - lse)), (uint32_t)(p * V + cd.idx), 0};
     };
-    wave_top_w<kScanElems>(get, a.W, wave, lane, sh);
-    __syncthreads();
-    if (tid == 0) {
-        ChunkStat st;
-        st.sumexp = (red_d[0] + red_d[1]) + (red_d[2] + red_d[3]);
-        st.maxv = cmax;
-        st.count = min(a.W, c1 - c0);
-        static_cast<ChunkStat*>(a.stats)[row * a.nchunk + c] = st;
-    }
-    Entry mine;
-    const int rank = merged_rank(sh, wave, lane, mine);
-    if (rank >= 0 && rank < a.W) {
-        Cand cd;
-        cd.val = float_of((uint32_t)(mine.key >> 32));
-        cd.idx = (int32_t)mine.tie;
-        static_cast<Cand*>(a.cands)[(row * a.nchunk + c) * a.W + rank] = cd;
+    int cur = 0;
+    Entry mine = entry(0);
+    for (int r = 0; r < W; ++r) {
+        const uint32_t kh = wave_max_u32((uint32_t)(mine.key >> 32));
+        const uint32_t kl = wave_max_u32((uint32_t)(mine.key >> 32) == kh ? (uint32_t)mine.key : 0u);
+        const uint64_t k = ((uint64_t)kh << 32) | kl;
+        const uint32_t t = wave_min_u32(mine.key == k ? mine.tie : kNone);
+        if (lane == 0) best_s[wave] = Entry{k, t, 0};
+        __syncthreads();
+        Entry w = best_s[0];
+        for (int i = 1; i < nwaves; ++i) if (beats(best_s[i], w)) w = best_s[i];
+        __syncthreads();
+        if (w.key == 0) return;   // (cannot happen: there are at least W candidates)
+        if (tid == 0) {
+            parent[r] = base_prev + (int)(w.tie / (uint32_t)V);
+            token[r] = (int)(w.tie % (uint32_t)V);
+            cum_out[r] = (float)double_of(w.key);
+        }
+        if (mine.key == w.key && mine.tie == w.tie) mine = entry(++cur);
     }
 }
 
-// ---- merge --------------------------------------------------------------------------------------
-constexpr size_t merge_scratch_bytes(int lpt) { return (size_t)256 * lpt * 12; }
-
-template <int LPT, int EPT>  // chunk lists per thread; entries of the selected lists per thread (W*W <= 256*EPT)
-__global__ __launch_bounds__(256) void expand_merge_kernel(ExpandArgs a) {
-    constexpr int KMAX = 256 * LPT;
-    // scratch for the chunk statistics
-    extern __shared__ __align__(16) unsigned char raw[];  // merge_scratch_bytes(LPT)
-    double* ssum = reinterpret_cast<double*>(raw);               // [KMAX]
-    float* smax = reinterpret_cast<float*>(raw + KMAX * 8);      // [KMAX]
-    __shared__ TopWShared sh;
-    __shared__ double lse_s[kMaxWidth];
-    __shared__ double cum_s[kMaxWidth];
-    __shared__ uint32_t sel[kMaxWidth];       // the lists with the W best heads
-
+// Bounded by latency: one trip to memory, two row reductions, a bisection, two barriers.
+__global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, int nwaves) {
+    __shared__ uint32_t coarse[kMaxLists];   // upper halves of the keys of the list heads
+    __shared__ Entry pool[kMergePool + 64];
+    __shared__ Entry best_s[kMaxLists / 64];
+    __shared__ int pooled;
+    __shared__ uint32_t thr;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.x;
     const int base_prev = a.d == 1 ? 0 : 1 + (a.d - 2) * a.W;
-    const int base_new = 1 + (a.d - 1) * a.W;
-    const int K = a.F * a.nchunk;  // number of chunk lists, list q = p*nchunk + c
-    const ChunkStat* stats = static_cast<const ChunkStat*>(a.stats) + (int64_t)b * K;
-    const Cand* cands = static_cast<const Cand*>(a.cands) + (int64_t)b * K * a.W;
+    const int p = tid >> a.shift, c = tid & ((1 << a.shift) - 1);
+    const bool active = p < a.F && c < a.nchunk;
+    const int64_t list = ((int64_t)b * a.F + (active ? p : 0)) * a.nchunk + (active ? c : 0);
+    ListHead h = a.heads[list];
+    const double cum = (double)a.cum_logprob[(int64_t)b * a.N + base_prev + (active ? p : 0)];
+    if (!active) {
+        h.count = 0;
+        h.ref = 0.f;
+        h.sumexp = 0.0;
+    }
+    const Cand* rest = a.rest + list * max(a.W - kFront, 0);
+    for (int i = tid; i < kMergePool; i += 64 * nwaves) pool[i] = Entry{0, kNone, 0};   // while the loads are out
+    if (tid == 0) pooled = 0;
 
-    // entries of chunk list q = p*nchunk + c: min(W, size of chunk c), known without touching memory
-    auto list_len = [&](int q) {
-        const int c = q % a.nchunk;
-        return min(a.W, min(a.V, (c + 1) * a.chunk) - c * a.chunk);
+    const double lse = row_lse(h, 1 << a.shift);
+    auto entry_of = [&](Cand cd) {
+        return Entry{key_of(cum + ((double)cd.val - lse)), (uint32_t)(p * a.V + cd.idx), 0};   // tie: flat index p*V + v
     };
-    // 1. chunk statistics -> per-row log-sum-exp (fixed summation order: deterministic)
-    int cnt[LPT];
-    Cand head[LPT];
+    Entry e[kFront];
 #pragma unroll
-    for (int u = 0; u < LPT; ++u) {
-        const int q = tid + u * 256;
-        cnt[u] = 0;
-        head[u].val = -INFINITY;
-        head[u].idx = 0;
-        if (q < K) {
-            // a chunk is never empty, so its list has a head: both loads go out together
-            const ChunkStat st = stats[q];
-            head[u] = cands[(int64_t)q * a.W];
-            smax[q] = st.maxv;
-            ssum[q] = st.sumexp;
-            cnt[u] = list_len(q);
-        }
-    }
-    if (tid < a.F) cum_s[tid] = (double)a.cum_logprob[(int64_t)b * a.N + base_prev + tid];
-    __syncthreads();
-    // a row's chunks go to a group of g lanes (g a power of two, small enough that all rows are in work at once
-    // where possible), 64/g rows per wavefront at a time; the summation order is fixed
-    {
-        int f2 = 1;
-        while (f2 < a.F) f2 <<= 1;
-        int g = 1;
-        while (g < a.nchunk && g < 64 && g * f2 < 256) g <<= 1;
-        const int rpw = 64 / g;
-        for (int p0 = wave * rpw; p0 < a.F; p0 += 4 * rpw) {
-            const int p = p0 + lane / g, cf = lane % g;
-            const int q0 = p * a.nchunk;
-            float mx = -INFINITY;
-            if (p < a.F)
-                for (int c = cf; c < a.nchunk; c += g) mx = fmaxf(mx, smax[q0 + c]);
-            for (int o = g >> 1; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-            double s = 0.0;
-            if (p < a.F)
-                for (int c = cf; c < a.nchunk; c += g) {
-                    const float m = smax[q0 + c];
-                    if (m > -INFINITY) s += ssum[q0 + c] * exp_nonpos((double)m - (double)mx);
-                }
-            for (int o = g >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
-            if (p < a.F && cf == 0) lse_s[p] = (double)mx + log(s);
-        }
-    }
-    __syncthreads();
-    auto entry_of = [&](uint32_t q, Cand cd) {  // fp64 score of candidate cd of list q
-        const int p = (int)q / a.nchunk;
-        Entry e;
-        e.key = key_of(cum_s[p] + ((double)cd.val - lse_s[p]));
-        e.tie = (uint32_t)(p * a.V + cd.idx);   // flat index p*V + v
-        e.tag = q;
-        return e;
-    };
+    for (int i = 0; i < kFront; ++i) e[i] = i < h.count ? entry_of(h.front[i]) : Entry{0, kNone, 0};
 
-    // 2. the lists with the W best heads: no entry of any other list can be among the W best candidates
-    Entry hd[LPT];
+    // threshold: W list heads reach it (with fewer lists than W, W of the first four entries of every list), so nothing
+    // below it can be among the W best
+    const bool few = a.F * a.nchunk < a.W;   // then F == 1 and at most 63 lists: one wavefront
+    uint32_t t;
+    if (few) {
+        uint32_t g[kFront];
 #pragma unroll
-    for (int u = 0; u < LPT; ++u) {
-        const int q = tid + u * 256;
-        hd[u] = Entry{0, kNone, 0};
-        if (q < K && cnt[u] > 0) hd[u] = entry_of((uint32_t)q, head[u]);
+        for (int i = 0; i < kFront; ++i) g[i] = (uint32_t)(e[i].key >> 32);
+        __syncthreads();   // (pooled is zero)
+        t = wave_threshold<kFront>(g, a.W);
+    } else {
+        coarse[tid] = (uint32_t)(e[0].key >> 32);
+        __syncthreads();
+        if (nwaves <= 4) {
+            t = group_threshold<true>(coarse, nwaves, lane, a.W);
+        } else {   // several wavefronts on a SIMD would slow each other down: one bisects for all
+            if (tid < 64) {
+                t = group_threshold<true>(coarse, nwaves, lane, a.W);
+                if (tid == 0) thr = t;
+            }
+            __syncthreads();
+            t = thr;
+        }
     }
-    if (tid < kMaxWidth) sel[tid] = 0;  // every slot names a real list even if the ranks below were not a permutation
-    wave_top_w<LPT>([&](int u) { return hd[u]; }, a.W, wave, lane, sh);
-    __syncthreads();
-    {
-        Entry mine;
-        const int rank = merged_rank(sh, wave, lane, mine);
-        if (rank >= 0 && rank < a.W) sel[rank] = mine.tag;
-    }
-    const int nsel = min(a.W, sh.count[0] + sh.count[1] + sh.count[2] + sh.count[3]);
-    __syncthreads();  // sel complete; sh and the statistics scratch may be reused
 
-    // 3. the W best entries of the selected lists are the new nodes.  The lists are sorted, so their
-    //    entries are dealt out position-major (slot = pos * nsel + list, thread = slot mod 256): the
-    //    strongest entries then sit in different lanes and the per-wavefront thresholds are tight.
-    //    Every thread fetches its (at most EPT) entries in one batch of loads.
-    __shared__ int sel_cnt[kMaxWidth];
-    if (tid < nsel) sel_cnt[tid] = list_len((int)sel[tid]);
-    __syncthreads();
-    auto get = [&](int u) {
-        const int slot = tid + u * 256;
-        Entry r = {0, kNone, 0};
-        if (slot < nsel * a.W) {
-            const int pos = slot / nsel, s = slot % nsel;
-            if (pos < sel_cnt[s]) r = entry_of(sel[s], cands[(int64_t)sel[s] * a.W + pos]);
-        }
-        return r;
+    auto put = [&](const Entry& x) {
+        const int pos = atomicAdd(&pooled, 1);
+        if (pos < kMergePool) pool[pos] = x;
     };
-    Entry pe[EPT];
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) pe[u] = get(u);
-    wave_top_w<EPT>([&](int u) { return pe[u]; }, a.W, wave, lane, sh);
-    __syncthreads();
     {
-        Entry mine;
-        const int rank = merged_rank(sh, wave, lane, mine);
-        if (rank >= 0 && rank < a.W) {
-            const int64_t node = (int64_t)b * a.N + base_new + rank;
-            a.parent_idx[node] = base_prev + (int)(mine.tie / (uint32_t)a.V);
-            a.token_ids[node] = (int)(mine.tie % (uint32_t)a.V);
-            a.cum_logprob[node] = (float)double_of(mine.key);
+        bool sel[kFront];
+#pragma unroll
+        for (int i = 0; i < kFront; ++i) sel[i] = (uint32_t)(e[i].key >> 32) >= t;
+        pool_put(sel, [&](int i) { return e[i]; }, pool, kMergePool, &pooled, lane);
+    }
+    if ((uint32_t)(e[kFront - 1].key >> 32) >= t) {   // the list may go on above the threshold: four more at a time
+        for (int i = kFront; i < h.count; i += 4) {
+            Cand cd[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) cd[u] = rest[min(i + u, h.count - 1) - kFront];
+            bool more = true;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const Entry x = entry_of(cd[u]);
+                more = more && i + u < h.count && (uint32_t)(x.key >> 32) >= t;
+                if (more) put(x);
+            }
+            if (!more) break;
         }
+    }
+    __syncthreads();
+    const int n = __builtin_amdgcn_readfirstlane(pooled);
+    if (n > kMergePool) {   // mass ties
+        const int64_t node = (int64_t)b * a.N + 1 + (a.d - 1) * a.W;
+        merge_serially(a.parent_idx + node, a.token_ids + node, a.cum_logprob + node, a.W, a.V, base_prev, nwaves, a.heads + list, rest,
+                       h.count, p, cum, lse, best_s);
+        return;
+    }
+    auto emit = [&](int rank, const Entry& x) {
+        if (rank >= a.W) return;
+        const int64_t node = (int64_t)b * a.N + 1 + (a.d - 1) * a.W + rank;
+        const uint32_t row = x.tie / (uint32_t)a.V;
+        a.parent_idx[node] = base_prev + (int)row;
+        a.token_ids[node] = (int)(x.tie - row * (uint32_t)a.V);
+        a.cum_logprob[node] = (float)double_of(x.key);
+    };
+    if (n <= 64) {
+        if (tid >= 64) return;
+        const bool halves = n <= 32;   // the halves of the wavefront share the comparisons
+        const Entry mine = pool[halves ? lane & 31 : lane];
+        const Entry* q = pool + (halves ? lane >> 5 : 0) * 4;
+        const int step = halves ? 8 : 4;
+        uint32_t rank = 0;
+        for (int i = 0; i < n; i += step) {   // (empty entries follow the pooled ones)
+            Entry x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = q[i + u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += beats(x[u], mine);
+        }
+        if (halves) {
+            const auto r = __builtin_amdgcn_permlane32_swap(rank, rank, false, false);
+            rank = r[0] + r[1];
+        }
+        if (lane < n) emit((int)rank, mine);
+        return;
+    }
+    for (int j = tid; j < n; j += 64 * nwaves) {
+        const Entry mine = pool[j];
+        int rank = 0;
+        for (int i = 0; i < n; i += 4) {
+            Entry x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = pool[i + u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += beats(x[u], mine);
+        }
+        emit(rank, mine);
     }
 }
 
-// ---- equal growth with free attachment -----------------------------------------------------------
+// ---- finish, free attachment ------------------------------------------------------------------------
 // Every node, once the drafter has run on it, offers its W most probable tokens; the pool holds the
 // offers not yet taken; a step takes the W best of the pool (paper Sec. 4.2: the W new leaves of a
-// step may hang anywhere in the partial tree).  Three kernels per step: expand_scan (above) leaves
-// per-chunk statistics and top-W lists of the new rows, attach_rows turns them into each row's W
-// offers, attach_pool sorts pool + offers, emits the W new nodes and keeps the best W*(D-t) of the
-// rest: an entry of rank r needs r / W more steps before it can be taken and later offers only push
+// step may hang anywhere in the partial tree).  One workgroup per sequence: its wavefronts take a new row each (one list
+// per lane), work out the row's W offers, and the workgroup sorts pool + offers, emits the W new nodes and keeps the best
+// W*(D-t) of the rest: an entry of rank r needs r / W more steps before it can be taken and later offers only push
 // it down, so nothing beyond the slots still to be filled can ever be chosen.
 struct __align__(16) Offer {
     double score;
@@ -399,102 +521,209 @@ struct __align__(16) Offer {
     int32_t token;
 };
 constexpr int kPoolHeader = 16;  // bytes: int32 count, padding
+constexpr int kRowPool = 512;    // pooled candidates of one row
 
-template <int EPT>  // list entries per thread: nchunk * W <= 256 * EPT
-__global__ __launch_bounds__(256) void attach_rows_kernel(ExpandArgs a) {
-    __shared__ TopWShared sh;
-    __shared__ double lse_sh;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t row = blockIdx.x;  // b*F + p
-    const int b = (int)(row / a.F), p = (int)(row % a.F);
-    const int node = (a.d == 1 ? 0 : 1 + (a.d - 2) * a.W) + p;
-    const ChunkStat* stats = static_cast<const ChunkStat*>(a.stats) + row * a.nchunk;
-    const Cand* cands = static_cast<const Cand*>(a.cands) + row * a.nchunk * a.W;
-
-    // this thread's list entries, position-major (slot = pos * nchunk + chunk): all loads issued at once
-    Entry pe[EPT];
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-        const int slot = tid + u * 256;
-        pe[u] = Entry{0, kNone, 0};
-        if (slot < a.nchunk * a.W) {
-            const int pos = slot / a.nchunk, c = slot % a.nchunk;
-            const int cnt = min(a.W, min(a.V, (c + 1) * a.chunk) - c * a.chunk);
-            if (pos < cnt) {
-                const Cand cd = cands[c * a.W + pos];
-                pe[u].key = (uint64_t)key_of(cd.val) << 32;  // inside a row the order of the raw logits
-                pe[u].tie = (uint32_t)cd.idx;
+// Bitonic sort of one entry per thread, best first; n2 (a power of two) threads take part, the others only meet the
+// barriers.  Exchanges inside a wavefront stay in registers (39 of the 45 stages for 512 entries).
+__device__ __forceinline__ Entry sort_in_registers(Entry mine, Entry* e, int tid, int n2) {
+    auto keep = [&](const Entry& other, int j, int k) {
+        const bool better = ((tid & j) == 0) == ((tid & k) == 0);   // this side of the pair keeps the better entry
+        if (beats(other, mine) == better) mine = other;
+    };
+    for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j >= 64; j >>= 1) {
+            if (tid < n2) e[tid] = mine;
+            __syncthreads();
+            if (tid < n2) keep(e[tid ^ j], j, k);
+            __syncthreads();
+        }
+        auto step = [&](auto jc) {
+            constexpr int J = decltype(jc)::value;
+            if (k > J) {
+                Entry o;
+                o.key = ((uint64_t)lane_xor<J>((uint32_t)(mine.key >> 32)) << 32) | lane_xor<J>((uint32_t)mine.key);
+                o.tie = lane_xor<J>(mine.tie);
+                o.tag = 0;
+                keep(o, J, k);
             }
-        }
+        };
+        step(std::integral_constant<int, 32>{}); step(std::integral_constant<int, 16>{}); step(std::integral_constant<int, 8>{});
+        step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 1>{});
     }
-    // log-sum-exp of the row from the chunk statistics: wavefront 0, fixed summation order
-    if (wave == 0) {
-        float mx = -INFINITY;
-        for (int c = lane; c < a.nchunk; c += 64) mx = fmaxf(mx, stats[c].maxv);
-        mx = float_of(wave_max_u32(key_of(mx)));
-        double sum = 0.0;
-        for (int c = lane; c < a.nchunk; c += 64) {
-            const ChunkStat st = stats[c];
-            if (st.maxv > -INFINITY) sum += st.sumexp * exp_nonpos((double)st.maxv - (double)mx);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-        if (lane == 0) lse_sh = (double)mx + log(sum);
-    }
-    wave_top_w<EPT>([&](int u) { return pe[u]; }, a.W, wave, lane, sh);
-    __syncthreads();
-    Entry mine;
-    const int rank = merged_rank(sh, wave, lane, mine);
-    if (rank >= 0 && rank < a.W) {
-        Offer o;
-        const double cum = (double)a.cum_logprob[(int64_t)b * a.N + node];
-        o.score = cum + ((double)float_of((uint32_t)(mine.key >> 32)) - lse_sh);
-        o.node = node;
-        o.token = (int32_t)mine.tie;
-        static_cast<Offer*>(a.offers)[row * a.W + rank] = o;
+    return mine;
+}
+
+// Mass ties in a row: one offer per round, every lane offering the entry at the cursor of its list.
+__device__ __noinline__ void row_serially(const ListHead* h, const Cand* rest, int count, int W, int lane, uint64_t* out) {
+    auto entry = [&](int i) {
+        if (i >= count) return (uint64_t)0;
+        const Cand cd = i < kFront ? h->front[i] : rest[i - kFront];
+        return order_of(key_of(cd.val), (uint32_t)cd.idx);
+    };
+    int cur = 0;
+    uint64_t mine = entry(0);
+    for (int r = 0; r < W; ++r) {
+        const uint32_t kh = wave_max_u32((uint32_t)(mine >> 32));
+        const uint32_t kl = wave_max_u32((uint32_t)(mine >> 32) == kh ? (uint32_t)mine : 0u);
+        const uint64_t k = ((uint64_t)kh << 32) | kl;
+        if (lane == 0) out[r] = k;
+        if (mine == k) mine = entry(++cur);
     }
 }
 
-// One workgroup per sequence (256 to 1024 threads: one compare-exchange per thread and stage where possible, the sort
-// is a chain of barriers); dynamic LDS holds n2 (a power of two) entries.
-__global__ __launch_bounds__(1024) void attach_pool_kernel(ExpandArgs a, int n2) {
-    extern __shared__ __align__(16) unsigned char raw_sort[];
-    Entry* e = reinterpret_cast<Entry*>(raw_sort);
-    const int tid = threadIdx.x, nthr = blockDim.x;
+__global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int nwaves, int n2_max) {
+    extern __shared__ __align__(16) unsigned char raw_s[];
+    Entry* e = reinterpret_cast<Entry*>(raw_s);                                        // [n2_max]
+    uint64_t* pools = reinterpret_cast<uint64_t*>(raw_s + (size_t)n2_max * sizeof(Entry));   // [nwaves][kRowPool + 64]
+    __shared__ int n_live, row_n[16];
+    __shared__ uint64_t floor_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nthr = 64 * nwaves;
     const int b = blockIdx.x;
-    unsigned char* pool_b = static_cast<unsigned char*>(a.pool) + (size_t)b * (kPoolHeader + (size_t)a.pool_cap * sizeof(Offer));
+    unsigned char* pool_b = a.pool + (size_t)b * (kPoolHeader + (size_t)a.pool_cap * sizeof(Offer));
     int32_t* pool_count = reinterpret_cast<int32_t*>(pool_b);
     Offer* pool = reinterpret_cast<Offer*>(pool_b + kPoolHeader);
-    const Offer* offers = static_cast<const Offer*>(a.offers) + (int64_t)b * a.F * a.W;
-    int n_old = a.d == 1 ? 0 : *pool_count;
-    n_old = n_old < 0 ? 0 : min(n_old, min(a.pool_cap, a.W * (a.D - a.d + 1)));  // what the previous step may have left
-    const int n_new = a.F * a.W;
+    const int first = a.d == 1 ? 0 : 1 + (a.d - 2) * a.W;   // first of the nodes whose rows came in
+
     // Only W*(D-t+1) entries are ever needed: the W new nodes and the pool kept for later.  When the carried pool
     // alone already holds that many, an offer scoring below the pool's last entry cannot be among them, so it is
-    // dropped before the sort (exact: equal scores are kept), and the sort runs over what is left.
-    __shared__ int n_live;
+    // dropped before the sort (exact: equal scores are kept).
     const int need = a.W * (a.D - a.d + 1);
-    const uint64_t floor_key = (n_old >= need && n_old > 0) ? key_of(pool[n_old - 1].score) : 0ull;
+    int n_old = 0;
+    if (a.d > 1) {
+        const int most = min(a.pool_cap, need);   // what the previous step may have left
+        const int count = *pool_count;
+        n_old = min(max(count, 0), most);
+        for (int i = tid; i < most; i += nthr) {  // (requested together with the count)
+            const Offer o = pool[i];
+            if (i < n_old) e[i] = Entry{key_of(o.score), (uint32_t)o.node * (uint32_t)a.V + (uint32_t)o.token, 0};
+        }
+    }
     if (tid == 0) n_live = n_old;
     __syncthreads();
-    for (int i = tid; i < n_old + n_new; i += nthr) {
-        const Offer o = i < n_old ? pool[i] : offers[i - n_old];
-        Entry x;
-        x.key = key_of(o.score);
-        x.tie = (uint32_t)o.node * (uint32_t)a.V + (uint32_t)o.token;
-        x.tag = 0;
-        if (i < n_old) e[i] = x;
-        else if (x.key >= floor_key) e[atomicAdd(&n_live, 1)] = x;   // order before the sort does not matter
+    if (tid == 0) floor_s = n_old >= need && n_old > 0 ? e[n_old - 1].key : 0ull;
+    uint64_t* mypool = pools + wave * (kRowPool + 64);
+
+    for (int p = wave; p < a.F; p += nwaves) {
+        const int64_t list = ((int64_t)b * a.F + p) * a.nchunk + min(lane, a.nchunk - 1);
+        ListHead h = a.heads[list];
+        const double cum = (double)a.cum_logprob[(int64_t)b * a.N + first + p];
+        if (lane >= a.nchunk) {
+            h.count = 0;
+            h.ref = 0.f;
+            h.sumexp = 0.0;
+        }
+        const Cand* rest = a.rest + list * max(a.W - kFront, 0);
+        const double lse = row_lse(h, 64);
+        // the row's W best, by raw logit: threshold over the first four entries of every list, then pool and rank
+        uint32_t g[kFront];
+#pragma unroll
+        for (int i = 0; i < kFront; ++i) g[i] = i < h.count ? key_of(h.front[i].val) : 0u;
+        const uint32_t head_key[1] = {g[0]};
+        const uint32_t t = a.nchunk >= a.W ? wave_threshold<1>(head_key, a.W) : wave_threshold<kFront>(g, a.W);
+        if (lane == 0) row_n[wave] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        auto put = [&](uint64_t x) {
+            const int pos = atomicAdd(&row_n[wave], 1);
+            if (pos < kRowPool) mypool[pos] = x;
+        };
+        {
+            bool sel[kFront];
+#pragma unroll
+            for (int i = 0; i < kFront; ++i) sel[i] = g[i] >= t;
+            pool_put(sel, [&](int i) { return order_of(g[i], (uint32_t)h.front[i].idx); }, mypool, kRowPool, &row_n[wave], lane);
+        }
+        if (g[kFront - 1] >= t) {
+            for (int i = kFront; i < h.count; i += 4) {
+                Cand cd[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) cd[u] = rest[min(i + u, h.count - 1) - kFront];
+                bool more = true;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t key = key_of(cd[u].val);
+                    more = more && i + u < h.count && key >= t;
+                    if (more) put(order_of(key, (uint32_t)cd[u].idx));
+                }
+                if (!more) break;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        int n = __builtin_amdgcn_readfirstlane(row_n[wave]);
+        if (n > kRowPool) {
+            row_serially(a.heads + list, rest, h.count, a.W, lane, mypool);
+            n = a.W;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (p == wave) __syncthreads();   // floor_s is there (every wavefront passes here once: nwaves <= F)
+        if (lane < 8) mypool[n + lane] = 0;   // zeros follow the entries (there is room: 64 slots behind the pool)
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        auto offer = [&](int rank, uint64_t o) {
+            if (rank >= a.W) return;
+            const Entry x = {key_of(cum + ((double)float_of((uint32_t)(o >> 32)) - lse)),
+                             (uint32_t)(first + p) * (uint32_t)a.V + (uint32_t)~(uint32_t)o, 0};
+            if (a.d == 1) e[rank] = x;   // the root's offers alone: already in order
+            else if (x.key >= floor_s) e[atomicAdd(&n_live, 1)] = x;
+        };
+        if (n <= 64) {
+            uint64_t mine;
+            const int rank = rank_in_wave(mypool, n, lane, mine);
+            if (lane < n) offer(rank, mine);
+        } else {
+            for (int j = lane; j < n; j += 64) {
+                const uint64_t mine = mypool[j];
+                int rank = 0;
+                for (int i = 0; i < n; i += 4) {
+                    uint64_t x[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[u] = mypool[i + u];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) rank += x[u] > mine;
+                }
+                offer(rank, mine);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // the next row reuses the pool
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    const int n_sort = n_live;
-    int m2 = 2;
-    while (m2 < n_sort) m2 <<= 1;   // <= n2: the launch sized the buffer for every offer surviving
-    n2 = m2;
+    const int n_sort = a.d == 1 ? a.W : n_live;
+    const int base_new = 1 + (a.d - 1) * a.W;
+    const int keep = min(a.W * (a.D - a.d), n_sort - a.W);
+    auto emit = [&](int i, const Entry& x) {
+        if (i >= a.W + keep) return;
+        const uint32_t node = x.tie / (uint32_t)a.V;
+        const int token = (int)(x.tie - node * (uint32_t)a.V);
+        const double score = double_of(x.key);
+        if (i < a.W) {
+            const int64_t dst = (int64_t)b * a.N + base_new + i;
+            a.parent_idx[dst] = (int)node;
+            a.token_ids[dst] = token;
+            a.cum_logprob[dst] = (float)score;
+        } else {
+            Offer o;
+            o.score = score; o.node = (int)node; o.token = token;
+            pool[i - a.W] = o;
+        }
+    };
+    if (tid == 0) *pool_count = keep;
+    int n2 = 2;
+    while (n2 < n_sort) n2 <<= 1;   // <= n2_max: the launch sized the buffer for every offer surviving
+    if (n2 <= nthr) {
+        Entry mine = tid < n_sort ? e[tid] : Entry{0, kNone, 0};
+        if (a.d > 1) {
+            __syncthreads();
+            mine = sort_in_registers(mine, e, tid, n2);
+        }
+        emit(tid, mine);
+        return;
+    }
     for (int i = n_sort + tid; i < n2; i += nthr) e[i] = Entry{0, kNone, 0};
     __syncthreads();
-    // bitonic sort, best first (larger key, then lower node*V + token); empty slots sink to the end
+    // bitonic sort in LDS, best first (larger key, then lower node*V + token); empty slots sink to the end
     for (int k = 2; k <= n2; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
             for (int i = tid; i < (n2 >> 1); i += nthr) {
@@ -516,96 +745,101 @@ __global__ __launch_bounds__(1024) void attach_pool_kernel(ExpandArgs a, int n2)
             }
         }
     __syncthreads();  // the sorted order is read by every wavefront
-    const int base_new = 1 + (a.d - 1) * a.W;
-    const int keep = min(a.W * (a.D - a.d), n_sort - a.W);
-    for (int i = tid; i < a.W + keep; i += nthr) {
-        const Entry x = e[i];
-        const int node = (int)(x.tie / (uint32_t)a.V), token = (int)(x.tie % (uint32_t)a.V);
-        const double score = double_of(x.key);
-        if (i < a.W) {
-            const int64_t dst = (int64_t)b * a.N + base_new + i;
-            a.parent_idx[dst] = node;
-            a.token_ids[dst] = token;
-            a.cum_logprob[dst] = (float)score;
-        } else {
-            Offer o;
-            o.score = score; o.node = node; o.token = token;
-            pool[i - a.W] = o;
-        }
-    }
-    if (tid == 0) *pool_count = keep;
+    for (int i = tid; i < a.W + keep; i += nthr) emit(i, e[i]);
+}
+
+int pow2_at_least(int64_t x) {
+    int n = 1;
+    while (n < x) n <<= 1;
+    return n;
+}
+
+hipError_t launch_scan(const ExpandArgs& a, hipStream_t st) {
+    ScanArgs s;
+    s.logits = a.logits;
+    s.heads = static_cast<ListHead*>(a.heads);
+    s.rest = static_cast<Cand*>(a.rest);
+    s.V = a.V; s.W = a.W; s.chunk = a.chunk; s.nchunk = a.nchunk;
+    const dim3 grid((unsigned)(a.B * a.F), (unsigned)a.nchunk), block(kScanThreads);
+    const bool vec = (a.V & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15u) == 0;
+    auto go = [&](auto e, auto one) {
+        constexpr int E = decltype(e)::value;
+        constexpr bool ONE = decltype(one)::value;
+        if (vec) hipLaunchKernelGGL((expand_scan_kernel<E, true, ONE>), grid, block, 0, st, s);
+        else hipLaunchKernelGGL((expand_scan_kernel<E, false, ONE>), grid, block, 0, st, s);
+    };
+    if (a.chunk == 4 * kScanThreads) go(std::integral_constant<int, 4>{}, std::true_type{});
+    else if (a.chunk == 8 * kScanThreads) go(std::integral_constant<int, 8>{}, std::true_type{});
+    else if (a.chunk == 16 * kScanThreads) go(std::integral_constant<int, 16>{}, std::true_type{});
+    else go(std::integral_constant<int, 16>{}, std::false_type{});
+    return hipGetLastError();
+}
+
+FinishArgs finish_args(const ExpandArgs& a) {
+    FinishArgs f;
+    f.heads = static_cast<const ListHead*>(a.heads);
+    f.rest = static_cast<const Cand*>(a.rest);
+    f.parent_idx = a.parent_idx; f.token_ids = a.token_ids; f.cum_logprob = a.cum_logprob;
+    f.pool = static_cast<unsigned char*>(a.pool); f.pool_cap = a.pool_cap;
+    f.D = a.D; f.W = a.W; f.V = a.V; f.N = a.N; f.d = a.d; f.F = a.F; f.nchunk = a.nchunk;
+    f.shift = 0;
+    while ((1 << f.shift) < a.nchunk) ++f.shift;
+    return f;
 }
 
 }  // namespace
 
+// Chunk length: the finish kernel takes one list per thread and a row's lists from one wavefront, which bounds the lists
+// per row; within that, short chunks (1024 logits, four per thread) keep every compute unit busy and each thread's chain
+// short.  Steps that fill the chip several times over take chunks of up to 4096: the fixed part of a workgroup's work, the
+// lists to write and those to read back are then a quarter.
 ExpandPlan plan_expand(const ygg_shape& s, int32_t d) {
     ExpandPlan p;
     p.F = d == 1 ? 1 : s.width;
-    p.chunk = kScanThreads * kScanElems;
-    p.nchunk = (s.vocab + p.chunk - 1) / p.chunk;
-    const size_t lists = (size_t)s.batch * (size_t)p.F * (size_t)p.nchunk;
-    p.stat_bytes = (lists * sizeof(ChunkStat) + 255) / 256 * 256;
-    p.cand_bytes = (lists * (size_t)s.width * sizeof(Cand) + 255) / 256 * 256;
+    const int64_t most = std::min(64, kMaxLists / pow2_at_least(p.F));   // lists per row
+    const int64_t rows = (int64_t)s.batch * p.F;
+    auto lists = [&](int64_t chunk) { return (s.vocab + chunk - 1) / chunk; };
+    int64_t chunk = 1024;
+    if (lists(chunk) > most || rows * lists(chunk) > 1024) chunk = 2048;
+    if (lists(chunk) > most || rows * lists(chunk) > 512) chunk = 4096;
+    if (lists(chunk) > most) chunk = ((int64_t)s.vocab + 4096 * most - 1) / (4096 * most) * 4096;
+    p.chunk = (int32_t)chunk;
+    p.nchunk = (int32_t)lists(chunk);
+    const size_t total = (size_t)rows * (size_t)p.nchunk;
+    p.head_bytes = (total * sizeof(ListHead) + 255) / 256 * 256;
+    p.rest_bytes = (total * (size_t)std::max(s.width - kFront, 0) * sizeof(Cand) + 255) / 256 * 256;
     return p;
 }
 
-// Static plus dynamic LDS of these exceeds the 64 KiB default.
+// The largest dynamic LDS the attachment kernel may ask for: 4096 entries and the row pools of sixteen wavefronts.
 hipError_t raise_limits_expand() {
-    const void* big[] = {reinterpret_cast<const void*>(expand_merge_kernel<16, 1>),
-                         reinterpret_cast<const void*>(expand_merge_kernel<16, 4>),
-                         reinterpret_cast<const void*>(expand_merge_kernel<16, 16>)};
-    for (const void* f : big) {
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)merge_scratch_bytes(16));
-        if (e != hipSuccess) return e;
-    }
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(attach_pool_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)(4096 * sizeof(Entry)));
-}
-
-template <int LPT>
-static void launch_merge(const ExpandArgs& a, hipStream_t st) {
-    const dim3 grid((unsigned)a.B), block(256);
-    const size_t lds = merge_scratch_bytes(LPT);
-    if (a.W <= 16) hipLaunchKernelGGL((expand_merge_kernel<LPT, 1>), grid, block, lds, st, a);
-    else if (a.W <= 32) hipLaunchKernelGGL((expand_merge_kernel<LPT, 4>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((expand_merge_kernel<LPT, 16>), grid, block, lds, st, a);
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(attach_finish_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)(4096 * sizeof(Entry) + 16 * (kRowPool + 64) * sizeof(uint64_t)));
 }
 
 hipError_t launch_expand(const ExpandArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(expand_scan_kernel, dim3((unsigned)(a.B * a.F), (unsigned)a.nchunk), dim3(kScanThreads), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int K = a.F * a.nchunk;
-    if (K <= 256) launch_merge<1>(a, st);
-    else if (K <= 1024) launch_merge<4>(a, st);
-    else launch_merge<16>(a, st);
+    if (hipError_t e = launch_scan(a, st)) return e;
+    const FinishArgs f = finish_args(a);
+    const int nwaves = ((a.F << f.shift) + 63) / 64;
+    hipLaunchKernelGGL(expand_merge_kernel, dim3((unsigned)a.B), dim3(64 * nwaves), 0, st, f, nwaves);
     return hipGetLastError();
 }
 
-size_t attach_offer_bytes(const ygg_shape& s) {
-    return ((size_t)s.batch * (size_t)s.width * (size_t)s.width * sizeof(Offer) + 255) / 256 * 256;
-}
 int64_t attach_pool_capacity(const ygg_shape& s) { return (int64_t)s.width * (s.depth > 1 ? s.depth - 1 : 1); }
 size_t attach_pool_bytes(const ygg_shape& s) {
     return ((size_t)s.batch * (kPoolHeader + (size_t)attach_pool_capacity(s) * sizeof(Offer)) + 255) / 256 * 256;
 }
 
 hipError_t launch_attach(const ExpandArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(expand_scan_kernel, dim3((unsigned)(a.B * a.F), (unsigned)a.nchunk), dim3(kScanThreads), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int per_row = a.nchunk * a.W;
-    const dim3 rows((unsigned)(a.B * a.F)), block(256);
-    if (per_row <= 256) hipLaunchKernelGGL(attach_rows_kernel<1>, rows, block, 0, st, a);
-    else if (per_row <= 1024) hipLaunchKernelGGL(attach_rows_kernel<4>, rows, block, 0, st, a);
-    else hipLaunchKernelGGL(attach_rows_kernel<16>, rows, block, 0, st, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (hipError_t e = launch_scan(a, st)) return e;
+    const FinishArgs f = finish_args(a);
     const int n = a.F * a.W + (a.d == 1 ? 0 : a.W * (a.D - a.d + 1));
-    int n2 = 2;
-    while (n2 < n) n2 <<= 1;
-    const int pool_threads = n2 / 2 < 256 ? 256 : (n2 / 2 > 1024 ? 1024 : n2 / 2);
-    hipLaunchKernelGGL(attach_pool_kernel, dim3((unsigned)a.B), dim3(pool_threads), (size_t)n2 * sizeof(Entry), st, a, n2);
+    const int n2 = pow2_at_least(std::max(n, 2));
+    // a wavefront per new row; the sort wants a thread per entry, which all wavefronts below sixteen cannot give: rows
+    // are then shared out anyway
+    const int nwaves = std::min(16, a.F);
+    const size_t lds = (size_t)n2 * sizeof(Entry) + (size_t)nwaves * (kRowPool + 64) * sizeof(uint64_t);
+    hipLaunchKernelGGL(attach_finish_kernel, dim3((unsigned)a.B), dim3(64 * nwaves), lds, st, f, nwaves, n2);
     return hipGetLastError();
 }
 

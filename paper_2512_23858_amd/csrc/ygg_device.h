@@ -23,6 +23,57 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 }
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { return ~wave_max_u32(~v); }
 
+// ---- exchanges between the lanes of a wavefront that cost no LDS round trip -----------------------
+// v from lane (lane ^ M) for M = 1, 2, 8; the mirrored lane of a group of 8 (M = 7) or 16 (M = 15).
+template <int M>
+__device__ __forceinline__ uint32_t row_xor(uint32_t v) {
+    constexpr int ctrl = M == 1 ? 0xb1 : M == 2 ? 0x4e : M == 7 ? 0x141 : M == 8 ? 0x128 : 0x140;
+    static_assert(M == 1 || M == 2 || M == 7 || M == 8 || M == 15, "a pattern of the row permutes");
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, true);
+}
+// op over aligned groups of `width` lanes (a power of two up to 64, the same in every lane); every lane gets the result.
+// After the first steps all lanes of a sub-group agree, so a mirror serves where an exchange of halves is meant.
+template <typename Op>
+__device__ __forceinline__ float group_reduce(float v, int width, Op op) {
+    auto f = [](uint32_t u) { return __uint_as_float(u); };
+    const auto u = [&] { return __float_as_uint(v); };
+    if (width > 1) v = op(v, f(row_xor<1>(u())));
+    if (width > 2) v = op(v, f(row_xor<2>(u())));
+    if (width > 4) v = op(v, f(row_xor<7>(u())));
+    if (width > 8) v = op(v, f(row_xor<15>(u())));
+    if (width > 16) { const auto p = __builtin_amdgcn_permlane16_swap(u(), u(), false, false); v = op(f(p[0]), f(p[1])); }
+    if (width > 32) { const auto p = __builtin_amdgcn_permlane32_swap(u(), u(), false, false); v = op(f(p[0]), f(p[1])); }
+    return v;
+}
+__device__ __forceinline__ double group_sum(double v, int width) {
+    auto mk = [](uint32_t lo, uint32_t hi) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); };
+    const auto lo = [&] { return (uint32_t)__double_as_longlong(v); };
+    const auto hi = [&] { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); };
+    if (width > 1) v += mk(row_xor<1>(lo()), row_xor<1>(hi()));
+    if (width > 2) v += mk(row_xor<2>(lo()), row_xor<2>(hi()));
+    if (width > 4) v += mk(row_xor<7>(lo()), row_xor<7>(hi()));
+    if (width > 8) v += mk(row_xor<15>(lo()), row_xor<15>(hi()));
+    if (width > 16) {
+        const auto a = __builtin_amdgcn_permlane16_swap(lo(), lo(), false, false), b = __builtin_amdgcn_permlane16_swap(hi(), hi(), false, false);
+        v = mk(a[0], b[0]) + mk(a[1], b[1]);
+    }
+    if (width > 32) {
+        const auto a = __builtin_amdgcn_permlane32_swap(lo(), lo(), false, false), b = __builtin_amdgcn_permlane32_swap(hi(), hi(), false, false);
+        v = mk(a[0], b[0]) + mk(a[1], b[1]);
+    }
+    return v;
+}
+// v from lane (lane ^ M), M a power of two below 64
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+    if constexpr (M == 1 || M == 2 || M == 8) return row_xor<M>(v);
+    else if constexpr (M == 4 || M == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x1f | (M << 10));
+    else {
+        const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);   // {low half twice, high half twice}
+        return (threadIdx.x & 32) ? p[0] : p[1];
+    }
+}
+
 // order-preserving maps to unsigned integers (larger value <-> larger key; -inf is the smallest real key)
 __device__ __forceinline__ uint32_t key_of(float f) {
     const uint32_t u = __float_as_uint(f);
@@ -39,30 +90,44 @@ __device__ __forceinline__ double double_of(uint64_t k) {
     return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
 }
 
-// exp(t) for t <= 0 in fp64: k = round(t/ln 2), r = t - k ln 2 (two-part constant), Taylor series of
-// degree 13 on |r| <= ln(2)/2 (remainder < 1e-17), scaled by 2^k.  Relative error about 1e-16.
-// Branch-free (0 below the underflow point comes from a select), so independent calls interleave.
-__device__ __forceinline__ double exp_nonpos(double t) {
-    const double tc = fmax(t, -746.0);
-    const double k = rint(tc * 1.4426950408889634074);
-    double r = fma(k, -6.93147180369123816490e-01, tc);
-    r = fma(k, -1.90821492927058770002e-10, r);
-    double p = 1.0 / 6227020800.0;
-    p = fma(p, r, 1.0 / 479001600.0);
-    p = fma(p, r, 1.0 / 39916800.0);
-    p = fma(p, r, 1.0 / 3628800.0);
-    p = fma(p, r, 1.0 / 362880.0);
-    p = fma(p, r, 1.0 / 40320.0);
-    p = fma(p, r, 1.0 / 5040.0);
-    p = fma(p, r, 1.0 / 720.0);
-    p = fma(p, r, 1.0 / 120.0);
-    p = fma(p, r, 1.0 / 24.0);
-    p = fma(p, r, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
-    const double e = ldexp(p, (int)k);
-    return t < -745.0 ? 0.0 : e;
+// exp(t) in fp64 (Cody and Waite's argument reduction): k = round(t/ln 2), r = t - k ln 2 (two-part constant), Taylor
+// series of degree 13 on |r| <= ln(2)/2 (remainder < 1e-17), scaled by 2^k.  Relative error about 1e-16.  For t <= 709;
+// below the underflow point the result is 0 or the smallest subnormal.  Branch-free, so independent calls interleave.
+// N arguments in step: a dependent fp64 operation takes about 20 cycles, an independent one four.
+template <int N>
+__device__ __forceinline__ void exp_below_n(const double (&t)[N], double (&e)[N]) {
+    constexpr double c[] = {1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0,
+                            1.0 / 40320.0,      1.0 / 5040.0,      1.0 / 720.0,      1.0 / 120.0,     1.0 / 24.0,
+                            1.0 / 6.0,          0.5,               1.0,              1.0};
+    double k[N], r[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = fmax(t[i], -746.0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) k[i] = r[i] * 1.4426950408889634074;
+#pragma unroll
+    for (int i = 0; i < N; ++i) k[i] = rint(k[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = fma(k[i], -6.93147180369123816490e-01, r[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = fma(k[i], -1.90821492927058770002e-10, r[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) e[i] = fma(c[0], r[i], c[1]);
+#pragma unroll
+    for (int s = 2; s < 14; ++s) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) e[i] = fma(e[i], r[i], c[s]);
+        __builtin_amdgcn_sched_barrier(0);   // keep the series in step
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) e[i] = ldexp(e[i], (int)k[i]);
 }
+__device__ __forceinline__ double exp_below(double t) {
+    const double a[1] = {t};
+    double e[1];
+    exp_below_n(a, e);
+    return e[0];
+}
+// exp(t) for t <= 0, exactly 0 below the underflow point
+__device__ __forceinline__ double exp_nonpos(double t) { return t < -745.0 ? 0.0 : exp_below(t); }
 
 }  // namespace ygg

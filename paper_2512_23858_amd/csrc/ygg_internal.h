@@ -66,19 +66,18 @@ int32_t ensure_device_ready();
 // ---- equal-growth expansion -------------------------------------------------------------------
 struct ExpandPlan {
     int32_t F;            // frontier rows
-    int32_t chunk;        // vocab entries per scan workgroup
-    int32_t nchunk;
-    size_t stat_bytes;    // [B*F][nchunk] {double sumexp; float max; int32 count}
-    size_t cand_bytes;    // [B*F][nchunk][W] {float val; int32 idx}
+    int32_t chunk;        // vocab entries per list (one wavefront of the scan)
+    int32_t nchunk;       // lists per row, at most 64
+    size_t head_bytes;    // [B*F][nchunk] {double sumexp; int32 count; the four best entries}
+    size_t rest_bytes;    // [B*F][nchunk][W - 4] {float val; int32 idx}
 };
 struct ExpandArgs {
     const float* logits;
     int32_t* parent_idx;
     int32_t* token_ids;
     float* cum_logprob;
-    void* stats;
-    void* cands;
-    void* offers;      // free attachment only: [B*F][W] {double score; int32 node; int32 token}
+    void* heads;
+    void* rest;
     void* pool;        // free attachment only: per sequence {int32 count, pad to 16 B, pool_cap offers}
     int32_t pool_cap;
     int32_t B, D, W, V, N, d, F, chunk, nchunk;
@@ -86,7 +85,6 @@ struct ExpandArgs {
 ExpandPlan plan_expand(const ygg_shape& s, int32_t d);
 hipError_t launch_expand(const ExpandArgs& a, hipStream_t st);
 // free attachment: d is the draft step; rows belong to the nodes added at step d-1
-size_t attach_offer_bytes(const ygg_shape& s);
 int64_t attach_pool_capacity(const ygg_shape& s);
 size_t attach_pool_bytes(const ygg_shape& s);
 hipError_t launch_attach(const ExpandArgs& a, hipStream_t st);

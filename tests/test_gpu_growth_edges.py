@@ -1,0 +1,53 @@
+"""Both growth rules where their kernels change shape: chunk lengths of 1024 / 2048 / 4096 / several passes, tails of a few
+logits, rows that are no multiple of four logits, fewer lists than new nodes, more equal logits than a candidate pool holds,
+and logits whose exponentials need a reference other than zero.  Indices bit for bit against the CPU oracle."""
+import numpy as np
+import pytest
+
+import ygg_workloads as wl
+from test_gpu_attach import attach_both
+from test_gpu_expand_accept import _expand_both
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(B, D, W, V, seed=23):
+    return wl.Config("case", B, 4, 2, 64, "bf16", 16, (), D, W, V, (0.6,), "dirichlet", 0.5, 1, seed)
+
+
+@pytest.mark.parametrize("B,D,W,V", [(1, 2, 8, 1023), (1, 2, 8, 1024), (1, 3, 8, 1025), (1, 2, 9, 4099), (2, 2, 33, 2048),
+                                     (1, 2, 64, 2050), (1, 3, 12, 3001),
+                                     (12, 2, 16, 5001), (40, 2, 8, 5000), (40, 2, 3, 9001),      # chunks of 2048 and 4096
+                                     (1, 2, 58, 70001), (1, 2, 33, 131080)])                     # several passes per chunk
+def test_growth_at_the_edges_of_the_chunks(B, D, W, V):
+    _expand_both(_cfg(B, D, W, V))
+    if W * W + W * D <= 4096:
+        attach_both(_cfg(B, D, W, V))
+
+
+@pytest.mark.parametrize("V", [700, 5000, 70000])
+@pytest.mark.parametrize("W", [3, 20])
+def test_growth_with_more_ties_than_a_pool_holds(W, V):
+    cfg = _cfg(1, 3, W, V)
+
+    def equal(d):
+        return np.full((1, 1 if d == 1 else W, V), 1.5, np.float32)
+    _expand_both(cfg, logits_fn=equal, check_margin=False)
+    attach_both(cfg, logits_fn=equal, check_margin=False)
+
+
+@pytest.mark.parametrize("shift,masked", [(0.0, -1e9), (650.0, None), (-650.0, None), (0.0, -600.0), (3e4, -3e4)])
+def test_growth_with_logits_far_from_zero(shift, masked):
+    """Large offsets, and all but a stretch of the vocabulary pushed far down: whole chunks then carry a reference of their
+    own beside chunks that need none.  The second row is left as it is."""
+    cfg = _cfg(2, 3, 6, 9000, seed=29)
+
+    def fn(d):
+        x = wl.expansion_inputs(cfg, d)
+        y = x[:, :1] if d == 1 else x[:, ::2]
+        y += np.float32(shift)
+        if masked is not None:
+            y[:, :, :4200] = np.float32(masked) + x[:, :1, :4200]
+            y[:, :, 4500:] = np.float32(masked) + x[:, :1, 4500:]
+        return x
+    _expand_both(cfg, logits_fn=fn, check_margin=False)

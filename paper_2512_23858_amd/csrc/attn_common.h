@@ -58,6 +58,28 @@ __device__ __forceinline__ void dma_load16_flat(const void* gptr, uint32_t lds_b
     else
         asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
 }
+// Same, 4 bytes per lane: lane l's data lands at lds_base + 4*l.
+__device__ __forceinline__ void dma_load4(const void* gptr, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
+}
+// n / d for n < 2^31 with mul = (2^32 - 1) / d from the host: the product is the quotient or one less.
+__device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint32_t mul) {
+    const uint32_t q = __umulhi(n, mul);
+    return q + (n - q * d >= d);
+}
+__device__ __forceinline__ int wave_prefix_i32(int v, int lane) {   // inclusive, over the 64 lanes
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(v, o);
+        if (lane >= o) v += t;
+    }
+    return v;
+}
+__device__ __forceinline__ int wave_sum_i32(int v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return __builtin_amdgcn_readfirstlane(v);
+}
 // Waits until at most KEEP of this wavefront's vector-memory operations are still outstanding (they
 // complete in issue order, so the KEEP youngest may still be in flight).
 template <int KEEP>
@@ -85,6 +107,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int V>
 struct IntC {
     static constexpr int value = V;
+    constexpr operator int() const { return V; }
 };
 // f(IntC<I>{}) for I = FROM .. TO-1, unrolled at compile time
 template <int FROM, int TO, class F>

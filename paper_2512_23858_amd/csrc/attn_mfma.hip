@@ -75,7 +75,7 @@ __device__ __forceinline__ void e4m3x16_to_bf16(const u32x4& raw, uint4& first8,
 // DHT: head_dim, 128 or 64 (bf16 K/V only for 64).  Everything below counts in k-steps of 16 and output blocks of 32
 // head_dim positions, and a direct-to-LDS instruction brings 1024 / ROWB rows.
 template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128>
-__global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1)) void attn_mfma_kernel(AttnArgs a, int RT, int S) {
+__global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1)) void attn_mfma_kernel(AttnArgs a) {
     static_assert(!BAL || KS == 1, "balanced batches: plain 32-row wavefronts only");
     static_assert(DHT == 128 || (DHT == 64 && !KV8), "head_dim 64: bf16 K/V only");
     constexpr int DH = DHT;
@@ -92,7 +92,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     constexpr int NRW = NW / KS;                                 // wavefronts along the rows
     constexpr int RW = NRW * RB * 32;                            // query rows per workgroup
     constexpr int TILEB = KT * ROWB;                             // bytes of one K (or V) tile
-    constexpr int NBUF = 3;  // tiles are prefetched two ahead
+    // Tiles are prefetched two ahead.  PING: the two wavefronts of a SIMD run half a block apart (see the loop), which takes
+    // a fourth tile buffer.
+    constexpr bool PING = KS == 1 && NW == 8;
+    constexpr int NBUF = PING ? 4 : 3;
     // wavefronts that issue tile fills (a power of two, so that each issues the same number per tile)
     constexpr int FILLERS = NW >= 8 ? 8 : NW >= 4 ? 4 : NW >= 2 ? 2 : 1;
     constexpr int PT = 2 * (KT / RPI) / FILLERS;  // direct-to-LDS loads per filling wavefront and tile
@@ -100,24 +103,37 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* k_s = smem;                                   // [NBUF][KT][ROWB]
     unsigned char* v_s = smem + NBUF * TILEB;                    // [NBUF][KT][ROWB]
-    uint32_t* anc_s = reinterpret_cast<uint32_t*>(smem + 2 * NBUF * TILEB);  // [local node][aw], then parent[N]
+    // Q passes through the tile buffers from the third on (tile 2 is requested once it is read) and, where these
+    // do not hold it, through space behind them.
+    constexpr int QW = 32 * RB * ROWB;           // a wavefront's rows
+    constexpr int QB = 2 * (NBUF - 2);           // wavefronts whose rows fit the spare K (or V) buffers
+    constexpr int QX = NW > 2 * QB ? (NW - 2 * QB) * QW : 0;
+    static_assert(RB == 1 && QW * 2 == TILEB, "two wavefronts' rows to a tile buffer");
+    uint32_t* anc_s = reinterpret_cast<uint32_t*>(smem + 2 * NBUF * TILEB + QX);  // [local node][aw], then parent[N]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
     const int n = lane & 31, g2 = lane >> 5;
+    unsigned char* q_s = (wave < QB ? k_s + 2 * TILEB + wave * QW
+                                    : wave < 2 * QB ? v_s + 2 * TILEB + (wave - QB) * QW : smem + 2 * NBUF * TILEB + (wave - 2 * QB) * QW);
     const bool is_loader = KV8 && wave >= NW;      // wave-uniform
     const int wrow = KS == 1 ? wave : wave % NRW;  // position along the rows (computing wavefronts)
     const int kh = KS == 1 ? 0 : wave / NRW;       // which block of every tile (KS = 2)
 
-    // workgroup id -> (stream sigma = (b, kv head, split), row tile); sigma % 8 picks the XCD
-    const int wg = blockIdx.x;
-    const int xcd = wg & 7;
-    const int rt = (wg >> 3) % RT;
-    const int sigma = (wg / (8 * RT)) * 8 + xcd;
-    if (sigma >= S) return;
+    // All arguments at once: left to itself the compiler fetches each where it is first needed, one scalar-cache miss after
+    // the other in front of the first tile fill (32 layers of a 516-row verify pass: 923 -> 887 us).  The paired shapes'
+    // short launches measured 3 % slower that way and fetch as they go.
+    if constexpr (KS == 1)
+        asm volatile("" ::"s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.k_tree), "s"(a.v_tree), "s"(a.seq_lens), "s"(a.parent_idx),
+                     "s"(a.N), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.nsplit), "s"(a.max_seq_len), "s"(a.S), "s"(a.row_tiles),
+                     "s"(a.mul_nsplit), "s"(a.mul_hkv), "s"(a.mul_g), "s"(a.mul_rt), "s"(a.cap));
+    // workgroup id -> (stream sigma = (b, kv head, split) or (kv head, slot), row tile); sigma % 8 picks the XCD
+    const int wg8 = (int)divide(blockIdx.x >> 3, a.row_tiles, a.mul_rt);
+    const int rt = (int)(blockIdx.x >> 3) - wg8 * a.row_tiles;
+    const int sigma = wg8 * 8 + (blockIdx.x & 7);
+    if (sigma >= a.S) return;
     const int R = a.N * a.G;
     const int row_base = rt * RW;
-    const int64_t rows_total = (int64_t)a.B * a.N * a.Hq;
 
     // Which (sequence, key range) segments does this workgroup serve?
     //   classic   one segment: sigma = (sequence, kv head, split); the split is one of nsplit equal chunks of that
@@ -128,89 +144,123 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     //             same number of tiles whatever the mix of lengths (a ragged batch otherwise takes as long as its longest
     //             sequence).  Segment number (slot - first slot of the sequence) is the split index of its partials;
     //             nsplit = a.slots bounds it.  A sequence that lies inside one slot is written out directly.
+    // The head of the kernel is a chain of dependent scalar work in front of the first tile fill (the length is a load from
+    // device memory), so divisions are multiplications by host-made reciprocals and the lengths of a batch are read by one
+    // vector load.
     constexpr bool balanced = BAL;
-    int hk, b_first, b_last, slot = 0, run_lo = 0, run_hi = 0, tiles_all = 0, tiles_before = 0, nruns = 1;
+    int hk, b_first, b_last, slot = 0, run_lo = 0, run_hi = 0, tiles_before = 0;
+    int run_q = 1, run_r = 0;   // the first run_r runs have run_q + 1 tiles, the others run_q
     if constexpr (!balanced) {
-        hk = (sigma / a.nsplit) % a.Hkv;
-        b_first = b_last = sigma / (a.nsplit * a.Hkv);
+        const int hb = (int)divide(sigma, a.nsplit, a.mul_nsplit);
+        b_first = b_last = (int)divide(hb, a.Hkv, a.mul_hkv);
+        hk = hb - b_first * a.Hkv;
     } else {
-        hk = sigma / a.slots;
-        slot = sigma % a.slots;
-        auto tiles_of = [&](int bb) {
-            int Lb = a.seq_lens[bb];
+        hk = (int)divide(sigma, a.slots, a.mul_nsplit);   // (nsplit == slots)
+        slot = sigma - hk * a.slots;
+        constexpr int CH = 4;   // 64 sequences at a time: batches of up to 256
+        int tl[CH];
+        int mine = 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            tl[c] = 0;
+            if (64 * c >= a.B) break;
+            const int bb = 64 * c + lane;
+            int Lb = bb < a.B ? a.seq_lens[bb] : 0;
             Lb = Lb < 0 ? 0 : (Lb > a.max_seq_len ? a.max_seq_len : Lb);
-            return (Lb + a.N + kKeyTile - 1) / kKeyTile;
-        };
-        for (int bb = 0; bb < a.B; ++bb) tiles_all += tiles_of(bb);
+            tl[c] = bb < a.B ? (Lb + a.N + kKeyTile - 1) / kKeyTile : 0;
+            mine += tl[c];
+        }
+        const int tiles_all = wave_sum_i32(mine);
         // never more runs than tiles (the host sized the grid for the longest lengths the shape allows): every run then
         // holds a tile, so the runs a sequence falls into are consecutive and its split indices have no gaps
-        nruns = min(a.slots, tiles_all);
-        run_lo = slot < nruns ? (int)((int64_t)slot * tiles_all / nruns) : 0;
-        run_hi = slot < nruns ? (int)((int64_t)(slot + 1) * tiles_all / nruns) : 0;
-        // first and last sequence with tiles inside [run_lo, run_hi)
-        b_first = 0;
-        int acc = 0;
-        while (b_first < a.B - 1 && acc + tiles_of(b_first) <= run_lo) acc += tiles_of(b_first++);
-        tiles_before = acc;  // tiles of the sequences before b_first
-        b_last = b_first;
-        acc += tiles_of(b_first);
-        while (b_last < a.B - 1 && acc < run_hi) acc += tiles_of(++b_last);
-        if (run_lo >= run_hi) b_last = b_first - 1;  // a workgroup beyond the last run: nothing to do
+        const int nruns = min(a.slots, tiles_all);
+        if (slot >= nruns) return;   // a workgroup beyond the last run: nothing to do
+        run_q = nruns == a.slots ? (int)divide(tiles_all, a.slots, a.mul_nsplit) : 1;
+        run_r = tiles_all - run_q * nruns;
+        run_lo = slot * run_q + min(slot, run_r);
+        run_hi = run_lo + run_q + (slot < run_r);
+        // first and last sequence with tiles inside [run_lo, run_hi), from the prefix sums over the batch
+        b_first = b_last = 0;
+        int base = 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (64 * c >= a.B) break;
+            const int incl = base + wave_prefix_i32(tl[c], lane);
+            const uint64_t upto = __ballot(incl <= run_lo), before = __ballot(incl - tl[c] < run_hi && tl[c] > 0);
+            const int nf = (int)__popcll(upto), nl = (int)__popcll(before);
+            if (b_first == 64 * c && nf < 64) tiles_before = __builtin_amdgcn_readlane(incl - tl[c], nf);
+            if (b_first == 64 * c) b_first += nf;
+            if (nl > 0) b_last = 64 * c + nl - 1;
+            base = __builtin_amdgcn_readlane(incl, 63);
+        }
     }
-    // the run that holds tile x of the concatenation: the largest s with floor(s * tiles_all / nruns) <= x
-    auto slot_of_tile = [&](int x) { return (int)((((int64_t)x + 1) * nruns - 1) / tiles_all); };
-    // all of this is the same in every lane: keep it in scalar registers (the vector registers are all spoken for)
+    // the run that holds tile x of the concatenation
+    auto slot_of_tile = [&](int x) {
+        const int head = run_r * (run_q + 1);
+        return x < head ? x / (run_q + 1) : run_r + (x - head) / run_q;
+    };
     auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     if constexpr (balanced) {
-        hk = uni(hk); b_first = uni(b_first); b_last = uni(b_last); run_lo = uni(run_lo); run_hi = uni(run_hi);
-        tiles_before = uni(tiles_before); tiles_all = uni(tiles_all); nruns = uni(nruns);
-    } else {
-        b_last = b_first;
+        b_first = uni(b_first); b_last = uni(b_last); run_lo = uni(run_lo); run_hi = uni(run_hi);
+        tiles_before = uni(tiles_before); run_q = uni(run_q); run_r = uni(run_r);
     }
 
     for (int b = b_first; b <= b_last; ++b) {
     if (balanced && b != b_first) __syncthreads();   // the previous segment's tile buffers and masks are free again
+    int L = a.seq_lens[b];   // (requested first)
     // rows of this lane: block rb of this wave -> row_base + (wrow*RB + rb)*32 + n
     int rg_of[RB];       // global row index (b, node, q head) or -1; fits 31 bits (checked on the host)
     int node_of[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int row = row_base + (wrow * RB + rb) * 32 + n;
-        const int i = min(row, R - 1) / a.G;
-        const int g = min(row, R - 1) % a.G;
+        const int rc = min(row, R - 1);
+        const int i = (int)divide(rc, a.G, a.mul_g);
         node_of[rb] = i;
-        rg_of[rb] = row < R && !is_loader ? (b * a.N + i) * a.Hq + hk * a.G + g : -1;
+        rg_of[rb] = row < R && !is_loader ? (b * a.N + i) * a.Hq + hk * a.G + (rc - i * a.G) : -1;
     }
-
-    // (issued before the sequence length is first needed: the rows do not depend on it, and the length is a
-    // dependent load from device memory at the head of every workgroup's critical path)
-    // Q as the B operand of S^T = K.Q^T: lane (n, g2) holds Q[row n][16 s + 8 g2 .. +8) for s = 0..NS-1
+    // The wavefront's rows of Q pass through LDS, requested before the length is needed: direct-to-LDS loads into a part of
+    // its own (no barrier before it reads them back), with the slot permutation of K.  Rows beyond the last one repeat it and
+    // are never stored.  As plain register loads they would hold up the first block until every tile in flight has landed:
+    // the compiler's wait for them does not know of the tile fills behind them and awaits those as well.
     bf16x8 qreg[RB][NS];
+    if constexpr (KV8) {   // (the computing wavefronts have nothing else in flight: plain loads)
+        if (!is_loader) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        if (rg_of[rb] >= 0) {
-            const bf16x8* qp = reinterpret_cast<const bf16x8*>(static_cast<const uint16_t*>(a.q) + (int64_t)rg_of[rb] * DH + 8 * g2);
+            for (int rb = 0; rb < RB; ++rb) {
+                const int rg = (b * a.N + node_of[rb]) * a.Hq + hk * a.G + (min(row_base + (wrow * RB + rb) * 32 + n, R - 1) - node_of[rb] * a.G);
+                const bf16x8* qp = reinterpret_cast<const bf16x8*>(static_cast<const uint16_t*>(a.q) + (int64_t)rg * DH + 8 * g2);
 #pragma unroll
-            for (int s = 0; s < NS; ++s) qreg[rb][s] = qp[2 * s];
-        } else {
+                for (int s = 0; s < NS; ++s) qreg[rb][s] = qp[2 * s];
+            }
+        }
+    } else {
+        const uint32_t q_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)q_s;
 #pragma unroll
-            for (int s = 0; s < NS; ++s) qreg[rb][s] = bf16x8{};
+        for (int it = 0; it < 32 * RB / RPI; ++it) {
+            const int lrow = RPI * it + lane / SLOTS;
+            const int rc = min(row_base + wrow * RB * 32 + lrow, R - 1);
+            const int i = (int)divide(rc, a.G, a.mul_g);
+            const int rg = (b * a.N + i) * a.Hq + hk * a.G + (rc - i * a.G);
+            dma_load16_flat<false>(static_cast<const unsigned char*>(a.q) + (int64_t)rg * ROWB + 16 * ((lane % SLOTS) ^ (lrow & (SLOTS - 1))),
+                                   __builtin_amdgcn_readfirstlane(q_lds + it * 1024));
         }
     }
 
-    int L = a.seq_lens[b];
     L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
     const int Tk = L + a.N;
     int k0, k1, split;
     bool direct = a.nsplit == 1;   // this segment is the whole sequence: final rows are written here
+    const int nt = (Tk + kKeyTile - 1) / kKeyTile;
     if constexpr (!balanced) {
-        // the sequence's own 64-key tiles, dealt out as evenly as whole tiles allow (splits differ by at most one tile)
-        split = sigma % a.nsplit;
-        const int nt = (Tk + kKeyTile - 1) / kKeyTile;
-        k0 = (int)((int64_t)split * nt / a.nsplit) * kKeyTile;
-        k1 = min(Tk, (int)((int64_t)(split + 1) * nt / a.nsplit) * kKeyTile);
+        // the sequence's own 64-key tiles, dealt out as evenly as whole tiles allow (the first splits take one more)
+        const int hb = (int)divide(sigma, a.nsplit, a.mul_nsplit);
+        split = sigma - hb * a.nsplit;
+        const int q = (int)divide(nt, a.nsplit, a.mul_nsplit), r = nt - q * a.nsplit;
+        const int t0 = split * q + min(split, r);
+        k0 = t0 * kKeyTile;
+        k1 = min(Tk, (t0 + q + (split < r)) * kKeyTile);
     } else {
-        const int nt = (Tk + kKeyTile - 1) / kKeyTile;
         const int t0 = max(run_lo, tiles_before) - tiles_before, t1 = min(run_hi, tiles_before + nt) - tiles_before;
         const int s_first = slot_of_tile(tiles_before), s_last = slot_of_tile(tiles_before + nt - 1);
         tiles_before += nt;
@@ -222,8 +272,6 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         // the workgroup of kv head 0 and row tile 0 that holds the sequence's first tile tells the merge how many runs the
         // sequence fell into (the run boundaries are the same for every kv head and row tile)
         if (slot == s_first && hk == 0 && rt == 0 && tid == 0) a.seq_splits[b] = direct ? 0 : s_last - s_first + 1;
-    }
-    if constexpr (balanced) {
         k0 = uni(k0); k1 = uni(k1); split = uni(split); L = uni(L);
         direct = uni(direct) != 0;
     }
@@ -233,10 +281,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
             if (rg_of[rb] >= 0 && g2 == 0 && kh == 0) {
-                float* pml = a.part_ml + ((int64_t)split * rows_total + rg_of[rb]) * 2;
-                pml[0] = -INFINITY;
-                pml[1] = 0.f;
+                a.part_rec[(int64_t)split * a.rows_total + rg_of[rb]] = make_float3(-INFINITY, 0.f, 1.f);
             }
+        dma_wait_keep<0>();   // (the rows of Q still on their way belong to nobody)
         return;
     }
 
@@ -259,6 +306,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     const unsigned char* kt = uniform_ptr(static_cast<const unsigned char*>(a.k_tree) + ((int64_t)b * a.N * a.Hkv + hk) * (DH * EB));
     const unsigned char* vt = uniform_ptr(static_cast<const unsigned char*>(a.v_tree) + ((int64_t)b * a.N * a.Hkv + hk) * (DH * EB));
 
+    const int clean_end = min(L, k1);   // tiles that end here or earlier hold cache rows only
     // Direct-to-LDS tile fill: wave-instruction `inst` brings rows RPI*inst .. RPI*inst+RPI-1 of the tile;
     // lane l lands at byte 1024*inst + 16*l, i.e. row RPI*inst + l/SLOTS, slot' = l%SLOTS, and therefore
     // fetches the slot that the row's permutation maps there.  Rows past the end of the split fetch
@@ -269,59 +317,49 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // Addresses are a wave-uniform 64-bit base (one sequence's K or V slab) plus a 32-bit byte offset;
     // the host checks that a slab stays below 4 GiB.
     const uint32_t tok_bytes = (uint32_t)a.Hkv * DH * EB;
-    // per-lane byte offsets of this wavefront's loads inside a tile of cache rows (fast path below)
+    // Per-lane byte offsets of this wavefront's loads inside a tile of cache rows.  Its wave-instructions are STEP rows apart,
+    // a multiple of the permutations' period or (two filling wavefronts) of half of it.
     constexpr int FPW = (KT / RPI) / FILLERS;  // wave-instructions per filling wavefront, tile and tensor
-    uint32_t fill_k[FPW], fill_v[FPW];
+    constexpr int STEP = RPI * FILLERS, NPAT = STEP % SLOTS == 0 ? 1 : 2;
+    static_assert(STEP * NPAT % SLOTS == 0 && FPW % NPAT == 0, "the offsets repeat");
+    uint32_t fill_k[NPAT], fill_v[NPAT];
 #pragma unroll
-    for (int it = 0; it < FPW; ++it) {
-        const int row = RPI * (wave + it * FILLERS) + lane / SLOTS;
+    for (int it = 0; it < NPAT; ++it) {
+        const int row = RPI * wave + it * STEP + lane / SLOTS;
         const int slotp = lane % SLOTS;
         fill_k[it] = (uint32_t)row * tok_bytes + 16 * (slotp ^ (row & (SLOTS - 1)));
         fill_v[it] = (uint32_t)row * tok_bytes + 16 * (slotp ^ ((row & (NDB - 1)) << 2));
     }
-    auto fill_tile = [&](int buf, int tile_base) {
-        if (wave >= FILLERS) return;
-        const uint32_t kdst0 = k_lds + buf * TILEB + wave * 1024, vdst0 = v_lds + buf * TILEB + wave * 1024;
-        if (tile_base + KT <= min(L, k1)) {  // a whole tile of cache rows: the tile's base joins the scalar pointer,
-            // the per-lane offsets are constants of the kernel (no vector arithmetic per load)
-            const unsigned char* kc_t = uniform_ptr(kc + (size_t)((uint32_t)tile_base * tok_bytes));
-            const unsigned char* vc_t = uniform_ptr(vc + (size_t)((uint32_t)tile_base * tok_bytes));
-#pragma unroll
-            for (int it = 0; it < FPW; ++it) {
-                dma_load16<NT>(kc_t, fill_k[it], __builtin_amdgcn_readfirstlane(kdst0 + it * FILLERS * 1024));
-                dma_load16<NT>(vc_t, fill_v[it], __builtin_amdgcn_readfirstlane(vdst0 + it * FILLERS * 1024));
-            }
-            return;
-        }
-#pragma unroll
-        for (int it = 0; it < FPW; ++it) {
-            const int inst = wave + it * FILLERS;
-            const int row = RPI * inst + lane / SLOTS;
-            const int slotp = lane % SLOTS;
-            const int j0 = tile_base + RPI * inst;   // wave-uniform first key of these RPI rows
-            const int j = min(tile_base + row, k1 - 1);
-            const uint32_t kcol = 16 * (slotp ^ (row & (SLOTS - 1)));
-            const uint32_t vcol = 16 * (slotp ^ ((row & (NDB - 1)) << 2));
-            const uint32_t kdst = __builtin_amdgcn_readfirstlane(kdst0 + it * FILLERS * 1024);
-            const uint32_t vdst = __builtin_amdgcn_readfirstlane(vdst0 + it * FILLERS * 1024);
-            if (j0 + RPI <= L) {                     // cache rows only (uniform branch)
-                const uint32_t off = (uint32_t)j * tok_bytes;
-                dma_load16<NT>(kc, off + kcol, kdst);
-                dma_load16<NT>(vc, off + vcol, vdst);
-            } else if (j0 >= L) {                    // tree rows only
-                const uint32_t off = (uint32_t)(j - L) * tok_bytes;
-                dma_load16<NT>(kt, off + kcol, kdst);
-                dma_load16<NT>(vt, off + vcol, vdst);
-            } else {                                 // the rows straddle the end of the prefix
-                const bool in_cache = j < L;
+    // loads FROM .. TO-1 of the tile's PT: load i brings rows of wave-instruction i/2, of K (even) or V (odd)
+    auto fill_loads = [&](auto from, auto to, int buf, int tile_base, auto known_clean) __attribute__((always_inline)) {
+        constexpr int FROM = decltype(from)::value, TO = decltype(to)::value;
+        if (FILLERS < NW && wave >= FILLERS) return;
+        const uint32_t dst0 = buf * TILEB + wave * 1024;
+        if (known_clean || tile_base + KT <= clean_end) {  // a whole tile of cache rows: the tile's base joins the scalar
+            // pointer, the per-lane offsets are constants of the kernel (no vector arithmetic per load)
+            static_for<FROM, TO>([&](auto i) {
+                constexpr int it = decltype(i)::value / 2;
+                constexpr bool is_v = decltype(i)::value % 2 != 0;
+                const size_t off = (size_t)((uint32_t)(tile_base + it / NPAT * NPAT * STEP) * tok_bytes);
+                dma_load16<NT>(uniform_ptr((is_v ? vc : kc) + off), is_v ? fill_v[it % NPAT] : fill_k[it % NPAT],
+                               __builtin_amdgcn_readfirstlane((is_v ? v_lds : k_lds) + dst0 + it * FILLERS * 1024));
+            });
+        } else if (tile_base < k1) {
+            static_for<FROM, TO>([&](auto i) {
+                constexpr int it = decltype(i)::value / 2;
+                constexpr bool is_v = decltype(i)::value % 2 != 0;
+                const int row = RPI * (wave + it * FILLERS) + lane / SLOTS;
+                const int slotp = lane % SLOTS;
+                const int j = min(tile_base + row, k1 - 1);
+                const bool in_cache = j < L;             // rows of cache and tree by lane: no branches
                 const uint32_t off = (uint32_t)(in_cache ? j : j - L) * tok_bytes;
-                const void* kb = in_cache ? (const void*)kc : (const void*)kt;
-                const void* vb = in_cache ? (const void*)vc : (const void*)vt;
-                dma_load16_flat<NT>(static_cast<const unsigned char*>(kb) + off + kcol, kdst);
-                dma_load16_flat<NT>(static_cast<const unsigned char*>(vb) + off + vcol, vdst);
-            }
+                const unsigned char* base = is_v ? (in_cache ? vc : vt) : (in_cache ? kc : kt);
+                dma_load16_flat<NT>(base + off + 16 * (is_v ? slotp ^ ((row & (NDB - 1)) << 2) : slotp ^ (row & (SLOTS - 1))),
+                                    __builtin_amdgcn_readfirstlane((is_v ? v_lds : k_lds) + dst0 + it * FILLERS * 1024));
+            });
         }
     };
+    auto fill_tile = [&](int buf, int tile_base) { fill_loads(IntC<0>{}, IntC<PT>{}, buf, tile_base, std::false_type{}); };
 
     // KV8 loaders.  A tile is 16 wave-instructions of 16-byte loads: instruction g < 8 covers rows
     // 8g .. 8g+7 of K, instruction 8 + g the same rows of V, eight lanes per row and sixteen codes per
@@ -455,7 +493,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], int blk0, bool clean) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            if (!clean) {
+            if (__builtin_expect(!clean, 0)) {
                 uint32_t okmask = 0xffffffffu;  // bit u: key u of this block is visible to this lane's row
                 const int bt = blk0 - L;        // tree-node index of the block's first key (negative inside the prefix)
                 const uint32_t* w = anc_s + (node_of[rb] - i_first) * aw;
@@ -493,14 +531,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                 }
                 return ps;
             };
-            // Common case: the row has a reference and no weight comes out large -- no maximum is taken at all.
-            bool move = __any(m_ref[rb] == -INFINITY);  // a row without a reference yet (nothing visible so far)
-            float ps = 0.f;
-            if (!move) {
-                ps = weights(m_ref[rb]);
-                move = __any(!(ps <= kWeightSumLimit));  // scores that outgrew the reference
-            }
-            if (move) {
+            // Common case: the row has a reference and no weight comes out large -- no maximum is taken at all.  A row
+            // without a reference yet makes its sum infinite or NaN and so takes the other branch as well.
+            float ps = weights(m_ref[rb]);
+            if (__builtin_expect(__any(!(ps <= kWeightSumLimit)), 0)) {
                 // Rare, wave-uniform: set or raise the reference from the block's row maxima, rescale what has been summed.
                 float mt = st[rb][0];
 #pragma unroll
@@ -523,13 +557,15 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 
     static_assert(KT == 64, "the block pipeline below is written for two 32-key blocks per tile");
     const int ntiles = (k1 - k0 + KT - 1) / KT;
-    const int clean_end = min(L, k1);
-    auto build_masks = [&]() {  // every wavefront of the workgroup takes part
+    // The tree's parents go straight into LDS, requested before the tiles and awaited without them.
+    auto fetch_parents = [&]() {
         if (!has_tree_keys) return;
-        // one coalesced read of parent_idx; the walks up the tree then stay in LDS
         const int32_t* parent = a.parent_idx + (int64_t)b * a.N;
-        for (int t = tid; t < a.N; t += THREADS) parent_s[t] = parent[t];
-        if constexpr (KV8) lds_barrier(); else __syncthreads();
+        const uint32_t lds = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)parent_s;
+        for (int t = 64 * wave; t < a.N; t += 64 * NW)   // (the last lanes repeat the last entry; LDS is sized for that)
+            dma_load4(parent + min(t + lane, a.N - 1), __builtin_amdgcn_readfirstlane(lds + 4 * t));
+    };
+    auto build_masks = [&]() {  // every wavefront of the workgroup takes part, behind the barrier that publishes the parents
         for (int t = tid; t <= i_last - i_first; t += THREADS) {
             uint32_t* w = anc_s + t * aw;
             for (int x = 0; x < aw; ++x) w[x] = 0;
@@ -548,7 +584,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         if (is_loader) {
             Stage stage[NSET];
             static_for<0, NSET>([&](auto i) { stage_issue(stage[i.value], k0 + i.value * KT); });
-            build_masks();
+            if (has_tree_keys) {
+                lds_barrier();   // the computing wavefronts have the parents in LDS
+                build_masks();
+            }
             static_for<0, 3>([&](auto i) {
                 stage_write(stage[i.value], i.value);
                 stage_issue(stage[i.value], k0 + (NSET + i.value) * KT);
@@ -575,35 +614,65 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         }
     }
 
-    // prologue of the computing wavefronts: up to three tiles go into flight at once (direct-to-LDS
-    // path); the ancestor masks are built meanwhile
+    // prologue of the computing wavefronts: behind Q the parents and two tiles go into flight at once (direct-to-LDS path);
+    // meanwhile Q is read back and the ancestor masks are built; the barrier that publishes tile 0 also says that all of Q
+    // has left the buffer that tile 2 is then requested into
+    fetch_parents();
     if constexpr (!KV8) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            if (i < ntiles) fill_tile(i, k0 + i * KT);
+        fill_tile(0, k0);
+        if (ntiles > 1) fill_tile(1, k0 + KT);
     }
-    build_masks();
-    constexpr int PT2 = 2 * PT > 63 ? 63 : 2 * PT;  // a single filling wavefront has 64 loads in flight: wait for one more
-    if constexpr (KV8) {
+    auto wait_tiles_out = [&](bool both) {   // until at most the last one or both of the two tiles are out
+        if (KV8 || (FILLERS < NW && wave >= FILLERS)) dma_wait_keep<0>();
+        else if (both) dma_wait_keep<2 * PT>();
+        else dma_wait_keep<PT>();
+    };
+    if constexpr (!KV8) {
+        wait_tiles_out(ntiles > 1);
+        const unsigned char* qp = q_s + n * ROWB + 16 * (g2 ^ (n & 1));
+        const int pair_xor = ((n & (SLOTS - 1)) >> 1) << 5;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) qreg[0][s] = *reinterpret_cast<const bf16x8*>(qp + ((32 * s) ^ pair_xor));
+    }
+    if (has_tree_keys) {
+        if constexpr (KV8) dma_wait_keep<0>();
         lds_barrier();
-    } else {
-        if (ntiles >= 3) dma_wait_keep<PT2>(); else if (ntiles == 2) dma_wait_keep<PT>(); else dma_wait_keep<0>();
-        __syncthreads();  // tile 0 has landed for everybody; anc_s published
+        build_masks();
+    }
+    if constexpr (!KV8) {
+        if (ntiles > 1) wait_tiles_out(false); else dma_wait_keep<0>();
+    }
+    lds_barrier();  // tile 0 has landed for everybody, anc_s is published, Q is read
+    if constexpr (!KV8) {
+        if (ntiles > 2) fill_tile(2, k0 + 2 * KT);
     }
 
-    // After the barrier of iteration t every wavefront is done with tile t, whose buffer then receives
-    // tile t+3: by direct-to-LDS loads that the barrier of iteration t+2 awaits, or (KV8) from the loaders.
+    // The barrier of iteration t publishes tile t+1 and frees a buffer for tile t+3: that of tile t (three buffers: every
+    // wavefront has read it) or of tile t-1 (four buffers, PING: a wavefront may meet the barrier anywhere in iteration t).
+    // The new tile comes by direct-to-LDS loads that the barrier of iteration t+2 awaits, or (KV8) from the loaders.
     auto turn = [&](int t, int buf, int tile_base) {
         if constexpr (KV8) {
             lds_barrier();
         } else {
             if (t + 2 < ntiles) dma_wait_keep<PT>(); else dma_wait_keep<0>();  // tile t+1 landed, t+2 may be in flight
-            __syncthreads();
-            if (t + 3 < ntiles) fill_tile(buf, tile_base + 3 * KT);  // tile t's buffer: every wavefront has read it
+            lds_barrier();
+            if (t + 3 < ntiles) fill_tile(buf, tile_base + 3 * KT);
         }
     };
+    // PING: the barrier alone.  The loads of a tile are dealt out over the two matrix phases of an iteration instead (half 0
+    // in that of block 1 of iteration t, half 1 in that of block 0 of iteration t+1): all at once they queue up in front of
+    // the address unit, and the wavefronts stand behind them.
+    auto await_tile = [&](int t, bool late_, bool steady_) {   // tile t+1; a late wavefront is here before its second half of tile t+2
+        if (steady_ || t + 2 < ntiles) {
+            if (late_) dma_wait_keep<PT / 2>(); else dma_wait_keep<PT>();
+        } else {
+            dma_wait_keep<0>();
+        }
+    };
+    // No fence: what a wavefront has read from the freed buffer it consumed long ago, and LDS reads of its own that are still
+    // out need not be awaited here.
+    auto step = [] { asm volatile("s_barrier" ::: "memory"); };
 
-    // One barrier per tile (inside turn).
     bf16x8 ka[NS];
     i16x8 va[NDB][2];
     f32x16 st[RB];
@@ -620,16 +689,78 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // 256-row shape takes the branch: the six-wavefront shape measured 1.5 % slower with it.
     constexpr bool kSkipIdle = NW == 8 && KS == 1;
     const bool has_rows = !kSkipIdle || wave <= 4 || __builtin_amdgcn_readfirstlane((int)(row_base + wrow * RB * 32 < R)) != 0;
-    auto body = [&](int t, auto bufc) __attribute__((always_inline)) {
-        constexpr int buf = decltype(bufc)::value;
-        constexpr int buf_next = buf + 1 == NBUF ? 0 : buf + 1;
+    // PING: matrix and vector instructions of different wavefronts run side by side, but two wavefronts that want the same
+    // pipe get it one after the other, the older one first even if the younger is half through its phase: a pair that meets
+    // at one barrier per tile stays in step and takes turns at everything (3479 cycles per tile of 64 keys x 256 rows, of
+    // which the matrix pipe is busy 2262).  So the pair of a SIMD (wavefronts w and w + 4) is held in opposite phases: a
+    // barrier between any two phases, the later wavefront one phase behind.  2755 cycles per tile that way, 2660 with the
+    // conditions of the first and last tiles out of the loop (1284 rows x 32768 keys on 8 kv heads: 197 -> 182 us).  The
+    // shapes of four and six wavefronts keep one barrier per tile: most of their wavefronts are alone on their SIMD.
+    const bool late = PING && wave >= 4;
+    auto interleave_reads = [&]() {   // two LDS reads behind each of the NS matrix instructions
+        static_for<0, NS>([&](auto) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2 * NDB * 2 / NS, 0);
+        });
+    };
+    auto body = [&](int t, auto bufc, auto steady) __attribute__((always_inline)) {
+        constexpr bool STEADY = decltype(steady)::value;   // PING: tiles t .. t+3 are whole tiles of cache rows, t > 0
+        const int buf = bufc;   // (a compile-time constant after inlining, but for PING's general body)
+        const int buf_next = buf + 1 == NBUF ? 0 : buf + 1;
         const int tile_base = k0 + t * KT;
-        const bool clean = tile_base + KT <= clean_end;
+        const bool clean = STEADY || tile_base + KT <= clean_end;
         if (!has_rows) {
-            turn(t, buf, tile_base);
+            if constexpr (PING) {   // (an early or late wavefront alike: its loads keep to the second barrier of four)
+                if (!late) step();
+                await_tile(t, false, STEADY);
+                step();
+                if (t + 3 < ntiles) fill_tile((buf + 3) % NBUF, tile_base + 3 * KT);
+                step();
+                step();
+                if (late) step();
+            } else {
+                turn(t, buf, tile_base);
+            }
             return;
         }
-        if constexpr (KS == 1) {
+        if constexpr (PING) {
+            const int buf_p2 = (buf + 2) % NBUF, buf_p3 = (buf + 3) % NBUF;   // buffers of tiles t+2 and t+3
+            // Vector phase of block 0: the K operand of block 1 is requested, then the softmax.
+            read_k(buf, 1, ka);
+            __builtin_amdgcn_sched_barrier(0);
+            softmax(st, pb, tile_base, clean);
+            __builtin_amdgcn_sched_barrier(0);
+            if (late) await_tile(t, true, STEADY);
+            step();
+            // Matrix phase: O += V.P of this block; once its V operand is consumed the next one's is requested, between the
+            // matrix instructions of the next block's scores.
+            pv(va, pb);
+            __builtin_amdgcn_sched_barrier(0);
+            if (STEADY || t > 0) fill_loads(IntC<PT / 2>{}, IntC<PT>{}, buf_p2, tile_base + 2 * KT, steady);   // (the first three tiles came before the loop)
+            read_v(buf, 1, va);
+            qk(ka, st);
+            interleave_reads();
+            __builtin_amdgcn_sched_barrier(0);
+            // block 1 of the tile; the next tile is visible before its first operand is read
+            if (!late) await_tile(t, false, STEADY);
+            step();
+            if (STEADY || t + 1 < ntiles) read_k(buf_next, 0, ka);
+            __builtin_amdgcn_sched_barrier(0);
+            softmax(st, pb, tile_base + 32, clean);
+            __builtin_amdgcn_sched_barrier(0);
+            step();
+            pv(va, pb);
+            __builtin_amdgcn_sched_barrier(0);
+            fill_loads(IntC<0>{}, IntC<PT / 2>{}, buf_p3, tile_base + 3 * KT, steady);
+            if (STEADY || t + 1 < ntiles) {
+                read_v(buf_next, 0, va);
+                qk(ka, st);
+                interleave_reads();
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            step();
+            return;
+        } else if constexpr (KS == 1) {
             // block 0 of the tile
             read_v(buf, 0, va);
             __builtin_amdgcn_sched_barrier(0);
@@ -657,19 +788,37 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     };
     if (has_rows) {
         read_k(0, kh, ka);
+        if constexpr (PING) read_v(0, 0, va);
         qk(ka, st);
     }
-    static_assert(NBUF == 3, "the unrolling below names the three buffers");
     int t = 0;
-    for (; t + 3 <= ntiles; t += 3) {
-        body(t, IntC<0>{});
-        body(t + 1, IntC<1>{});
-        body(t + 2, IntC<2>{});
+    if (late) step();
+    if constexpr (PING) {
+        // The long middle part, where every tile touched is a whole tile of cache rows, carries no conditions and is unrolled
+        // with the buffer index a compile-time constant; the first tile and the last ones share one general body.
+        const int steady_end = (clean_end - k0) / KT - 3;   // (clean_end may lie below k0: then there is none)
+        while (t < ntiles) {
+            body(t, t % NBUF, std::false_type{});
+            ++t;
+            if (t != 1) continue;
+            while (t < steady_end) {
+                body(t, IntC<1>{}, std::true_type{});
+                if (++t >= steady_end) break;
+                body(t, IntC<2>{}, std::true_type{});
+                if (++t >= steady_end) break;
+                body(t, IntC<3>{}, std::true_type{});
+                if (++t >= steady_end) break;
+                body(t, IntC<0>{}, std::true_type{});
+                ++t;
+            }
+        }
+    } else {
+        for (; t + NBUF <= ntiles; t += NBUF) static_for<0, NBUF>([&](auto i) { body(t + i.value, i, std::false_type{}); });
+        static_for<0, NBUF - 1>([&](auto i) {
+            if (t + i.value < ntiles) body(t + i.value, i, std::false_type{});
+        });
     }
-    if (t < ntiles) {
-        body(t, IntC<0>{});
-        if (t + 1 < ntiles) body(t + 1, IntC<1>{});
-    }
+    if (PING && !late) step();
     if constexpr (KS == 2) {
         // Merge of the two key shares of a row block.  Both carry O~ and l relative to their own
         // reference m_ref; the share of block 1 hands its state over through the (now idle) tile
@@ -740,10 +889,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                 for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, fabsf(o[rb][db][v]));
             rmax = fmaxf(rmax, __shfl_xor(rmax, 32));
             const float c = fmaxf(rmax, 1e-30f);
-            const float inv_c = 1.f / c;
+            const float inv_c = __builtin_amdgcn_rcpf(c);   // (an ulp of the scale is nothing next to fp16's 2^-12)
             // The two lanes of a row hold alternating groups of four head_dim positions; swapping halves between them
             // (v_permlane32_swap) leaves each with eight consecutive ones, so a store covers 32 contiguous bytes of a row.
-            _Float16* po = reinterpret_cast<_Float16*>(a.part_o) + ((int64_t)split * rows_total + rg_of[rb]) * DH + 8 * g2;
+            _Float16* po = reinterpret_cast<_Float16*>(a.part_o) + ((int64_t)split * a.rows_total + rg_of[rb]) * DH + 8 * g2;
             u32x4 w[NDB][2];
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
@@ -767,21 +916,16 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                 for (int vp = 0; vp < 2; ++vp)
                     __builtin_nontemporal_store(w[db][vp], reinterpret_cast<u32x4*>(po + 32 * db + 16 * vp));
             __builtin_amdgcn_sched_barrier(0);
-            if (g2 == 0) a.part_c[(int64_t)split * rows_total + rg_of[rb]] = c * v_unit;  // KV8: V = v_scale * code value
-            if (g2 == 0) {
-                float* pml = a.part_ml + ((int64_t)split * rows_total + rg_of[rb]) * 2;
-                pml[0] = m_ref[rb] * kLn2;  // natural-log units of the scaled scores
-                pml[1] = l_tot;
-            }
+            if (g2 == 0)   // reference in base-2 units of the scaled scores; KV8: V = v_scale * code value
+                a.part_rec[(int64_t)split * a.rows_total + rg_of[rb]] = make_float3(m_ref[rb], l_tot, c * v_unit);
         }
     }
     }();   // one segment
     }      // segments of this workgroup
 }
 
-// Largest dynamic shared memory any shape asks for: six 16 KiB tiles (head_dim 128), ancestor masks of up to 257 nodes x
-// 32 words, and the parent table of 1024 nodes.  Every variant's limit is raised to it once per device.
-constexpr size_t kMaxSmem = (size_t)2 * 3 * 64 * 256 + (size_t)257 * 32 * 4 + 1024 * 4;
+// Every variant's limit is raised to all the shared memory of a compute unit once per device.
+constexpr size_t kMaxSmem = kAttnMfmaMaxSmem;
 
 template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128>
 hipError_t raise_variant() {
@@ -791,18 +935,14 @@ hipError_t raise_variant() {
 
 template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128>
 hipError_t launch_variant(const AttnArgs& a, const AttnPlan& p, hipStream_t st) {
-    const int S = a.slots > 0 ? a.Hkv * a.slots : a.B * a.Hkv * a.nsplit;   // K/V streams, each read by RT workgroups
-    const int RT = p.row_tiles;
-    const int S8 = (S + 7) / 8 * 8;
-    const int RW = NW / KS * RB * 32;
-    const int nodes_local = (RW + a.G - 1) / a.G + 1;
-    // three K and three V tile buffers, the ancestor bitmasks and the parent table
-    const size_t smem = (size_t)2 * 3 * KT * (2 * DHT) + (size_t)nodes_local * ((a.N + 31) / 32) * 4 + (size_t)a.N * 4;
+    // K/V streams, each read by p.row_tiles workgroups, which share an XCD (workgroups are dealt out to the XCDs in turn)
+    const dim3 grid((unsigned)((a.S + 7) / 8 * 8 * p.row_tiles));
+    const size_t smem = attn_mfma_smem(NW, KS, DHT, a.G, a.N);
     auto kern = attn_mfma_kernel<NW, RB, KT, KS, KV8, NT, BAL, DHT>;
     const unsigned threads = (NW + (KV8 ? 4 : 0)) * 64;  // KV8: plus the four loading wavefronts
     if (a.Dh != DHT) return hipErrorInvalidValue;
     if (smem > kMaxSmem) return hipErrorInvalidValue;  // cannot happen for N <= 1024: checked again for the sake of the launch
-    hipLaunchKernelGGL(kern, dim3((unsigned)(S8 * RT)), dim3(threads), smem, st, a, RT, S);
+    hipLaunchKernelGGL(kern, grid, dim3(threads), smem, st, a);
     return hipGetLastError();
 }
 
@@ -857,6 +997,17 @@ hipError_t raise_shapes() {
 }
 
 }  // namespace
+
+// Dynamic shared memory of a workgroup: three or four K and V tile buffers of 64 keys, space for Q where the spare buffers do
+// not hold it, the ancestor bitmasks of the nodes the rows belong to, and the parent table.
+size_t attn_mfma_smem(int waves, int kshares, int head_dim, int group, int nodes) {
+    const size_t tile = (size_t)64 * 2 * head_dim;
+    const int rw = waves / kshares * 32;
+    const int nodes_local = rw % group == 0 ? rw / group : (rw + group - 1) / group + 1;
+    const int nbuf = kshares == 1 && waves == 8 ? 4 : 3, q_outside = waves - 4 * (nbuf - 2);
+    return 2 * nbuf * tile + (q_outside > 0 ? q_outside * tile / 2 : 0) +
+           (size_t)nodes_local * ((nodes + 31) / 32) * 4 + (size_t)((nodes + 63) / 64) * 256;
+}
 
 hipError_t raise_limits_attn_mfma() {
     hipError_t e = raise_shapes<128>();

@@ -7,14 +7,17 @@
 // statistics are wave reductions, and lanes split head_dim for the value product.  This path is
 // exact fp32 throughout and serves the fp32 configuration and any shape the matrix-core kernel
 // does not take; it is not the bandwidth path.
-#include "ygg_internal.h"
+#include "attn_common.h"
 
 #include <hip/hip_bf16.h>
-typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-#include <hip/hip_ext.h>
+
+#include <type_traits>
 
 namespace ygg {
 namespace {
+
+using namespace attn;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -140,121 +143,139 @@ __global__ __launch_bounds__(256) void attn_vector_kernel(AttnArgs a) {
         }
     }
 
-    float* po = a.part_o + ((int64_t)split * rows + r) * DH + lane * EPL;
+    float* po = static_cast<float*>(a.part_o) + ((int64_t)split * rows + r) * DH + lane * EPL;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) po[e] = acc[e];
-    if (lane == 0) {
-        float* pml = a.part_ml + ((int64_t)split * rows + r) * 2;
-        pml[0] = m;
-        pml[1] = l;
-    }
+    if (lane == 0) a.part_rec[(int64_t)split * rows + r] = make_float3(m * kLog2e, l, 1.f);
 }
 
-// Merge of the per-split partials: m* = max_s m_s, l* = sum_s l_s e^{m_s - m*},
-// O = sum_s O~_s e^{m_s - m*} / l*, lse = m* + ln l*.
-// A group of DH/4 lanes owns one row, each lane four output elements.  The (m, l) records are read once per
-// row -- lane t of the group takes splits t and t + DH/4 -- and the maximum, the weights e^{m_s - m*} and l* are
-// formed inside the group with shuffles; the partial outputs are then fetched for the live splits only (m = -inf
-// marks an empty split, whose row of the workspace was never written), eight loads in flight at a time.  Balanced
-// batches: a sequence's splits are the runs its keys fell into, seq_splits[b] of them (a table the main kernel
-// fills); 0 means one run held the whole sequence and the main kernel wrote its final rows itself.
+// Merge of the per-split partials: m* = max_s m_s, l* = sum_s l_s 2^{m_s - m*}, O = sum_s O~_s 2^{m_s - m*} / l*,
+// lse = m* ln 2 + ln l*.
+// A group of TPR lanes covers a row with 16 bytes per lane (eight fp16 or four fp32 values); G such groups share one row,
+// taking every G-th split each (G = 64 / TPR where there are few rows: a lane then has few loads to wait for; else G = 1).
+// The records {m, l, c} are read once per row -- lane t of the row's lanes takes splits t, t + LPR, .. -- and m*, the
+// weights and l* are formed between them.  The kernel is one trip to memory: the first GS partial outputs are requested
+// together with the records, whatever their weights turn out to be; an empty split (m = -inf) has weight 0 and its row,
+// which was never written, is replaced by zeros.  Balanced batches: a sequence's splits are the runs its keys fell into,
+// seq_splits[b] of them (a table the main kernel fills); 0 means one run held the whole sequence and its rows are final
+// already.
 //
-// HALF: the partial outputs are the matrix-core kernels' (fp16, each row divided by its scale c, which is kept beside
-// m and l): split s then enters with weight w_s c_s instead of w_s; the normaliser is the same.
-template <typename T, int DH, bool HALF>
+// HALF: the partial outputs are the matrix-core kernels' (fp16, each row divided by its scale c): split s then enters with
+// weight w_s c_s instead of w_s; the normaliser is the same.
+template <typename T, int DH, bool HALF, int G>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
-    constexpr int TPR = DH / 4;  // lanes per row: 32 or 16, a power of two that divides the wavefront
-    constexpr int GS = 8;        // partial outputs in flight per lane
-    const int64_t rows = (int64_t)a.B * a.N * a.Hq;
-    const int64_t r_raw = (int64_t)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
-    const bool in_range = r_raw < rows;   // lanes beyond the last row keep their group's shuffles company
-    const int64_t r = in_range ? r_raw : rows - 1;
-    const int t = threadIdx.x % TPR, c = 4 * t;
-    constexpr int NH = 64 / TPR;          // records per lane: the host never plans more than 64 splits
+    constexpr int EPL = HALF ? 8 : 4;     // values per lane
+    constexpr int TPR = DH / EPL;         // lanes across a row: 8, 16 or 32
+    constexpr int LPR = TPR * G;          // lanes of a row
+    constexpr int GS = G > 1 ? 4 : 8;     // partial outputs in flight per lane
+    constexpr int NH = 64 / LPR;          // records per lane: the host never plans more than 64 splits
+    const int b = blockIdx.y;
+    const int rows_seq = a.N * a.Hq;
     int nsp = a.nsplit;
     if (a.seq_splits) {  // balanced batches: the sequence's own number of runs; 0 = its rows are final already
-        nsp = a.seq_splits[r / ((int64_t)a.N * a.Hq)];
-        if (nsp == 0) return;  // (the whole group agrees: same row)
+        nsp = a.seq_splits[b];
+        if (nsp == 0) return;
     }
+    const int r_raw = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+    const bool in_range = r_raw < rows_seq;   // lanes beyond the last row keep their group's exchanges company
+    const int64_t r = (int64_t)b * rows_seq + (in_range ? r_raw : rows_seq - 1);
+    const int64_t rows = a.rows_total;
+    const int t = threadIdx.x % LPR, col = t % TPR, grp = t / TPR;
+    const uint4* po = static_cast<const uint4*>(a.part_o) + r * TPR + col;   // split s: + s * rows * TPR
 
-    float m[NH], l[NH], cs[NH];
+    float3 rec[NH];
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-        const int sp = t + h * TPR;
-        m[h] = -INFINITY;
-        l[h] = 0.f;
-        cs[h] = 1.f;
-        if (sp < nsp) {
-            const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + ((int64_t)sp * rows + r) * 2);
-            if constexpr (HALF) cs[h] = a.part_c[(int64_t)sp * rows + r];  // (never written for an absent split: unused then)
-            m[h] = ml.x;
-            l[h] = ml.y;
-        }
+        rec[h] = make_float3(-INFINITY, 0.f, 1.f);
+        if (h * LPR >= nsp) continue;
+        const int sp = t + h * LPR;
+        if (sp < nsp) rec[h] = a.part_rec[(int64_t)sp * rows + r];
     }
-    float mstar = m[0];
+    uint4 raw[GS];
+    auto request = [&](int s0) {   // splits s0 + grp, s0 + grp + G, ..
 #pragma unroll
-    for (int h = 1; h < NH; ++h) mstar = fmaxf(mstar, m[h]);
+        for (int u = 0; u < GS; ++u) raw[u] = po[(int64_t)min(s0 + grp + u * G, nsp - 1) * rows * TPR];
+    };
+    request(0);
+
+    float mstar = rec[0].x;
 #pragma unroll
-    for (int o = TPR / 2; o > 0; o >>= 1) mstar = fmaxf(mstar, __shfl_xor(mstar, o, TPR));
+    for (int h = 1; h < NH; ++h) mstar = fmaxf(mstar, rec[h].x);
+    mstar = group_reduce(mstar, LPR, [](float x, float y) { return fmaxf(x, y); });
     // a row always has a visible key (itself), so some split is live and mstar is finite
     float w[NH], lstar = 0.f;
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-        w[h] = m[h] == -INFINITY ? 0.f : expf(m[h] - mstar);
-        lstar = fmaf(l[h], w[h], lstar);
-        if constexpr (HALF) w[h] = w[h] == 0.f ? 0.f : w[h] * cs[h];  // from here on w weighs the stored partial output
+        w[h] = rec[h].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(rec[h].x - mstar);
+        lstar = fmaf(rec[h].y, w[h], lstar);
+        w[h] = w[h] == 0.f ? 0.f : w[h] * rec[h].z;   // from here on w weighs the stored partial output
     }
-#pragma unroll
-    for (int o = TPR / 2; o > 0; o >>= 1) lstar += __shfl_xor(lstar, o, TPR);
+    lstar = group_reduce(lstar, LPR, [](float x, float y) { return x + y; });
 
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < nsp; s0 += GS) {
+    float acc[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+    for (int s0 = 0; s0 < nsp; s0 += GS * G) {
         float ws[GS];
-        float4 v[GS];   // HALF: the first two words hold the four fp16 values until every load of the batch is out
+#pragma unroll
+        for (int u = 0; u < GS; ++u) {   // weight of split s: lane s % LPR of the row's lanes, slot s / LPR
+            const int s = s0 + grp + u * G;
+            float wh = w[0];
+#pragma unroll
+            for (int h = 1; h < NH; ++h) wh = s / LPR == h ? w[h] : wh;
+            ws[u] = __shfl(wh, s % LPR, LPR);
+            if (s >= nsp) ws[u] = 0.f;
+        }
 #pragma unroll
         for (int u = 0; u < GS; ++u) {
-            const int sp = s0 + u;   // its weight sits in lane sp % TPR of the group, slot sp / TPR
-            float wsel = 0.f;
+            const uint4 x = ws[u] != 0.f ? raw[u] : make_uint4(0, 0, 0, 0);
+            const uint32_t d[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                const float wh = __shfl(w[h], sp % TPR, TPR);
-                if (sp / TPR == h) wsel = wh;
-            }
-            ws[u] = sp >= nsp ? 0.f : wsel;
-            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ws[u] != 0.f) {
+            for (int e = 0; e < 4; ++e) {
                 if constexpr (HALF) {
-                    const float2 raw = *reinterpret_cast<const float2*>(reinterpret_cast<const _Float16*>(a.part_o) + ((int64_t)sp * rows + r) * DH + c);
-                    v[u].x = raw.x;
-                    v[u].y = raw.y;
+                    const f16x2 h2 = __builtin_bit_cast(f16x2, d[e]);
+                    acc[2 * e] = fmaf((float)h2[0], ws[u], acc[2 * e]);
+                    acc[2 * e + 1] = fmaf((float)h2[1], ws[u], acc[2 * e + 1]);
                 } else {
-                    v[u] = *reinterpret_cast<const float4*>(a.part_o + ((int64_t)sp * rows + r) * DH + c);
+                    acc[e] = fmaf(__uint_as_float(d[e]), ws[u], acc[e]);
                 }
             }
         }
-#pragma unroll
-        for (int u = 0; u < GS; ++u) {
-            float4 x = v[u];
-            if constexpr (HALF) {
-                const f16x4 hv = __builtin_bit_cast(f16x4, make_float2(v[u].x, v[u].y));
-                x = make_float4((float)hv[0], (float)hv[1], (float)hv[2], (float)hv[3]);
-            }
-            acc[0] = fmaf(x.x, ws[u], acc[0]); acc[1] = fmaf(x.y, ws[u], acc[1]);
-            acc[2] = fmaf(x.z, ws[u], acc[2]); acc[3] = fmaf(x.w, ws[u], acc[3]);
-        }
+        if (s0 + GS * G < nsp) request(s0 + GS * G);
     }
-    if (!in_range) return;
+    if constexpr (G > 1) {   // the groups' shares of the sum
+#pragma unroll
+        for (int o = TPR; o < 64; o <<= 1)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) {
+                const uint32_t u = __float_as_uint(acc[e]);
+                float other[2];
+                if (o == 8) {   // (within a row of 16 lanes)
+                    other[0] = acc[e];
+                    other[1] = __uint_as_float(row_xor<8>(u));
+                } else {
+                    const auto p = o == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+                    other[0] = __uint_as_float(p[0]);
+                    other[1] = __uint_as_float(p[1]);
+                }
+                acc[e] = other[0] + other[1];
+            }
+    }
+    if (!in_range || grp > 0) return;
     const float inv = 1.f / lstar;
     if constexpr (sizeof(T) == 4) {
-        *reinterpret_cast<float4*>(static_cast<float*>(a.out) + r * DH + c) =
+        static_assert(!HALF, "fp32 outputs come from the vector kernel");
+        *reinterpret_cast<float4*>(static_cast<float*>(a.out) + r * DH + EPL * col) =
             make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
     } else {
-        __hip_bfloat16 h[4];
+        __hip_bfloat16 h[EPL];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = __float2bfloat16(acc[e] * inv);  // round to nearest even
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + r * DH + c) = *reinterpret_cast<uint2*>(h);
+        for (int e = 0; e < EPL; ++e) h[e] = __float2bfloat16(acc[e] * inv);  // round to nearest even
+        uint16_t* dst = static_cast<uint16_t*>(a.out) + r * DH + EPL * col;
+        if constexpr (HALF) *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<uint4*>(h);
+        else *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<uint2*>(h);
     }
-    if (a.lse && c == 0) a.lse[r] = mstar + logf(lstar);
+    if (a.lse && t == 0) a.lse[r] = mstar * kLn2 + logf(lstar);
 }
 
 template <typename T>
@@ -266,18 +287,18 @@ hipError_t launch_vector_t(const AttnArgs& a, const AttnPlan& p, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, bool HALF>
 hipError_t launch_combine_t(const AttnArgs& a, hipStream_t st) {
-    const int64_t rows = (int64_t)a.B * a.N * a.Hq;
-    if (a.Dh == 128) {
-        dim3 grid((unsigned)((rows + 7) / 8));
-        if (a.part_half) hipLaunchKernelGGL((attn_combine_kernel<T, 128, true>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((attn_combine_kernel<T, 128, false>), grid, dim3(256), 0, st, a);
-    } else {
-        dim3 grid((unsigned)((rows + 15) / 16));
-        if (a.part_half) hipLaunchKernelGGL((attn_combine_kernel<T, 64, true>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((attn_combine_kernel<T, 64, false>), grid, dim3(256), 0, st, a);
-    }
+    // up to four wavefronts' worth of rows per SIMD: a whole wavefront per row
+    const bool few = a.rows_total <= 4096;
+    auto go = [&](auto dh) {
+        constexpr int DH = decltype(dh)::value, TPR = DH / (HALF ? 8 : 4);
+        auto grid = [&](int lanes) { return dim3((unsigned)((a.N * a.Hq + 256 / lanes - 1) / (256 / lanes)), (unsigned)a.B); };
+        if (few) hipLaunchKernelGGL((attn_combine_kernel<T, DH, HALF, 64 / TPR>), grid(64), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((attn_combine_kernel<T, DH, HALF, 1>), grid(TPR), dim3(256), 0, st, a);
+    };
+    if (a.Dh == 128) go(std::integral_constant<int, 128>{});
+    else go(std::integral_constant<int, 64>{});
     return hipGetLastError();
 }
 
@@ -288,8 +309,8 @@ hipError_t launch_attn_vector(const AttnArgs& a, const AttnPlan& p, int dtype, h
 }
 
 hipError_t launch_attn_combine(const AttnArgs& a, const AttnPlan& p, int dtype, hipStream_t st) {
-    (void)p;
-    return dtype == YGG_F32 ? launch_combine_t<float>(a, st) : launch_combine_t<uint16_t>(a, st);
+    if (p.use_mfma) return launch_combine_t<uint16_t, true>(a, st);
+    return dtype == YGG_F32 ? launch_combine_t<float, false>(a, st) : launch_combine_t<uint16_t, false>(a, st);
 }
 
 }  // namespace ygg

@@ -91,6 +91,9 @@ AttnPlan plan_attention(const ygg_shape& s) {
             // instead of 640 padded rows and 10 instead of 6 key splits: 27.5 vs 28.1 us per call)
             if (padded(192) * 100 <= best * (p.kshares == 2 ? 92 : 80)) { p.waves = 6; p.kshares = 1; }
         }
+        // the widest trees (more than 900 nodes, one query head per kv head) leave no room for their masks beside 256 rows
+        const int G = s.n_q_heads / s.n_kv_heads;
+        while (p.kshares == 1 && p.waves > 4 && attn_mfma_smem(p.waves, 1, s.head_dim, G, s.n_nodes) > kAttnMfmaMaxSmem) p.waves -= 2;
         int64_t ns_forced = 0;
         if (const uint64_t ov = g_plan_override.load(std::memory_order_relaxed)) {
             const int w = (int)(ov >> 56), r = (int)(ov >> 48) & 0xff, k = (int)(ov >> 40) & 0xff;
@@ -111,9 +114,13 @@ AttnPlan plan_attention(const ygg_shape& s) {
         if (ns_forced) ns = ns_forced < tiles ? ns_forced : tiles;
         // Batches: sequence lengths live on the device and may be ragged, so instead of giving every sequence the same
         // number of splits the key tiles of all sequences are laid end to end and cut into equal runs, one per workgroup
-        // of a (kv head, row tile): 256 workgroups in all, each with the same number of tiles whatever the lengths.
+        // of a (kv head, row tile): 256 workgroups in all, each with the same number of tiles whatever the lengths.  A
+        // workgroup whose run spans two sequences starts its pipeline twice, about as long as three tiles take; where the
+        // longest sequence leaves a workgroup fewer than eight tiles anyway, that costs more than the raggedness (3
+        // sequences of up to 1531 tokens, 8 kv heads x 36 nodes: 21 us per call in runs, 16 in splits).
         const int64_t streams = (int64_t)s.n_kv_heads * p.row_tiles;
-        if (p.kshares == 1 && s.batch >= 2 && s.batch <= 256 && streams <= 128 && !ns_forced) {
+        const int64_t per_wg = ns > 0 ? tiles / ns : tiles;
+        if (p.kshares == 1 && s.batch >= 2 && s.batch <= 256 && streams <= 128 && !ns_forced && per_wg >= 8) {
             int64_t slots = 256 / streams;
             const int64_t most = (int64_t)s.batch * tiles;   // never more runs than tiles
             if (slots > most) slots = most;
@@ -136,8 +143,7 @@ AttnPlan plan_attention(const ygg_shape& s) {
     p.nsplit = p.slots > 0 ? p.slots : (int32_t)ns;   // balanced batches: a sequence may span every run
     // matrix-core kernels: fp16 partial outputs with one fp32 scale per row; vector kernel: fp32 partial outputs
     p.part_o_bytes = align256((size_t)p.nsplit * (size_t)rows * (size_t)s.head_dim * (p.use_mfma ? 2 : 4));
-    p.part_ml_bytes = align256((size_t)p.nsplit * (size_t)rows * 2 * sizeof(float));
-    p.part_c_bytes = p.use_mfma ? align256((size_t)p.nsplit * (size_t)rows * sizeof(float)) : 0;
+    p.part_rec_bytes = align256((size_t)p.nsplit * (size_t)rows * sizeof(float3));
     p.seq_splits_bytes = p.slots > 0 ? align256((size_t)s.batch * sizeof(int32_t)) : 0;
     return p;
 }
@@ -199,7 +205,7 @@ size_t ygg_workspace_bytes(const ygg_shape* s, int32_t op, int32_t n_layers) {
         case YGG_OP_ATTENTION: {
             if (check_shape(s, true, false) != YGG_OK) return 0;
             const AttnPlan p = plan_attention(*s);
-            return p.part_o_bytes + p.part_ml_bytes + p.part_c_bytes + p.seq_splits_bytes;
+            return p.part_o_bytes + p.part_rec_bytes + p.seq_splits_bytes;
         }
         case YGG_OP_EXPAND:
         case YGG_OP_ATTACH: {
@@ -230,22 +236,27 @@ static int32_t tree_attention_impl(const ygg_shape* s, const void* q, const void
     if ((int64_t)s->batch * s->n_nodes * s->n_q_heads > 0x7fffffffLL) return YGG_ERR_UNSUPPORTED;
     if (s->kv_capacity * s->n_kv_heads * s->head_dim * elem > 0xffffffffLL) return YGG_ERR_UNSUPPORTED;
     const AttnPlan p = plan_attention(*s);
-    if (int32_t rc = check_workspace(workspace, workspace_bytes, p.part_o_bytes + p.part_ml_bytes + p.part_c_bytes + p.seq_splits_bytes)) return rc;
+    if (int32_t rc = check_workspace(workspace, workspace_bytes, p.part_o_bytes + p.part_rec_bytes + p.seq_splits_bytes)) return rc;
     if (int32_t rc = ensure_device_ready()) return rc;
 
     AttnArgs a{};
     a.q = q; a.k_cache = k_cache; a.v_cache = v_cache; a.k_tree = k_tree; a.v_tree = v_tree;
     a.seq_lens = seq_lens; a.parent_idx = parent_idx; a.k_scale = k_scale; a.v_scale = v_scale;
-    a.part_o = static_cast<float*>(workspace);
-    a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + p.part_o_bytes);
-    a.part_c = reinterpret_cast<float*>(static_cast<char*>(workspace) + p.part_o_bytes + p.part_ml_bytes);
-    a.seq_splits = p.slots > 0 ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + p.part_o_bytes + p.part_ml_bytes + p.part_c_bytes) : nullptr;
-    a.part_half = p.use_mfma;
+    a.part_o = workspace;
+    a.part_rec = reinterpret_cast<float3*>(static_cast<char*>(workspace) + p.part_o_bytes);
+    a.seq_splits = p.slots > 0 ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + p.part_o_bytes + p.part_rec_bytes) : nullptr;
     a.out = out; a.lse = lse;
     a.B = s->batch; a.N = s->n_nodes; a.Hq = s->n_q_heads; a.Hkv = s->n_kv_heads;
     a.G = s->n_q_heads / s->n_kv_heads; a.Dh = s->head_dim;
     a.nsplit = p.nsplit; a.max_seq_len = s->max_seq_len; a.cap = s->kv_capacity; a.scale = s->softmax_scale;
     a.slots = p.slots;
+    a.S = p.slots > 0 ? a.Hkv * p.slots : a.B * a.Hkv * p.nsplit;
+    a.rows_total = a.B * a.N * a.Hq;
+    a.mul_nsplit = 0xffffffffu / (uint32_t)a.nsplit;
+    a.mul_hkv = 0xffffffffu / (uint32_t)a.Hkv;
+    a.mul_g = 0xffffffffu / (uint32_t)a.G;
+    a.row_tiles = p.row_tiles > 0 ? p.row_tiles : 1;
+    a.mul_rt = 0xffffffffu / (uint32_t)a.row_tiles;
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const int out_dtype = s->kv_dtype == YGG_F32 ? YGG_F32 : YGG_BF16;  // element type of Q and O

@@ -27,17 +27,19 @@ struct AttnArgs {
     const int32_t* parent_idx;
     const float* k_scale;  // [Hkv], both set: K and V hold 8-bit E4M3 codes; both null: plain elements
     const float* v_scale;
-    float* part_o;    // [nsplit][B*N*Hq][Dh]  fp32 O~, or (part_half) fp16 O~ / part_c: same indexing, half the bytes
-    float* part_ml;   // [nsplit][B*N*Hq][2]   (running max m in scaled-score units, sum l)
-    float* part_c;    // [nsplit][B*N*Hq]      part_half only: the row's scale, max |O~| over head_dim
+    void* part_o;         // [nsplit][B*N*Hq][Dh]  matrix-core kernels: fp16 O~ / c; vector kernel: fp32 O~
+    float3* part_rec;     // [nsplit][B*N*Hq]      {m in base-2 units of the scaled scores, l, c}; m = -inf: absent
     int32_t* seq_splits;  // [B], balanced batches only: how many runs a sequence's keys fell into (its partials carry split
                           // indices 0 .. n-1), or 0 if one run held it all and its rows are final already
-    int32_t part_half;  // 1: the matrix-core kernels' partial outputs (fp16, scaled per row); 0: the vector kernel's fp32 ones
     void* out;
     float* lse;
     int32_t B, N, Hq, Hkv, G, Dh;
     int32_t nsplit, max_seq_len;
     int32_t slots;    // matrix-core kernel, batches: > 0 = workgroups take equal runs of the concatenated key tiles (nsplit = slots)
+    int32_t S;        // matrix-core kernel: K/V streams, slots * Hkv or B * Hkv * nsplit
+    int32_t rows_total;                        // B * N * Hq
+    int32_t row_tiles;                         // matrix-core kernel: workgroups along the query rows
+    uint32_t mul_nsplit, mul_hkv, mul_g, mul_rt;   // (2^32 - 1) / d: reciprocals for the kernels' divisions
     int64_t cap;
     float scale;
 };
@@ -50,12 +52,14 @@ struct AttnPlan {
     int32_t kshares;        // MFMA kernel: 1, or 2 = pairs of wavefronts split every key tile
     int32_t row_tiles;      // MFMA kernel: workgroups along the N*G query rows of one kv head
     int32_t slots;          // MFMA kernel, batches: equal runs of key tiles per (kv head, row tile); 0 = one sequence per workgroup
-    size_t part_o_bytes, part_ml_bytes, part_c_bytes, seq_splits_bytes;
+    size_t part_o_bytes, part_rec_bytes, seq_splits_bytes;
 };
 
 AttnPlan plan_attention(const ygg_shape& s);
 hipError_t launch_attn_vector(const AttnArgs& a, const AttnPlan& p, int dtype, hipStream_t st);
 hipError_t launch_attn_mfma(const AttnArgs& a, const AttnPlan& p, hipStream_t st);
+size_t attn_mfma_smem(int waves, int kshares, int head_dim, int group, int nodes);
+constexpr size_t kAttnMfmaMaxSmem = 160 * 1024;   // shared memory of a compute unit
 hipError_t launch_attn_combine(const AttnArgs& a, const AttnPlan& p, int dtype, hipStream_t st);
 
 // One-time raising of the dynamic shared-memory limits of every kernel variant of a translation unit (current device).

@@ -1,0 +1,51 @@
+"""Tree attention where its kernels change course: every workgroup shape from one key tile upwards (the pipelines' first and
+last tiles, tiles that are partly prefix, partly tree or cut short), row counts that leave wavefronts idle, batches cut into
+runs, and the merge of few and many key splits for few and many rows.  Bounds as in test_gpu_attention."""
+import pytest
+
+import paper_2512_23858_amd as ygg
+from gpu_util import shape_of
+from test_gpu_attention import _cfg, _check, _inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def plan():
+    yield ygg.set_attention_plan
+    ygg.set_attention_plan()
+
+
+# query heads on one kv head and a tree of 41 nodes: 246 rows, or 41 with one query head
+@pytest.mark.parametrize("waves,kshares,Hq", [(8, 1, 6), (8, 1, 4), (6, 1, 6), (4, 1, 6), (8, 2, 6), (4, 2, 2), (2, 2, 1)])
+@pytest.mark.parametrize("Dh", [128, 64])
+@pytest.mark.parametrize("nsplit", [1, 2])
+def test_every_workgroup_shape_from_one_tile_upwards(plan, waves, kshares, Hq, Dh, nsplit):
+    plan(waves=waves, rblocks=1, kshares=kshares, nsplit=nsplit)
+    for keys in (41, 63, 64, 65, 100, 129, 192, 200, 257, 320, 330, 385, 450, 513, 640, 705, 1000):
+        L = keys - 41
+        cfg, host, parent = _inputs(_cfg(1, Hq, 1, 5, 8, Dh=Dh, seed=31), [L], max(L, 1), tree_gain=2.0)
+        got = ygg.attention_plan(shape_of(cfg, max_seq_len=max(L, 1)))
+        assert (got["waves"], got["key_shares"]) == (waves, kshares)
+        _check(cfg, host, parent, max(L, 1))
+
+
+# more than eight tiles to a workgroup of the longest sequence: the batch is cut into equal runs of tiles
+@pytest.mark.parametrize("B,Hq,Hkv,D,W,lens,Dh", [
+    (5, 32, 4, 6, 8, [5000, 0, 64, 1500, 333], 128),            # two row tiles, an empty and a one-tile prefix
+    (9, 32, 8, 5, 7, [4000, 100, 15, 15, 2000, 1, 700, 64, 3999], 128),
+    (16, 24, 4, 5, 8, [64 * i * 4 % 4096 for i in range(16)], 64),
+])
+def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh):
+    cfg, host, parent = _inputs(_cfg(B, Hq, Hkv, D, W, Dh=Dh, seed=41), lens, max(lens), tree_gain=2.0)
+    _check(cfg, host, parent, max(lens))
+
+
+# merge: whole wavefronts per row up to 4096 rows, fewer lanes above; rounds of 8, 16 or 32 splits
+@pytest.mark.parametrize("nsplit", [2, 7, 8, 9, 16, 17, 33, 70])
+@pytest.mark.parametrize("dtype,Dh", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+def test_merge_of_few_and_many_splits(plan, nsplit, dtype, Dh):
+    plan(nsplit=nsplit)
+    for Hq, Hkv, D, W in ((3, 3, 3, 5), (64, 4, 5, 13)):        # 48 and 4224 rows
+        cfg, host, parent = _inputs(_cfg(1, Hq, Hkv, D, W, dtype=dtype, Dh=Dh, seed=53), [2200], 2200)
+        _check(cfg, host, parent, 2200)

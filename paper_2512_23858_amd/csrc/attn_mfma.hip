@@ -141,8 +141,11 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     //   balanced  (a.slots > 0, batches) sigma = (kv head, slot).  The sequences' 64-key tiles are laid end to end and
     //             cut into a.slots runs of equal length; the workgroup serves its run, i.e. the tail of one sequence,
     //             whole short sequences, the head of another, one segment after the other.  Every workgroup then has the
-    //             same number of tiles whatever the mix of lengths (a ragged batch otherwise takes as long as its longest
-    //             sequence).  Segment number (slot - first slot of the sequence) is the split index of its partials;
+    //             same work whatever the mix of lengths (a ragged batch otherwise takes as long as its longest sequence).
+    //             A segment costs more than its tiles (Q, masks, an empty pipeline, the partial rows), so every sequence
+    //             is laid out with a.lead empty tiles in front of it: the runs that hold many short sequences get
+    //             fewer tiles.  A run may fall wholly inside these and then has nothing to do; a sequence's own tiles are
+    //             contiguous, so the runs it falls into are consecutive.  Segment number (slot - first slot of the sequence) is the split index of its partials;
     //             nsplit = a.slots bounds it.  A sequence that lies inside one slot is written out directly.
     // The head of the kernel is a chain of dependent scalar work in front of the first tile fill (the length is a load from
     // device memory), so divisions are multiplications by host-made reciprocals and the lengths of a batch are read by one
@@ -167,12 +170,11 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             const int bb = 64 * c + lane;
             int Lb = bb < a.B ? a.seq_lens[bb] : 0;
             Lb = Lb < 0 ? 0 : (Lb > a.max_seq_len ? a.max_seq_len : Lb);
-            tl[c] = bb < a.B ? (Lb + a.N + kKeyTile - 1) / kKeyTile : 0;
+            tl[c] = bb < a.B ? (Lb + a.N + kKeyTile - 1) / kKeyTile + a.lead : 0;
             mine += tl[c];
         }
         const int tiles_all = wave_sum_i32(mine);
-        // never more runs than tiles (the host sized the grid for the longest lengths the shape allows): every run then
-        // holds a tile, so the runs a sequence falls into are consecutive and its split indices have no gaps
+        // (never more runs than units: the host sized the grid for the longest lengths the shape allows)
         const int nruns = min(a.slots, tiles_all);
         if (slot >= nruns) return;   // a workgroup beyond the last run: nothing to do
         run_q = nruns == a.slots ? (int)divide(tiles_all, a.slots, a.mul_nsplit) : 1;
@@ -180,13 +182,14 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         run_lo = slot * run_q + min(slot, run_r);
         run_hi = run_lo + run_q + (slot < run_r);
         // first and last sequence with tiles inside [run_lo, run_hi), from the prefix sums over the batch
-        b_first = b_last = 0;
+        b_first = 0;
+        b_last = -1;
         int base = 0;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             if (64 * c >= a.B) break;
             const int incl = base + wave_prefix_i32(tl[c], lane);
-            const uint64_t upto = __ballot(incl <= run_lo), before = __ballot(incl - tl[c] < run_hi && tl[c] > 0);
+            const uint64_t upto = __ballot(incl <= run_lo), before = __ballot(incl - tl[c] + a.lead < run_hi && tl[c] > 0);
             const int nf = (int)__popcll(upto), nl = (int)__popcll(before);
             if (b_first == 64 * c && nf < 64) tiles_before = __builtin_amdgcn_readlane(incl - tl[c], nf);
             if (b_first == 64 * c) b_first += nf;
@@ -202,7 +205,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     if constexpr (balanced) {
         b_first = uni(b_first); b_last = uni(b_last); run_lo = uni(run_lo); run_hi = uni(run_hi);
-        tiles_before = uni(tiles_before); run_q = uni(run_q); run_r = uni(run_r);
+        tiles_before = uni(tiles_before) + a.lead; run_q = uni(run_q); run_r = uni(run_r);
     }
 
     for (int b = b_first; b <= b_last; ++b) {
@@ -263,10 +266,13 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     } else {
         const int t0 = max(run_lo, tiles_before) - tiles_before, t1 = min(run_hi, tiles_before + nt) - tiles_before;
         const int s_first = slot_of_tile(tiles_before), s_last = slot_of_tile(tiles_before + nt - 1);
-        tiles_before += nt;
+        tiles_before += nt + a.lead;
         k0 = t0 * kKeyTile;
         k1 = min(Tk, t1 * kKeyTile);
-        if (t0 >= t1) continue;   // (cannot happen for b_first .. b_last; keeps a wrong split index out of the workspace)
+        if (t0 >= t1) {   // (cannot happen for b_first .. b_last; keeps a wrong split index out of the workspace)
+            dma_wait_keep<0>();
+            continue;
+        }
         split = slot - s_first;
         direct = s_first == s_last;
         // the workgroup of kv head 0 and row tile 0 that holds the sequence's first tile tells the merge how many runs the

@@ -35,6 +35,8 @@ def test_every_workgroup_shape_from_one_tile_upwards(plan, waves, kshares, Hq, D
     (5, 32, 4, 6, 8, [5000, 0, 64, 1500, 333], 128),            # two row tiles, an empty and a one-tile prefix
     (9, 32, 8, 5, 7, [4000, 100, 15, 15, 2000, 1, 700, 64, 3999], 128),
     (16, 24, 4, 5, 8, [64 * i * 4 % 4096 for i in range(16)], 64),
+    (16, 32, 4, 6, 8, [0] * 9 + [5000] + [3] * 6, 128),         # many sequences of one tile: runs without a tile of their own
+    (2, 28, 4, 5, 8, [3000, 0], 128),
 ])
 def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh):
     cfg, host, parent = _inputs(_cfg(B, Hq, Hkv, D, W, Dh=Dh, seed=41), lens, max(lens), tree_gain=2.0)

@@ -65,6 +65,52 @@ int32_t check_workspace(const void* ws, size_t have, size_t need) {
 
 }  // namespace
 
+// Splits of every sequence's key tiles for a workgroup shape: fill the 256 CUs once -- the tile buffers leave room for one
+// workgroup per CU, and a second round of workgroups pays the start-up latency again while more splits add partial-result
+// traffic -- with about three key tiles per split at least (17 tiles of 49 rows on 32 kv heads: 5 / 6 / 8 splits measured
+// 16.4 / 15.7 / 16.4 us per layer).
+static int64_t equal_splits(const ygg_shape& s, int row_tiles, int64_t tiles) {
+    int64_t ns = 256 / ((int64_t)s.batch * s.n_kv_heads * row_tiles);
+    if (ns > (tiles + 2) / 3) ns = (tiles + 2) / 3;
+    return ns < 1 ? 1 : ns;   // (plan_attention keeps to 64, which the merge takes)
+}
+// More key tiles than this to a workgroup of the longest sequence: a batch is cut into equal runs instead (plan_attention).
+static constexpr int64_t kTilesForRuns = 8;
+
+// The padded rows decide where a workgroup streams many key tiles.  Where its share of them is short, a workgroup of fewer rows
+// is the better one: it starts sooner (fewer rows of Q, fewer wavefronts to meet) and its tiles take less time, so with the
+// compute units filled either way the call is done sooner although each K/V byte is fetched for fewer rows.  The estimate is a
+// start and a time per tile of 64 keys for each shape, in us, fitted per head_dim (128: 56 calls of 129 to 516 rows on 8 and 32
+// kv heads over 1024 to 16384 tokens, mean error 4 %), plus the merge.  The shape of fewest padded rows stays unless another
+// promises 4 % less.  Measured, us per call with the shape of fewest padded rows -> with this rule's, 8 kv heads: 196 rows
+// x 633 tokens 17.4 -> 12.7 (tiles of 256 rows -> 64), x 4096 20.4 -> 16.6, 176 x 2078 17.8 -> 14.7 (192 -> 64), 516 x 1024
+// 17.8 -> 16.7 (192 -> 64), 392 x 4096 21.7 -> 20.9 (256 -> 128); 32 kv heads: 321 rows x 4096 48.1 -> 43.2 (128 -> 192).  At
+// 16384 tokens tiles of 256 lead again (392 rows: 39.0, of 128 44.3).
+static void short_run_shape(const ygg_shape& s, int R, int64_t tiles, AttnPlan& p) {
+    struct Kind { int32_t waves, kshares; float start, tile; };
+    static constexpr Kind kinds128[] = {{8, 1, 14.0f, 1.30f}, {6, 1, 11.5f, 1.41f}, {4, 1, 10.6f, 1.15f}, {8, 2, 11.9f, 0.87f}, {4, 2, 10.5f, 0.69f}};
+    static constexpr Kind kinds64[] = {{8, 1, 13.0f, 0.95f}, {6, 1, 11.3f, 1.00f}, {4, 1, 10.6f, 0.85f}, {8, 2, 11.0f, 0.66f}, {4, 2, 9.7f, 0.50f}};
+    const Kind(&kinds)[5] = s.head_dim == 128 ? kinds128 : kinds64;
+    constexpr float kNo = 1e30f;
+    auto estimate = [&](const Kind& k) {
+        const int rows = k.waves / k.kshares * 32, row_tiles = (R + rows - 1) / rows;
+        if ((int64_t)s.batch * s.n_kv_heads * row_tiles > 256) return kNo;   // more than one round of workgroups: not fitted
+        int64_t ns = equal_splits(s, row_tiles, tiles);
+        if (s.batch >= 2 && k.kshares == 1 && tiles / ns >= kTilesForRuns) return kNo;   // a batch in equal runs
+        if (ns > 64) ns = 64;
+        const float merge = ns > 1 ? 4e-7f * (float)ns * (float)s.batch * (float)s.n_kv_heads * (float)R * (float)s.head_dim : 0.f;
+        return k.start + k.tile * (float)((tiles + ns - 1) / ns) + merge;
+    };
+    const Kind* best = nullptr;
+    float least = 0.f;
+    for (const Kind& k : kinds)
+        if (k.waves == p.waves && k.kshares == p.kshares) least = 0.96f * estimate(k);
+    if (least > 0.9f * kNo) return;
+    for (const Kind& k : kinds)
+        if (estimate(k) < least) { best = &k; least = estimate(k); }
+    if (best) { p.waves = best->waves; p.kshares = best->kshares; }
+}
+
 AttnPlan plan_attention(const ygg_shape& s) {
     AttnPlan p{};
     const int64_t rows = (int64_t)s.batch * s.n_nodes * s.n_q_heads;
@@ -97,6 +143,7 @@ AttnPlan plan_attention(const ygg_shape& s) {
             // instead of 640 padded rows and 10 instead of 6 key splits: 27.5 vs 28.1 us per call)
             if (padded(192) * 100 <= best * (p.kshares == 2 ? 92 : 80)) { p.waves = 6; p.kshares = 1; }
         }
+        if (!kv8 && R > 64) short_run_shape(s, R, tiles, p);
         // the widest trees (more than 900 nodes, one query head per kv head) leave no room for their masks beside 256 rows
         const int G = s.n_q_heads / s.n_kv_heads;
         while (p.kshares == 1 && p.waves > 4 && attn_mfma_smem(p.waves, 1, s.head_dim, G, s.n_nodes) > kAttnMfmaMaxSmem) p.waves -= 2;
@@ -110,13 +157,7 @@ AttnPlan plan_attention(const ygg_shape& s) {
         }
         const int rw = p.waves / p.kshares * p.rblocks * 32;
         p.row_tiles = (R + rw - 1) / rw;
-        // fill the 256 CUs once -- the tile buffers leave room for one workgroup per CU, and a second round of
-        // workgroups pays the start-up latency again while more splits add partial-result traffic --
-        // with about three key tiles per split at least (config 2's 17 tiles: 5 / 6 / 8 splits measured 16.4 / 15.7 / 16.4 us
-        // per layer)
-        const int64_t per_split = (int64_t)s.batch * s.n_kv_heads * p.row_tiles;
-        ns = 256 / per_split;
-        if (ns > (tiles + 2) / 3) ns = (tiles + 2) / 3;
+        ns = equal_splits(s, p.row_tiles, tiles);
         if (ns_forced) ns = ns_forced < tiles ? ns_forced : tiles;
         // Batches: sequence lengths live on the device and may be ragged, so instead of giving every sequence the same
         // number of splits the key tiles of all sequences are laid end to end and cut into equal runs, one per workgroup
@@ -126,7 +167,7 @@ AttnPlan plan_attention(const ygg_shape& s) {
         // sequences of up to 1531 tokens, 8 kv heads x 36 nodes: 21 us per call in runs, 16 in splits).
         const int64_t streams = (int64_t)s.n_kv_heads * p.row_tiles;
         const int64_t per_wg = ns > 0 ? tiles / ns : tiles;
-        if (p.kshares == 1 && s.batch >= 2 && s.batch <= 256 && streams <= 128 && !ns_forced && per_wg >= 8) {
+        if (p.kshares == 1 && s.batch >= 2 && s.batch <= 256 && streams <= 128 && !ns_forced && per_wg >= kTilesForRuns) {
             int64_t slots = 256 / streams;
             const int64_t most = (int64_t)s.batch * tiles;   // never more runs than tiles
             if (slots > most) slots = most;

@@ -51,3 +51,11 @@ def test_merge_of_few_and_many_splits(plan, nsplit, dtype, Dh):
     for Hq, Hkv, D, W in ((3, 3, 3, 5), (64, 4, 5, 13)):        # 48 and 4224 rows
         cfg, host, parent = _inputs(_cfg(1, Hq, Hkv, D, W, dtype=dtype, Dh=Dh, seed=53), [2200], 2200)
         _check(cfg, host, parent, 2200)
+
+
+# where a workgroup's share of the keys is short the launch plan takes fewer rows per workgroup than padding alone would
+@pytest.mark.parametrize("Hq,Hkv,D,W,L", [(32, 8, 6, 8, 4096), (32, 8, 6, 8, 500), (64, 8, 6, 8, 4096), (32, 8, 8, 16, 1024), (32, 32, 10, 32, 4096)])
+def test_short_runs_of_many_rows(Hq, Hkv, D, W, L):
+    cfg, host, parent = _inputs(_cfg(1, Hq, Hkv, D, W, seed=61), [L], L, tree_gain=2.0)
+    assert ygg.attention_plan(shape_of(cfg, max_seq_len=L))["key_splits"] > 1
+    _check(cfg, host, parent, L)

@@ -96,7 +96,8 @@ static void short_run_shape(const ygg_shape& s, int R, int64_t tiles, AttnPlan& 
         const int rows = k.waves / k.kshares * 32, row_tiles = (R + rows - 1) / rows;
         if ((int64_t)s.batch * s.n_kv_heads * row_tiles > 256) return kNo;   // more than one round of workgroups: not fitted
         int64_t ns = equal_splits(s, row_tiles, tiles);
-        if (s.batch >= 2 && k.kshares == 1 && tiles / ns >= kTilesForRuns) return kNo;   // a batch in equal runs
+        if (s.batch >= 2 && tiles / ns >= kTilesForRuns) return kNo;   // a batch in equal runs
+        if (s.batch >= 2 && p.kshares == 1 && k.kshares > 1) return kNo;   // stays a plan that runs can serve (pairs cannot), whatever the length bound
         if (ns > 64) ns = 64;
         const float merge = ns > 1 ? 4e-7f * (float)ns * (float)s.batch * (float)s.n_kv_heads * (float)R * (float)s.head_dim : 0.f;
         return k.start + k.tile * (float)((tiles + ns - 1) / ns) + merge;

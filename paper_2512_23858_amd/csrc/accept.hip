@@ -50,23 +50,26 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(AcceptArgs a) {
 
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    // 16-byte loads need the row start and the chunk start 16-byte aligned: V % 4 == 0 (chunk is)
-    if ((a.V & 3) == 0) {
-        const float4* x4 = reinterpret_cast<const float4*>(x);
-        for (int j = c0 / 4 + tid; j < c1 / 4; j += 256) {
-            const float4 v = x4[j];
-            // ascending index order inside the thread, strict > keeps the first maximum
-            if (v.x > bv || bi == 0x7fffffff) { bv = v.x; bi = 4 * j; }
-            if (v.y > bv) { bv = v.y; bi = 4 * j + 1; }
-            if (v.z > bv) { bv = v.z; bi = 4 * j + 2; }
-            if (v.w > bv) { bv = v.w; bi = 4 * j + 3; }
-        }
-    } else {
-        for (int j = c0 + tid; j < c1; j += 256) {
-            const float v = x[j];
-            if (v > bv || bi == 0x7fffffff) { bv = v; bi = j; }
-        }
+    // Bound by the stream of logits (5.4 TB/s on 321 rows of 128256).  The 16-byte loads start at the chunk's first 16-byte
+    // boundary, whatever V and the buffer's own alignment are; up to three logits in front of them and behind them go to a
+    // thread each.  Ascending index order inside the thread, strict > keeps the first maximum.  Whole call, 4-byte loads where V
+    // is no multiple of four -> this: 129 rows of 127997 28.8 -> 22.7 us (of 128256: 22.8), 2 x 36 rows of 9973 10.6 -> 9.5.
+    auto look = [&](float v, int j) {
+        if (v > bv || bi == 0x7fffffff) { bv = v; bi = j; }
+    };
+    const int lead = min(c1 - c0, (int)(-(reinterpret_cast<uintptr_t>(x + c0) >> 2) & 3));
+    const int first = c0 + lead, quads = (c1 - first) / 4, rest = first + 4 * quads;
+    if (tid < lead) look(x[c0 + tid], c0 + tid);
+    const float4* x4 = reinterpret_cast<const float4*>(x + first);
+    for (int j = tid; j < quads; j += 256) {
+        const float4 v = x4[j];
+        const int at = first + 4 * j;
+        look(v.x, at);
+        if (v.y > bv) { bv = v.y; bi = at + 1; }
+        if (v.z > bv) { bv = v.z; bi = at + 2; }
+        if (v.w > bv) { bv = v.w; bi = at + 3; }
     }
+    if (tid < c1 - rest) look(x[rest + tid], rest + tid);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) take_first_max(bv, bi, __shfl_xor(bv, o), __shfl_xor(bi, o));
     if (lane == 0) { sv[wave] = bv; si[wave] = bi; }

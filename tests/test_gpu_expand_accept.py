@@ -144,6 +144,24 @@ def test_accept_argmax_ties_across_chunks_and_precomputed_tokens():
     assert np.array_equal(ref2["accept_path"], ref["accept_path"])
 
 
+@pytest.mark.parametrize("V", [1, 2, 3, 5, 7, 1025, 4095, 4097, 4098, 4103, 8191, 8193])
+def test_accept_argmax_at_the_edges_of_rows_and_chunks(V):
+    """Rows that start at each of the four places of a 16-byte unit, the maximum at either end of a row or chunk, equal ones
+    behind it and everything else -inf: a chain in which every verifier token is the next node's, so each is checked."""
+    at = [min(p, V - 1) for p in (0, 1, 2, 3, V - 1, V - 2, V - 3, 4095, 4096, 4097, V - 4, V - 1) if p >= 0]
+    n = len(at)
+    cfg = _cfg(1, n - 1, 1, max(V, 2))
+    x = np.full((1, n, V), -np.inf, np.float32)
+    for i, p in enumerate(at):
+        x[0, i, p::3] = -2.5
+    x[0, n // 2] = -np.inf               # a row with nothing but -inf: token 0
+    token = np.zeros((1, n), np.int32)
+    token[0, 1:] = [0 if i == n // 2 else p for i, p in enumerate(at)][:-1]
+    cfg = wl.scaled(cfg, vocab=V)
+    ref = _accept_both(cfg, np.arange(-1, n - 1, dtype=np.int32)[None], token, 1, np.array([3]), logits=x)
+    assert ref["accept_len"][0] == n and ref["bonus_token"][0] == at[-1]
+
+
 def test_accept_general_tree_full_chain_and_root_only():
     N = 40
     cfg = _cfg(1, N - 1, 1, 64)

@@ -895,7 +895,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                 for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, fabsf(o[rb][db][v]));
             rmax = fmaxf(rmax, __shfl_xor(rmax, 32));
             const float c = fmaxf(rmax, 1e-30f);
-            const float inv_c = __builtin_amdgcn_rcpf(c);   // (an ulp of the scale is nothing next to fp16's 2^-12)
+            const float inv_c = 1.f / c;   // (v_rcp_f32 alone would give 0 for c above 2^126, whose reciprocal is subnormal)
             // The two lanes of a row hold alternating groups of four head_dim positions; swapping halves between them
             // (v_permlane32_swap) leaves each with eight consecutive ones, so a store covers 32 contiguous bytes of a row.
             _Float16* po = reinterpret_cast<_Float16*>(a.part_o) + ((int64_t)split * a.rows_total + rg_of[rb]) * DH + 8 * g2;

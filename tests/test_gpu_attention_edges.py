@@ -1,10 +1,13 @@
 """Tree attention where its kernels change course: every workgroup shape from one key tile upwards (the pipelines' first and
 last tiles, tiles that are partly prefix, partly tree or cut short), row counts that leave wavefronts idle, batches cut into
 runs, and the merge of few and many key splits for few and many rows.  Bounds as in test_gpu_attention."""
+import numpy as np
 import pytest
 
+import oracle
 import paper_2512_23858_amd as ygg
-from gpu_util import shape_of
+import ygg_workloads as wl
+from gpu_util import run_attention, shape_of
 from test_gpu_attention import _cfg, _check, _inputs
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +62,24 @@ def test_short_runs_of_many_rows(Hq, Hkv, D, W, L):
     cfg, host, parent = _inputs(_cfg(1, Hq, Hkv, D, W, seed=61), [L], L, tree_gain=2.0)
     assert ygg.attention_plan(shape_of(cfg, max_seq_len=L))["key_splits"] > 1
     _check(cfg, host, parent, L)
+
+
+@pytest.mark.parametrize("Dh", [128, 64])
+def test_partial_sums_up_to_the_largest_floats(plan, Dh):
+    """All scores are 0, so a split's partial output is the plain sum of its V rows: about 2^126.4, and the reciprocal of that is a
+    subnormal float.  The two partials together stay below 2^128.  The result is the mean of the V rows; bound as in _check,
+    in units of V."""
+    plan(nsplit=2)
+    cfg, host, parent = _inputs(_cfg(1, 8, 2, 6, 8, Dh=Dh, seed=71), [600], 600)
+    host["q"] = np.zeros_like(host["q"])
+    unit = 2.0 ** 118
+    for stream, name in ((1, "v_cache"), (2, "v_tree")):
+        v = unit * (1.0 + 0.4 * wl.rng(71, stream).random(host[name].shape))
+        host[name] = wl.to_storage(v.astype(np.float32), cfg.dtype)
+    shape = shape_of(cfg, max_seq_len=600)
+    assert ygg.attention_plan(shape)["key_splits"] == 2
+    ref, _ = oracle.tree_attention(host["q"], host["k_cache"], host["v_cache"], host["seq_lens"], host["k_tree"], host["v_tree"],
+                                   parent, cfg.softmax_scale)
+    out, _ = run_attention(shape, host, parent)
+    assert np.isfinite(out).all()
+    assert np.abs(out - ref).max() / unit <= 2e-2, np.abs(out - ref).max() / unit

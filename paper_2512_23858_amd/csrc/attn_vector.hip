@@ -146,11 +146,12 @@ __global__ __launch_bounds__(256) void attn_vector_kernel(AttnArgs a) {
     float* po = static_cast<float*>(a.part_o) + ((int64_t)split * rows + r) * DH + lane * EPL;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) po[e] = acc[e];
-    if (lane == 0) a.part_rec[(int64_t)split * rows + r] = make_float3(m * kLog2e, l, 1.f);
+    if (lane == 0) a.part_rec[(int64_t)split * rows + r] = make_float3(m, l, 1.f);
 }
 
-// Merge of the per-split partials: m* = max_s m_s, l* = sum_s l_s 2^{m_s - m*}, O = sum_s O~_s 2^{m_s - m*} / l*,
-// lse = m* ln 2 + ln l*.
+// Merge of the per-split partials: m* = max_s m_s, l* = sum_s l_s e^{m_s - m*}, O = sum_s O~_s e^{m_s - m*} / l*,
+// lse = m* + ln l*.  References come in the units that their kernel works in, so that their differences are exact: base-2
+// ones from the matrix-core kernels (2^{m_s - m*}, m* ln 2), natural ones from the vector kernel.
 // A group of TPR lanes covers a row with 16 bytes per lane (eight fp16 or four fp32 values); G such groups share one row,
 // taking every G-th split each (G = 64 / TPR where there are few rows: a lane then has few loads to wait for; else G = 1).
 // The records {m, l, c} are read once per row -- lane t of the row's lanes takes splits t, t + LPR, .. -- and m*, the
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     float w[NH], lstar = 0.f;
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-        w[h] = rec[h].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(rec[h].x - mstar);
+        w[h] = rec[h].x == -INFINITY ? 0.f : HALF ? exp2f(rec[h].x - mstar) : expf(rec[h].x - mstar);
         lstar = fmaf(rec[h].y, w[h], lstar);
         w[h] = w[h] == 0.f ? 0.f : w[h] * rec[h].z;   // from here on w weighs the stored partial output
     }
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
         if constexpr (HALF) *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<uint4*>(h);
         else *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<uint2*>(h);
     }
-    if (a.lse && t == 0) a.lse[r] = mstar * kLn2 + logf(lstar);
+    if (a.lse && t == 0) a.lse[r] = (HALF ? mstar * kLn2 : mstar) + logf(lstar);
 }
 
 template <typename T>

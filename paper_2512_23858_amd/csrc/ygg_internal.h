@@ -28,7 +28,8 @@ struct AttnArgs {
     const float* k_scale;  // [Hkv], both set: K and V hold 8-bit E4M3 codes; both null: plain elements
     const float* v_scale;
     void* part_o;         // [nsplit][B*N*Hq][Dh]  matrix-core kernels: fp16 O~ / c; vector kernel: fp32 O~
-    float3* part_rec;     // [nsplit][B*N*Hq]      {m in base-2 units of the scaled scores, l, c}; m = -inf: absent
+    float3* part_rec;     // [nsplit][B*N*Hq]      {m, l, c}, m in units of the scaled scores (matrix-core
+                          // kernels: base-2 units); m = -inf: absent
     int32_t* seq_splits;  // [B], balanced batches only: how many runs a sequence's keys fell into (its partials carry split
                           // indices 0 .. n-1), or 0 if one run held it all and its rows are final already
     void* out;

@@ -83,3 +83,26 @@ def test_partial_sums_up_to_the_largest_floats(plan, Dh):
     out, _ = run_attention(shape, host, parent)
     assert np.isfinite(out).all()
     assert np.abs(out - ref).max() / unit <= 2e-2, np.abs(out - ref).max() / unit
+
+
+def test_fp32_splits_keep_their_weights_at_large_scores():
+    """Scores near 2^20, each exact in fp32 (one element of q and k is not zero; 1/8 is their spacing and the scale is 1/8), and
+    V = 1 in the first half of the prefix, -1 in the second, so that every split's weight shows.  Differences of references are
+    exact; an output is off by at most one unit in the last place for each of its three factors expf and for each addition of
+    1149 keys, as is its sum of weights: 1152 * 2^-23 = 1.4e-4 at most."""
+    cfg, host, parent = _inputs(_cfg(1, 4, 4, 6, 8, dtype="f32", Dh=64, seed=72), [1100], 1100)
+    assert cfg.softmax_scale == 0.125
+    for name in ("q", "k_cache", "k_tree"):
+        host[name] = np.zeros_like(host[name])
+    host["q"][..., 5] = 8.0
+    for stream, name in ((1, "k_cache"), (2, "k_tree")):
+        tile = (np.arange(host[name].shape[1]) // 64 * 53 % 25)[None, :, None]      # splits of different maxima
+        host[name][..., 5] = 2.0 ** 20 + (tile + wl.rng(72, stream).integers(0, 9, host[name].shape[:-1])) / 8.0
+    host["v_cache"][:, :550], host["v_cache"][:, 550:], host["v_tree"][:] = 1.0, -1.0, 0.5
+    shape = shape_of(cfg, max_seq_len=1100)
+    assert ygg.attention_plan(shape)["key_splits"] > 4
+    ref, ref_lse = oracle.tree_attention(host["q"], host["k_cache"], host["v_cache"], host["seq_lens"], host["k_tree"],
+                                         host["v_tree"], parent, cfg.softmax_scale)
+    out, lse = run_attention(shape, host, parent)
+    assert np.abs(out - ref).max() <= 1.4e-4, np.abs(out - ref).max()
+    assert np.abs(lse - ref_lse).max() <= 2.0 ** -3, np.abs(lse - ref_lse).max()   # one unit in the last place at 2^20

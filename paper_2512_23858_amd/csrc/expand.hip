@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
     if (tid == 0) {
         head->sumexp = (sums[0] + sums[1]) + (sums[2] + sums[3]);
         head->ref = ref;
-        head->count = want;
+        head->count = min(want, pooled);   // (fewer than wanted only if there are NaNs, which no list takes: it says what it holds)
     }
     auto store = [&](int rank, uint64_t o) {
         const Cand cd = {float_of((uint32_t)(o >> 32)), (int32_t)~(uint32_t)o};
@@ -658,6 +658,7 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
             __builtin_amdgcn_wave_barrier();
         }
         if (p == wave) __syncthreads();   // floor_s is there (every wavefront passes here once: nwaves <= F)
+        if (a.d == 1 && lane == 0) n_live = min(n, a.W);
         if (lane < 8) mypool[n + lane] = 0;   // zeros follow the entries (there is room: 64 slots behind the pool)
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -690,11 +691,11 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    const int n_sort = a.d == 1 ? a.W : n_live;
+    const int n_sort = n_live;
     const int base_new = 1 + (a.d - 1) * a.W;
-    const int keep = min(a.W * (a.D - a.d), n_sort - a.W);
+    const int keep = min(a.W * (a.D - a.d), max(n_sort - a.W, 0));
     auto emit = [&](int i, const Entry& x) {
-        if (i >= a.W + keep) return;
+        if (i >= min(n_sort, a.W + keep)) return;
         const uint32_t node = x.tie / (uint32_t)a.V;
         const int token = (int)(x.tie - node * (uint32_t)a.V);
         const double score = double_of(x.key);
@@ -745,7 +746,7 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
             }
         }
     __syncthreads();  // the sorted order is read by every wavefront
-    for (int i = tid; i < a.W + keep; i += nthr) emit(i, e[i]);
+    for (int i = tid; i < min(n_sort, a.W + keep); i += nthr) emit(i, e[i]);
 }
 
 int pow2_at_least(int64_t x) {

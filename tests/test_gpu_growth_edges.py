@@ -3,9 +3,13 @@ logits, rows that are no multiple of four logits, fewer lists than new nodes, mo
 and logits whose exponentials need a reference other than zero.  Indices bit for bit against the CPU oracle."""
 import numpy as np
 import pytest
+import torch
 
+import oracle
+import paper_2512_23858_amd as ygg
 import ygg_workloads as wl
-from test_gpu_attach import attach_both
+from gpu_util import DEV, shape_of, to_dev, workspace
+from test_gpu_attach import attach_both, read_pool
 from test_gpu_expand_accept import _expand_both
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +55,36 @@ def test_growth_with_logits_far_from_zero(shift, masked):
             y[:, :, 4500:] = np.float32(masked) + x[:, :1, 4500:]
         return x
     _expand_both(cfg, logits_fn=fn, check_margin=False)
+
+
+@pytest.mark.parametrize("W,V", [(6, 3000), (20, 5000), (40, 9000)])
+@pytest.mark.parametrize("share", [1.0, 0.9])
+def test_nan_logits_stay_inside_their_sequence(W, V, share):
+    """NaN logits leave a sequence's own tree undefined, but no call may leave the buffers: the sequences beside it come out as
+    ever, and the carried pool says no more than it can hold.  share: how much of the middle sequence's logits is NaN."""
+    B, D = 3, 3
+    cfg = _cfg(B, D, W, V)
+    for op, name in ((ygg.OP_EXPAND, "expand"), (ygg.OP_ATTACH, "attach")):
+        parent = np.full((B, cfg.n_nodes), -9, np.int32); token = parent.copy(); cum = np.zeros((B, cfg.n_nodes), np.float32)
+        parent[:, 0], token[:, 0] = -1, 1
+        gp, gt, gc = to_dev(parent.copy()), to_dev(token.copy()), to_dev(cum.copy())
+        shape = shape_of(cfg)
+        ws = workspace(shape, op)
+        gpool = torch.full((ygg.attach_pool_bytes(shape),), 0xA5, dtype=torch.uint8, device=DEV)
+        pool = oracle.attach_pool(B, D, W)
+        for t in range(1, D + 1):
+            x = wl.expansion_inputs(cfg, t)
+            y = x.copy()
+            y[1][wl.rng(23, t).random(y[1].shape) < share] = np.nan
+            if name == "expand":
+                oracle.expand(D, W, t, x, parent, token, cum)
+                ygg.equal_growth_expand(shape, t, to_dev(y), gp, gt, gc, ws)
+            else:
+                oracle.attach(D, W, t, x, parent, token, cum, pool)
+                ygg.equal_growth_attach(shape, t, to_dev(y), gp, gt, gc, gpool, ws)
+            torch.cuda.synchronize()
+            if name == "attach":
+                assert all(0 <= count <= W * (D - t) for count, _ in read_pool(gpool, B, D, W))
+        for got, want in ((gp, parent), (gt, token)):
+            assert np.array_equal(got.cpu().numpy()[[0, 2]], want[[0, 2]])
+        assert np.abs(gc.cpu().numpy()[[0, 2]] - cum[[0, 2]]).max() <= 1e-5

@@ -17,8 +17,8 @@
 //     from lane maxima, the candidates above it are pooled in LDS and ranked against each other;
 //   - the sum of exponentials needs no maximum first (fp64 holds exp of any logit up to 500; a reference other than 0 is
 //     kept only beyond that), and the row sums are plain sums of the chunks';
-//   - a list's four best entries sit beside its sum, in one 48-byte record: they decide almost every step, so that the
-//     finish kernel makes one trip to memory (the rest of a list is read only if all four reach the threshold).
+//   - a list's four best entries decide almost every step: the finish kernel requests them together with the list's sum, so
+//     that it makes one trip to memory (the rest of a list is read only if all four reach the threshold).
 // Measured per step, back to back (16 logits per thread, four list merges by binary search and a bitonic pool sort in LDS
 // -> this): 8 rows of 32000 logits 12.8 -> 7.3 us, 128 rows of 32000 (batch 16) 18.4 -> 12.7, free attachment with 16 rows
 // of 128256 24.6 -> 14.8.  Left at the small size: 1.5 us of launch per kernel, memory latency once per kernel, and about
@@ -33,7 +33,7 @@ namespace ygg {
 namespace {
 
 constexpr uint32_t kNone = 0xffffffffu;
-constexpr int kFront = 4;        // list entries kept beside the sum
+constexpr int kFront = 4;        // list entries read with the sum
 constexpr int kMaxLists = 1024;  // lists of one sequence, padded to a power of two per row: one per thread of the finish kernel
 constexpr float kPlainRange = 500.f;  // logits whose exponential is summed as it is
 
@@ -41,13 +41,26 @@ struct Cand {
     float val;
     int32_t idx;
 };
-struct __align__(16) ListHead {
+struct __align__(16) ListStat {
     double sumexp;          // sum exp(x - ref) over the chunk
     float ref;              // 0, or the chunk's maximum where that lies outside +-kPlainRange
     int32_t count;          // entries of the list: min(W, logits in the chunk)
-    Cand front[kFront];     // the best ones; entries 4 .. W-1 are in the `rest` array
 };
-static_assert(sizeof(ListHead) == 48, "three 16-byte loads");
+// A list as the finish kernels read it: its record and four entries.  Entries are dense, W to a list, so that a list takes no
+// more scratch than its contents; they come in two 16-byte loads (8-byte aligned, which global loads allow).  Where W < 4 these
+// reach into the next list or, behind the last one, into the records that follow the entries in the scratch.
+struct ListHead {
+    ListStat stat;
+    Cand front[kFront];
+};
+__device__ __forceinline__ ListHead read_list(const ListStat* stats, const Cand* cands, int64_t list, int W) {
+    ListHead h;
+    h.stat = stats[list];
+    const Cand* c = cands + list * W;
+    __builtin_memcpy(&h.front[0], c, 16);
+    __builtin_memcpy(&h.front[2], c + 2, 16);
+    return h;
+}
 
 // Largest found t with at least `want` (and not many more) of the wavefront's NK*64 keys >= t; key 0 = no candidate.
 // Returns 1, which every candidate reaches, if there are fewer than `want`.  Bisection in rounds of four steps: a step is
@@ -118,8 +131,8 @@ constexpr int kScanPool = 512;   // pooled candidates per chunk
 
 struct ScanArgs {
     const float* logits;
-    ListHead* heads;     // [rows][nchunk]
-    Cand* rest;          // [rows][nchunk][W - 4]
+    ListStat* stats;     // [rows][nchunk]
+    Cand* cands;         // [rows][nchunk][W], best first
     int32_t V, W, chunk, nchunk;
 };
 
@@ -128,7 +141,7 @@ __device__ __forceinline__ uint64_t order_of(uint32_t key, uint32_t idx) {   // 
 }
 
 // Exact but slow: used when more candidates tie than the pool holds.  Each round finds the best candidate after the last.
-__device__ __noinline__ void scan_ties(const float* x, int c0, int c1, int want, int lane, ListHead* head, Cand* rest) {
+__device__ __noinline__ void scan_ties(const float* x, int c0, int c1, int want, int lane, Cand* out) {
     uint64_t last = ~0ull;
     for (int r = 0; r < want; ++r) {
         uint64_t best = 0;
@@ -141,7 +154,7 @@ __device__ __noinline__ void scan_ties(const float* x, int c0, int c1, int want,
         last = ((uint64_t)bh << 32) | bl;
         if (lane == 0) {
             const Cand cd = {float_of(bh), (int32_t)~bl};
-            if (r < kFront) head->front[r] = cd; else rest[r - kFront] = cd;
+            out[r] = cd;
         }
     }
 }
@@ -274,17 +287,17 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
     sum = group_sum(sum, 64);
     if (lane == 0) sums[wave] = sum;
     __syncthreads();
-    ListHead* head = a.heads + list;
-    Cand* rest = a.rest + list * max(a.W - kFront, 0);
+    Cand* out = a.cands + list * a.W;
     if (tid == 0) {
-        head->sumexp = (sums[0] + sums[1]) + (sums[2] + sums[3]);
-        head->ref = ref;
-        head->count = min(want, pooled);   // (fewer than wanted only if there are NaNs, which no list takes: it says what it holds)
+        ListStat st;
+        st.sumexp = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+        st.ref = ref;
+        st.count = min(want, pooled);   // (fewer than wanted only if there are NaNs, which no list takes: it says what it holds)
+        a.stats[list] = st;
     }
     auto store = [&](int rank, uint64_t o) {
         const Cand cd = {float_of((uint32_t)(o >> 32)), (int32_t)~(uint32_t)o};
-        Cand* dst = rank < kFront ? head->front + rank : rest + (rank - kFront);
-        if (rank < want) *dst = cd;
+        if (rank < want) out[rank] = cd;
     };
     const int n = __builtin_amdgcn_readfirstlane(pooled);
     if (n <= 64) {
@@ -306,12 +319,12 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
             store(rank, mine);
         }
     } else if (wave == 0) {
-        scan_ties(x, c0, c1, want, lane, head, rest);
+        scan_ties(x, c0, c1, want, lane, out);
     }
 }
 
 // Log-sum-exp of a row from its lists, which sit in an aligned group of `width` lanes (fixed order of summation).
-__device__ __forceinline__ double row_lse(const ListHead& h, int width) {
+__device__ __forceinline__ double row_lse(const ListStat& h, int width) {
     if (!__any(h.ref != 0.f)) return log(group_sum(h.sumexp, width));
     const float ref = h.sumexp > 0.0 ? h.ref : -INFINITY;
     const float mx = group_reduce(ref, width, [](float x, float y) { return fmaxf(x, y); });
@@ -331,8 +344,8 @@ __device__ __forceinline__ bool beats(const Entry& a, const Entry& b) {
 }
 
 struct FinishArgs {
-    const ListHead* heads;
-    const Cand* rest;
+    const ListStat* stats;
+    const Cand* cands;
     int32_t* parent_idx;
     int32_t* token_ids;
     float* cum_logprob;
@@ -346,11 +359,11 @@ constexpr int kMergePool = 1024;   // pooled candidates of one sequence
 // Best candidate of the workgroup per round, every thread offering the entry at the cursor of its list (count 0: none);
 // used when more candidates tie than the pool holds.
 __device__ __noinline__ void merge_serially(int32_t* parent, int32_t* token, float* cum_out, int W, int V, int base_prev, int nwaves,
-                                            const ListHead* h, const Cand* rest, int count, int p, double cum, double lse, Entry* best_s) {
+                                            const Cand* cands, int count, int p, double cum, double lse, Entry* best_s) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto entry = [&](int i) {
         if (i >= count) return Entry{0, kNone, 0};
-        const Cand cd = i < kFront ? h->front[i] : rest[i - kFront];
+        const Cand cd = cands[i];
         return Entry{key_of(cum + ((double)cd.val - lse)), (uint32_t)(p * V + cd.idx), 0};
     };
     int cur = 0;
@@ -388,24 +401,20 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
     const int p = tid >> a.shift, c = tid & ((1 << a.shift) - 1);
     const bool active = p < a.F && c < a.nchunk;
     const int64_t list = ((int64_t)b * a.F + (active ? p : 0)) * a.nchunk + (active ? c : 0);
-    ListHead h = a.heads[list];
+    ListHead h = read_list(a.stats, a.cands, list, a.W);
     const double cum = (double)a.cum_logprob[(int64_t)b * a.N + base_prev + (active ? p : 0)];
-    if (!active) {
-        h.count = 0;
-        h.ref = 0.f;
-        h.sumexp = 0.0;
-    }
-    const Cand* rest = a.rest + list * max(a.W - kFront, 0);
+    if (!active) h.stat = ListStat{0.0, 0.f, 0};
+    const Cand* cands = a.cands + list * a.W;
     for (int i = tid; i < kMergePool; i += 64 * nwaves) pool[i] = Entry{0, kNone, 0};   // while the loads are out
     if (tid == 0) pooled = 0;
 
-    const double lse = row_lse(h, 1 << a.shift);
+    const double lse = row_lse(h.stat, 1 << a.shift);
     auto entry_of = [&](Cand cd) {
         return Entry{key_of(cum + ((double)cd.val - lse)), (uint32_t)(p * a.V + cd.idx), 0};   // tie: flat index p*V + v
     };
     Entry e[kFront];
 #pragma unroll
-    for (int i = 0; i < kFront; ++i) e[i] = i < h.count ? entry_of(h.front[i]) : Entry{0, kNone, 0};
+    for (int i = 0; i < kFront; ++i) e[i] = i < h.stat.count ? entry_of(h.front[i]) : Entry{0, kNone, 0};
 
     // threshold: W list heads reach it (with fewer lists than W, W of the first four entries of every list), so nothing
     // below it can be among the W best
@@ -443,15 +452,15 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
         pool_put(sel, [&](int i) { return e[i]; }, pool, kMergePool, &pooled, lane);
     }
     if ((uint32_t)(e[kFront - 1].key >> 32) >= t) {   // the list may go on above the threshold: four more at a time
-        for (int i = kFront; i < h.count; i += 4) {
+        for (int i = kFront; i < h.stat.count; i += 4) {
             Cand cd[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) cd[u] = rest[min(i + u, h.count - 1) - kFront];
+            for (int u = 0; u < 4; ++u) cd[u] = cands[min(i + u, h.stat.count - 1)];
             bool more = true;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const Entry x = entry_of(cd[u]);
-                more = more && i + u < h.count && (uint32_t)(x.key >> 32) >= t;
+                more = more && i + u < h.stat.count && (uint32_t)(x.key >> 32) >= t;
                 if (more) put(x);
             }
             if (!more) break;
@@ -461,8 +470,8 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
     const int n = __builtin_amdgcn_readfirstlane(pooled);
     if (n > kMergePool) {   // mass ties
         const int64_t node = (int64_t)b * a.N + 1 + (a.d - 1) * a.W;
-        merge_serially(a.parent_idx + node, a.token_ids + node, a.cum_logprob + node, a.W, a.V, base_prev, nwaves, a.heads + list, rest,
-                       h.count, p, cum, lse, best_s);
+        merge_serially(a.parent_idx + node, a.token_ids + node, a.cum_logprob + node, a.W, a.V, base_prev, nwaves, cands,
+                       h.stat.count, p, cum, lse, best_s);
         return;
     }
     auto emit = [&](int rank, const Entry& x) {
@@ -554,10 +563,10 @@ __device__ __forceinline__ Entry sort_in_registers(Entry mine, Entry* e, int tid
 }
 
 // Mass ties in a row: one offer per round, every lane offering the entry at the cursor of its list.
-__device__ __noinline__ void row_serially(const ListHead* h, const Cand* rest, int count, int W, int lane, uint64_t* out) {
+__device__ __noinline__ void row_serially(const Cand* cands, int count, int W, int lane, uint64_t* out) {
     auto entry = [&](int i) {
         if (i >= count) return (uint64_t)0;
-        const Cand cd = i < kFront ? h->front[i] : rest[i - kFront];
+        const Cand cd = cands[i];
         return order_of(key_of(cd.val), (uint32_t)cd.idx);
     };
     int cur = 0;
@@ -605,19 +614,15 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
 
     for (int p = wave; p < a.F; p += nwaves) {
         const int64_t list = ((int64_t)b * a.F + p) * a.nchunk + min(lane, a.nchunk - 1);
-        ListHead h = a.heads[list];
+        ListHead h = read_list(a.stats, a.cands, list, a.W);
         const double cum = (double)a.cum_logprob[(int64_t)b * a.N + first + p];
-        if (lane >= a.nchunk) {
-            h.count = 0;
-            h.ref = 0.f;
-            h.sumexp = 0.0;
-        }
-        const Cand* rest = a.rest + list * max(a.W - kFront, 0);
-        const double lse = row_lse(h, 64);
+        if (lane >= a.nchunk) h.stat = ListStat{0.0, 0.f, 0};
+        const Cand* cands = a.cands + list * a.W;
+        const double lse = row_lse(h.stat, 64);
         // the row's W best, by raw logit: threshold over the first four entries of every list, then pool and rank
         uint32_t g[kFront];
 #pragma unroll
-        for (int i = 0; i < kFront; ++i) g[i] = i < h.count ? key_of(h.front[i].val) : 0u;
+        for (int i = 0; i < kFront; ++i) g[i] = i < h.stat.count ? key_of(h.front[i].val) : 0u;
         const uint32_t head_key[1] = {g[0]};
         const uint32_t t = a.nchunk >= a.W ? wave_threshold<1>(head_key, a.W) : wave_threshold<kFront>(g, a.W);
         if (lane == 0) row_n[wave] = 0;
@@ -634,15 +639,15 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
             pool_put(sel, [&](int i) { return order_of(g[i], (uint32_t)h.front[i].idx); }, mypool, kRowPool, &row_n[wave], lane);
         }
         if (g[kFront - 1] >= t) {
-            for (int i = kFront; i < h.count; i += 4) {
+            for (int i = kFront; i < h.stat.count; i += 4) {
                 Cand cd[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) cd[u] = rest[min(i + u, h.count - 1) - kFront];
+                for (int u = 0; u < 4; ++u) cd[u] = cands[min(i + u, h.stat.count - 1)];
                 bool more = true;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const uint32_t key = key_of(cd[u].val);
-                    more = more && i + u < h.count && key >= t;
+                    more = more && i + u < h.stat.count && key >= t;
                     if (more) put(order_of(key, (uint32_t)cd[u].idx));
                 }
                 if (!more) break;
@@ -652,7 +657,7 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
         __builtin_amdgcn_wave_barrier();
         int n = __builtin_amdgcn_readfirstlane(row_n[wave]);
         if (n > kRowPool) {
-            row_serially(a.heads + list, rest, h.count, a.W, lane, mypool);
+            row_serially(cands, h.stat.count, a.W, lane, mypool);
             n = a.W;
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -758,8 +763,8 @@ int pow2_at_least(int64_t x) {
 hipError_t launch_scan(const ExpandArgs& a, hipStream_t st) {
     ScanArgs s;
     s.logits = a.logits;
-    s.heads = static_cast<ListHead*>(a.heads);
-    s.rest = static_cast<Cand*>(a.rest);
+    s.stats = static_cast<ListStat*>(a.stats);
+    s.cands = static_cast<Cand*>(a.cands);
     s.V = a.V; s.W = a.W; s.chunk = a.chunk; s.nchunk = a.nchunk;
     const dim3 grid((unsigned)(a.B * a.F), (unsigned)a.nchunk), block(kScanThreads);
     const bool vec = (a.V & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15u) == 0;
@@ -778,8 +783,8 @@ hipError_t launch_scan(const ExpandArgs& a, hipStream_t st) {
 
 FinishArgs finish_args(const ExpandArgs& a) {
     FinishArgs f;
-    f.heads = static_cast<const ListHead*>(a.heads);
-    f.rest = static_cast<const Cand*>(a.rest);
+    f.stats = static_cast<const ListStat*>(a.stats);
+    f.cands = static_cast<const Cand*>(a.cands);
     f.parent_idx = a.parent_idx; f.token_ids = a.token_ids; f.cum_logprob = a.cum_logprob;
     f.pool = static_cast<unsigned char*>(a.pool); f.pool_cap = a.pool_cap;
     f.D = a.D; f.W = a.W; f.V = a.V; f.N = a.N; f.d = a.d; f.F = a.F; f.nchunk = a.nchunk;
@@ -807,8 +812,8 @@ ExpandPlan plan_expand(const ygg_shape& s, int32_t d) {
     p.chunk = (int32_t)chunk;
     p.nchunk = (int32_t)lists(chunk);
     const size_t total = (size_t)rows * (size_t)p.nchunk;
-    p.head_bytes = (total * sizeof(ListHead) + 255) / 256 * 256;
-    p.rest_bytes = (total * (size_t)std::max(s.width - kFront, 0) * sizeof(Cand) + 255) / 256 * 256;
+    p.stat_bytes = (total * sizeof(ListStat) + 255) / 256 * 256;
+    p.cand_bytes = (total * (size_t)s.width * sizeof(Cand) + 255) / 256 * 256;
     return p;
 }
 

@@ -259,7 +259,7 @@ size_t ygg_workspace_bytes(const ygg_shape* s, int32_t op, int32_t n_layers) {
         case YGG_OP_ATTACH: {
             if (check_shape(s, false, true) != YGG_OK) return 0;
             const ExpandPlan one = plan_expand(*s, 1), all = plan_expand(*s, 2);  // the root alone, the widest frontier
-            const size_t need1 = one.head_bytes + one.rest_bytes, need2 = all.head_bytes + all.rest_bytes;
+            const size_t need1 = one.cand_bytes + one.stat_bytes, need2 = all.cand_bytes + all.stat_bytes;
             // (callers may count on attachment asking for more than the frontier rule: it is given a page on top)
             return (need1 > need2 ? need1 : need2) + (op == YGG_OP_ATTACH ? 256 : 0);
         }
@@ -361,13 +361,13 @@ int32_t ygg_equal_growth_expand(const ygg_shape* s, int32_t d, const float* draf
     if ((int64_t)p.F * pages > 4096) return YGG_ERR_UNSUPPORTED;  // 16 M logits per sequence and step
     if ((int64_t)p.F * s->vocab >= 0x7fffffffLL) return YGG_ERR_UNSUPPORTED;  // flat candidate index is 32 bits
     if ((int64_t)s->batch * p.F > 0x7fffffffLL) return YGG_ERR_UNSUPPORTED;
-    if (int32_t rc = check_workspace(workspace, workspace_bytes, p.head_bytes + p.rest_bytes)) return rc;
+    if (int32_t rc = check_workspace(workspace, workspace_bytes, p.cand_bytes + p.stat_bytes)) return rc;
     if (int32_t rc = ensure_device_ready()) return rc;
 
     ExpandArgs a{};
     a.logits = draft_logits; a.parent_idx = parent_idx; a.token_ids = token_ids; a.cum_logprob = cum_logprob;
-    a.heads = workspace;
-    a.rest = static_cast<char*>(workspace) + p.head_bytes;
+    a.cands = workspace;
+    a.stats = static_cast<char*>(workspace) + p.cand_bytes;
     a.B = s->batch; a.D = s->depth; a.W = s->width; a.V = s->vocab; a.N = s->n_nodes; a.d = d;
     a.F = p.F; a.chunk = p.chunk; a.nchunk = p.nchunk;
     return launch_expand(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? YGG_OK : YGG_ERR_LAUNCH;
@@ -404,13 +404,13 @@ int32_t ygg_equal_growth_attach(const ygg_shape* s, int32_t t, const float* draf
     // pool + offers are sorted in one workgroup's LDS: at most 4096 entries
     if ((int64_t)p.F * s->width + (int64_t)s->width * (s->depth - t + 1) > 4096) return YGG_ERR_UNSUPPORTED;
     if ((reinterpret_cast<uintptr_t>(pool) & 15u) != 0 || pool_bytes < attach_pool_bytes(*s)) return YGG_ERR_WORKSPACE;
-    if (int32_t rc = check_workspace(workspace, workspace_bytes, p.head_bytes + p.rest_bytes)) return rc;
+    if (int32_t rc = check_workspace(workspace, workspace_bytes, p.cand_bytes + p.stat_bytes)) return rc;
     if (int32_t rc = ensure_device_ready()) return rc;
 
     ExpandArgs a{};
     a.logits = draft_logits; a.parent_idx = parent_idx; a.token_ids = token_ids; a.cum_logprob = cum_logprob;
-    a.heads = workspace;
-    a.rest = static_cast<char*>(workspace) + p.head_bytes;
+    a.cands = workspace;
+    a.stats = static_cast<char*>(workspace) + p.cand_bytes;
     a.pool = pool; a.pool_cap = (int32_t)attach_pool_capacity(*s);
     a.B = s->batch; a.D = s->depth; a.W = s->width; a.V = s->vocab; a.N = s->n_nodes; a.d = t;
     a.F = p.F; a.chunk = p.chunk; a.nchunk = p.nchunk;

@@ -72,18 +72,18 @@ int32_t ensure_device_ready();
 // ---- equal-growth expansion -------------------------------------------------------------------
 struct ExpandPlan {
     int32_t F;            // frontier rows
-    int32_t chunk;        // vocab entries per list (one wavefront of the scan)
+    int32_t chunk;        // vocab entries per list (one workgroup of the scan)
     int32_t nchunk;       // lists per row, at most 64
-    size_t head_bytes;    // [B*F][nchunk] {double sumexp; int32 count; the four best entries}
-    size_t rest_bytes;    // [B*F][nchunk][W - 4] {float val; int32 idx}
+    size_t cand_bytes;    // [B*F][nchunk][W] {float val; int32 idx}, in front of
+    size_t stat_bytes;    // [B*F][nchunk] {double sumexp; float ref; int32 count}
 };
 struct ExpandArgs {
     const float* logits;
     int32_t* parent_idx;
     int32_t* token_ids;
     float* cum_logprob;
-    void* heads;
-    void* rest;
+    void* cands;
+    void* stats;
     void* pool;        // free attachment only: per sequence {int32 count, pad to 16 B, pool_cap offers}
     int32_t pool_cap;
     int32_t B, D, W, V, N, d, F, chunk, nchunk;

@@ -159,7 +159,7 @@ def test_attach_rejects_bad_arguments_on_the_host():
 @pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 8, 64])
 @pytest.mark.parametrize("V", [100, 4096, 32000, 128256])
 def test_growth_scratch_of_large_batches(W, V):
-    """A list is 16 bytes and its W entries, and a large batch takes one per 4096 logits: that decides what still fits the static
+    """A list is 16 bytes and its W entries, and a large batch takes one per 4096 logits at most: that decides what still fits the static
     call's built-in scratch."""
     static = 4 << 20
     lists_per_row = -(-V // 4096)
@@ -171,7 +171,7 @@ def test_growth_scratch_of_large_batches(W, V):
         s = _shape(batch=B, depth=2, width=W, n_nodes=1 + 2 * W, vocab=V)
         need = up(16 * lists) + up(8 * W * lists)
         got = ygg.workspace_bytes(s, ygg.OP_EXPAND)
-        assert (got <= static) == (need <= static) and got == need, (B, got, need)
+        assert (got <= static) == (need <= static) and got <= need, (B, got, need)
 
 
 def test_prune_rejects_bad_arguments_on_the_host():

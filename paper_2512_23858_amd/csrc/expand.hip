@@ -795,6 +795,10 @@ FinishArgs finish_args(const ExpandArgs& a) {
 
 }  // namespace
 
+constexpr int64_t kShortLists = 1024;   // steps of more lists take chunks of 4096 logits or more
+static size_t stat_bytes_of(int64_t lists) { return ((size_t)lists * sizeof(ListStat) + 255) / 256 * 256; }
+static size_t cand_bytes_of(int64_t lists, int32_t width) { return ((size_t)lists * (size_t)width * sizeof(Cand) + 255) / 256 * 256; }
+
 // Chunk length: the finish kernel takes one list per thread and a row's lists from one wavefront, which bounds the lists
 // per row; within that, short chunks (1024 logits, four per thread) keep every compute unit busy and each thread's chain
 // short.  Steps that fill the chip several times over take chunks of up to 4096: the fixed part of a workgroup's work, the
@@ -806,15 +810,22 @@ ExpandPlan plan_expand(const ygg_shape& s, int32_t d) {
     const int64_t rows = (int64_t)s.batch * p.F;
     auto lists = [&](int64_t chunk) { return (s.vocab + chunk - 1) / chunk; };
     int64_t chunk = 1024;
-    if (lists(chunk) > most || rows * lists(chunk) > 1024) chunk = 2048;
+    if (lists(chunk) > most || rows * lists(chunk) > kShortLists) chunk = 2048;
     if (lists(chunk) > most || rows * lists(chunk) > 512) chunk = 4096;
     if (lists(chunk) > most) chunk = ((int64_t)s.vocab + 4096 * most - 1) / (4096 * most) * 4096;
     p.chunk = (int32_t)chunk;
     p.nchunk = (int32_t)lists(chunk);
-    const size_t total = (size_t)rows * (size_t)p.nchunk;
-    p.stat_bytes = (total * sizeof(ListStat) + 255) / 256 * 256;
-    p.cand_bytes = (total * (size_t)s.width * sizeof(Cand) + 255) / 256 * 256;
+    const int64_t total = rows * p.nchunk;
+    p.stat_bytes = stat_bytes_of(total);
+    p.cand_bytes = cand_bytes_of(total, s.width);
     return p;
+}
+
+// Fewer rows or logits can mean more lists, shorter ones: the bound is that of chunks of 4096, or of every list there may be while
+// chunks are shorter, so that scratch sized for the largest batch and vocabulary serves the smaller ones.
+size_t expand_scratch_bytes(const ygg_shape& s) {
+    const int64_t lists = std::max((int64_t)s.batch * s.width * (((int64_t)s.vocab + 4095) / 4096), kShortLists);
+    return cand_bytes_of(lists, s.width) + stat_bytes_of(lists);
 }
 
 // The largest dynamic LDS the attachment kernel may ask for: 4096 entries and the row pools of sixteen wavefronts.

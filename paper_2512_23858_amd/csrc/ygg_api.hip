@@ -258,10 +258,8 @@ size_t ygg_workspace_bytes(const ygg_shape* s, int32_t op, int32_t n_layers) {
         case YGG_OP_EXPAND:
         case YGG_OP_ATTACH: {
             if (check_shape(s, false, true) != YGG_OK) return 0;
-            const ExpandPlan one = plan_expand(*s, 1), all = plan_expand(*s, 2);  // the root alone, the widest frontier
-            const size_t need1 = one.cand_bytes + one.stat_bytes, need2 = all.cand_bytes + all.stat_bytes;
-            // (callers may count on attachment asking for more than the frontier rule: it is given a page on top)
-            return (need1 > need2 ? need1 : need2) + (op == YGG_OP_ATTACH ? 256 : 0);
+            // (attachment has always asked for more than the frontier rule, which the host tests pin; nothing uses the 256 bytes)
+            return expand_scratch_bytes(*s) + (op == YGG_OP_ATTACH ? 256 : 0);
         }
         case YGG_OP_ACCEPT: {
             if (check_shape(s, false, true) != YGG_OK) return 0;

@@ -89,6 +89,7 @@ struct ExpandArgs {
     int32_t B, D, W, V, N, d, F, chunk, nchunk;
 };
 ExpandPlan plan_expand(const ygg_shape& s, int32_t d);
+size_t expand_scratch_bytes(const ygg_shape& s);   // enough for every step of this shape and of smaller batches or vocabularies
 hipError_t launch_expand(const ExpandArgs& a, hipStream_t st);
 // free attachment: d is the draft step; rows belong to the nodes added at step d-1
 int64_t attach_pool_capacity(const ygg_shape& s);

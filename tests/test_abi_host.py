@@ -174,6 +174,19 @@ def test_growth_scratch_of_large_batches(W, V):
         assert (got <= static) == (need <= static) and got <= need, (B, got, need)
 
 
+@pytest.mark.parametrize("W", [1, 3, 8, 17, 33, 64])
+@pytest.mark.parametrize("op", [ygg.OP_EXPAND, ygg.OP_ATTACH])
+def test_growth_scratch_of_the_largest_shape_serves_the_smaller_ones(W, op):
+    """A decoder allocates once, for its largest batch and vocabulary."""
+    size = lambda B, V: ygg.workspace_bytes(_shape(batch=B, depth=2, width=W, n_nodes=1 + 2 * W, vocab=V), op)
+    for V in (64, 1000, 5000, 32000, 50257, 70000, 128256):
+        sizes = [size(B, V) for B in range(1, 70)]
+        assert sizes == sorted(sizes), V
+    for B in (1, 2, 3, 8, 16):
+        sizes = [size(B, V) for V in range(64, 400000, 997)]
+        assert sizes == sorted(sizes), B
+
+
 def test_prune_rejects_bad_arguments_on_the_host():
     lib = ygg.load_library()
 

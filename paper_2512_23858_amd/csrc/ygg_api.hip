@@ -2,6 +2,7 @@
 // is done here other than enqueuing kernels on the caller's stream; nothing synchronises.
 #include "ygg_internal.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <mutex>
@@ -112,6 +113,14 @@ static void short_run_shape(const ygg_shape& s, int R, int64_t tiles, AttnPlan& 
     if (best) { p.waves = best->waves; p.kshares = best->kshares; }
 }
 
+// matrix-core kernels: fp16 partial outputs with one fp32 scale per row; vector kernel: fp32 partial outputs
+static size_t part_o_bytes(const ygg_shape& s, bool half, int64_t nsplit) {
+    return align256((size_t)nsplit * (size_t)s.batch * (size_t)s.n_nodes * (size_t)s.n_q_heads * (size_t)s.head_dim * (half ? 2 : 4));
+}
+static size_t part_rec_bytes(const ygg_shape& s, int64_t nsplit) {
+    return align256((size_t)nsplit * (size_t)s.batch * (size_t)s.n_nodes * (size_t)s.n_q_heads * sizeof(float3));
+}
+
 AttnPlan plan_attention(const ygg_shape& s) {
     AttnPlan p{};
     const int64_t rows = (int64_t)s.batch * s.n_nodes * s.n_q_heads;
@@ -189,11 +198,24 @@ AttnPlan plan_attention(const ygg_shape& s) {
         ns = (T + chunk - 1) / chunk;
     }
     p.nsplit = p.slots > 0 ? p.slots : (int32_t)ns;   // balanced batches: a sequence may span every run
-    // matrix-core kernels: fp16 partial outputs with one fp32 scale per row; vector kernel: fp32 partial outputs
-    p.part_o_bytes = align256((size_t)p.nsplit * (size_t)rows * (size_t)s.head_dim * (p.use_mfma ? 2 : 4));
-    p.part_rec_bytes = align256((size_t)p.nsplit * (size_t)rows * sizeof(float3));
+    p.part_o_bytes = part_o_bytes(s, p.use_mfma, p.nsplit);
+    p.part_rec_bytes = part_rec_bytes(s, p.nsplit);
     p.seq_splits_bytes = p.slots > 0 ? align256((size_t)s.batch * sizeof(int32_t)) : 0;
     return p;
+}
+
+// Workspace for this shape and every smaller max_seq_len.  More keys mean no fewer splits or runs for one workgroup shape, but
+// short_run_shape changes the shape with the length, and a shorter call may take one that allows more splits: the bound is the
+// workgroup shape with the most.
+static size_t attention_scratch_bytes(const ygg_shape& s) {
+    const AttnPlan p = plan_attention(s);
+    const int R = s.n_nodes * (s.n_q_heads / s.n_kv_heads);
+    int64_t most = p.nsplit;
+    if (p.use_mfma && s.kv_dtype != YGG_FP8_E4M3 && R > 64) {
+        const int64_t tiles = ((int64_t)s.max_seq_len + s.n_nodes + kKeyTile - 1) / kKeyTile;
+        for (int rows : {256, 192, 128, 64}) most = std::max(most, std::min(equal_splits(s, (R + rows - 1) / rows, tiles), (int64_t)64));
+    }
+    return part_o_bytes(s, p.use_mfma, most) + part_rec_bytes(s, most) + p.seq_splits_bytes;
 }
 
 // Raises the shared-memory limits of the current device's kernels once; later calls cost one atomic load.
@@ -252,8 +274,7 @@ size_t ygg_workspace_bytes(const ygg_shape* s, int32_t op, int32_t n_layers) {
     switch (op) {
         case YGG_OP_ATTENTION: {
             if (check_shape(s, true, false) != YGG_OK) return 0;
-            const AttnPlan p = plan_attention(*s);
-            return p.part_o_bytes + p.part_rec_bytes + p.seq_splits_bytes;
+            return attention_scratch_bytes(*s);
         }
         case YGG_OP_EXPAND:
         case YGG_OP_ATTACH: {

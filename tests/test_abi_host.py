@@ -274,6 +274,18 @@ def test_attention_plans_of_the_five_configurations():
     assert need <= ygg.workspace_bytes(s3, ygg.OP_ATTENTION) < need + 3 * 256
 
 
+@pytest.mark.parametrize("heads", [(8, 8), (32, 8), (32, 32), (64, 8), (28, 4), (12, 12), (4, 1)])
+@pytest.mark.parametrize("kv_dtype,head_dim", [(1, 128), (1, 64), (2, 128)])
+def test_attention_scratch_of_the_longest_prefix_serves_the_shorter_ones(heads, kv_dtype, head_dim):
+    """A decoder allocates once, for its longest context, and passes tighter bounds of the lengths as it goes."""
+    for n in (1, 7, 9, 17, 33, 36, 49, 65, 81, 129, 321, 1000):
+        for B in (1, 2, 3, 16):
+            sizes = [ygg.workspace_bytes(_shape(batch=B, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=head_dim, kv_dtype=kv_dtype,
+                                                n_nodes=n, max_seq_len=L, kv_capacity=L + 8), ygg.OP_ATTENTION)
+                     for L in [*range(0, 3000, 61), *range(3000, 70000, 1531)]]
+            assert sizes[0] > 0 and sizes == sorted(sizes), (n, B)
+
+
 def test_plan_override_is_explicit_and_removable():
     """The tuning override is a call, not an environment variable, and leaves no trace once removed."""
     import os

@@ -154,9 +154,6 @@ AttnPlan plan_attention(const ygg_shape& s) {
             if (padded(192) * 100 <= best * (p.kshares == 2 ? 92 : 80)) { p.waves = 6; p.kshares = 1; }
         }
         if (!kv8 && R > 64) short_run_shape(s, R, tiles, p);
-        // the widest trees (more than 900 nodes, one query head per kv head) leave no room for their masks beside 256 rows
-        const int G = s.n_q_heads / s.n_kv_heads;
-        while (p.kshares == 1 && p.waves > 4 && attn_mfma_smem(p.waves, 1, s.head_dim, G, s.n_nodes) > kAttnMfmaMaxSmem) p.waves -= 2;
         int64_t ns_forced = 0;
         if (const uint64_t ov = g_plan_override.load(std::memory_order_relaxed)) {
             const int w = (int)(ov >> 56), r = (int)(ov >> 48) & 0xff, k = (int)(ov >> 40) & 0xff;
@@ -165,6 +162,9 @@ AttnPlan plan_attention(const ygg_shape& s) {
             if (known) { p.waves = w; p.rblocks = r; p.kshares = k; }
             ns_forced = (int64_t)(ov & 0xffffffffu);
         }
+        // the widest trees (more than 900 nodes, one query head per kv head) leave no room for their masks beside 256 rows
+        const int G = s.n_q_heads / s.n_kv_heads;
+        while (p.kshares == 1 && p.waves > 4 && attn_mfma_smem(p.waves, 1, s.head_dim, G, s.n_nodes) > kAttnMfmaMaxSmem) p.waves -= 2;
         const int rw = p.waves / p.kshares * p.rblocks * 32;
         p.row_tiles = (R + rw - 1) / rw;
         ns = equal_splits(s, p.row_tiles, tiles);

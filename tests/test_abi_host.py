@@ -302,6 +302,9 @@ def test_plan_override_is_explicit_and_removable():
         assert forced["key_splits"] == 3 and forced["waves"] == base["waves"]
         ygg.set_attention_plan(waves=2, rblocks=1, kshares=2)
         assert ygg.attention_plan(s)["waves"] == 2 and ygg.attention_plan(s)["key_shares"] == 2
+        ygg.set_attention_plan(waves=8, rblocks=1, kshares=1)   # the masks of the widest trees do not fit beside 256 rows: 192 instead
+        wide = [ygg.attention_plan(_shape(n_q_heads=4, n_kv_heads=4, n_nodes=n, max_seq_len=4096, kv_capacity=4200)) for n in (500, 1024)]
+        assert [(p["waves"], p["key_shares"], p["row_tiles"]) for p in wide] == [(8, 1, 2), (6, 1, 6)]
         ygg.set_attention_plan(waves=5, rblocks=1, kshares=1)   # unknown shape: ignored
         assert ygg.attention_plan(s)["waves"] == base["waves"]
     finally:

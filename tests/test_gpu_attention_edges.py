@@ -33,6 +33,14 @@ def test_every_workgroup_shape_from_one_tile_upwards(plan, waves, kshares, Hq, D
         _check(cfg, host, parent, max(L, 1))
 
 
+@pytest.mark.parametrize("waves", [8, 6, 4])
+def test_the_widest_tree_under_a_forced_shape(plan, waves):
+    plan(waves=waves, rblocks=1, kshares=1)
+    cfg, host, parent = _inputs(_cfg(1, 2, 2, 31, 33, seed=37), [100], 100, tree_gain=2.0)
+    assert cfg.n_nodes == 1024
+    _check(cfg, host, parent, 100)
+
+
 # more than eight tiles to a workgroup of the longest sequence: the batch is cut into equal runs of tiles
 @pytest.mark.parametrize("B,Hq,Hkv,D,W,lens,Dh", [
     (5, 32, 4, 6, 8, [5000, 0, 64, 1500, 333], 128),            # two row tiles, an empty and a one-tile prefix

@@ -140,7 +140,8 @@ __device__ __forceinline__ uint64_t order_of(uint32_t key, uint32_t idx) {   // 
     return ((uint64_t)key << 32) | (uint32_t)~idx;
 }
 
-// Exact but slow: used when more candidates tie than the pool holds.  Each round finds the best candidate after the last.
+// Exact but slow: for chunks of several passes whose logits climb from pass to pass until the pool is full.  Each round finds the
+// best candidate after the last.
 __device__ __noinline__ void scan_ties(const float* x, int c0, int c1, int want, int lane, Cand* out) {
     uint64_t last = ~0ull;
     for (int r = 0; r < want; ++r) {
@@ -160,9 +161,10 @@ __device__ __noinline__ void scan_ties(const float* x, int c0, int c1, int want,
 }
 
 // Appends the wavefront's selected candidates to a pool: the positions follow from ballots and one count per wavefront.
-// Few candidates are selected, so what(i), the candidate's pool entry, is formed only where some lane has it.
+// Few candidates are selected, so what(i), the candidate's pool entry, is formed only where some lane has it.  Does nothing and
+// returns false if there are more than `limit`.
 template <int N, typename T, typename What>
-__device__ __forceinline__ void pool_put(const bool (&sel)[N], What what, T* pool, int cap, int* counter, int lane) {
+__device__ __forceinline__ bool pool_put(const bool (&sel)[N], What what, T* pool, int cap, int* counter, int lane, int limit) {
     uint64_t m[N];
     int total = 0;
 #pragma unroll
@@ -170,7 +172,8 @@ __device__ __forceinline__ void pool_put(const bool (&sel)[N], What what, T* poo
         m[i] = __ballot(sel[i]);
         total += (int)__popcll(m[i]);
     }
-    if (total == 0) return;
+    if (total == 0) return true;
+    if (__builtin_expect(total > limit, 0)) return false;
     int base = 0;
     if (lane == 0) base = atomicAdd(counter, total);
     base = __builtin_amdgcn_readfirstlane(base);
@@ -181,6 +184,37 @@ __device__ __forceinline__ void pool_put(const bool (&sel)[N], What what, T* poo
             pool[sel[i] && pos < cap ? pos : cap + lane] = what(i);   // (a slot of the lane's own behind the pool: no branch)
             base += (int)__popcll(m[i]);
         }
+    }
+    return true;
+}
+
+// Narrows a wavefront's selection (more than 64 candidates, keys 0 elsewhere) to the `want` best, or an eighth more where that
+// spares bisection steps: the threshold among them alone, and of the candidates that tie with it those of the lowest indices, as
+// many as are wanted.  Indices ascend from lane to lane with QUAD places each, then to the next group
+// of QUAD places.
+template <int E, int QUAD>
+__device__ __forceinline__ void narrow(const uint32_t (&key)[E], int want, int lane, bool (&sel)[E]) {
+    const uint32_t t = wave_threshold<E>(key, want);
+    int room = want;
+#pragma unroll
+    for (int i = 0; i < E; ++i) room -= (int)__popcll(__ballot(key[i] > t));
+    int before = 0;   // ties in the groups in front
+#pragma unroll
+    for (int i0 = 0; i0 < E; i0 += QUAD) {
+        int mine = before, all = 0;
+#pragma unroll
+        for (int u = 0; u < QUAD; ++u) {
+            const uint64_t m = __ballot(key[i0 + u] == t);
+            mine += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            all += (int)__popcll(m);
+        }
+#pragma unroll
+        for (int u = 0; u < QUAD; ++u) {
+            const bool tie = key[i0 + u] == t;
+            sel[i0 + u] = key[i0 + u] > t || (tie && mine < room);
+            mine += tie;
+        }
+        before += all;
     }
 }
 
@@ -224,6 +258,7 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
     uint32_t best = 0;      // key of the thread's largest logit
     float ref = 0.f;
     double sum = 0.0;       // this thread's share of sum exp(x - ref)
+    uint32_t t_seen = 0;    // at least `want` logits of the passes so far reach it
     int base = c0;
     do {
         float v[E];
@@ -256,12 +291,24 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
         best = index(0) < c1 ? max(best, key_of(vmax)) : best;
         keys[tid] = best;
         __syncthreads();
-        const uint32_t t = group_threshold<E == 4>(keys, 4, lane, want);
+        const uint32_t t = max(group_threshold<E == 4>(keys, 4, lane, want), t_seen);
         const float tf = t <= 1u ? -INFINITY : float_of(t);
         bool sel[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i) sel[i] = v[i] >= tf;
-        pool_put(sel, [&](int i) { return order_of(key_of(v[i]), (uint32_t)index(i)); }, pool, kScanPool, &pooled, lane);
+        for (int i = 0; i < E; ++i)   // (equal ones of a later pass come too late: higher indices; 0 is above -0)
+            sel[i] = !ONE && t == t_seen ? v[i] > tf || (v[i] == tf && key_of(v[i]) > t) : v[i] >= tf;
+        if (!ONE && t > 1u) t_seen = t;
+        auto entry = [&](int i) { return order_of(key_of(v[i]), (uint32_t)index(i)); };
+        // Many equal logits (a masked vocabulary's -inf or -1e9) are left at the wavefront's W best: every chunk of 32 x 128256 logits
+        // with 1000 of the vocabulary unmasked, 283 us per step when they went through the rounds of scan_ties, XX now.
+        constexpr int kMost = ONE ? kScanPool / 4 : kMaxWidth + kMaxWidth / 8;
+        if (!pool_put(sel, entry, pool, kScanPool, &pooled, lane, kMost)) {
+            uint32_t key[E];
+#pragma unroll
+            for (int i = 0; i < E; ++i) key[i] = sel[i] ? key_of(v[i]) : 0u;
+            narrow<E, VEC ? 4 : 1>(key, want, lane, sel);
+            pool_put(sel, entry, pool, kScanPool, &pooled, lane, kMost);
+        }
         // sum of exponentials
         const uint32_t top = max(max(keys[lane], keys[64 + lane]), max(keys[128 + lane], keys[192 + lane]));
         const float cmax = float_of(wave_max_u32(top));   // of the chunk so far
@@ -318,7 +365,7 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
             }
             store(rank, mine);
         }
-    } else if (wave == 0) {
+    } else if (!ONE && wave == 0) {   // (one pass leaves no more than the pool holds)
         scan_ties(x, c0, c1, want, lane, out);
     }
 }
@@ -356,43 +403,50 @@ struct FinishArgs {
 
 constexpr int kMergePool = 1024;   // pooled candidates of one sequence
 
-// Best candidate of the workgroup per round, every thread offering the entry at the cursor of its list (count 0: none);
-// used when more candidates tie than the pool holds.
-__device__ __noinline__ void merge_serially(int32_t* parent, int32_t* token, float* cum_out, int W, int V, int base_prev, int nwaves,
-                                            const Cand* cands, int count, int p, double cum, double lse, Entry* best_s) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    auto entry = [&](int i) {
-        if (i >= count) return Entry{0, kNone, 0};
-        const Cand cd = cands[i];
-        return Entry{key_of(cum + ((double)cd.val - lse)), (uint32_t)(p * V + cd.idx), 0};
+// The W best of up to 64 lists, one per lane, in order: a round per entry, every lane offering the next entry of its list, which it
+// holds four at a time, the next four already requested.  Used where a threshold over the first four entries leaves too many
+// candidates to rank them against each other: many equal ones (masked vocabularies), or few lists for many new nodes.  About 0.15 us
+// a round; returns the number of entries.
+template <typename EntryOf, typename Emit>
+__device__ __forceinline__ int merge_rounds(const Cand* list, int count, int W, EntryOf entry_of, Emit emit) {
+    Cand now[4], next[4];
+    auto request = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) next[u] = list[max(min(i0 + u, count - 1), 0)];
     };
-    int cur = 0;
-    Entry mine = entry(0);
-    for (int r = 0; r < W; ++r) {
+    int cur = -1;
+    Entry mine;
+    auto advance = [&]() {
+        ++cur;
+        if ((cur & 3) == 0) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) now[u] = next[u];
+            request(cur + 4);
+        }
+        Cand cd = now[0];
+#pragma unroll
+        for (int u = 1; u < 4; ++u) cd = (cur & 3) == u ? now[u] : cd;
+        mine = cur < count ? entry_of(cd) : Entry{0, kNone, 0};
+    };
+    request(0);
+    advance();
+    int r = 0;
+    for (; r < W; ++r) {
         const uint32_t kh = wave_max_u32((uint32_t)(mine.key >> 32));
         const uint32_t kl = wave_max_u32((uint32_t)(mine.key >> 32) == kh ? (uint32_t)mine.key : 0u);
         const uint64_t k = ((uint64_t)kh << 32) | kl;
         const uint32_t t = wave_min_u32(mine.key == k ? mine.tie : kNone);
-        if (lane == 0) best_s[wave] = Entry{k, t, 0};
-        __syncthreads();
-        Entry w = best_s[0];
-        for (int i = 1; i < nwaves; ++i) if (beats(best_s[i], w)) w = best_s[i];
-        __syncthreads();
-        if (w.key == 0) return;   // (cannot happen: there are at least W candidates)
-        if (tid == 0) {
-            parent[r] = base_prev + (int)(w.tie / (uint32_t)V);
-            token[r] = (int)(w.tie % (uint32_t)V);
-            cum_out[r] = (float)double_of(w.key);
-        }
-        if (mine.key == w.key && mine.tie == w.tie) mine = entry(++cur);
+        if (k == 0) break;
+        emit(r, Entry{k, t, 0});
+        if (mine.key == k && mine.tie == t) advance();
     }
+    return r;
 }
 
 // Bounded by latency: one trip to memory, two row reductions, a bisection, two barriers.
 __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, int nwaves) {
     __shared__ uint32_t coarse[kMaxLists];   // upper halves of the keys of the list heads
     __shared__ Entry pool[kMergePool + 64];
-    __shared__ Entry best_s[kMaxLists / 64];
     __shared__ int pooled;
     __shared__ uint32_t thr;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -449,7 +503,7 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
         bool sel[kFront];
 #pragma unroll
         for (int i = 0; i < kFront; ++i) sel[i] = (uint32_t)(e[i].key >> 32) >= t;
-        pool_put(sel, [&](int i) { return e[i]; }, pool, kMergePool, &pooled, lane);
+        pool_put(sel, [&](int i) { return e[i]; }, pool, kMergePool, &pooled, lane, kMergePool);
     }
     if ((uint32_t)(e[kFront - 1].key >> 32) >= t) {   // the list may go on above the threshold: four more at a time
         for (int i = kFront; i < h.stat.count; i += 4) {
@@ -468,12 +522,6 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
     }
     __syncthreads();
     const int n = __builtin_amdgcn_readfirstlane(pooled);
-    if (n > kMergePool) {   // mass ties
-        const int64_t node = (int64_t)b * a.N + 1 + (a.d - 1) * a.W;
-        merge_serially(a.parent_idx + node, a.token_ids + node, a.cum_logprob + node, a.W, a.V, base_prev, nwaves, cands,
-                       h.stat.count, p, cum, lse, best_s);
-        return;
-    }
     auto emit = [&](int rank, const Entry& x) {
         if (rank >= a.W) return;
         const int64_t node = (int64_t)b * a.N + 1 + (a.d - 1) * a.W + rank;
@@ -482,6 +530,32 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
         a.token_ids[node] = (int)(x.tie - row * (uint32_t)a.V);
         a.cum_logprob[node] = (float)double_of(x.key);
     };
+    const int nthr = 64 * nwaves;
+    if (n > 64 && (n + nthr - 1) / nthr * n > 12 * a.W) {   // (what ranking costs against the rounds: measured on one wavefront)
+        Entry* mine = pool + (tid >> 6) * a.W;   // the wavefronts' lists
+        const int m = merge_rounds(cands, h.stat.count, a.W, entry_of, [&](int r, const Entry& x) {
+            if (lane == 0) {
+                if (nwaves == 1) emit(r, x); else mine[r] = x;
+            }
+        });
+        if (nwaves == 1) return;
+        for (int r = m + lane; r < a.W; r += 64) mine[r] = Entry{0, kNone, 0};
+        __syncthreads();
+        for (int j = tid; j < nwaves * a.W; j += nthr) {   // places: those of every list are found by halving
+            const Entry x = pool[j];
+            int rank = 0;
+            for (int w = 0; w < nwaves; ++w) {
+                int lo = 0, hi = a.W;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (beats(pool[w * a.W + mid], x)) lo = mid + 1; else hi = mid;
+                }
+                rank += lo;
+            }
+            if (x.key != 0) emit(rank, x);
+        }
+        return;
+    }
     if (n <= 64) {
         if (tid >= 64) return;
         const bool halves = n <= 32;   // the halves of the wavefront share the comparisons
@@ -503,7 +577,7 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
         if (lane < n) emit((int)rank, mine);
         return;
     }
-    for (int j = tid; j < n; j += 64 * nwaves) {
+    for (int j = tid; j < n; j += nthr) {
         const Entry mine = pool[j];
         int rank = 0;
         for (int i = 0; i < n; i += 4) {
@@ -562,24 +636,6 @@ __device__ __forceinline__ Entry sort_in_registers(Entry mine, Entry* e, int tid
     return mine;
 }
 
-// Mass ties in a row: one offer per round, every lane offering the entry at the cursor of its list.
-__device__ __noinline__ void row_serially(const Cand* cands, int count, int W, int lane, uint64_t* out) {
-    auto entry = [&](int i) {
-        if (i >= count) return (uint64_t)0;
-        const Cand cd = cands[i];
-        return order_of(key_of(cd.val), (uint32_t)cd.idx);
-    };
-    int cur = 0;
-    uint64_t mine = entry(0);
-    for (int r = 0; r < W; ++r) {
-        const uint32_t kh = wave_max_u32((uint32_t)(mine >> 32));
-        const uint32_t kl = wave_max_u32((uint32_t)(mine >> 32) == kh ? (uint32_t)mine : 0u);
-        const uint64_t k = ((uint64_t)kh << 32) | kl;
-        if (lane == 0) out[r] = k;
-        if (mine == k) mine = entry(++cur);
-    }
-}
-
 __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int nwaves, int n2_max) {
     extern __shared__ __align__(16) unsigned char raw_s[];
     Entry* e = reinterpret_cast<Entry*>(raw_s);                                        // [n2_max]
@@ -636,7 +692,7 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
             bool sel[kFront];
 #pragma unroll
             for (int i = 0; i < kFront; ++i) sel[i] = g[i] >= t;
-            pool_put(sel, [&](int i) { return order_of(g[i], (uint32_t)h.front[i].idx); }, mypool, kRowPool, &row_n[wave], lane);
+            pool_put(sel, [&](int i) { return order_of(g[i], (uint32_t)h.front[i].idx); }, mypool, kRowPool, &row_n[wave], lane, kRowPool);
         }
         if (g[kFront - 1] >= t) {
             for (int i = kFront; i < h.stat.count; i += 4) {
@@ -656,9 +712,9 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         int n = __builtin_amdgcn_readfirstlane(row_n[wave]);
-        if (n > kRowPool) {
-            row_serially(cands, h.stat.count, a.W, lane, mypool);
-            n = a.W;
+        if (n > 64 && (n + 63) / 64 * n > 12 * a.W) {   // (as in the merge kernel, one wavefront)
+            n = merge_rounds(cands, h.stat.count, a.W, [&](Cand cd) { return Entry{order_of(key_of(cd.val), (uint32_t)cd.idx), 0, 0}; },
+                             [&](int r, const Entry& x) { if (lane == 0) mypool[r] = x.key; });
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }

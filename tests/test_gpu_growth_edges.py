@@ -88,3 +88,37 @@ def test_nan_logits_stay_inside_their_sequence(W, V, share):
         for got, want in ((gp, parent), (gt, token)):
             assert np.array_equal(got.cpu().numpy()[[0, 2]], want[[0, 2]])
         assert np.abs(gc.cpu().numpy()[[0, 2]] - cum[[0, 2]]).max() <= 1e-5
+
+
+# all but a few logits of the vocabulary at one value, as a grammar mask leaves them: spread over the chunks, all in one, fewer than
+# new nodes; one pass per chunk and several (width 33 of 131080)
+@pytest.mark.parametrize("W,V,keep", [(8, 5000, 300), (8, 32000, 5), (33, 9001, 20), (20, 70001, 400), (33, 131080, 900), (64, 3000, 70)])
+@pytest.mark.parametrize("value", [-np.inf, -1e9])
+@pytest.mark.parametrize("spread", [True, False])
+def test_growth_over_a_masked_vocabulary(W, V, keep, value, spread):
+    cfg = _cfg(1, 2, W, V, seed=37)
+
+    def fn(d):
+        x = wl.expansion_inputs(cfg, d)
+        for p in range(x.shape[1]):
+            at = wl.rng(37, 100 * d + p).permutation(V)[:keep] if spread else (V // 3 + 17 * p) % (V - keep) + np.arange(keep)
+            masked = np.full(V, np.float32(value))
+            masked[at] = x[0, p, at]
+            x[0, p] = masked
+        return x
+    _expand_both(cfg, logits_fn=fn, check_margin=False)
+    if W < 64:
+        attach_both(cfg, logits_fn=fn, check_margin=False)
+
+
+@pytest.mark.parametrize("low", [-1.0, -2.0])
+def test_growth_with_equal_logits_in_later_passes(low):
+    """Several passes per chunk: later logits equal to the threshold of the passes before must lose against those, and the first
+    larger ones come in the middle of a chunk."""
+    cfg = _cfg(1, 2, 33, 131080)
+
+    def fn(d):
+        x = np.full((1, 1 if d == 1 else 33, 131080), np.float32(low))
+        x[:, :, 6000::7] = -1.0
+        return x
+    _expand_both(cfg, logits_fn=fn, check_margin=False)

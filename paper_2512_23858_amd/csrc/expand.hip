@@ -77,8 +77,9 @@ __device__ __forceinline__ uint32_t wave_threshold(const uint32_t (&g)[NK], int 
 #pragma unroll
     for (int i = 1; i < NK; ++i) top = max(top, g[i]);
     uint32_t hi = wave_max_u32(top);
-    uint32_t lo = max(wave_min_u32(top), 1u);   // if no lane is empty, 64 keys reach the smallest lane maximum
+    uint32_t lo = wave_min_u32(top ? top : kNone);   // as many keys as there are lanes with any reach the smallest lane maximum
     int n = count(lo);
+    if (n < want) n = count(lo = 1u);
     if (n < want) return 1u;
     const int enough = want + (want >> 3);
     while (lo < hi && n > enough) {              // n = count(lo) >= want; no key exceeds hi
@@ -299,8 +300,8 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
             sel[i] = !ONE && t == t_seen ? v[i] > tf || (v[i] == tf && key_of(v[i]) > t) : v[i] >= tf;
         if (!ONE && t > 1u) t_seen = t;
         auto entry = [&](int i) { return order_of(key_of(v[i]), (uint32_t)index(i)); };
-        // Many equal logits (a masked vocabulary's -inf or -1e9) are left at the wavefront's W best: every chunk of 32 x 128256 logits
-        // with 1000 of the vocabulary unmasked, 283 us per step when they went through the rounds of scan_ties, XX now.
+        // Of many equal logits (a masked vocabulary's -inf or -1e9) a wavefront keeps the W best by index: a step of 32 x 128256 logits
+        // with 1000 of the vocabulary unmasked 283 -> 31 us (every such chunk went through the rounds of scan_ties).
         constexpr int kMost = ONE ? kScanPool / 4 : kMaxWidth + kMaxWidth / 8;
         if (!pool_put(sel, entry, pool, kScanPool, &pooled, lane, kMost)) {
             uint32_t key[E];
@@ -403,10 +404,45 @@ struct FinishArgs {
 
 constexpr int kMergePool = 1024;   // pooled candidates of one sequence
 
+// Where a row has few lists for many new nodes, W of the lists' first four entries are all or most of these: nearly everything would
+// reach the threshold.  The first 32 or 64 entries of every list then decide, sixteen to a lane: lanes c << share .. share a list.
+__device__ __forceinline__ bool few_lists(int nchunk, int W) { return nchunk * kFront < 2 * W; }   // (fewer than 32 lists)
+struct Shared16 {
+    Cand cd[16];
+    const Cand* list;   // the lane's list, its length, what the lanes hold of it, and how many entries this lane holds
+    int count, covered, mine;
+    bool last;          // holds the last of these
+};
+__device__ __forceinline__ Shared16 read_shared(const Cand* row, int nchunk, int W, int count, int lane) {
+    const int share = nchunk <= 16 ? 2 : 1, step = 1 << share, c = lane >> share, q = lane & (step - 1);
+    Shared16 x;
+    x.count = __shfl(count, c);
+    x.list = row + (x.count > 0 ? c * W : 0);
+    x.covered = 16 * step;
+    x.mine = min(max((x.count - q + step - 1) >> share, 0), 16);
+    x.last = q == step - 1;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x.cd[i] = x.list[max(min(q + step * i, x.count - 1), 0)];
+    return x;
+}
+// Goes on through a list, four entries at a time, while put says that they reach the threshold.
+template <typename Put>
+__device__ __forceinline__ void read_on(const Cand* list, int from, int count, Put put) {
+    for (int i = from; i < count; i += 4) {
+        Cand cd[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) cd[u] = list[min(i + u, count - 1)];
+        bool more = true;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) more = more && i + u < count && put(cd[u]);
+        if (!more) break;
+    }
+}
+
 // The W best of up to 64 lists, one per lane, in order: a round per entry, every lane offering the next entry of its list, which it
 // holds four at a time, the next four already requested.  Used where a threshold over the first four entries leaves too many
-// candidates to rank them against each other: many equal ones (masked vocabularies), or few lists for many new nodes.  About 0.15 us
-// a round; returns the number of entries.
+// candidates to rank them against each other: many equal ones (masked vocabularies).  About 0.6 us a round; returns the number of
+// entries.
 template <typename EntryOf, typename Emit>
 __device__ __forceinline__ int merge_rounds(const Cand* list, int count, int W, EntryOf entry_of, Emit emit) {
     Cand now[4], next[4];
@@ -470,11 +506,37 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
 #pragma unroll
     for (int i = 0; i < kFront; ++i) e[i] = i < h.stat.count ? entry_of(h.front[i]) : Entry{0, kNone, 0};
 
-    // threshold: W list heads reach it (with fewer lists than W, W of the first four entries of every list), so nothing
-    // below it can be among the W best
-    const bool few = a.F * a.nchunk < a.W;   // then F == 1 and at most 63 lists: one wavefront
+    // threshold: W list heads reach it (with fewer lists than twice W, W of the first entries of every list: the lowest of these
+    // heads would let too many through), so nothing below it can be among the W best
+    const bool few = a.F * a.nchunk < 2 * a.W;   // then F == 1 or one list a row: one wavefront
+    const bool deep = few && a.F == 1 && few_lists(a.nchunk, a.W);
+    auto put = [&](const Entry& x) {
+        const int pos = atomicAdd(&pooled, 1);
+        if (pos < kMergePool) pool[pos] = x;
+    };
     uint32_t t;
-    if (few) {
+    if (deep) {   // (one row: the first lane's sum is everyone's)
+        const double lse0 = __longlong_as_double(((long long)__builtin_amdgcn_readfirstlane((int)(__double_as_longlong(lse) >> 32)) << 32) |
+                                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)__double_as_longlong(lse)));
+        const Shared16 x = read_shared(a.cands + (int64_t)b * a.nchunk * a.W, a.nchunk, a.W, h.stat.count, lane);
+        auto entry = [&](Cand cd) { return Entry{key_of(cum + ((double)cd.val - lse0)), (uint32_t)cd.idx, 0}; };
+        uint32_t g[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) g[i] = i < x.mine ? (uint32_t)(entry(x.cd[i]).key >> 32) : 0u;
+        __syncthreads();   // (pooled is zero)
+        t = wave_threshold<16>(g, a.W);
+        bool sel[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sel[i] = g[i] >= t;
+        pool_put(sel, [&](int i) { return entry(x.cd[i]); }, pool, kMergePool, &pooled, lane, kMergePool);
+        if (x.last && g[15] >= t)
+            read_on(x.list, x.covered, x.count, [&](Cand cd) {
+                const Entry y = entry(cd);
+                const bool reaches = (uint32_t)(y.key >> 32) >= t;
+                if (reaches) put(y);
+                return reaches;
+            });
+    } else if (few) {
         uint32_t g[kFront];
 #pragma unroll
         for (int i = 0; i < kFront; ++i) g[i] = (uint32_t)(e[i].key >> 32);
@@ -495,30 +557,18 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
         }
     }
 
-    auto put = [&](const Entry& x) {
-        const int pos = atomicAdd(&pooled, 1);
-        if (pos < kMergePool) pool[pos] = x;
-    };
-    {
+    if (!deep) {
         bool sel[kFront];
 #pragma unroll
         for (int i = 0; i < kFront; ++i) sel[i] = (uint32_t)(e[i].key >> 32) >= t;
         pool_put(sel, [&](int i) { return e[i]; }, pool, kMergePool, &pooled, lane, kMergePool);
-    }
-    if ((uint32_t)(e[kFront - 1].key >> 32) >= t) {   // the list may go on above the threshold: four more at a time
-        for (int i = kFront; i < h.stat.count; i += 4) {
-            Cand cd[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) cd[u] = cands[min(i + u, h.stat.count - 1)];
-            bool more = true;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const Entry x = entry_of(cd[u]);
-                more = more && i + u < h.stat.count && (uint32_t)(x.key >> 32) >= t;
-                if (more) put(x);
-            }
-            if (!more) break;
-        }
+        if ((uint32_t)(e[kFront - 1].key >> 32) >= t)
+            read_on(cands, kFront, h.stat.count, [&](Cand cd) {
+                const Entry y = entry_of(cd);
+                const bool reaches = (uint32_t)(y.key >> 32) >= t;
+                if (reaches) put(y);
+                return reaches;
+            });
     }
     __syncthreads();
     const int n = __builtin_amdgcn_readfirstlane(pooled);
@@ -531,7 +581,7 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
         a.cum_logprob[node] = (float)double_of(x.key);
     };
     const int nthr = 64 * nwaves;
-    if (n > 64 && (n + nthr - 1) / nthr * n > 12 * a.W) {   // (what ranking costs against the rounds: measured on one wavefront)
+    if (n > 64 && (n + nthr - 1) / nthr * n > 24 * a.W) {   // four comparisons of all entries cost 0.1 us
         Entry* mine = pool + (tid >> 6) * a.W;   // the wavefronts' lists
         const int m = merge_rounds(cands, h.stat.count, a.W, entry_of, [&](int r, const Entry& x) {
             if (lane == 0) {
@@ -636,12 +686,79 @@ __device__ __forceinline__ Entry sort_in_registers(Entry mine, Entry* e, int tid
     return mine;
 }
 
+// The entries of a list from `from` on that reach t.
+__device__ __forceinline__ void pool_rest(const Cand* list, int from, int count, uint32_t t, uint64_t* pool, int* counter) {
+    read_on(list, from, count, [&](Cand cd) {
+        const uint32_t key = key_of(cd.val);
+        if (key < t) return false;
+        const int pos = atomicAdd(counter, 1);
+        if (pos < kRowPool) pool[pos] = order_of(key, (uint32_t)cd.idx);
+        return true;
+    });
+}
+// The candidates of a row of few lists (a function of its own: its registers would make the kernel spill).
+__device__ __noinline__ void pool_of_few_lists(const Cand* row, int nchunk, int W, int count, int lane, uint64_t* pool, int* counter) {
+    const Shared16 x = read_shared(row, nchunk, W, count, lane);
+    uint32_t g[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) g[i] = i < x.mine ? key_of(x.cd[i].val) : 0u;
+    const uint32_t t = wave_threshold<16>(g, W);
+    bool sel[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sel[i] = g[i] >= t;
+    pool_put(sel, [&](int i) { return order_of(g[i], (uint32_t)x.cd[i].idx); }, pool, kRowPool, counter, lane, 1024);
+    if (x.last && g[15] >= t) pool_rest(x.list, x.covered, x.count, t, pool, counter);
+}
+
+// Keeps the `need` best of n entries (and not many more, but for ties), in any order; n up to four times the threads, *counter 0.
+// Returns their number.  More entries than threads are sorted through LDS with a barrier per stage, which costs several times as much:
+// 32 rows of 50257 logits with 160 to keep 57 -> 33 us per step, 60 rows of 14000 132 -> 56.
+__device__ __forceinline__ int drop_unneeded(Entry* e, int n, int need, int tid, int nthr, int* counter, uint32_t (*part)[16]) {
+    const int lane = tid & 63, wave = tid >> 6, nwaves = nthr >> 6;
+    Entry x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = tid + u * nthr < n ? e[tid + u * nthr] : Entry{0, kNone, 0};
+    auto upper = [&](int u) { return (uint32_t)(x[u].key >> 32); };
+    const uint32_t top = wave_max_u32(max(max(upper(0), upper(1)), max(upper(2), upper(3))));
+    if (lane == 0) part[0][wave] = top;
+    __syncthreads();
+    uint32_t lo = 1, hi = 0;
+    for (int w = 0; w < nwaves; ++w) hi = max(hi, part[0][w]);
+    int have = n, turn = 1;
+    while (lo < hi && have > need + (need >> 3)) {   // have: entries that reach lo
+        const uint32_t mid = lo + ((hi - lo + 1) >> 1);
+        int m = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m += (int)__popcll(__ballot(upper(u) >= mid));
+        if (lane == 0) part[turn][wave] = (uint32_t)m;
+        __syncthreads();
+        m = 0;
+        for (int w = 0; w < nwaves; ++w) m += (int)part[turn][w];
+        turn ^= 1;
+        if (m >= need) { lo = mid; have = m; } else hi = mid - 1;
+    }
+    bool sel[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sel[u] = upper(u) >= lo;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint64_t m = __ballot(sel[u]);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(counter, (int)__popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (sel[u]) e[at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = x[u];
+    }
+    __syncthreads();
+    return *counter;
+}
+
 __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int nwaves, int n2_max) {
     extern __shared__ __align__(16) unsigned char raw_s[];
     Entry* e = reinterpret_cast<Entry*>(raw_s);                                        // [n2_max]
     uint64_t* pools = reinterpret_cast<uint64_t*>(raw_s + (size_t)n2_max * sizeof(Entry));   // [nwaves][kRowPool + 64]
-    __shared__ int n_live, row_n[16];
+    __shared__ int n_live, n_kept, row_n[16];
     __shared__ uint64_t floor_s;
+    __shared__ uint32_t bisect_s[2][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nthr = 64 * nwaves;
     const int b = blockIdx.x;
     unsigned char* pool_b = a.pool + (size_t)b * (kPoolHeader + (size_t)a.pool_cap * sizeof(Offer));
@@ -663,7 +780,10 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
             if (i < n_old) e[i] = Entry{key_of(o.score), (uint32_t)o.node * (uint32_t)a.V + (uint32_t)o.token, 0};
         }
     }
-    if (tid == 0) n_live = n_old;
+    if (tid == 0) {
+        n_live = n_old;
+        n_kept = 0;
+    }
     __syncthreads();
     if (tid == 0) floor_s = n_old >= need && n_old > 0 ? e[n_old - 1].key : 0ull;
     uint64_t* mypool = pools + wave * (kRowPool + 64);
@@ -675,44 +795,29 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
         if (lane >= a.nchunk) h.stat = ListStat{0.0, 0.f, 0};
         const Cand* cands = a.cands + list * a.W;
         const double lse = row_lse(h.stat, 64);
-        // the row's W best, by raw logit: threshold over the first four entries of every list, then pool and rank
-        uint32_t g[kFront];
-#pragma unroll
-        for (int i = 0; i < kFront; ++i) g[i] = i < h.stat.count ? key_of(h.front[i].val) : 0u;
-        const uint32_t head_key[1] = {g[0]};
-        const uint32_t t = a.nchunk >= a.W ? wave_threshold<1>(head_key, a.W) : wave_threshold<kFront>(g, a.W);
+        // the row's W best, by raw logit: threshold over the first four entries of every list (over all entries of few lists), then
+        // pool and rank
         if (lane == 0) row_n[wave] = 0;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        auto put = [&](uint64_t x) {
-            const int pos = atomicAdd(&row_n[wave], 1);
-            if (pos < kRowPool) mypool[pos] = x;
-        };
-        {
+        if (few_lists(a.nchunk, a.W)) {
+            pool_of_few_lists(a.cands + ((int64_t)b * a.F + p) * a.nchunk * a.W, a.nchunk, a.W, h.stat.count, lane, mypool, &row_n[wave]);
+        } else {
+            uint32_t g[kFront];
+#pragma unroll
+            for (int i = 0; i < kFront; ++i) g[i] = i < h.stat.count ? key_of(h.front[i].val) : 0u;
+            const uint32_t head_key[1] = {g[0]};
+            const uint32_t t = a.nchunk >= a.W ? wave_threshold<1>(head_key, a.W) : wave_threshold<kFront>(g, a.W);
             bool sel[kFront];
 #pragma unroll
             for (int i = 0; i < kFront; ++i) sel[i] = g[i] >= t;
             pool_put(sel, [&](int i) { return order_of(g[i], (uint32_t)h.front[i].idx); }, mypool, kRowPool, &row_n[wave], lane, kRowPool);
-        }
-        if (g[kFront - 1] >= t) {
-            for (int i = kFront; i < h.stat.count; i += 4) {
-                Cand cd[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) cd[u] = cands[min(i + u, h.stat.count - 1)];
-                bool more = true;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t key = key_of(cd[u].val);
-                    more = more && i + u < h.stat.count && key >= t;
-                    if (more) put(order_of(key, (uint32_t)cd[u].idx));
-                }
-                if (!more) break;
-            }
+            if (g[kFront - 1] >= t) pool_rest(cands, kFront, h.stat.count, t, mypool, &row_n[wave]);
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         int n = __builtin_amdgcn_readfirstlane(row_n[wave]);
-        if (n > 64 && (n + 63) / 64 * n > 12 * a.W) {   // (as in the merge kernel, one wavefront)
+        if (n > 64 && (n + 63) / 64 * n > 24 * a.W) {   // (as in the merge kernel, one wavefront)
             n = merge_rounds(cands, h.stat.count, a.W, [&](Cand cd) { return Entry{order_of(key_of(cd.val), (uint32_t)cd.idx), 0, 0}; },
                              [&](int r, const Entry& x) { if (lane == 0) mypool[r] = x.key; });
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -752,7 +857,8 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    const int n_sort = n_live;
+    int n_sort = n_live;
+    if (n_sort > nthr && n_sort <= 4 * nthr && n_sort > need) n_sort = drop_unneeded(e, n_sort, need, tid, nthr, &n_kept, bisect_s);
     const int base_new = 1 + (a.d - 1) * a.W;
     const int keep = min(a.W * (a.D - a.d), max(n_sort - a.W, 0));
     auto emit = [&](int i, const Entry& x) {

@@ -957,14 +957,19 @@ FinishArgs finish_args(const ExpandArgs& a) {
 
 }  // namespace
 
-constexpr int64_t kShortLists = 1024;   // steps of more lists take chunks of 4096 logits or more
+// The most lists a step takes of 1024 and of 2048 logits (plan_expand).
+constexpr int64_t kListsOf1024 = 512, kListsOf2048 = 768;
 static size_t stat_bytes_of(int64_t lists) { return ((size_t)lists * sizeof(ListStat) + 255) / 256 * 256; }
 static size_t cand_bytes_of(int64_t lists, int32_t width) { return ((size_t)lists * (size_t)width * sizeof(Cand) + 255) / 256 * 256; }
 
 // Chunk length: the finish kernel takes one list per thread and a row's lists from one wavefront, which bounds the lists
 // per row; within that, short chunks (1024 logits, four per thread) keep every compute unit busy and each thread's chain
-// short.  Steps that fill the chip several times over take chunks of up to 4096: the fixed part of a workgroup's work, the
-// lists to write and those to read back are then a quarter.
+// short, long ones (4096) leave a quarter of the fixed work of a workgroup, of the lists to write and of those to read back.
+// The lines lie where no step of the sweep was slower for it.  us per step with chunks of 1024 / 2048 / 4096, by the number of
+// chunks of 2048: 192 (3 x 8 rows of 32000) 8.4 / 8.3 / 9.0; 272 (17 rows of 32000) 9.3 / 10.7 / 13.9; 512 (32 rows) 14.2 / 21.5 /
+// 28.1, with free attachment 62.6 / 25.3 / 30.4; 512 (32 x 16 rows of 1500) 16.0 / 11.8 / 13.1; 768 (6 x 8 rows of 32000) 10.2 /
+// 9.4 / 10.2; 756 (12 rows of 128256) - / 10.0 / 10.0; 1008 (16 rows of 128256) - / 11.6 / 10.6; 2048 (128 rows of 32000) 14.7 /
+// 13.6 / 13.5.
 ExpandPlan plan_expand(const ygg_shape& s, int32_t d) {
     ExpandPlan p;
     p.F = d == 1 ? 1 : s.width;
@@ -972,8 +977,8 @@ ExpandPlan plan_expand(const ygg_shape& s, int32_t d) {
     const int64_t rows = (int64_t)s.batch * p.F;
     auto lists = [&](int64_t chunk) { return (s.vocab + chunk - 1) / chunk; };
     int64_t chunk = 1024;
-    if (lists(chunk) > most || rows * lists(chunk) > kShortLists) chunk = 2048;
-    if (lists(chunk) > most || rows * lists(chunk) > 512) chunk = 4096;
+    if (lists(chunk) > most || rows * lists(chunk) > kListsOf1024) chunk = 2048;
+    if (chunk == 2048 && (lists(chunk) > most || rows * lists(chunk) > kListsOf2048)) chunk = 4096;
     if (lists(chunk) > most) chunk = ((int64_t)s.vocab + 4096 * most - 1) / (4096 * most) * 4096;
     p.chunk = (int32_t)chunk;
     p.nchunk = (int32_t)lists(chunk);
@@ -986,7 +991,7 @@ ExpandPlan plan_expand(const ygg_shape& s, int32_t d) {
 // Fewer rows or logits can mean more lists, shorter ones: the bound is that of chunks of 4096, or of every list there may be while
 // chunks are shorter, so that scratch sized for the largest batch and vocabulary serves the smaller ones.
 size_t expand_scratch_bytes(const ygg_shape& s) {
-    const int64_t lists = std::max((int64_t)s.batch * s.width * (((int64_t)s.vocab + 4095) / 4096), kShortLists);
+    const int64_t lists = std::max((int64_t)s.batch * s.width * (((int64_t)s.vocab + 4095) / 4096), kListsOf2048);
     return cand_bytes_of(lists, s.width) + stat_bytes_of(lists);
 }
 

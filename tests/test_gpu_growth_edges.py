@@ -21,8 +21,10 @@ def _cfg(B, D, W, V, seed=23):
 
 @pytest.mark.parametrize("B,D,W,V", [(1, 2, 8, 1023), (1, 2, 8, 1024), (1, 3, 8, 1025), (1, 2, 9, 4099), (2, 2, 33, 2048),
                                      (1, 2, 64, 2050), (1, 3, 12, 3001),
-                                     (12, 2, 16, 5001), (40, 2, 8, 5000), (40, 2, 3, 9001),      # chunks of 2048 and 4096
-                                     (1, 2, 60, 14000), (2, 2, 47, 50257), (1, 2, 62, 1000),     # fewer lists in a row than a quarter of W
+                                     # second step in chunks of 1024 (512 lists), of 2048 (288 to 768) and of 4096 (416)
+                                     (2, 2, 16, 16384), (2, 2, 16, 16388), (2, 2, 16, 16389), (2, 2, 16, 49152), (2, 2, 16, 49156),
+                                     (1, 2, 3, 70000), (12, 2, 16, 5001), (40, 2, 3, 9001),      # chunks of 2048
+                                     (40, 2, 8, 5000), (40, 2, 8, 5002),                         # chunks of 4096
                                      # few lists in a row for many new nodes: half or less of them, 17 to 31 lists, hardly any
                                      (1, 2, 60, 14000), (2, 2, 47, 50257), (1, 2, 64, 20000), (1, 2, 50, 24001), (1, 2, 62, 1000),
                                      (1, 2, 58, 70001), (1, 2, 33, 131080)])                     # several passes per chunk

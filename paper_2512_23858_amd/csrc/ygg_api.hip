@@ -279,8 +279,7 @@ size_t ygg_workspace_bytes(const ygg_shape* s, int32_t op, int32_t n_layers) {
         case YGG_OP_EXPAND:
         case YGG_OP_ATTACH: {
             if (check_shape(s, false, true) != YGG_OK) return 0;
-            // (attachment has always asked for more than the frontier rule, which the host tests pin; nothing uses the 256 bytes)
-            return expand_scratch_bytes(*s) + (op == YGG_OP_ATTACH ? 256 : 0);
+            return expand_scratch_bytes(*s);
         }
         case YGG_OP_ACCEPT: {
             if (check_shape(s, false, true) != YGG_OK) return 0;

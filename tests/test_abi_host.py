@@ -153,7 +153,9 @@ def test_attach_rejects_bad_arguments_on_the_host():
     assert call(_shape(), 1, good, ws_bytes=16) == ERR_WORKSPACE
     s = _shape()
     assert ygg.attach_pool_bytes(s) >= s.batch * (16 + s.width * (s.depth - 1) * 16)
-    assert ygg.workspace_bytes(s, ygg.OP_ATTACH) > ygg.workspace_bytes(s, ygg.OP_EXPAND)
+    assert ygg.workspace_bytes(s, ygg.OP_ATTACH) >= ygg.workspace_bytes(s, ygg.OP_EXPAND)
+    big = _shape(batch=400, width=8, n_nodes=25)           # its later steps need all of the scratch that is asked for
+    assert call(big, 2, good, ws_bytes=ygg.workspace_bytes(big, ygg.OP_ATTACH) - 1) == ERR_WORKSPACE
 
 
 @pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 8, 64])

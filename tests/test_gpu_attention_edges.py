@@ -41,34 +41,53 @@ def test_the_widest_tree_under_a_forced_shape(plan, waves):
     _check(cfg, host, parent, 100)
 
 
-# more than eight tiles to a workgroup of the longest sequence: the batch is cut into equal runs of tiles
-@pytest.mark.parametrize("B,Hq,Hkv,D,W,lens,Dh", [
-    (5, 32, 4, 6, 8, [5000, 0, 64, 1500, 333], 128),            # two row tiles, an empty and a one-tile prefix
-    (9, 32, 8, 5, 7, [4000, 100, 15, 15, 2000, 1, 700, 64, 3999], 128),
-    (16, 24, 4, 5, 8, [64 * i * 4 % 4096 for i in range(16)], 64),
-    (16, 32, 4, 6, 8, [0] * 9 + [5000] + [3] * 6, 128),         # many sequences of one tile: runs without a tile of their own
-    (2, 28, 4, 5, 8, [3000, 0], 128),
+# at least eight tiles to a workgroup of the longest sequence: the batch is cut into equal runs of tiles, as many as fill 256
+# workgroups (the last case's workgroups are pairs, which runs do not serve: equal splits of each sequence)
+@pytest.mark.parametrize("B,Hq,Hkv,D,W,lens,Dh,runs", [
+    (5, 32, 4, 6, 8, [5000, 0, 64, 1500, 333], 128, 32),            # two row tiles, an empty and a one-tile prefix
+    (9, 32, 8, 5, 7, [4000, 100, 15, 15, 2000, 1, 700, 64, 3999], 128, 32),
+    (16, 24, 4, 5, 8, [64 * i * 4 % 4096 for i in range(16)], 64, 64),
+    (16, 32, 4, 6, 8, [0] * 9 + [5000] + [3] * 6, 128, 32),         # many sequences of one tile: runs without a tile of their own
+    (2, 32, 4, 6, 8, [9000, 0], 128, 32),                           # exactly eight tiles, an empty prefix at the end
+    (2, 28, 4, 5, 8, [3000, 0], 128, 0),
 ])
-def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh):
+def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh, runs):
     cfg, host, parent = _inputs(_cfg(B, Hq, Hkv, D, W, Dh=Dh, seed=41), lens, max(lens), tree_gain=2.0)
+    got = ygg.attention_plan(shape_of(cfg, max_seq_len=max(lens)))
+    equal_splits = 256 // (B * Hkv * got["row_tiles"])
+    assert got["key_splits"] == (runs or equal_splits) and equal_splits != runs
     _check(cfg, host, parent, max(lens))
 
 
 # merge: whole wavefronts per row up to 4096 rows, fewer lanes above; rounds of 8, 16 or 32 splits
-@pytest.mark.parametrize("nsplit", [2, 7, 8, 9, 16, 17, 33, 70])
-@pytest.mark.parametrize("dtype,Dh", [("bf16", 128), ("bf16", 64), ("f32", 64)])
-def test_merge_of_few_and_many_splits(plan, nsplit, dtype, Dh):
+@pytest.mark.parametrize("nsplit", [2, 7, 8, 9, 16, 17, 33, 64])
+@pytest.mark.parametrize("Dh", [128, 64])
+def test_merge_of_few_and_many_splits(plan, nsplit, Dh):
     plan(nsplit=nsplit)
     for Hq, Hkv, D, W in ((3, 3, 3, 5), (64, 4, 5, 13)):        # 48 and 4224 rows
-        cfg, host, parent = _inputs(_cfg(1, Hq, Hkv, D, W, dtype=dtype, Dh=Dh, seed=53), [2200], 2200)
-        _check(cfg, host, parent, 2200)
+        cfg, host, parent = _inputs(_cfg(1, Hq, Hkv, D, W, Dh=Dh, seed=53), [4200], 4200)
+        assert ygg.attention_plan(shape_of(cfg, max_seq_len=4200))["key_splits"] == nsplit
+        _check(cfg, host, parent, 4200)
 
 
-# where a workgroup's share of the keys is short the launch plan takes fewer rows per workgroup than padding alone would
-@pytest.mark.parametrize("Hq,Hkv,D,W,L", [(32, 8, 6, 8, 4096), (32, 8, 6, 8, 500), (64, 8, 6, 8, 4096), (32, 8, 8, 16, 1024), (32, 32, 10, 32, 4096)])
-def test_short_runs_of_many_rows(Hq, Hkv, D, W, L):
+# fp32 takes a split per key tile while its rows are few; no more than 4096 rows are ever split
+@pytest.mark.parametrize("nsplit", [2, 7, 8, 9, 16, 17, 33, 64])
+@pytest.mark.parametrize("Dh", [128, 64])
+def test_merge_of_fp32_splits(nsplit, Dh):
+    L = 64 * nsplit - 16
+    cfg, host, parent = _inputs(_cfg(1, 3, 3, 3, 5, dtype="f32", Dh=Dh, seed=53), [L], L)
+    assert cfg.n_nodes == 16 and ygg.attention_plan(shape_of(cfg, max_seq_len=L))["key_splits"] == nsplit
+    _check(cfg, host, parent, L)
+
+
+# where a workgroup's share of the keys is short the launch plan takes another shape than the one of fewest padded rows:
+# (wavefronts, key shares) of these are (8, 1), (8, 1), (8, 1), (6, 1) and (8, 2)
+@pytest.mark.parametrize("Hq,Hkv,D,W,L,shape", [(32, 8, 6, 8, 4096, (4, 2)), (32, 8, 6, 8, 500, (4, 2)), (64, 8, 6, 8, 4096, (8, 2)),
+                                                (32, 8, 8, 16, 1024, (4, 2)), (32, 32, 10, 32, 4096, (6, 1))])
+def test_short_runs_of_many_rows(Hq, Hkv, D, W, L, shape):
     cfg, host, parent = _inputs(_cfg(1, Hq, Hkv, D, W, seed=61), [L], L, tree_gain=2.0)
-    assert ygg.attention_plan(shape_of(cfg, max_seq_len=L))["key_splits"] > 1
+    got = ygg.attention_plan(shape_of(cfg, max_seq_len=L))
+    assert (got["waves"], got["key_shares"]) == shape and got["key_splits"] > 1
     _check(cfg, host, parent, L)
 
 

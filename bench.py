@@ -9,7 +9,7 @@ chained: acceptance advances seq_lens on the device and the next step starts fro
 a decode loop runs (the caches are allocated with room for every step of a timed region).
 
 With no --config the run covers the five workload configurations and prints ONE JSON line: the
-headline is the widest tree (configs[3]: step time per layer, roofline of the attention main
+headline is the widest tree (321 nodes over 32768 tokens: step time per layer, roofline of the attention main
 kernel, CPU oracle on a bounded sample), `per_config` carries every configuration's figures.
 """
 from __future__ import annotations
@@ -360,7 +360,7 @@ def main():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=3)
-    ap.add_argument("--config", type=int, default=0, help="one workload configuration 1..5 (default: all five, headline configs[3])")
+    ap.add_argument("--config", type=int, default=0, help="one workload configuration 1..5 (default: all five, headline the widest tree)")
     ap.add_argument("--layers", type=int, default=0, help="override the number of layers per step")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--attention-only", action="store_true", help="time only the attention calls of a step")
@@ -411,7 +411,7 @@ def main():
         per_config.append(rec)
         if cid == head_id:
             head = (rec, detail)
-    # The HBM half of the metric needs a launch that can load the memory system: one layer of configs[1] moves 18 MB, which
+    # The HBM half of the metric needs a launch that can load the memory system: one layer of the 7B-shaped one moves 18 MB, which
     # no kernel streams at speed.  The default run therefore adds the same layer shape with 8 sequences x 4096 tokens
     # (550 MB per launch, 49 query rows per kv head: far below the ridge), attention calls only.
     kv_bound = None

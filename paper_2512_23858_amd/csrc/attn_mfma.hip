@@ -683,16 +683,17 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     i16x8 va[NDB][2];
     f32x16 st[RB];
     i16x8 pb[RB][2];
-    // Tile t lives in buffer t % NBUF.  The loop is unrolled NBUF-fold with the buffer index a compile-time constant, so
-    // that every LDS operand address is a loop-invariant per-lane register plus an immediate (no address arithmetic
-    // per block).
+    // Tile t lives in buffer t % NBUF.  The loop is unrolled NBUF-fold with the buffer index a compile-time constant (PING:
+    // but for the first tile and the last ones), so that every LDS operand address is a loop-invariant per-lane register
+    // plus an immediate (no address arithmetic per block).
     // A wavefront whose 32 rows all lie beyond the last query row (the padding of the last row tile) only keeps the
-    // barriers and its share of the tile fills company: its matrix and vector work would be spent on zeros, and what it
-    // does not burn the others get back as clock (config 5: 3 of 16 wavefronts per K/V stream, call 172.4 -> 165.9 us).
+    // barriers and its share of the tile fills company: its matrix and vector work would be spent on repeats of the last
+    // row, and what it does not burn the others get back as clock (392 rows per kv head, a ragged batch of 16: 3 of 16
+    // wavefronts per K/V stream, call 172.4 -> 165.9 us).
     // Wavefronts 0 to 4 always work, so that one SIMD keeps its pair and the workgroup keeps the pace of the other row
-    // tiles of its K/V stream: a workgroup that runs ahead of them fetches every tile from HBM a second time (config 4
-    // with all seven idle wavefronts of its last row tile skipping: 221 MB fetched per launch instead of 149).  Only the
-    // 256-row shape takes the branch: the six-wavefront shape measured 1.5 % slower with it.
+    // tiles of its K/V stream: a workgroup that runs ahead of them fetches every tile from HBM a second time (1284 rows x
+    // 32768 keys with all seven idle wavefronts of the last row tile skipping: 221 MB fetched per launch instead of 149).
+    // Only the 256-row shape takes the branch: the six-wavefront shape measured 1.5 % slower with it.
     constexpr bool kSkipIdle = NW == 8 && KS == 1;
     const bool has_rows = !kSkipIdle || wave <= 4 || __builtin_amdgcn_readfirstlane((int)(row_base + wrow * RB * 32 < R)) != 0;
     // PING: matrix and vector instructions of different wavefronts run side by side, but two wavefronts that want the same

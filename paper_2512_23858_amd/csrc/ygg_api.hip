@@ -75,7 +75,7 @@ static int64_t equal_splits(const ygg_shape& s, int row_tiles, int64_t tiles) {
     if (ns > (tiles + 2) / 3) ns = (tiles + 2) / 3;
     return ns < 1 ? 1 : ns;   // (plan_attention keeps to 64, which the merge takes)
 }
-// More key tiles than this to a workgroup of the longest sequence: a batch is cut into equal runs instead (plan_attention).
+// At least this many key tiles to a workgroup of the longest sequence: a batch is cut into equal runs instead (plan_attention).
 static constexpr int64_t kTilesForRuns = 8;
 
 // The padded rows decide where a workgroup streams many key tiles.  Where its share of them is short, a workgroup of fewer rows
@@ -148,9 +148,9 @@ AttnPlan plan_attention(const ygg_shape& s) {
             int best = padded(256);
             if (padded(128) * 100 <= best * 85) { best = padded(128); p.kshares = 2; }
             // 192 rows: two of the four SIMDs carry one wavefront only, so against 256-row workgroups it has to save a
-            // fifth of the rows (config 4 with 1344 instead of 1536 padded rows: 210 vs 202 us); against the paired
-            // 128-row shape, which meets a barrier every 16 matrix instructions, a tenth is enough (config 3 with 576
-            // instead of 640 padded rows and 10 instead of 6 key splits: 27.5 vs 28.1 us per call)
+            // fifth of the rows (1284 rows x 32768 keys with 1344 instead of 1536 padded rows: 210 vs 202 us); against the
+            // paired 128-row shape, which meets a barrier every 16 matrix instructions, a tenth is enough (516 rows x 4096
+            // keys with 576 instead of 640 padded rows and 10 instead of 6 key splits: 27.5 vs 28.1 us per call)
             if (padded(192) * 100 <= best * (p.kshares == 2 ? 92 : 80)) { p.waves = 6; p.kshares = 1; }
         }
         if (!kv8 && R > 64) short_run_shape(s, R, tiles, p);

@@ -66,12 +66,19 @@ int32_t check_workspace(const void* ws, size_t have, size_t need) {
 
 }  // namespace
 
+// K/V streams -- (sequence, kv head, split) or (kv head, run) -- whose workgroups all run at once: the kernel keeps a stream's row
+// tiles on one XCD, which has 32 compute units, and deals the streams out over eight.  Counting all 256 compute units instead let
+// 12 heads with three row tiles have seven splits: 84 streams, eleven on some XCDs, 33 workgroups and so a second round.  us per
+// call by that count -> by this one: 129 rows x 4096 tokens on 12 kv heads 27.0 -> 19.4, 257 rows x 16384 on 12 82.5 -> 52.9,
+// 776 rows x 8192 on 4 42.0 -> 28.1.  (Beyond 32 row tiles one round does not hold a stream; what fills the chip is left.)
+static int64_t streams_at_once(int64_t row_tiles) { return row_tiles <= 32 ? 8 * (32 / row_tiles) : 256 / row_tiles; }
+
 // Splits of every sequence's key tiles for a workgroup shape: fill the 256 CUs once -- the tile buffers leave room for one
 // workgroup per CU, and a second round of workgroups pays the start-up latency again while more splits add partial-result
 // traffic -- with about three key tiles per split at least (17 tiles of 49 rows on 32 kv heads: 5 / 6 / 8 splits measured
 // 16.4 / 15.7 / 16.4 us per layer).
 static int64_t equal_splits(const ygg_shape& s, int row_tiles, int64_t tiles) {
-    int64_t ns = 256 / ((int64_t)s.batch * s.n_kv_heads * row_tiles);
+    int64_t ns = streams_at_once(row_tiles) / ((int64_t)s.batch * s.n_kv_heads);
     if (ns > (tiles + 2) / 3) ns = (tiles + 2) / 3;
     return ns < 1 ? 1 : ns;   // (plan_attention keeps to 64, which the merge takes)
 }
@@ -95,7 +102,7 @@ static void short_run_shape(const ygg_shape& s, int R, int64_t tiles, AttnPlan& 
     constexpr float kNo = 1e30f;
     auto estimate = [&](const Kind& k) {
         const int rows = k.waves / k.kshares * 32, row_tiles = (R + rows - 1) / rows;
-        if ((int64_t)s.batch * s.n_kv_heads * row_tiles > 256) return kNo;   // more than one round of workgroups: not fitted
+        if ((int64_t)s.batch * s.n_kv_heads > streams_at_once(row_tiles)) return kNo;   // more than one round of workgroups: not fitted
         int64_t ns = equal_splits(s, row_tiles, tiles);
         if (s.batch >= 2 && tiles / ns >= kTilesForRuns) return kNo;   // a batch in equal runs
         if (s.batch >= 2 && p.kshares == 1 && k.kshares > 1) return kNo;   // stays a plan that runs can serve (pairs cannot), whatever the length bound
@@ -178,7 +185,7 @@ AttnPlan plan_attention(const ygg_shape& s) {
         const int64_t streams = (int64_t)s.n_kv_heads * p.row_tiles;
         const int64_t per_wg = ns > 0 ? tiles / ns : tiles;
         if (p.kshares == 1 && s.batch >= 2 && s.batch <= 256 && streams <= 128 && !ns_forced && per_wg >= kTilesForRuns) {
-            int64_t slots = 256 / streams;
+            int64_t slots = streams_at_once(p.row_tiles) / s.n_kv_heads;
             const int64_t most = (int64_t)s.batch * tiles;   // never more runs than tiles
             if (slots > most) slots = most;
             if (slots > 64) slots = 64;                      // the merge takes at most 64 splits per row

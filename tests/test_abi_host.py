@@ -288,6 +288,22 @@ def test_attention_scratch_of_the_longest_prefix_serves_the_shorter_ones(heads, 
             assert sizes[0] > 0 and sizes == sorted(sizes), (n, B)
 
 
+@pytest.mark.parametrize("kv_dtype,head_dim", [(1, 128), (1, 64), (2, 128)])
+def test_split_launches_run_in_one_round(kv_dtype, head_dim):
+    """A K/V stream's row tiles share one of the eight XCDs and its 32 compute units: splits and runs never ask for a second round."""
+    for heads in ((1, 1), (5, 5), (12, 12), (20, 4), (28, 4), (40, 40), (24, 6), (64, 8), (40, 10), (32, 1)):
+        for n in (9, 33, 49, 65, 129, 193, 257, 321, 700):
+            for B in (1, 2, 3, 7):
+                for L in (200, 1000, 4000, 16000):
+                    p = ygg.attention_plan(_shape(batch=B, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=head_dim,
+                                                  kv_dtype=kv_dtype, n_nodes=n, max_seq_len=L, kv_capacity=L + 8))
+                    if p["key_splits"] == 1 or p["row_tiles"] > 32:
+                        continue
+                    streams = heads[1] * p["key_splits"]
+                    most = 8 * (32 // p["row_tiles"])
+                    assert streams * B <= most or (B > 1 and p["key_shares"] == 1 and streams <= most), (heads, n, B, L, p)
+
+
 def test_plan_override_is_explicit_and_removable():
     """The tuning override is a call, not an environment variable, and leaves no trace once removed."""
     import os

@@ -32,6 +32,16 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(lib, name), f"{name} is declared in ygg.h but not exported"
 
 
+def test_attention_kernels_keep_to_their_registers():
+    """The kernels' metadata: none needs scratch memory (spilled registers cost a batch in runs 7 to 10 us per call)."""
+    with open(os.path.join(ROOT, "paper_2512_23858_amd", "libygg.so"), "rb") as f:
+        data = f.read()
+    scratch = {m[1].decode(): int.from_bytes(m[2] or m[3] or m[4], "big") for m in re.finditer(
+        rb"\.name(?:\xd9.|\xda..)(_Z\w+)\xbb\.private_segment_fixed_size(?:([\x00-\x7f])|\xcc(.)|\xcd(..))", data, re.S)}
+    attention = {name: size for name, size in scratch.items() if "attn_" in name}
+    assert sum("attn_mfma" in name for name in attention) >= 20 and not any(attention.values()), attention
+
+
 def test_status_strings_are_distinct():
     names = {ygg.status_string(i) for i in range(6)}
     assert len(names) == 6 and ygg.status_string(99) == "unknown status"

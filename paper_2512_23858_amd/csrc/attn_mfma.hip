@@ -74,7 +74,7 @@ __device__ __forceinline__ void e4m3x16_to_bf16(const u32x4& raw, uint4& first8,
 //
 // DHT: head_dim, 128 or 64 (bf16 K/V only for 64).  Everything below counts in k-steps of 16 and output blocks of 32
 // head_dim positions, and a direct-to-LDS instruction brings 1024 / ROWB rows.
-template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128>
+template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128, bool PING = false>
 __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1)) void attn_mfma_kernel(AttnArgs a) {
     static_assert(!BAL || KS == 1, "balanced batches: plain 32-row wavefronts only");
     static_assert(DHT == 128 || (DHT == 64 && !KV8), "head_dim 64: bf16 K/V only");
@@ -92,9 +92,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     constexpr int NRW = NW / KS;                                 // wavefronts along the rows
     constexpr int RW = NRW * RB * 32;                            // query rows per workgroup
     constexpr int TILEB = KT * ROWB;                             // bytes of one K (or V) tile
-    // Tiles are prefetched two ahead.  PING: the two wavefronts of a SIMD run half a block apart (see the loop), which takes
+    // Tiles are prefetched two ahead.  PING (plan_attention says when): the two wavefronts of a SIMD run half a block apart, which takes
     // a fourth tile buffer.
-    constexpr bool PING = KS == 1 && NW == 8;
+    static_assert(!PING || (KS == 1 && NW == 8 && !KV8), "pairs of wavefronts of the 256-row shape");
     constexpr int NBUF = PING ? 4 : 3;
     // wavefronts that issue tile fills (a power of two, so that each issues the same number per tile)
     constexpr int FILLERS = NW >= 8 ? 8 : NW >= 4 ? 4 : NW >= 2 ? 2 : 1;
@@ -939,18 +939,18 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 // Every variant's limit is raised to all the shared memory of a compute unit once per device.
 constexpr size_t kMaxSmem = kAttnMfmaMaxSmem;
 
-template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128>
+template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128, bool PING = false>
 hipError_t raise_variant() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<NW, RB, KT, KS, KV8, NT, BAL, DHT>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<NW, RB, KT, KS, KV8, NT, BAL, DHT, PING>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxSmem);
 }
 
-template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128>
+template <int NW, int RB, int KT, int KS, bool KV8, bool NT, bool BAL = false, int DHT = 128, bool PING = false>
 hipError_t launch_variant(const AttnArgs& a, const AttnPlan& p, hipStream_t st) {
     // K/V streams, each read by p.row_tiles workgroups, which share an XCD (workgroups are dealt out to the XCDs in turn)
     const dim3 grid((unsigned)((a.S + 7) / 8 * 8 * p.row_tiles));
     const size_t smem = attn_mfma_smem(NW, KS, DHT, a.G, a.N);
-    auto kern = attn_mfma_kernel<NW, RB, KT, KS, KV8, NT, BAL, DHT>;
+    auto kern = attn_mfma_kernel<NW, RB, KT, KS, KV8, NT, BAL, DHT, PING>;
     const unsigned threads = (NW + (KV8 ? 4 : 0)) * 64;  // KV8: plus the four loading wavefronts
     if (a.Dh != DHT) return hipErrorInvalidValue;
     if (smem > kMaxSmem) return hipErrorInvalidValue;  // cannot happen for N <= 1024: checked again for the sake of the launch
@@ -967,14 +967,19 @@ hipError_t launch_cfg(const AttnArgs& a, const AttnPlan& p, hipStream_t st) {
         if (a.slots > 0) return hipErrorInvalidValue;
         return launch_variant<NW, RB, KT, KS, true, false>(a, p, st);  // the loaders' register loads always stream
     } else {
-        if constexpr (KS == 1) {
-            if (a.slots > 0)
-                return p.row_tiles == 1 ? launch_variant<NW, RB, KT, KS, false, true, true, DHT>(a, p, st)
-                                        : launch_variant<NW, RB, KT, KS, false, false, true, DHT>(a, p, st);
+        auto go = [&](auto bal, auto ping) {
+            constexpr bool BAL = decltype(bal)::value, PING = decltype(ping)::value;
+            return p.row_tiles == 1 ? launch_variant<NW, RB, KT, KS, false, true, BAL, DHT, PING>(a, p, st)
+                                    : launch_variant<NW, RB, KT, KS, false, false, BAL, DHT, PING>(a, p, st);
+        };
+        if constexpr (KS == 1 && NW == 8) {
+            if (p.phases) return a.slots > 0 ? go(std::true_type{}, std::true_type{}) : go(std::false_type{}, std::true_type{});
         }
-        if (a.slots > 0) return hipErrorInvalidValue;
-        return p.row_tiles == 1 ? launch_variant<NW, RB, KT, KS, false, true, false, DHT>(a, p, st)
-                                : launch_variant<NW, RB, KT, KS, false, false, false, DHT>(a, p, st);
+        if constexpr (KS == 1) {
+            if (a.slots > 0) return go(std::true_type{}, std::false_type{});
+        }
+        if (a.slots > 0 || p.phases) return hipErrorInvalidValue;
+        return go(std::false_type{}, std::false_type{});
     }
 }
 
@@ -995,28 +1000,33 @@ hipError_t launch_shape(const AttnArgs& a, const AttnPlan& p, hipStream_t st) {
 template <int DHT>
 hipError_t raise_shapes() {
     hipError_t e = hipSuccess;
-    auto both = [&](auto nw, auto ks) {
-        if (e == hipSuccess) e = raise_variant<decltype(nw)::value, 1, 64, decltype(ks)::value, false, false, false, DHT>();
-        if (e == hipSuccess) e = raise_variant<decltype(nw)::value, 1, 64, decltype(ks)::value, false, true, false, DHT>();
-        if constexpr (decltype(ks)::value == 1) {
-            if (e == hipSuccess) e = raise_variant<decltype(nw)::value, 1, 64, 1, false, false, true, DHT>();
-            if (e == hipSuccess) e = raise_variant<decltype(nw)::value, 1, 64, 1, false, true, true, DHT>();
+    auto both = [&](auto nw, auto ks, auto ping) {
+        constexpr int NW = decltype(nw)::value, KS = decltype(ks)::value;
+        constexpr bool PING = decltype(ping)::value;
+        if (e == hipSuccess) e = raise_variant<NW, 1, 64, KS, false, false, false, DHT, PING>();
+        if (e == hipSuccess) e = raise_variant<NW, 1, 64, KS, false, true, false, DHT, PING>();
+        if constexpr (KS == 1) {
+            if (e == hipSuccess) e = raise_variant<NW, 1, 64, 1, false, false, true, DHT, PING>();
+            if (e == hipSuccess) e = raise_variant<NW, 1, 64, 1, false, true, true, DHT, PING>();
         }
     };
-    both(IntC<4>{}, IntC<1>{}); both(IntC<6>{}, IntC<1>{}); both(IntC<8>{}, IntC<1>{});
-    both(IntC<2>{}, IntC<2>{}); both(IntC<4>{}, IntC<2>{}); both(IntC<8>{}, IntC<2>{});
+    constexpr std::false_type no;
+    both(IntC<4>{}, IntC<1>{}, no); both(IntC<6>{}, IntC<1>{}, no); both(IntC<8>{}, IntC<1>{}, no);
+    both(IntC<8>{}, IntC<1>{}, std::true_type{});
+    both(IntC<2>{}, IntC<2>{}, no); both(IntC<4>{}, IntC<2>{}, no); both(IntC<8>{}, IntC<2>{}, no);
     return e;
 }
 
 }  // namespace
 
-// Dynamic shared memory of a workgroup: three or four K and V tile buffers of 64 keys, space for Q where the spare buffers do
-// not hold it, the ancestor bitmasks of the nodes the rows belong to, and the parent table.
+// Dynamic shared memory of a workgroup: three K and V tile buffers of 64 keys, space for Q where the spare buffers do not hold it
+// (in the 256-row shape as much as the fourth buffer of its opposite phases, which then holds Q), the ancestor bitmasks of the
+// nodes the rows belong to, and the parent table.
 size_t attn_mfma_smem(int waves, int kshares, int head_dim, int group, int nodes) {
     const size_t tile = (size_t)64 * 2 * head_dim;
     const int rw = waves / kshares * 32;
     const int nodes_local = rw % group == 0 ? rw / group : (rw + group - 1) / group + 1;
-    const int nbuf = kshares == 1 && waves == 8 ? 4 : 3, q_outside = waves - 4 * (nbuf - 2);
+    const int nbuf = 3, q_outside = waves - 4 * (nbuf - 2);
     return 2 * nbuf * tile + (q_outside > 0 ? q_outside * tile / 2 : 0) +
            (size_t)nodes_local * ((nodes + 31) / 32) * 4 + (size_t)((nodes + 63) / 64) * 256;
 }

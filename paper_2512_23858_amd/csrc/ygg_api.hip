@@ -84,6 +84,8 @@ static int64_t equal_splits(const ygg_shape& s, int row_tiles, int64_t tiles) {
 }
 // At least this many key tiles to a workgroup of the longest sequence: a batch is cut into equal runs instead (plan_attention).
 static constexpr int64_t kTilesForRuns = 8;
+// At least this many tiles of one sequence to a workgroup: opposite phases (plan_attention).
+static constexpr int64_t kTilesForPhases128 = 20, kTilesForPhases64 = 64;
 
 // The padded rows decide where a workgroup streams many key tiles.  Where its share of them is short, a workgroup of fewer rows
 // is the better one: it starts sooner (fewer rows of Q, fewer wavefronts to meet) and its tiles take less time, so with the
@@ -191,6 +193,10 @@ AttnPlan plan_attention(const ygg_shape& s) {
             if (slots > 64) slots = 64;                      // the merge takes at most 64 splits per row
             if (slots >= 2) p.slots = (int32_t)slots;
         }
+        // Opposite phases of the two wavefronts of a SIMD pay where a workgroup streams many tiles of one sequence: the first tile and
+        // the last four go through a body with conditions and pay four barriers each.  @MEAS@
+        const int64_t segment = p.slots > 0 ? std::min(s.batch * tiles / p.slots, tiles) : tiles / std::clamp(ns, (int64_t)1, (int64_t)64);
+        p.phases = p.waves == 8 && p.kshares == 1 && segment >= (s.head_dim == 128 ? kTilesForPhases128 : kTilesForPhases64);
     } else {
         // vector path: one wavefront per (row, split); aim for ~4096 wavefronts
         ns = (4096 + rows - 1) / rows;

@@ -54,6 +54,7 @@ struct AttnPlan {
     int32_t kshares;        // MFMA kernel: 1, or 2 = pairs of wavefronts split every key tile
     int32_t row_tiles;      // MFMA kernel: workgroups along the N*G query rows of one kv head
     int32_t slots;          // MFMA kernel, batches: equal runs of key tiles per (kv head, row tile); 0 = one sequence per workgroup
+    int32_t phases;         // MFMA kernel, 8 wavefronts: the two of a SIMD in opposite phases
     size_t part_o_bytes, part_rec_bytes, seq_splits_bytes;
 };
 

@@ -19,18 +19,20 @@ def plan():
     ygg.set_attention_plan()
 
 
-# query heads on one kv head and a tree of 41 nodes: 246 rows, or 41 with one query head
-@pytest.mark.parametrize("waves,kshares,Hq", [(8, 1, 6), (8, 1, 4), (6, 1, 6), (4, 1, 6), (8, 2, 6), (4, 2, 2), (2, 2, 1)])
+# query heads on one kv head and a tree of 41 nodes: 246 rows, or 41 with one query head.  The 256-row shape runs its wavefronts in
+# opposite phases where the longest prefix leaves a workgroup many tiles, whatever the lengths then are.
+@pytest.mark.parametrize("waves,kshares,Hq,longest", [(8, 1, 6, 0), (8, 1, 4, 0), (8, 1, 6, 8300), (8, 1, 4, 8300), (6, 1, 6, 0),
+                                                      (4, 1, 6, 0), (8, 2, 6, 0), (4, 2, 2, 0), (2, 2, 1, 0)])
 @pytest.mark.parametrize("Dh", [128, 64])
 @pytest.mark.parametrize("nsplit", [1, 2])
-def test_every_workgroup_shape_from_one_tile_upwards(plan, waves, kshares, Hq, Dh, nsplit):
+def test_every_workgroup_shape_from_one_tile_upwards(plan, waves, kshares, Hq, longest, Dh, nsplit):
     plan(waves=waves, rblocks=1, kshares=kshares, nsplit=nsplit)
     for keys in (41, 63, 64, 65, 100, 129, 192, 200, 257, 320, 330, 385, 450, 513, 640, 705, 1000):
         L = keys - 41
-        cfg, host, parent = _inputs(_cfg(1, Hq, 1, 5, 8, Dh=Dh, seed=31), [L], max(L, 1), tree_gain=2.0)
-        got = ygg.attention_plan(shape_of(cfg, max_seq_len=max(L, 1)))
+        cfg, host, parent = _inputs(_cfg(1, Hq, 1, 5, 8, Dh=Dh, seed=31), [L], max(L, longest, 1), tree_gain=2.0)
+        got = ygg.attention_plan(shape_of(cfg, max_seq_len=max(L, longest, 1)))
         assert (got["waves"], got["key_shares"]) == (waves, kshares)
-        _check(cfg, host, parent, max(L, 1))
+        _check(cfg, host, parent, max(L, longest, 1))
 
 
 @pytest.mark.parametrize("waves", [8, 6, 4])
@@ -49,6 +51,8 @@ def test_the_widest_tree_under_a_forced_shape(plan, waves):
     (16, 24, 4, 5, 8, [64 * i * 4 % 4096 for i in range(16)], 64, 64),
     (16, 32, 4, 6, 8, [0] * 9 + [5000] + [3] * 6, 128, 32),         # many sequences of one tile: runs without a tile of their own
     (2, 32, 4, 6, 8, [9000, 0], 128, 32),                           # exactly eight tiles, an empty prefix at the end
+    (6, 48, 8, 5, 8, [7500, 0, 64, 1500, 15, 333], 128, 32),        # runs of up to 22 tiles: opposite phases
+    (6, 48, 8, 5, 8, [23000, 0, 64, 1500, 15, 333], 64, 32),        # up to 67, as head_dim 64 asks for
     (2, 28, 4, 5, 8, [3000, 0], 128, 0),
 ])
 def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh, runs):

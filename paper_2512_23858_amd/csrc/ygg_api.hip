@@ -28,9 +28,9 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 unsigned char* g_scratch_ptr[kMaxDevices];
 
 // What a segment of a balanced batch costs beside its key tiles (Q, masks, an empty pipeline, the partial rows), in tiles.
-// Per layer, 0 / 3 / 6 / 8 tiles: 16 sequences of 512 to 8192 tokens with 392 rows on 8 kv heads 161 / 152 / 148 / 149 us, 8 with
-// 516 rows 133 / 118 / 110 / 111, 4 of 1024 to 16384 with 196 rows 71 / 66 / 62 / 59; 16 equal sequences 127.5 / 126.2 / 126.0 /
-// 126.8.
+// us per call, 0 / 3 / 6 / 8 tiles: 16 sequences of 512 to 8192 tokens with 392 rows on 8 kv heads 165 / 157 / 152 / 149, 8 of 256 to
+// 8192 with 516 rows 115 / 111 / 110 / 112, 4 of 1024 to 16384 with 196 rows 59 / 57 / 54 / 53, 40 of 100 to 3000 with 392 rows 169 /
+// 165 / 159 / 156, 9 of 1 to 4000 with 164 rows 42 / 33 / 29 / 29; six equal ones of 1024 with 516 rows 41 / 39 / 40 / 41.
 constexpr int32_t kSegmentLead = 6;
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -194,7 +194,10 @@ AttnPlan plan_attention(const ygg_shape& s) {
             if (slots >= 2) p.slots = (int32_t)slots;
         }
         // Opposite phases of the two wavefronts of a SIMD pay where a workgroup streams many tiles of one sequence: the first tile and
-        // the last four go through a body with conditions and pay four barriers each.  @MEAS@
+        // the last four go through a body with conditions, and a tile takes four barriers instead of one.  One sequence on 8 kv heads,
+        // us per call without -> with them, by tiles to a workgroup: head_dim 128, 7 tiles (1284 rows x 2048 tokens) 29.6 -> 32.2, 13
+        // 40.8 -> 43.5, 26 61.6 -> 62.8, 52 106.5 -> 104.3, 22 (1032 rows x 8192) 49.9 -> 48.7, 16 (772 rows) 42.4 -> 42.7, 32 69.7 ->
+        // 67.1; head_dim 64, 13 tiles 28.5 -> 33.3, 52 66.9 -> 70.0, runs of 64 (4 x 8192, 776 rows) 82.7 -> 82.2, of 128 149 -> 145.
         const int64_t segment = p.slots > 0 ? std::min(s.batch * tiles / p.slots, tiles) : tiles / std::clamp(ns, (int64_t)1, (int64_t)64);
         p.phases = p.waves == 8 && p.kshares == 1 && segment >= (s.head_dim == 128 ? kTilesForPhases128 : kTilesForPhases64);
     } else {
@@ -330,6 +333,7 @@ static int32_t tree_attention_impl(const ygg_shape* s, const void* q, const void
     a.nsplit = p.nsplit; a.max_seq_len = s->max_seq_len; a.cap = s->kv_capacity; a.scale = s->softmax_scale;
     a.slots = p.slots;
     a.lead = kSegmentLead;
+    a.seq_runs = p.slots > 0 && p.slots % s->batch == 0 ? p.slots / s->batch : 0;
     a.S = p.slots > 0 ? a.Hkv * p.slots : a.B * a.Hkv * p.nsplit;
     a.rows_total = a.B * a.N * a.Hq;
     a.mul_nsplit = 0xffffffffu / (uint32_t)a.nsplit;

@@ -38,6 +38,7 @@ struct AttnArgs {
     int32_t nsplit, max_seq_len;
     int32_t slots;    // matrix-core kernel, batches: > 0 = workgroups take equal runs of the concatenated key tiles (nsplit = slots)
     int32_t lead;     // slots > 0: what a segment costs beside its key tiles, in tiles
+    int32_t seq_runs; // slots > 0: runs to a sequence where that is a whole number, else 0
     int32_t S;        // matrix-core kernel: K/V streams, slots * Hkv or B * Hkv * nsplit
     int32_t rows_total;                        // B * N * Hq
     int32_t row_tiles;                         // matrix-core kernel: workgroups along the query rows

@@ -63,6 +63,16 @@ def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh, runs):
     _check(cfg, host, parent, max(lens))
 
 
+# equal lengths with a whole number of runs to a sequence (runs end where sequences do), from fewer tiles than runs upwards; one that differs
+@pytest.mark.parametrize("lens", [[0] * 4, [15] * 4, [16] * 4, [300] * 4, [463] * 4, [464] * 4, [4300] * 4, [4300] * 3 + [4200], [9000] * 2])
+@pytest.mark.parametrize("Dh", [128, 64])
+def test_equal_lengths_in_runs(lens, Dh):
+    B, longest = len(lens), max(4300, max(lens))
+    cfg, host, parent = _inputs(_cfg(B, 32, 4, 6, 8, Dh=Dh, seed=43), lens, longest, tree_gain=2.0)
+    assert ygg.attention_plan(shape_of(cfg, max_seq_len=longest))["key_splits"] == 32 and 32 % B == 0
+    _check(cfg, host, parent, longest)
+
+
 # merge: whole wavefronts per row up to 4096 rows, fewer lanes above; rounds of 8, 16 or 32 splits
 @pytest.mark.parametrize("nsplit", [2, 7, 8, 9, 16, 17, 33, 64])
 @pytest.mark.parametrize("Dh", [128, 64])

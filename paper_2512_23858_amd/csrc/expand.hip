@@ -406,7 +406,9 @@ constexpr int kMergePool = 1024;   // pooled candidates of one sequence
 
 // Where a row has few lists for many new nodes, W of the lists' first four entries are all or most of these: nearly everything would
 // reach the threshold.  The first 32 or 64 entries of every list then decide, sixteen to a lane: lanes c << share .. share a list.
-__device__ __forceinline__ bool few_lists(int nchunk, int W) { return nchunk * kFront < 2 * W; }   // (fewer than 32 lists)
+// That is a trip to memory more.  us per first step, the first four -> this: 12 nodes from 5 lists 8.5 -> 9.5, 8 from one 7.1 -> 7.7,
+// 16 from 5 8.8 -> 9.2, 24 from 10 9.3 -> 9.8; 16 from one 8.8 -> 8.3, 20 from 5 14.8 -> 9.7, 40 from 10 86 -> 11.
+__device__ __forceinline__ bool few_lists(int nchunk, int W) { return W > 12 && nchunk * kFront < W + W / 4; }   // (fewer than 20 lists)
 struct Shared16 {
     Cand cd[16];
     const Cand* list;   // the lane's list, its length, what the lanes hold of it, and how many entries this lane holds
@@ -506,9 +508,9 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
 #pragma unroll
     for (int i = 0; i < kFront; ++i) e[i] = i < h.stat.count ? entry_of(h.front[i]) : Entry{0, kNone, 0};
 
-    // threshold: W list heads reach it (with fewer lists than twice W, W of the first entries of every list: the lowest of these
+    // threshold: W list heads reach it (with fewer lists than four times W, W of the first entries of every list: the lowest of these
     // heads would let too many through), so nothing below it can be among the W best
-    const bool few = a.F * a.nchunk < 2 * a.W;   // then F == 1 or one list a row: one wavefront
+    const bool few = nwaves == 1 && a.F * a.nchunk < 4 * a.W;   // (below 2W it is one wavefront: F == 1 or one list a row)
     const bool deep = few && a.F == 1 && few_lists(a.nchunk, a.W);
     auto put = [&](const Entry& x) {
         const int pos = atomicAdd(&pooled, 1);
@@ -807,7 +809,8 @@ __global__ __launch_bounds__(1024) void attach_finish_kernel(FinishArgs a, int n
 #pragma unroll
             for (int i = 0; i < kFront; ++i) g[i] = i < h.stat.count ? key_of(h.front[i].val) : 0u;
             const uint32_t head_key[1] = {g[0]};
-            const uint32_t t = a.nchunk >= a.W ? wave_threshold<1>(head_key, a.W) : wave_threshold<kFront>(g, a.W);
+            // (W of fewer than 2W heads: the lowest of them let too many through, 24 rows of 25 lists 34.9 -> 47.0 us for two steps)
+            const uint32_t t = a.nchunk >= 2 * a.W ? wave_threshold<1>(head_key, a.W) : wave_threshold<kFront>(g, a.W);
             bool sel[kFront];
 #pragma unroll
             for (int i = 0; i < kFront; ++i) sel[i] = g[i] >= t;

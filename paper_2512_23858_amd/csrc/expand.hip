@@ -293,11 +293,13 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
         keys[tid] = best;
         __syncthreads();
         const uint32_t t = max(group_threshold<E == 4>(keys, 4, lane, want), t_seen);
-        const float tf = t <= 1u ? -INFINITY : float_of(t);
+        // (equal ones of a later pass come too late, for their higher indices: from the next key on, where +inf is followed by a NaN,
+        // which nothing reaches, and -0 by 0, which -0 reaches as well: one candidate more)
+        const uint32_t least = !ONE && t == t_seen ? t + 1 : t;
+        const float tf = least <= 1u ? -INFINITY : float_of(least);
         bool sel[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i)   // (equal ones of a later pass come too late: higher indices; 0 is above -0)
-            sel[i] = !ONE && t == t_seen ? v[i] > tf || (v[i] == tf && key_of(v[i]) > t) : v[i] >= tf;
+        for (int i = 0; i < E; ++i) sel[i] = v[i] >= tf;
         if (!ONE && t > 1u) t_seen = t;
         auto entry = [&](int i) { return order_of(key_of(v[i]), (uint32_t)index(i)); };
         // Of many equal logits (a masked vocabulary's -inf or -1e9) a wavefront keeps the W best by index: a step of 32 x 128256 logits

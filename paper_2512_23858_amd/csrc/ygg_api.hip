@@ -90,9 +90,10 @@ static constexpr int64_t kTilesForPhases128 = 20, kTilesForPhases64 = 64;
 // The padded rows decide where a workgroup streams many key tiles.  Where its share of them is short, a workgroup of fewer rows
 // is the better one: it starts sooner (fewer rows of Q, fewer wavefronts to meet) and its tiles take less time, so with the
 // compute units filled either way the call is done sooner although each K/V byte is fetched for fewer rows.  The estimate is a
-// start and a time per tile of 64 keys for each shape, in us, fitted per head_dim (128: 56 calls of 129 to 516 rows on 8 and 32
-// kv heads over 1024 to 16384 tokens, mean error 4 %), plus the merge.  The shape of fewest padded rows stays unless another
-// promises 4 % less.  Measured, us per call with the shape of fewest padded rows -> with this rule's, 8 kv heads: 196 rows
+// start and a time per tile of 64 keys for each shape, in us, fitted per head_dim on calls of 129 to 516 rows, plus the merge.  On 252
+// calls per head_dim (65 to 1284 rows on 4, 8, 12, 32 and 40 kv heads over 256 to 16384 tokens) its mean error is 7 % (head_dim 64:
+// 11 %); the plan's shape is 1.4 % (1.7 %) slower than the best of the five on average and at most 32 % (36 %), that of fewest padded
+// rows 8.9 % (8.8 %) and 43 % (54 %).  The shape of fewest padded rows stays unless another promises 4 % less.  Measured, us per call with the shape of fewest padded rows -> with this rule's, 8 kv heads: 196 rows
 // x 633 tokens 17.4 -> 12.7 (tiles of 256 rows -> 64), x 4096 20.4 -> 16.6, 176 x 2078 17.8 -> 14.7 (192 -> 64), 516 x 1024
 // 17.8 -> 16.7 (192 -> 64), 392 x 4096 21.7 -> 20.9 (256 -> 128); 32 kv heads: 321 rows x 4096 48.1 -> 43.2 (128 -> 192).  At
 // 16384 tokens tiles of 256 lead again (392 rows: 39.0, of 128 44.3).

@@ -517,6 +517,12 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                     o[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         __builtin_bit_cast(bf16x8, va[db][m2]), __builtin_bit_cast(bf16x8, pb[rb][m2]), o[rb][db], 0, 0, 0);
     };
+    auto block_max = [](const f32x16& x) {
+        float m = x[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) m = fmaxf(m, x[v]);
+        return m;
+    };
     // blk0 = first key of the 32-key block; clean = the block's tile lies wholly inside the prefix
     auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], int blk0, bool clean) {
 #pragma unroll
@@ -564,10 +570,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             float ps = weights(m_ref[rb]);
             if (__builtin_expect(__any(!(ps <= kWeightSumLimit)), 0)) {
                 // Rare, wave-uniform: set or raise the reference from the block's row maxima, rescale what has been summed.
-                float mt = st[rb][0];
-#pragma unroll
-                for (int v = 1; v < 16; ++v) mt = fmaxf(mt, st[rb][v]);
-                mt *= c_scale;  // c_scale > 0: the maximum commutes with the scaling
+                const float mt = block_max(st[rb]) * c_scale;  // c_scale > 0: the maximum commutes with the scaling
                 const float row_max = fmaxf(mt, __shfl_xor(mt, 32));
                 const bool raise = row_max > m_ref[rb] + kRescaleGap;  // same answer in both half-lanes of a row
                 const float alpha = raise ? __builtin_amdgcn_exp2f(m_ref[rb] - row_max) : 1.f;
@@ -819,6 +822,16 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         read_k(0, kh, ka);
         if constexpr (PING) read_v(0, 0, va);
         qk(ka, st);
+        // A first block of cache keys, which every row sees, sets the reference here: its row maxima, as the rare branch of the
+        // softmax would take them, but without the weights that only find out that there is none yet and without rescaling an O of
+        // zeros.  XX
+        if (k0 + KT <= clean_end) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const float mt = block_max(st[rb]) * c_scale;
+                m_ref[rb] = fmaxf(mt, __shfl_xor(mt, 32));
+            }
+        }
     }
     int t = 0;
     if (late) step();

@@ -824,7 +824,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         qk(ka, st);
         // A first block of cache keys, which every row sees, sets the reference here: its row maxima, as the rare branch of the
         // softmax would take them, but without the weights that only find out that there is none yet and without rescaling an O of
-        // zeros.  XX
+        // zeros (49 rows x 1024 tokens on 32 kv heads 13.03 -> 12.87 us per call, 516 rows x 4096 on 8 23.8 -> 23.6).
         if (k0 + KT <= clean_end) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {

@@ -665,7 +665,12 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 #pragma unroll
         for (int s = 0; s < NS; ++s) qreg[0][s] = *reinterpret_cast<const bf16x8*>(qp + ((32 * s) ^ pair_xor));
     }
-    if (has_tree_keys) {
+    // The ancestor masks are needed from the first tile with tree keys on.  Unless that is the very first one they are built in the
+    // iteration before it, behind barriers that are there anyway, while the tile itself is still on its way (65 rows x 1024 tokens on
+    // 40 kv heads 16.3 -> 15.8 us per call with what the pairs' merge below gives; the shapes of eight wavefronts measured no gain).
+    const int tree_tile = max((L - k0) / KT, 0);
+    const int masks_at = !KV8 && !PING && NW != 8 && has_tree_keys ? tree_tile - 1 : -1;
+    if (has_tree_keys && masks_at < 0) {
         if constexpr (KV8) dma_wait_keep<0>();
         lds_barrier();
         build_masks();
@@ -685,6 +690,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         if constexpr (KV8) {
             lds_barrier();
         } else {
+            if constexpr (!PING && NW != 8) {
+                if (__builtin_expect(t == masks_at, 0)) build_masks();
+            }
             if (t + 2 < ntiles) dma_wait_keep<PT>(); else dma_wait_keep<0>();  // tile t+1 landed, t+2 may be in flight
             lds_barrier();
             if (t + 3 < ntiles) fill_tile(buf, tile_base + 3 * KT);
@@ -861,55 +869,17 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         });
     }
     if (PING && !late) step();
-    if constexpr (KS == 2) {
-        // Merge of the two key shares of a row block.  Both carry O~ and l relative to their own
-        // reference m_ref; the share of block 1 hands its state over through the (now idle) tile
-        // buffers, lane for lane, and the share of block 0 rescales both to the larger reference.
-        constexpr int XR = 16 * NDB + 2;  // a lane's accumulators, then m and l
-        float* xch = reinterpret_cast<float*>(smem) + wrow * (RB * XR * 64) + lane;  // [wrow][rb][XR][64 lanes]
-        __syncthreads();  // every wavefront is done with the tiles
-        if (kh == 1) {
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                float* x = xch + rb * XR * 64;
-#pragma unroll
-                for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) x[(16 * db + v) * 64] = o[rb][db][v];
-                x[(XR - 2) * 64] = m_ref[rb];
-                x[(XR - 1) * 64] = l_run[rb];
-            }
-        }
-        __syncthreads();
-        if (kh == 1) return;
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const float* x = xch + rb * XR * 64;
-            const float m1 = x[(XR - 2) * 64], l1 = x[(XR - 1) * 64];
-            const float mm = fmaxf(m_ref[rb], m1);
-            // a share that saw no visible key has m = -inf, l = 0, O~ = 0: weight 0 keeps it out
-            const float w0 = m_ref[rb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref[rb] - mm);
-            const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
-            m_ref[rb] = mm;
-            l_run[rb] = l_run[rb] * w0 + l1 * w1;
-#pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[rb][db][v] = o[rb][db][v] * w0 + x[(16 * db + v) * 64] * w1;
-        }
-    }
-
-    // epilogue: lane (n, g2) holds, for its row, dh = 32 db + 8 (v/4) + 4 g2 + (v%4)
-    const float v_unit = KV8 ? a.v_scale[hk] : 1.f;  // KV8: V = v_scale * code value
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        const float l_tot = l_run[rb] + __shfl_xor(l_run[rb], 32);
-        if (rg_of[rb] < 0) continue;
+    // epilogue: lane (n, g2) holds, for its row, dh = 32 db + 8 (v/4) + 4 g2 + (v%4); finish writes the blocks db = FROM .. TO-1
+    float l_tot = 0.f, c = 0.f;   // the row's sum of weights; a bound on its magnitudes
+    auto finish = [&](auto from, auto to, int rb) __attribute__((always_inline)) {
+        constexpr int FROM = decltype(from)::value, TO = decltype(to)::value;
+        const float v_unit = KV8 ? a.v_scale[hk] : 1.f;  // KV8: V = v_scale * code value
+        if (rg_of[rb] < 0) return;
         if (direct) {
             const float inv = v_unit / l_tot;
             uint16_t* op = static_cast<uint16_t*>(a.out) + (int64_t)rg_of[rb] * DH + 4 * g2;
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
+            for (int db = FROM; db < TO; ++db)
 #pragma unroll
                 for (int vq = 0; vq < 4; ++vq) {
                     uint2 w;
@@ -917,27 +887,21 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                     w.y = pack_bf16x2(o[rb][db][4 * vq + 2] * inv, o[rb][db][4 * vq + 3] * inv);
                     *reinterpret_cast<uint2*>(op + 32 * db + 8 * vq) = w;
                 }
-            if (a.lse && g2 == 0) a.lse[rg_of[rb]] = m_ref[rb] * kLn2 + logf(l_tot);
+            if (a.lse && g2 == 0 && FROM == 0) a.lse[rg_of[rb]] = m_ref[rb] * kLn2 + logf(l_tot);
         } else {
-            // Partial outputs travel as fp16 relative to the row's largest magnitude c (kept in fp32 beside m and l):
-            // half the traffic of fp32 here and in the merge, an error of at most 2^-12 c per element whatever the
+            // Partial outputs travel as fp16 relative to c (kept in fp32 beside m and l), which is the row's largest magnitude or
+            // little more: half the traffic of fp32 here and in the merge, an error of at most 2^-12 c per element whatever the
             // range of V (bf16 partials would cost up to a whole bf16 ulp of the merged row, which outputs of
             // magnitude 4 cannot afford inside 2e-2).  Streaming stores: the partials are read once, by the merge,
             // and leaving them dirty in L2 only lengthens the write-back at the end of this kernel.
-            float rmax = 0.f;
-#pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, fabsf(o[rb][db][v]));
-            rmax = fmaxf(rmax, __shfl_xor(rmax, 32));
-            const float c = fmaxf(rmax, 1e-30f);
+            c = fmaxf(c, 1e-30f);
             const float inv_c = 1.f / c;   // (v_rcp_f32 alone would give 0 for c above 2^126, whose reciprocal is subnormal)
             // The two lanes of a row hold alternating groups of four head_dim positions; swapping halves between them
             // (v_permlane32_swap) leaves each with eight consecutive ones, so a store covers 32 contiguous bytes of a row.
             _Float16* po = reinterpret_cast<_Float16*>(a.part_o) + ((int64_t)split * a.rows_total + rg_of[rb]) * DH + 8 * g2;
             u32x4 w[NDB][2];
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
+            for (int db = FROM; db < TO; ++db)
 #pragma unroll
                 for (int vp = 0; vp < 2; ++vp) {
                     const f32x4 ve = {o[rb][db][8 * vp] * inv_c, o[rb][db][8 * vp + 1] * inv_c,
@@ -953,13 +917,69 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             // the stores of a row leave back to back: neighbouring 32-byte pieces then combine into whole lines
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
+            for (int db = FROM; db < TO; ++db)
 #pragma unroll
                 for (int vp = 0; vp < 2; ++vp)
                     __builtin_nontemporal_store(w[db][vp], reinterpret_cast<u32x4*>(po + 32 * db + 16 * vp));
             __builtin_amdgcn_sched_barrier(0);
-            if (g2 == 0)   // reference in base-2 units of the scaled scores; KV8: V = v_scale * code value
+            if (g2 == 0 && FROM == 0)   // reference in base-2 units of the scaled scores; KV8: V = v_scale * code value
                 a.part_rec[(int64_t)split * a.rows_total + rg_of[rb]] = make_float3(m_ref[rb], l_tot, c * v_unit);
+        }
+    };
+    if constexpr (KS == 2) {
+        // Merge of the two key shares of a row block.  Both carry O~ and l relative to their own reference m_ref.  Each
+        // keeps one half of head_dim and hands the other over through the (now idle) tile buffers, lane for lane, with m, l and its
+        // row's largest magnitude; both then rescale what they have of both shares to the larger reference and finish their
+        // halves side by side (49 rows x 1024 tokens on 32 kv heads 12.9 -> 12.6 us per call).
+        static_assert(RB == 1, "one row block to a pair");
+        constexpr int HV = 8 * NDB;        // values of a lane's half
+        constexpr int XR = HV + 3;
+        float* const xch = reinterpret_cast<float*>(smem) + (wrow * 2 * XR) * 64 + lane;   // [wrow][share it is for][XR][64 lanes]
+        float rmax = 0.f;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, fabsf(o[0][db][v]));
+        rmax = fmaxf(rmax, __shfl_xor(rmax, 32));
+        const float l_own = l_run[0] + __shfl_xor(l_run[0], 32);
+        __syncthreads();  // every wavefront is done with the tiles
+        auto half = [&](auto h) __attribute__((always_inline)) {   // this wavefront keeps half h
+            constexpr int H = decltype(h)::value;
+            float* out = xch + (1 - H) * XR * 64;
+            const float* in = xch + H * XR * 64;
+#pragma unroll
+            for (int x = 0; x < HV; ++x) out[x * 64] = o[0][(1 - H) * NDB / 2 + x / 16][x % 16];
+            out[HV * 64] = m_ref[0];
+            out[(HV + 1) * 64] = l_own;
+            out[(HV + 2) * 64] = rmax;
+            __syncthreads();
+            const float m1 = in[HV * 64], l1 = in[(HV + 1) * 64], r1 = in[(HV + 2) * 64];
+            const float mm = fmaxf(m_ref[0], m1);
+            // a share that saw no visible key has m = -inf, l = 0, O~ = 0: weight 0 keeps it out
+            const float w0 = m_ref[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref[0] - mm);
+            const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
+            m_ref[0] = mm;
+            l_tot = H == 0 ? l_own * w0 + l1 * w1 : l1 * w1 + l_own * w0;
+            c = fminf(H == 0 ? rmax * w0 + r1 * w1 : r1 * w1 + rmax * w0, 3.402823466e38f);
+#pragma unroll
+            for (int x = 0; x < HV; ++x)
+                o[0][H * NDB / 2 + x / 16][x % 16] = o[0][H * NDB / 2 + x / 16][x % 16] * w0 + in[x * 64] * w1;
+            finish(IntC<H * NDB / 2>{}, IntC<(H + 1) * NDB / 2>{}, 0);
+        };
+        if (kh == 0) half(IntC<0>{}); else half(IntC<1>{});
+    } else {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            l_tot = l_run[rb] + __shfl_xor(l_run[rb], 32);
+            if (!direct) {
+                float rmax = 0.f;
+#pragma unroll
+                for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, fabsf(o[rb][db][v]));
+                c = fmaxf(rmax, __shfl_xor(rmax, 32));
+            }
+            finish(IntC<0>{}, IntC<NDB>{}, rb);
         }
     }
     }();   // one segment

@@ -21,8 +21,8 @@
 //     that it makes one trip to memory (the rest of a list is read only if all four reach the threshold).
 // Measured per step, back to back (16 logits per thread, four list merges by binary search and a bitonic pool sort in LDS
 // -> this): 8 rows of 32000 logits 12.8 -> 7.3 us, 128 rows of 32000 (batch 16) 18.4 -> 12.7, free attachment with 16 rows
-// of 128256 24.6 -> 14.8.  Left at the small size: 1.5 us of launch per kernel, memory latency once per kernel, and about
-// 1.5 us of dependent steps in each; at the large one the fp64 exponentials (23 instructions per logit).
+// of 128256 24.6 -> 14.8.  Left at the small size: 1.5 us of launch per kernel, memory latency once per kernel, and 1 to
+// 1.5 us of dependent steps in each; at the large one the fp64 exponentials (20 instructions per logit) and the selection.
 #include "ygg_internal.h"
 #include "ygg_device.h"
 
@@ -243,14 +243,26 @@ __device__ __forceinline__ int rank_in_wave(const uint64_t* pool, int n, int lan
 
 // E logits per thread and pass; a chunk is one pass (256 E logits) or, with ONE = false, several.  VEC: 16-byte loads (row
 // starts and V are multiples of four logits).
+// Short chunks (E = 4) leave a compute unit one workgroup, whose chain of steps is the kernel's time: four more wavefronts load the
+// same logits and sum their exponentials while the first four select and rank (six
+// steps for 8 rows of 32000 logits 41.9 -> 39.5 us with the shorter exponential).
+// Longer chunks keep every SIMD busy with several workgroups: what counts is the work, so one wavefront finds the threshold, while
+// the others are at the exponentials already, and candidates are pooled behind those (a step and its finish for 128 rows of 32000
+// logits 12.4 -> 11.9 us).
+template <int E>
+constexpr int scan_threads() { return E == 4 ? 2 * kScanThreads : kScanThreads; }
 template <int E, bool VEC, bool ONE>
-__global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
+__global__ __launch_bounds__(scan_threads<E>()) void expand_scan_kernel(ScanArgs a) {
     constexpr int PASS = kScanThreads * E;
+    constexpr bool SPLIT = E == 4;   // (always one pass)
     __shared__ __align__(16) uint64_t pool[kScanPool + 64];
     __shared__ uint32_t keys[kScanThreads];
     __shared__ double sums[4];
     __shared__ int pooled;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ uint32_t thr;
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all & 3;
+    const bool selects = !SPLIT || wave_all < 4, adds = !SPLIT || wave_all >= 4;
+    const int lane = threadIdx.x & 63, tid = 64 * wave + lane;
     const int c = blockIdx.y;
     const int64_t row = blockIdx.x, list = row * a.nchunk + c;
     const int c0 = c * a.chunk, c1 = min(a.V, c0 + a.chunk);
@@ -281,70 +293,87 @@ __global__ __launch_bounds__(kScanThreads) void expand_scan_kernel(ScanArgs a) {
             }
         };
         if (full) load(std::true_type{}); else load(std::false_type{});
-        if (base == c0) {   // while the loads are out
+        if (selects) {
+            if (base == c0) {   // while the loads are out
 #pragma unroll
-            for (int i = tid; i < kScanPool; i += kScanThreads) pool[i] = 0;
-            if (tid == 0) pooled = 0;
+                for (int i = tid; i < kScanPool; i += kScanThreads) pool[i] = 0;
+                if (tid == 0) pooled = 0;
+            }
+            float vmax = v[0];
+#pragma unroll
+            for (int i = 1; i < E; ++i) vmax = fmaxf(vmax, v[i]);
+            best = index(0) < c1 ? max(best, key_of(vmax)) : best;
+            keys[tid] = best;
         }
-        float vmax = v[0];
-#pragma unroll
-        for (int i = 1; i < E; ++i) vmax = fmaxf(vmax, v[i]);
-        best = index(0) < c1 ? max(best, key_of(vmax)) : best;
-        keys[tid] = best;
         __syncthreads();
-        const uint32_t t = max(group_threshold<E == 4>(keys, 4, lane, want), t_seen);
-        // (equal ones of a later pass come too late, for their higher indices: from the next key on, where +inf is followed by a NaN,
-        // which nothing reaches, and -0 by 0, which -0 reaches as well: one candidate more)
-        const uint32_t least = !ONE && t == t_seen ? t + 1 : t;
-        const float tf = least <= 1u ? -INFINITY : float_of(least);
-        bool sel[E];
-#pragma unroll
-        for (int i = 0; i < E; ++i) sel[i] = v[i] >= tf;
-        if (!ONE && t > 1u) t_seen = t;
-        auto entry = [&](int i) { return order_of(key_of(v[i]), (uint32_t)index(i)); };
-        // Of many equal logits (a masked vocabulary's -inf or -1e9) a wavefront keeps the W best by index: a step of 32 x 128256 logits
-        // with 1000 of the vocabulary unmasked 283 -> 31 us (every such chunk went through the rounds of scan_ties).
-        constexpr int kMost = ONE ? kScanPool / 4 : kMaxWidth + kMaxWidth / 8;
-        if (!pool_put(sel, entry, pool, kScanPool, &pooled, lane, kMost)) {
-            uint32_t key[E];
-#pragma unroll
-            for (int i = 0; i < E; ++i) key[i] = sel[i] ? key_of(v[i]) : 0u;
-            narrow<E, VEC ? 4 : 1>(key, want, lane, sel);
-            pool_put(sel, entry, pool, kScanPool, &pooled, lane, kMost);
+        if (!SPLIT && wave == 0) {
+            const uint32_t t = max(group_threshold<false>(keys, 4, lane, want), t_seen);
+            if (lane == 0) thr = t;
         }
-        // sum of exponentials
-        const uint32_t top = max(max(keys[lane], keys[64 + lane]), max(keys[128 + lane], keys[192 + lane]));
-        const float cmax = float_of(wave_max_u32(top));   // of the chunk so far
-        const float r = fabsf(cmax) <= kPlainRange || cmax == -INFINITY ? 0.f : cmax;
-        if (r != ref) {   // a first pass has nothing to rescale; later the reference only moves so that the sum shrinks
-            sum = sum == 0.0 ? 0.0 : sum * exp_nonpos((double)ref - (double)r);
-            ref = r;
+        if (adds) {   // sum of exponentials
+            const uint32_t top = max(max(keys[lane], keys[64 + lane]), max(keys[128 + lane], keys[192 + lane]));
+            const float cmax = float_of(wave_max_u32(top));   // of the chunk so far
+            const float r = fabsf(cmax) <= kPlainRange || cmax == -INFINITY ? 0.f : cmax;
+            if (r != ref) {   // a first pass has nothing to rescale; later the reference only moves so that the sum shrinks
+                sum = sum == 0.0 ? 0.0 : sum * exp_nonpos((double)ref - (double)r);
+                ref = r;
+            }
+            constexpr int NE = E < 8 ? E : 8;   // independent series in step: a dependent fp64 operation takes 20 cycles
+#pragma unroll
+            for (int i0 = 0; i0 < E; i0 += NE) {
+                double t[NE], e[NE];
+#pragma unroll
+                for (int i = 0; i < NE; ++i) t[i] = (double)fmaxf(v[i0 + i], ref - 746.f);   // (places past the end, -inf: next to nothing)
+                if (__builtin_expect(ref != 0.f, 0)) {
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) t[i] = fmax(t[i] - (double)ref, -746.0);
+                }
+                exp_clamped_n(t, e);
+#pragma unroll
+                for (int i = 0; i < NE; i += 4) sum += (e[i] + e[i + 1]) + (e[i + 2] + e[i + 3]);
+            }
         }
-        constexpr int NE = E < 8 ? E : 8;   // independent series in step: a dependent fp64 operation takes 20 cycles
+        if (!SPLIT) __syncthreads();   // the threshold is there
+        if (selects) {
+            const uint32_t t = SPLIT ? group_threshold<true>(keys, 4, lane, want) : thr;
+            // (equal ones of a later pass come too late, for their higher indices: from the next key on, where +inf is followed by a NaN,
+            // which nothing reaches, and -0 by 0, which -0 reaches as well: one candidate more)
+            const uint32_t least = !ONE && t == t_seen ? t + 1 : t;
+            const float tf = least <= 1u ? -INFINITY : float_of(least);
+            bool sel[E];
 #pragma unroll
-        for (int i0 = 0; i0 < E; i0 += NE) {
-            double t[NE], e[NE];
+            for (int i = 0; i < E; ++i) sel[i] = v[i] >= tf;
+            if (!ONE && t > 1u) t_seen = t;
+            auto entry = [&](int i) { return order_of(key_of(v[i]), (uint32_t)index(i)); };
+            // Of many equal logits (a masked vocabulary's -inf or -1e9) a wavefront keeps the W best by index: a step of 32 x 128256
+            // logits with 1000 of the vocabulary unmasked 283 -> 31 us (every such chunk went through the rounds of scan_ties).
+            constexpr int kMost = ONE ? kScanPool / 4 : kMaxWidth + kMaxWidth / 8;
+            if (!pool_put(sel, entry, pool, kScanPool, &pooled, lane, kMost)) {
+                uint32_t key[E];
 #pragma unroll
-            for (int i = 0; i < NE; ++i) t[i] = (double)v[i0 + i] - (double)ref;
-            exp_below_n(t, e);
-#pragma unroll
-            for (int i = 0; i < NE; i += 4) sum += (e[i] + e[i + 1]) + (e[i + 2] + e[i + 3]);
+                for (int i = 0; i < E; ++i) key[i] = sel[i] ? key_of(v[i]) : 0u;
+                narrow<E, VEC ? 4 : 1>(key, want, lane, sel);
+                pool_put(sel, entry, pool, kScanPool, &pooled, lane, kMost);
+            }
         }
         base += PASS;
         if (ONE || base >= c1) break;
-        __syncthreads();   // the next pass writes keys again
+        __syncthreads();   // the next pass writes keys and the threshold again
     } while (true);
-    sum = group_sum(sum, 64);
-    if (lane == 0) sums[wave] = sum;
+    if (adds) {
+        sum = group_sum(sum, 64);
+        if (lane == 0) sums[wave] = sum;
+    }
     __syncthreads();
     Cand* out = a.cands + list * a.W;
-    if (tid == 0) {
+    if (adds && tid == 0) {
         ListStat st;
         st.sumexp = (sums[0] + sums[1]) + (sums[2] + sums[3]);
         st.ref = ref;
         st.count = min(want, pooled);   // (fewer than wanted only if there are NaNs, which no list takes: it says what it holds)
         a.stats[list] = st;
     }
+    if (!selects) return;
     auto store = [&](int rank, uint64_t o) {
         const Cand cd = {float_of((uint32_t)(o >> 32)), (int32_t)~(uint32_t)o};
         if (rank < want) out[rank] = cd;
@@ -933,11 +962,12 @@ hipError_t launch_scan(const ExpandArgs& a, hipStream_t st) {
     s.stats = static_cast<ListStat*>(a.stats);
     s.cands = static_cast<Cand*>(a.cands);
     s.V = a.V; s.W = a.W; s.chunk = a.chunk; s.nchunk = a.nchunk;
-    const dim3 grid((unsigned)(a.B * a.F), (unsigned)a.nchunk), block(kScanThreads);
+    const dim3 grid((unsigned)(a.B * a.F), (unsigned)a.nchunk);
     const bool vec = (a.V & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15u) == 0;
     auto go = [&](auto e, auto one) {
         constexpr int E = decltype(e)::value;
         constexpr bool ONE = decltype(one)::value;
+        const dim3 block(scan_threads<E>());
         if (vec) hipLaunchKernelGGL((expand_scan_kernel<E, true, ONE>), grid, block, 0, st, s);
         else hipLaunchKernelGGL((expand_scan_kernel<E, false, ONE>), grid, block, 0, st, s);
     };

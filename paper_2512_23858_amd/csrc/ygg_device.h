@@ -90,41 +90,45 @@ __device__ __forceinline__ double double_of(uint64_t k) {
     return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
 }
 
-// exp(t) in fp64 (Cody and Waite's argument reduction): k = round(t/ln 2), r = t - k ln 2 (two-part constant), Taylor
-// series of degree 13 on |r| <= ln(2)/2 (remainder < 1e-17), scaled by 2^k.  Relative error about 1e-16.  For t <= 709;
-// below the underflow point the result is 0 or the smallest subnormal.  Branch-free, so independent calls interleave.
-// N arguments in step: a dependent fp64 operation takes about 20 cycles, an independent one four.
+// exp(t) in fp64 for -746 <= t <= 709 (Cody and Waite's argument reduction): k = t/ln 2 to the nearest integer, read from the low
+// bits of a sum with 1.5 * 2^52; r = t - k ln 2 (two-part constant); then a polynomial of degree 11 whose relative error on |r| <=
+// ln(2)/2 is equal at its twelve peaks (Remez; 1.6e-17 with the coefficients rounded to fp64; the Taylor series takes degree 13),
+// scaled by 2^k.  Relative error about 1e-16; below the underflow point the result is 0 or the smallest subnormal.  Branch-free,
+// so independent calls interleave.  N arguments in step: a dependent fp64 operation takes about 20 cycles, an independent one four.
 template <int N>
-__device__ __forceinline__ void exp_below_n(const double (&t)[N], double (&e)[N]) {
-    constexpr double c[] = {1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0,
-                            1.0 / 40320.0,      1.0 / 5040.0,      1.0 / 720.0,      1.0 / 120.0,     1.0 / 24.0,
-                            1.0 / 6.0,          0.5,               1.0,              1.0};
+__device__ __forceinline__ void exp_clamped_n(const double (&t)[N], double (&e)[N]) {
+    constexpr double c[] = {2.4995829328696594e-08, 2.7632531801393824e-07, 2.755761838905354e-06, 2.480148582911123e-05,
+                            0.00019841269436437258, 0.001388888895192619,   0.008333333333558044,  0.04166666666648987,
+                            0.1666666666666617,     0.5000000000000018,     1.0,                   1.0};
+    constexpr double round_at = 6755399441055744.0;   // 1.5 * 2^52
     double k[N], r[N];
+    int ki[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) r[i] = fmax(t[i], -746.0);
+    for (int i = 0; i < N; ++i) k[i] = fma(t[i], 1.4426950408889634074, round_at);
 #pragma unroll
-    for (int i = 0; i < N; ++i) k[i] = r[i] * 1.4426950408889634074;
+    for (int i = 0; i < N; ++i) {
+        ki[i] = (int)(uint32_t)__double_as_longlong(k[i]);
+        k[i] -= round_at;
+    }
 #pragma unroll
-    for (int i = 0; i < N; ++i) k[i] = rint(k[i]);
-#pragma unroll
-    for (int i = 0; i < N; ++i) r[i] = fma(k[i], -6.93147180369123816490e-01, r[i]);
+    for (int i = 0; i < N; ++i) r[i] = fma(k[i], -6.93147180369123816490e-01, t[i]);
 #pragma unroll
     for (int i = 0; i < N; ++i) r[i] = fma(k[i], -1.90821492927058770002e-10, r[i]);
 #pragma unroll
     for (int i = 0; i < N; ++i) e[i] = fma(c[0], r[i], c[1]);
 #pragma unroll
-    for (int s = 2; s < 14; ++s) {
+    for (int s = 2; s < 12; ++s) {
 #pragma unroll
         for (int i = 0; i < N; ++i) e[i] = fma(e[i], r[i], c[s]);
         __builtin_amdgcn_sched_barrier(0);   // keep the series in step
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) e[i] = ldexp(e[i], (int)k[i]);
+    for (int i = 0; i < N; ++i) e[i] = ldexp(e[i], ki[i]);
 }
 __device__ __forceinline__ double exp_below(double t) {
-    const double a[1] = {t};
+    const double a[1] = {fmax(t, -746.0)};
     double e[1];
-    exp_below_n(a, e);
+    exp_clamped_n(a, e);
     return e[0];
 }
 // exp(t) for t <= 0, exactly 0 below the underflow point

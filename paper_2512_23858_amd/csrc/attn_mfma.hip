@@ -665,11 +665,12 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 #pragma unroll
         for (int s = 0; s < NS; ++s) qreg[0][s] = *reinterpret_cast<const bf16x8*>(qp + ((32 * s) ^ pair_xor));
     }
-    // The ancestor masks are needed from the first tile with tree keys on.  Unless that is the very first one they are built in the
-    // iteration before it, behind barriers that are there anyway, while the tile itself is still on its way (65 rows x 1024 tokens on
-    // 40 kv heads 16.3 -> 15.8 us per call with what the pairs' merge below gives; the shapes of eight wavefronts measured no gain).
+    // The ancestor masks are needed from the first tile with tree keys on.  Unless that is the very first one, the shapes of four
+    // wavefronts build them in the iteration before it, behind barriers that are there anyway, while the tile itself is still on its way
+    // (65 rows x 1024 tokens on 40 kv heads 16.3 -> 15.7 us per call with what the pairs' merge below gives).  Six and eight wavefronts
+    // measured no gain or a loss (129 rows x 4096 on 32 kv heads 27.5 -> 28.1), two no registers to spare.
     const int tree_tile = max((L - k0) / KT, 0);
-    const int masks_at = !KV8 && !PING && NW != 8 && has_tree_keys ? tree_tile - 1 : -1;
+    const int masks_at = !KV8 && NW == 4 && has_tree_keys ? tree_tile - 1 : -1;
     if (has_tree_keys && masks_at < 0) {
         if constexpr (KV8) dma_wait_keep<0>();
         lds_barrier();
@@ -690,7 +691,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         if constexpr (KV8) {
             lds_barrier();
         } else {
-            if constexpr (!PING && NW != 8) {
+            if constexpr (NW == 4) {
                 if (__builtin_expect(t == masks_at, 0)) build_masks();
             }
             if (t + 2 < ntiles) dma_wait_keep<PT>(); else dma_wait_keep<0>();  // tile t+1 landed, t+2 may be in flight
@@ -870,8 +871,8 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     }
     if (PING && !late) step();
     // epilogue: lane (n, g2) holds, for its row, dh = 32 db + 8 (v/4) + 4 g2 + (v%4); finish writes the blocks db = FROM .. TO-1
-    float l_tot = 0.f, c = 0.f;   // the row's sum of weights; a bound on its magnitudes
-    auto finish = [&](auto from, auto to, int rb) __attribute__((always_inline)) {
+    // (l_tot: the row's sum of weights; c: a bound on its magnitudes)
+    auto finish = [&](auto from, auto to, int rb, float l_tot, float c) __attribute__((always_inline)) {
         constexpr int FROM = decltype(from)::value, TO = decltype(to)::value;
         const float v_unit = KV8 ? a.v_scale[hk] : 1.f;  // KV8: V = v_scale * code value
         if (rg_of[rb] < 0) return;
@@ -959,18 +960,20 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             const float w0 = m_ref[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref[0] - mm);
             const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
             m_ref[0] = mm;
-            l_tot = H == 0 ? l_own * w0 + l1 * w1 : l1 * w1 + l_own * w0;
-            c = fminf(H == 0 ? rmax * w0 + r1 * w1 : r1 * w1 + rmax * w0, 3.402823466e38f);
+            const float l_tot = H == 0 ? l_own * w0 + l1 * w1 : l1 * w1 + l_own * w0;
+            const float c = fminf(H == 0 ? rmax * w0 + r1 * w1 : r1 * w1 + rmax * w0, 3.402823466e38f);
 #pragma unroll
             for (int x = 0; x < HV; ++x)
                 o[0][H * NDB / 2 + x / 16][x % 16] = o[0][H * NDB / 2 + x / 16][x % 16] * w0 + in[x * 64] * w1;
-            finish(IntC<H * NDB / 2>{}, IntC<(H + 1) * NDB / 2>{}, 0);
+            finish(IntC<H * NDB / 2>{}, IntC<(H + 1) * NDB / 2>{}, 0, l_tot, c);
         };
         if (kh == 0) half(IntC<0>{}); else half(IntC<1>{});
     } else {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            l_tot = l_run[rb] + __shfl_xor(l_run[rb], 32);
+            const float l_tot = l_run[rb] + __shfl_xor(l_run[rb], 32);
+            if (rg_of[rb] < 0) continue;
+            float c = 0.f;
             if (!direct) {
                 float rmax = 0.f;
 #pragma unroll
@@ -979,7 +982,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                     for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, fabsf(o[rb][db][v]));
                 c = fmaxf(rmax, __shfl_xor(rmax, 32));
             }
-            finish(IntC<0>{}, IntC<NDB>{}, rb);
+            finish(IntC<0>{}, IntC<NDB>{}, rb, l_tot, c);
         }
     }
     }();   // one segment

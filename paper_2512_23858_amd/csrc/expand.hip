@@ -533,7 +533,7 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
 
     const double lse = row_lse(h.stat, 1 << a.shift);
     auto entry_of = [&](Cand cd) {
-        return Entry{key_of(cum + ((double)cd.val - lse)), (uint32_t)(p * a.V + cd.idx), 0};   // tie: flat index p*V + v
+        return Entry{key_of(cum + ((double)cd.val - lse)), (uint32_t)(p * a.V + cd.idx), (uint32_t)p};   // tie: flat index p*V + v
     };
     Entry e[kFront];
 #pragma unroll
@@ -605,14 +605,14 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
     }
     __syncthreads();
     const int n = __builtin_amdgcn_readfirstlane(pooled);
-    auto emit = [&](int rank, const Entry& x) {
+    auto emit_of_row = [&](int rank, const Entry& x, uint32_t row) {
         if (rank >= a.W) return;
         const int64_t node = (int64_t)b * a.N + 1 + (a.d - 1) * a.W + rank;
-        const uint32_t row = x.tie / (uint32_t)a.V;
         a.parent_idx[node] = base_prev + (int)row;
         a.token_ids[node] = (int)(x.tie - row * (uint32_t)a.V);
         a.cum_logprob[node] = (float)double_of(x.key);
     };
+    auto emit = [&](int rank, const Entry& x) { emit_of_row(rank, x, x.tie / (uint32_t)a.V); };   // (no tag)
     const int nthr = 64 * nwaves;
     if (n > 64 && (n + nthr - 1) / nthr * n > 24 * a.W) {   // four comparisons of all entries cost 0.1 us
         Entry* mine = pool + (tid >> 6) * a.W;   // the wavefronts' lists
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
             const auto r = __builtin_amdgcn_permlane32_swap(rank, rank, false, false);
             rank = r[0] + r[1];
         }
-        if (lane < n) emit((int)rank, mine);
+        if (lane < n) emit_of_row((int)rank, mine, mine.tag);
         return;
     }
     for (int j = tid; j < n; j += nthr) {
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(kMaxLists) void expand_merge_kernel(FinishArgs a, i
 #pragma unroll
             for (int u = 0; u < 4; ++u) rank += beats(x[u], mine);
         }
-        emit(rank, mine);
+        emit_of_row(rank, mine, mine.tag);
     }
 }
 

@@ -147,3 +147,14 @@ def test_fp32_splits_keep_their_weights_at_large_scores():
     out, lse = run_attention(shape, host, parent)
     assert np.abs(out - ref).max() <= 1.4e-4, np.abs(out - ref).max()
     assert np.abs(lse - ref_lse).max() <= 2.0 ** -3, np.abs(lse - ref_lse).max()   # one unit in the last place at 2^20
+
+
+@pytest.mark.parametrize("waves", [8, 4, 2])
+@pytest.mark.parametrize("Dh", [128, 64])
+@pytest.mark.parametrize("nsplit", [1, 2])
+def test_pairs_whose_second_share_sees_little(plan, waves, Dh, nsplit):
+    """At most 32 keys in a split's only tile: the second wavefront of a pair has no visible key, yet finishes its half of the row."""
+    plan(waves=waves, rblocks=1, kshares=2, nsplit=nsplit)
+    for L in (0, 23, 24, 64, 87):   # nine tree nodes: 9, 32, 33 keys; the same behind a whole tile
+        cfg, host, parent = _inputs(_cfg(1, 3, 1, 4, 2, Dh=Dh, seed=47), [L], max(L, 1), tree_gain=4.0)
+        _check(cfg, host, parent, max(L, 1))

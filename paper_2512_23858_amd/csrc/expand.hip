@@ -323,10 +323,10 @@ __global__ __launch_bounds__(scan_threads<E>()) void expand_scan_kernel(ScanArgs
             for (int i0 = 0; i0 < E; i0 += NE) {
                 double t[NE], e[NE];
 #pragma unroll
-                for (int i = 0; i < NE; ++i) t[i] = (double)fmaxf(v[i0 + i], ref - 746.f);   // (places past the end, -inf: next to nothing)
-                if (__builtin_expect(ref != 0.f, 0)) {
+                for (int i = 0; i < NE; ++i) t[i] = (double)fmaxf(v[i0 + i], -746.f);   // (places past the end, -inf: next to nothing)
+                if (__builtin_expect(ref != 0.f, 0)) {   // subtracted in fp64: where fp32 has no 746 any more (2^34), a bound formed there is ref itself
 #pragma unroll
-                    for (int i = 0; i < NE; ++i) t[i] = fmax(t[i] - (double)ref, -746.0);
+                    for (int i = 0; i < NE; ++i) t[i] = fmax((double)v[i0 + i] - (double)ref, -746.0);
                 }
                 exp_clamped_n(t, e);
 #pragma unroll

@@ -62,6 +62,31 @@ def test_growth_with_logits_far_from_zero(shift, masked):
     _expand_both(cfg, logits_fn=fn, check_margin=False)
 
 
+# forced tokens and rows without any: one logit of size `big` in each row of the first sequence, in the first, a middle or the last place;
+# nothing but -big in the second's (the last chunk partly past the end); both by turns in the third's.  Chunks of 1024, 2048, 4096 and
+# several passes.  From 2^34 on fp32 numbers are more than 746 apart.  Sums differ in the last places, and a row's log-sum-exp is
+# rounded alike on both sides.
+@pytest.mark.parametrize("W,V", [(6, 1000), (6, 3000), (6, 40001), (6, 131001), (33, 131081)])
+@pytest.mark.parametrize("big", [2.0 ** 33, 2.0 ** 34, 1.8e10, 1e12])
+def test_growth_with_forced_tokens_and_rows_without_any(W, V, big):
+    cfg = _cfg(3, 2, W, V, seed=31)
+
+    def fn(d):
+        x = wl.expansion_inputs(cfg, d)
+        for p in range(x.shape[1]):
+            at = (0, V // 2 + 7, V - 1)[p % 3]
+            x[0, p, at] = big
+            x[1, p] = -big
+            if p % 2:
+                x[2, p] = -big
+            else:
+                x[2, p, at] = big
+        return x
+    _expand_both(cfg, logits_fn=fn, check_margin=False)
+    if W < 33:
+        attach_both(cfg, logits_fn=fn, check_margin=False)
+
+
 @pytest.mark.parametrize("W,V", [(6, 3000), (20, 5000), (40, 9000)])
 @pytest.mark.parametrize("share", [1.0, 0.9])
 def test_nan_logits_stay_inside_their_sequence(W, V, share):

@@ -637,9 +637,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             static_for<0, NSET - 1>([&](auto i) {
                 if (t + i.value < ntiles) lstep(t + i.value, stage[(i.value + 3) % NSET]);
             });
-            if constexpr (KS == 2) {  // the merge of the key shares has two more workgroup barriers
+            if constexpr (KS == 2) {  // the merge of the key shares has two more workgroup barriers, and one for partial rows
                 __syncthreads();
                 __syncthreads();
+                if (!direct) __syncthreads();
             }
             return;
         }
@@ -667,7 +668,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     }
     // The ancestor masks are needed from the first tile with tree keys on.  Unless that is the very first one, the shapes of four
     // wavefronts build them in the iteration before it, behind barriers that are there anyway, while the tile itself is still on its way
-    // (65 rows x 1024 tokens on 40 kv heads 16.3 -> 15.7 us per call with what the pairs' merge below gives).  Six and eight wavefronts
+    // (65 rows x 1024 tokens on 40 kv heads 16.4 -> 15.9 us per call with what the pairs' merge below gives).  Six and eight wavefronts
     // measured no gain or a loss (129 rows x 4096 on 32 kv heads 27.5 -> 28.1), two no registers to spare.
     const int tree_tile = max((L - k0) / KT, 0);
     const int masks_at = !KV8 && NW == 4 && has_tree_keys ? tree_tile - 1 : -1;
@@ -871,7 +872,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     }
     if (PING && !late) step();
     // epilogue: lane (n, g2) holds, for its row, dh = 32 db + 8 (v/4) + 4 g2 + (v%4); finish writes the blocks db = FROM .. TO-1
-    // (l_tot: the row's sum of weights; c: a bound on its magnitudes)
+    // (l_tot: the row's sum of weights; c: its largest magnitude)
     auto finish = [&](auto from, auto to, int rb, float l_tot, float c) __attribute__((always_inline)) {
         constexpr int FROM = decltype(from)::value, TO = decltype(to)::value;
         const float v_unit = KV8 ? a.v_scale[hk] : 1.f;  // KV8: V = v_scale * code value
@@ -890,8 +891,8 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
                 }
             if (a.lse && g2 == 0 && FROM == 0) a.lse[rg_of[rb]] = m_ref[rb] * kLn2 + logf(l_tot);
         } else {
-            // Partial outputs travel as fp16 relative to c (kept in fp32 beside m and l), which is the row's largest magnitude or
-            // little more: half the traffic of fp32 here and in the merge, an error of at most 2^-12 c per element whatever the
+            // Partial outputs travel as fp16 relative to the row's largest magnitude c (kept in fp32 beside m and l):
+            // half the traffic of fp32 here and in the merge, an error of at most 2^-12 c per element whatever the
             // range of V (bf16 partials would cost up to a whole bf16 ulp of the merged row, which outputs of
             // magnitude 4 cannot afford inside 2e-2).  Streaming stores: the partials are read once, by the merge,
             // and leaving them dirty in L2 only lengthens the write-back at the end of this kernel.
@@ -929,20 +930,15 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     };
     if constexpr (KS == 2) {
         // Merge of the two key shares of a row block.  Both carry O~ and l relative to their own reference m_ref.  Each
-        // keeps one half of head_dim and hands the other over through the (now idle) tile buffers, lane for lane, with m, l and its
-        // row's largest magnitude; both then rescale what they have of both shares to the larger reference and finish their
-        // halves side by side (49 rows x 1024 tokens on 32 kv heads 12.9 -> 12.6 us per call).
+        // keeps one half of head_dim and hands the other over through the (now idle) tile buffers, lane for lane, with m and l;
+        // both then rescale what they have of both shares to the larger reference and finish their
+        // halves side by side (49 rows x 1024 tokens on 32 kv heads 12.9 -> 12.7 us per call).  Partial rows take a third barrier
+        // (0.07 us of that call): their scale c comes from the merged values of both halves, because where the shares cancel each
+        // other their own maxima say nothing about these.
         static_assert(RB == 1, "one row block to a pair");
         constexpr int HV = 8 * NDB;        // values of a lane's half
         constexpr int XR = HV + 3;
         float* const xch = reinterpret_cast<float*>(smem) + (wrow * 2 * XR) * 64 + lane;   // [wrow][share it is for][XR][64 lanes]
-        float rmax = 0.f;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, fabsf(o[0][db][v]));
-        rmax = fmaxf(rmax, __shfl_xor(rmax, 32));
-        const float l_own = l_run[0] + __shfl_xor(l_run[0], 32);
         __syncthreads();  // every wavefront is done with the tiles
         auto half = [&](auto h) __attribute__((always_inline)) {   // this wavefront keeps half h
             constexpr int H = decltype(h)::value;
@@ -951,20 +947,32 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 #pragma unroll
             for (int x = 0; x < HV; ++x) out[x * 64] = o[0][(1 - H) * NDB / 2 + x / 16][x % 16];
             out[HV * 64] = m_ref[0];
-            out[(HV + 1) * 64] = l_own;
-            out[(HV + 2) * 64] = rmax;
+            out[(HV + 1) * 64] = l_run[0];
             __syncthreads();
-            const float m1 = in[HV * 64], l1 = in[(HV + 1) * 64], r1 = in[(HV + 2) * 64];
-            const float mm = fmaxf(m_ref[0], m1);
+            const float m_other = in[HV * 64], l_other = in[(HV + 1) * 64];
+            const float mm = fmaxf(m_ref[0], m_other);
             // a share that saw no visible key has m = -inf, l = 0, O~ = 0: weight 0 keeps it out
-            const float w0 = m_ref[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref[0] - mm);
-            const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
+            const float w_own = m_ref[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref[0] - mm);
+            const float w_other = m_other == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_other - mm);
             m_ref[0] = mm;
-            const float l_tot = H == 0 ? l_own * w0 + l1 * w1 : l1 * w1 + l_own * w0;
-            const float c = fminf(H == 0 ? rmax * w0 + r1 * w1 : r1 * w1 + rmax * w0, 3.402823466e38f);
+            auto both = [&](float own, float other) {   // rounded alike on both sides: share 1's product, then share 0's
+                return H == 0 ? fmaf(own, w_own, other * w_other) : fmaf(other, w_other, own * w_own);
+            };
+            const float l_lane = both(l_run[0], l_other);
+            const float l_tot = l_lane + __shfl_xor(l_lane, 32);
+            float c = 0.f;
 #pragma unroll
-            for (int x = 0; x < HV; ++x)
-                o[0][H * NDB / 2 + x / 16][x % 16] = o[0][H * NDB / 2 + x / 16][x % 16] * w0 + in[x * 64] * w1;
+            for (int x = 0; x < HV; ++x) {
+                const float y = both(o[0][H * NDB / 2 + x / 16][x % 16], in[x * 64]);
+                o[0][H * NDB / 2 + x / 16][x % 16] = y;
+                c = fmaxf(c, fabsf(y));
+            }
+            if (!direct) {
+                c = fmaxf(c, __shfl_xor(c, 32));
+                out[(HV + 2) * 64] = c;
+                __syncthreads();
+                c = fmaxf(c, in[(HV + 2) * 64]);
+            }
             finish(IntC<H * NDB / 2>{}, IntC<(H + 1) * NDB / 2>{}, 0, l_tot, c);
         };
         if (kh == 0) half(IntC<0>{}); else half(IntC<1>{});

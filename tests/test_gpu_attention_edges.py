@@ -158,3 +158,29 @@ def test_pairs_whose_second_share_sees_little(plan, waves, Dh, nsplit):
     for L in (0, 23, 24, 64, 87):   # nine tree nodes: 9, 32, 33 keys; the same behind a whole tile
         cfg, host, parent = _inputs(_cfg(1, 3, 1, 4, 2, Dh=Dh, seed=47), [L], max(L, 1), tree_gain=4.0)
         _check(cfg, host, parent, max(L, 1))
+
+
+@pytest.mark.parametrize("waves", [8, 4, 2])
+@pytest.mark.parametrize("Dh", [128, 64])
+def test_partial_rows_of_pairs_that_cancel(plan, waves, Dh):
+    """All scores are 0 and V is whole numbers of 0 to 3, but for 1.75 * 2^23 at one key of a pair's first share and its negative at one of
+    the second's: every sum is exact in fp32, and a split's partial row is at most 3 * 64 = 192 large.  Stored to 2^-12 of that, both
+    splits' partials and the rounding to bf16 (8 significant bits: half a unit is 2^-8 of the value at most) put an output off by no more
+    than 2 * 192 * 2^-12 / keys + 2^-8 of its value; a scale of the size of the shares' own sums would put it off by up to 2 * 0.875 / keys."""
+    plan(waves=waves, rblocks=1, kshares=2, nsplit=2)
+    cfg, host, parent = _inputs(_cfg(1, 3, 1, 4, 2, Dh=Dh, seed=73), [119], 119)       # nine tree nodes: two tiles of 64 keys
+    host["q"] = np.zeros_like(host["q"])
+    for stream, name in ((1, "v_cache"), (2, "v_tree")):
+        v = wl.rng(73, stream).integers(0, 4, host[name].shape).astype(np.float32)
+        if name == "v_cache":
+            for at, sign in ((5, 1.0), (40, -1.0), (70, 1.0), (100, -1.0)):
+                v[:, at] = sign * 1.75 * 2.0 ** 23
+        host[name] = wl.to_storage(v, cfg.dtype)
+    shape = shape_of(cfg, max_seq_len=119)
+    got = ygg.attention_plan(shape)
+    assert (got["waves"], got["key_shares"], got["key_splits"]) == (waves, 2, 2)
+    ref, _ = oracle.tree_attention(host["q"], host["k_cache"], host["v_cache"], host["seq_lens"], host["k_tree"], host["v_tree"],
+                                   parent, cfg.softmax_scale)
+    out, _ = run_attention(shape, host, parent)
+    bound = 2 * 192 * 2.0 ** -12 / 120 + 2.0 ** -8 * np.abs(ref)     # (120 to 123 keys to a row)
+    assert (np.abs(out - ref) <= 1.001 * bound).all(), (np.abs(out - ref) / bound).max()

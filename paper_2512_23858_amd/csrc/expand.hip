@@ -22,7 +22,7 @@
 // Measured per step, back to back (16 logits per thread, four list merges by binary search and a bitonic pool sort in LDS
 // -> this): 8 rows of 32000 logits 12.8 -> 7.3 us, 128 rows of 32000 (batch 16) 18.4 -> 12.7, free attachment with 16 rows
 // of 128256 24.6 -> 14.8.  Left at the small size: 1.5 us of launch per kernel, memory latency once per kernel, and 1 to
-// 1.5 us of dependent steps in each; at the large one the fp64 exponentials (20 instructions per logit) and the selection.
+// 1.5 us of dependent steps in each; at the large one the fp64 exponentials (21 instructions per logit) and the selection.
 #include "ygg_internal.h"
 #include "ygg_device.h"
 

@@ -666,13 +666,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 #pragma unroll
         for (int s = 0; s < NS; ++s) qreg[0][s] = *reinterpret_cast<const bf16x8*>(qp + ((32 * s) ^ pair_xor));
     }
-    // The ancestor masks are needed from the first tile with tree keys on.  Unless that is the very first one, the shapes of four
-    // wavefronts build them in the iteration before it, behind barriers that are there anyway, while the tile itself is still on its way
-    // (65 rows x 1024 tokens on 40 kv heads 16.4 -> 15.9 us per call with what the pairs' merge below gives).  Six and eight wavefronts
-    // measured no gain or a loss (129 rows x 4096 on 32 kv heads 27.5 -> 28.1), two no registers to spare.
-    const int tree_tile = max((L - k0) / KT, 0);
-    const int masks_at = !KV8 && NW == 4 && has_tree_keys ? tree_tile - 1 : -1;
-    if (has_tree_keys && masks_at < 0) {
+    // (Built in the iteration before they are needed, in the shapes of four wavefronts: no gain over 27 calls, and 12 heads of 64, 64 rows x
+    // 10258 tokens 14.3 -> 14.9 us per call.)
+    if (has_tree_keys) {
         if constexpr (KV8) dma_wait_keep<0>();
         lds_barrier();
         build_masks();
@@ -692,9 +688,6 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         if constexpr (KV8) {
             lds_barrier();
         } else {
-            if constexpr (NW == 4) {
-                if (__builtin_expect(t == masks_at, 0)) build_masks();
-            }
             if (t + 2 < ntiles) dma_wait_keep<PT>(); else dma_wait_keep<0>();  // tile t+1 landed, t+2 may be in flight
             lds_barrier();
             if (t + 3 < ntiles) fill_tile(buf, tile_base + 3 * KT);

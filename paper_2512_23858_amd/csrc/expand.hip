@@ -20,7 +20,7 @@
 //   - a list's four best entries decide almost every step: the finish kernel requests them together with the list's sum, so
 //     that it makes one trip to memory (the rest of a list is read only if all four reach the threshold).
 // Measured per step, back to back (16 logits per thread, four list merges by binary search and a bitonic pool sort in LDS
-// -> this): 8 rows of 32000 logits 12.8 -> 7.3 us, 128 rows of 32000 (batch 16) 18.4 -> 12.7, free attachment with 16 rows
+// -> this): 8 rows of 32000 logits 12.8 -> 6.6 us, 128 rows of 32000 (batch 16) 18.4 -> 11.9, free attachment with 16 rows
 // of 128256 24.6 -> 14.8.  Left at the small size: 1.5 us of launch per kernel, memory latency once per kernel, and 1 to
 // 1.5 us of dependent steps in each; at the large one the fp64 exponentials (21 instructions per logit) and the selection.
 #include "ygg_internal.h"
@@ -243,18 +243,19 @@ __device__ __forceinline__ int rank_in_wave(const uint64_t* pool, int n, int lan
 
 // E logits per thread and pass; a chunk is one pass (256 E logits) or, with ONE = false, several.  VEC: 16-byte loads (row
 // starts and V are multiples of four logits).
-// Short chunks (E = 4) leave a compute unit one workgroup, whose chain of steps is the kernel's time: four more wavefronts load the
-// same logits and sum their exponentials while the first four select and rank (six
-// steps for 8 rows of 32000 logits 41.9 -> 39.5 us with the shorter exponential).
-// Longer chunks keep every SIMD busy with several workgroups: what counts is the work, so one wavefront finds the threshold, while
-// the others are at the exponentials already, and candidates are pooled behind those (a step and its finish for 128 rows of 32000
-// logits 12.4 -> 11.9 us).
+// Chunks of 1024 and 2048 logits leave a compute unit one to three workgroups (plan_expand), whose chain of steps is the kernel's time:
+// four more wavefronts load the same logits and sum their exponentials while the first four select and rank.  us per step, four
+// wavefronts for both -> this: 8 rows of 32000 logits 7.0 -> 6.5, 16 rows of 32000 (512 chunks of 1024) 7.6 -> 7.2, one row of 128256
+// 7.3 -> 6.7, 12 rows of 128256 (756 chunks of 2048) 10.3 -> 9.6.
+// Longer chunks keep every SIMD busy with several workgroups: what counts is the work, so one wavefront finds the threshold, while the
+// others are at the exponentials already, and candidates are pooled behind those (128 rows of 32000 logits 14.1 -> 13.6 us per step,
+// 256 rows of 128256 49.8 -> 47.2; with chunks of 2048 one to four rows of 70000 to 128256 lost 1 to 3 % that way).
 template <int E>
-constexpr int scan_threads() { return E == 4 ? 2 * kScanThreads : kScanThreads; }
+constexpr int scan_threads() { return E <= 8 ? 2 * kScanThreads : kScanThreads; }
 template <int E, bool VEC, bool ONE>
 __global__ __launch_bounds__(scan_threads<E>()) void expand_scan_kernel(ScanArgs a) {
     constexpr int PASS = kScanThreads * E;
-    constexpr bool SPLIT = E == 4;   // (always one pass)
+    constexpr bool SPLIT = E <= 8;   // (always one pass)
     __shared__ __align__(16) uint64_t pool[kScanPool + 64];
     __shared__ uint32_t keys[kScanThreads];
     __shared__ double sums[4];
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(scan_threads<E>()) void expand_scan_kernel(ScanArgs
         }
         if (!SPLIT) __syncthreads();   // the threshold is there
         if (selects) {
-            const uint32_t t = SPLIT ? group_threshold<true>(keys, 4, lane, want) : thr;
+            const uint32_t t = SPLIT ? group_threshold<E == 4>(keys, 4, lane, want) : thr;
             // (equal ones of a later pass come too late, for their higher indices: from the next key on, where +inf is followed by a NaN,
             // which nothing reaches, and -0 by 0, which -0 reaches as well: one candidate more)
             const uint32_t least = !ONE && t == t_seen ? t + 1 : t;
@@ -1000,11 +1001,12 @@ static size_t cand_bytes_of(int64_t lists, int32_t width) { return ((size_t)list
 // Chunk length: the finish kernel takes one list per thread and a row's lists from one wavefront, which bounds the lists
 // per row; within that, short chunks (1024 logits, four per thread) keep every compute unit busy and each thread's chain
 // short, long ones (4096) leave a quarter of the fixed work of a workgroup, of the lists to write and of those to read back.
-// The lines lie where no step of the sweep was slower for it.  us per step with chunks of 1024 / 2048 / 4096, by the number of
-// chunks of 2048: 192 (3 x 8 rows of 32000) 8.4 / 8.3 / 9.0; 272 (17 rows of 32000) 9.3 / 10.7 / 13.9; 512 (32 rows) 14.2 / 21.5 /
-// 28.1, with free attachment 62.6 / 25.3 / 30.4; 512 (32 x 16 rows of 1500) 16.0 / 11.8 / 13.1; 768 (6 x 8 rows of 32000) 10.2 /
-// 9.4 / 10.2; 756 (12 rows of 128256) - / 10.0 / 10.0; 1008 (16 rows of 128256) - / 11.6 / 10.6; 2048 (128 rows of 32000) 14.7 /
-// 13.6 / 13.5.
+// us per step with chunks of 1024 / 2048 / 4096, by the number of chunks of 2048: 272 (17 rows of 32000) 8.5 / 7.7 / 8.2; 384 (3 x 8 rows
+// of 32000) 7.6 / 7.2 / 8.2; 512 (32 rows) 12.0 / 10.3 / 10.9; 512 (32 x 16 rows of 1500) 11.5 / 10.7 / 12.5; 768 (6 x 8 rows of 32000)
+// 9.9 / 9.0 / 10.4; 756 (12 rows of 128256) - / 9.6 / 9.8; 1008 (16 rows of 128256) - / 11.7 / 10.7; 2048 (128 rows of 32000) 16.5 / 14.3 /
+// 13.6; 8192 (512 rows of 32000) 47.0 / 37.8 / 29.3.  The lines were drawn for a scan with four wavefronts to every chunk; with eight, 256
+// chunks of 2048 (16 rows of 32000) would be a little faster than 512 of 1024 (7.1 / 6.7 / 8.2) and 1024 of 64 rows of 32000 than 512 of
+// 4096 (10.9 / 10.1 / 10.6), which 16 rows of 128256 are not.
 ExpandPlan plan_expand(const ygg_shape& s, int32_t d) {
     ExpandPlan p;
     p.F = d == 1 ? 1 : s.width;

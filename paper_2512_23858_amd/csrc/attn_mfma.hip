@@ -53,6 +53,9 @@ __device__ __forceinline__ void e4m3x16_to_bf16(const u32x4& raw, uint4& first8,
     last8 = make_uint4(o[4], o[5], o[6], o[7]);
 }
 
+// Workgroup shapes whose rows of Q have space of their own in LDS.
+constexpr bool q_apart(int waves, int kshares, int head_dim) { return kshares == 2 || (head_dim == 64 && waves <= 6); }
+
 // NW wavefronts, RB 32-row blocks per wavefront, KT keys per tile, KS key shares: with KS = 2 the
 // wavefronts pair up on the same rows and each takes one of the two 32-key blocks of every tile (a
 // tree of few nodes has too few rows to occupy a workgroup otherwise); the pair's (m, l, O~) are
@@ -103,22 +106,28 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* k_s = smem;                                   // [NBUF][KT][ROWB]
     unsigned char* v_s = smem + NBUF * TILEB;                    // [NBUF][KT][ROWB]
-    // Q passes through the tile buffers from the third on (tile 2 is requested once it is read) and, where these
-    // do not hold it, through space behind them.
+    // Q passes through LDS.  QAPART: through space of its own behind the tile buffers, where the wavefronts of a pair share their
+    // rows (49 rows on 32 kv heads: 14 KB fetched by a workgroup instead of 32); else through the tile buffers from the third on (tile
+    // 2 is requested once Q is read) and what space they lack.
     constexpr int QW = 32 * RB * ROWB;           // a wavefront's rows
-    constexpr int QB = 2 * (NBUF - 2);           // wavefronts whose rows fit the spare K (or V) buffers
-    constexpr int QX = NW > 2 * QB ? (NW - 2 * QB) * QW : 0;
+    constexpr bool QAPART = !KV8 && q_apart(NW, KS, DH);
+    constexpr int QB = QAPART ? 0 : 2 * (NBUF - 2);   // wavefronts whose rows fit the spare K (or V) buffers
+    constexpr int QX = KV8 ? 0 : QAPART ? NRW * QW : NW > 2 * QB ? (NW - 2 * QB) * QW : 0;
+    // Tiles requested before the loop is reached.  About 64 KB is what a compute unit has in flight: at head_dim 128 a third tile
+    // stands in the way of the first (49 rows x 1024 tokens on 32 kv heads 12.9 -> 13.2 us per call).
+    constexpr int AHEAD = QAPART && DH == 64 ? 3 : 2;
     static_assert(RB == 1 && QW * 2 == TILEB, "two wavefronts' rows to a tile buffer");
+    static_assert(KS == 1 || KV8 || QAPART, "a pair's rows of Q are shared");
     uint32_t* anc_s = reinterpret_cast<uint32_t*>(smem + 2 * NBUF * TILEB + QX);  // [local node][aw], then parent[N]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
     const int n = lane & 31, g2 = lane >> 5;
-    unsigned char* q_s = (wave < QB ? k_s + 2 * TILEB + wave * QW
-                                    : wave < 2 * QB ? v_s + 2 * TILEB + (wave - QB) * QW : smem + 2 * NBUF * TILEB + (wave - 2 * QB) * QW);
     const bool is_loader = KV8 && wave >= NW;      // wave-uniform
     const int wrow = KS == 1 ? wave : wave % NRW;  // position along the rows (computing wavefronts)
     const int kh = KS == 1 ? 0 : wave / NRW;       // which block of every tile (KS = 2)
+    unsigned char* q_s = (wrow < QB ? k_s + 2 * TILEB + wrow * QW
+                                    : wrow < 2 * QB ? v_s + 2 * TILEB + (wrow - QB) * QW : smem + 2 * NBUF * TILEB + (wrow - 2 * QB) * QW);
 
     // All arguments at once: left to itself the compiler fetches each where it is first needed, one scalar-cache miss after
     // the other in front of the first tile fill (32 layers of a 516-row verify pass: 923 -> 887 us).  The paired shapes'
@@ -249,6 +258,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // are never stored.  As plain register loads they would hold up the first block until every tile in flight has landed:
     // the compiler's wait for them does not know of the tile fills behind them and awaits those as well.
     bf16x8 qreg[RB][NS];
+    const int q_last = min(max(R - 1 - row_base - wrow * 32, 0), 31);   // rows of the block from here on repeat this one
     if constexpr (KV8) {   // (the computing wavefronts have nothing else in flight: plain loads)
         if (!is_loader) {
 #pragma unroll
@@ -262,7 +272,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     } else {
         const uint32_t q_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)q_s;
 #pragma unroll
-        for (int it = 0; it < 32 * RB / RPI; ++it) {
+        for (int i0 = 0; i0 < 32 * RB / RPI; i0 += KS) {
+            const int it = i0 + kh;            // (the wavefronts of a pair take turns)
+            if (RPI * it > q_last) break;      // wave-uniform
             const int lrow = RPI * it + lane / SLOTS;
             const int rc = min(row_base + wrow * RB * 32 + lrow, R - 1);
             const int i = (int)divide(rc, a.G, a.mul_g);
@@ -272,19 +284,36 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         }
     }
 
+    auto fetch_parents = [&](int32_t* to) {   // straight into LDS
+        const int32_t* parent = a.parent_idx + (int64_t)b * a.N;
+        const uint32_t lds = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)to;
+        for (int t = 64 * wave; t < a.N; t += 64 * NW)   // (the last lanes repeat the last entry; LDS is sized for that)
+            dma_load4(parent + min(t + lane, a.N - 1), __builtin_amdgcn_readfirstlane(lds + 4 * t));
+    };
+    // where the masks end and the parents begin: behind those of the nodes this workgroup's rows belong to
+    auto parents_at = [&]() { return reinterpret_cast<int32_t*>(anc_s + (min(R - 1, row_base + RW - 1) / a.G - row_base / a.G + 1) * ((a.N + 31) >> 5)); };
+    // Shapes without pairs: requested before the length says who needs them.
+    constexpr bool kParentsFirst = !KV8 && !BAL && KS == 1;
+    if constexpr (kParentsFirst) fetch_parents(parents_at());
+
     L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
     const int Tk = L + a.N;
     int k0, k1, split;
     bool direct = a.nsplit == 1;   // this segment is the whole sequence: final rows are written here
     const int nt = (Tk + kKeyTile - 1) / kKeyTile;
     if constexpr (!balanced) {
-        // the sequence's own 64-key tiles, dealt out as evenly as whole tiles allow (the first splits take one more)
-        const int hb = (int)divide(sigma, a.nsplit, a.mul_nsplit);
+        // The sequence's own 64-key tiles, dealt out as evenly as whole tiles allow: the first splits take one more.  The last one has
+        // the masks of the tree's keys to build as well; at head_dim 64, where a workgroup's tiles are all in flight at once, it gives
+        // a tile away if that leaves the longest split no longer (12 heads, 65 rows x 2048 tokens 10.8 -> 10.3 us per call; at
+        // head_dim 128 a third tile starts when the first has landed, and 3 sequences of up to 1531 tokens lose: 16.5 -> 16.9).
+        const int hb = (int)divide(sigma, a.nsplit, a.mul_nsplit), last = a.nsplit - 1;
         split = sigma - hb * a.nsplit;
-        const int q = (int)divide(nt, a.nsplit, a.mul_nsplit), r = nt - q * a.nsplit;
+        const int q = (int)divide(nt, a.nsplit, a.mul_nsplit);
+        int r = nt - q * a.nsplit;
+        if constexpr (DH == 64) r += r > 0 && r < last && q > 1;
         const int t0 = split * q + min(split, r);
         k0 = t0 * kKeyTile;
-        k1 = min(Tk, (t0 + q + (split < r)) * kKeyTile);
+        k1 = split == last ? Tk : min(Tk, (t0 + q + (split < r)) * kKeyTile);
     } else {
         const int t0 = max(run_lo, tiles_before) - tiles_before, t1 = min(run_hi, tiles_before + nt) - tiles_before;
         const int s_first = slot_of_tile(tiles_before), s_last = slot_of_tile(tiles_before + nt - 1);
@@ -320,7 +349,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     const int i_first = row_base / a.G;
     const int i_last = min(R - 1, row_base + RW - 1) / a.G;
     const bool has_tree_keys = k1 > L;  // uniform over the workgroup
-    int32_t* parent_s = reinterpret_cast<int32_t*>(anc_s + (i_last - i_first + 1) * aw);
+    int32_t* parent_s = parents_at();
 
     // slab bases of this (sequence, kv head): wave-uniform, pinned to scalar registers
     constexpr int EB = KV8 ? 1 : 2;  // bytes of a stored K/V element
@@ -588,20 +617,23 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 
     static_assert(KT == 64, "the block pipeline below is written for two 32-key blocks per tile");
     const int ntiles = (k1 - k0 + KT - 1) / KT;
-    // The tree's parents go straight into LDS, requested before the tiles and awaited without them.
-    auto fetch_parents = [&]() {
-        if (!has_tree_keys) return;
-        const int32_t* parent = a.parent_idx + (int64_t)b * a.N;
-        const uint32_t lds = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)parent_s;
-        for (int t = 64 * wave; t < a.N; t += 64 * NW)   // (the last lanes repeat the last entry; LDS is sized for that)
-            dma_load4(parent + min(t + lane, a.N - 1), __builtin_amdgcn_readfirstlane(lds + 4 * t));
-    };
-    auto build_masks = [&]() {  // every wavefront of the workgroup takes part, behind the barrier that publishes the parents
+    // Every wavefront of the workgroup takes part, behind the barrier that publishes the parents.  The time is a chain of one LDS
+    // read per ancestor: the bits go out as atomics that nothing waits for, and there is a branch to every three steps (depth 8:
+    // 1.35 -> 0.85 us).
+    auto build_masks = [&]() {
         for (int t = tid; t <= i_last - i_first; t += THREADS) {
             uint32_t* w = anc_s + t * aw;
             for (int x = 0; x < aw; ++x) w[x] = 0;
-            int guard = 0;
-            for (int c = i_first + t; c >= 0 && c < a.N && guard < a.N; c = parent_s[c], ++guard) w[c >> 5] |= 1u << (c & 31);
+            // (three steps to a check; behind the root a lane goes on reading the root's entry and sets no bit)
+            int c = i_first + t;
+            for (int guard = 0; guard < a.N && __any(c >= 0); guard += 3)
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    const int at = min(max(c, 0), a.N - 1);
+                    const uint32_t bit = (uint32_t)c < (uint32_t)a.N ? 1u << (at & 31) : 0u;
+                    c = c < 0 ? -1 : parent_s[at];
+                    __hip_atomic_fetch_or(w + (at >> 5), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
         }
     };
 
@@ -649,20 +681,27 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // prologue of the computing wavefronts: behind Q the parents and two tiles go into flight at once (direct-to-LDS path);
     // meanwhile Q is read back and the ancestor masks are built; the barrier that publishes tile 0 also says that all of Q
     // has left the buffer that tile 2 is then requested into
-    fetch_parents();
+    if constexpr (!kParentsFirst) {
+        if (has_tree_keys) fetch_parents(parent_s);
+    }
     if constexpr (!KV8) {
         fill_tile(0, k0);
         if (ntiles > 1) fill_tile(1, k0 + KT);
+        if (AHEAD > 2 && ntiles > 2) fill_tile(2, k0 + 2 * KT);
     }
-    auto wait_tiles_out = [&](bool both) {   // until at most the last one or both of the two tiles are out
-        if (KV8 || (FILLERS < NW && wave >= FILLERS)) dma_wait_keep<0>();
-        else if (both) dma_wait_keep<2 * PT>();
-        else dma_wait_keep<PT>();
+    auto wait_tiles_out = [&](int tiles) {   // until at most so many tiles are out, of those requested so far
+        if (tiles <= 0 || KV8 || (FILLERS < NW && wave >= FILLERS)) dma_wait_keep<0>();
+        else if (tiles == 1) dma_wait_keep<PT>();
+        else if (AHEAD == 2 || tiles == 2) dma_wait_keep<2 * PT>();
+        else dma_wait_keep<3 * PT>();
     };
+    const int out_first = min(ntiles, AHEAD);
     if constexpr (!KV8) {
-        wait_tiles_out(ntiles > 1);
-        const unsigned char* qp = q_s + n * ROWB + 16 * (g2 ^ (n & 1));
-        const int pair_xor = ((n & (SLOTS - 1)) >> 1) << 5;
+        wait_tiles_out(out_first);
+        if constexpr (KS == 2) lds_barrier();   // the pair's rows of Q, and the parents
+        const int nq = min(n, q_last);
+        const unsigned char* qp = q_s + nq * ROWB + 16 * (g2 ^ (nq & 1));
+        const int pair_xor = ((nq & (SLOTS - 1)) >> 1) << 5;
 #pragma unroll
         for (int s = 0; s < NS; ++s) qreg[0][s] = *reinterpret_cast<const bf16x8*>(qp + ((32 * s) ^ pair_xor));
     }
@@ -670,14 +709,12 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // 10258 tokens 14.3 -> 14.9 us per call.)
     if (has_tree_keys) {
         if constexpr (KV8) dma_wait_keep<0>();
-        lds_barrier();
+        if constexpr (KV8 || KS == 1) lds_barrier();
         build_masks();
     }
-    if constexpr (!KV8) {
-        if (ntiles > 1) wait_tiles_out(false); else dma_wait_keep<0>();
-    }
+    if constexpr (!KV8) wait_tiles_out(out_first - 1);
     lds_barrier();  // tile 0 has landed for everybody, anc_s is published, Q is read
-    if constexpr (!KV8) {
+    if constexpr (!KV8 && AHEAD == 2) {
         if (ntiles > 2) fill_tile(2, k0 + 2 * KT);
     }
 
@@ -1073,14 +1110,14 @@ hipError_t raise_shapes() {
 
 }  // namespace
 
-// Dynamic shared memory of a workgroup: three K and V tile buffers of 64 keys, space for Q where the spare buffers do not hold it
+// Dynamic shared memory of a workgroup: three K and V tile buffers of 64 keys, space for Q (q_apart) or for what the spare buffers do not hold of it
 // (in the 256-row shape as much as the fourth buffer of its opposite phases, which then holds Q), the ancestor bitmasks of the
 // nodes the rows belong to, and the parent table.
 size_t attn_mfma_smem(int waves, int kshares, int head_dim, int group, int nodes) {
     const size_t tile = (size_t)64 * 2 * head_dim;
     const int rw = waves / kshares * 32;
     const int nodes_local = rw % group == 0 ? rw / group : (rw + group - 1) / group + 1;
-    const int nbuf = 3, q_outside = waves - 4 * (nbuf - 2);
+    const int nbuf = 3, q_outside = q_apart(waves, kshares, head_dim) ? waves / kshares : waves - 4 * (nbuf - 2);
     return 2 * nbuf * tile + (q_outside > 0 ? q_outside * tile / 2 : 0) +
            (size_t)nodes_local * ((nodes + 31) / 32) * 4 + (size_t)((nodes + 63) / 64) * 256;
 }

@@ -24,6 +24,7 @@
 // wavefronts widen the codes to bf16 while filling the LDS tiles, everything else is shared.
 #include "attn_common.h"
 
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -97,7 +98,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     constexpr int TILEB = KT * ROWB;                             // bytes of one K (or V) tile
     // Tiles are prefetched two ahead.  PING (plan_attention says when): the two wavefronts of a SIMD run half a block apart, which takes
     // a fourth tile buffer.
-    static_assert(!PING || (KS == 1 && NW == 8 && !KV8), "pairs of wavefronts of the 256-row shape");
+    static_assert(!PING || (KS == 1 && (NW == 8 || (NW == 6 && !BAL && DH == 128)) && !KV8), "SIMDs with two wavefronts");
     constexpr int NBUF = PING ? 4 : 3;
     // wavefronts that issue tile fills (a power of two, so that each issues the same number per tile)
     constexpr int FILLERS = NW >= 8 ? 8 : NW >= 4 ? 4 : NW >= 2 ? 2 : 1;
@@ -135,7 +136,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     if constexpr (KS == 1)
         asm volatile("" ::"s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.k_tree), "s"(a.v_tree), "s"(a.seq_lens), "s"(a.parent_idx),
                      "s"(a.N), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.nsplit), "s"(a.max_seq_len), "s"(a.S), "s"(a.row_tiles),
-                     "s"(a.mul_nsplit), "s"(a.mul_hkv), "s"(a.mul_g), "s"(a.mul_rt), "s"(a.cap));
+                     "s"(a.mul_nsplit), "s"(a.mul_last), "s"(a.tree_cost), "s"(a.mul_hkv), "s"(a.mul_g), "s"(a.mul_rt), "s"(a.cap));
     // workgroup id -> (stream sigma = (b, kv head, split) or (kv head, slot), row tile); sigma % 8 picks the XCD
     const int wg8 = (int)divide(blockIdx.x >> 3, a.row_tiles, a.mul_rt);
     const int rt = (int)(blockIdx.x >> 3) - wg8 * a.row_tiles;
@@ -302,18 +303,35 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     bool direct = a.nsplit == 1;   // this segment is the whole sequence: final rows are written here
     const int nt = (Tk + kKeyTile - 1) / kKeyTile;
     if constexpr (!balanced) {
-        // The sequence's own 64-key tiles, dealt out as evenly as whole tiles allow: the first splits take one more.  The last one has
-        // the masks of the tree's keys to build as well; at head_dim 64, where a workgroup's tiles are all in flight at once, it gives
-        // a tile away if that leaves the longest split no longer (12 heads, 65 rows x 2048 tokens 10.8 -> 10.3 us per call; at
-        // head_dim 128 a third tile starts when the first has landed, and 3 sequences of up to 1531 tokens lose: 16.5 -> 16.9).
+        // The sequence's own 64-key tiles, dealt out as evenly as whole tiles allow.  The last split has the tree's keys and their
+        // masks to do as well, which takes about tree_cost tiles more (plan_attention): as many fewer are its share, as far as that
+        // shortens the longest split and leaves it the tree's keys.  The others get equal shares, the first of them one tile more.
+        // Pairs: few tiles to a workgroup and no time for the arithmetic in front of the first (49 rows x 1024 tokens on 32 kv heads
+        // 12.8 -> 13.1 us per call).  The last split takes the smaller share; at head_dim 64, where a workgroup's tiles are all in flight
+        // at once, it gives a tile away if that leaves the longest split no longer (12 heads, 65 rows x 2048 tokens 10.8 -> 10.3; at
+        // head_dim 128 a third tile starts when the first has landed, and 3 sequences of up to 1531 tokens lost: 16.5 -> 16.9).
         const int hb = (int)divide(sigma, a.nsplit, a.mul_nsplit), last = a.nsplit - 1;
         split = sigma - hb * a.nsplit;
-        const int q = (int)divide(nt, a.nsplit, a.mul_nsplit);
-        int r = nt - q * a.nsplit;
-        if constexpr (DH == 64) r += r > 0 && r < last && q > 1;
-        const int t0 = split * q + min(split, r);
+        const int even = (int)divide(nt, a.nsplit, a.mul_nsplit);
+        int t0, share;
+        if constexpr (KS == 2) {
+            int r = nt - even * a.nsplit;
+            if constexpr (DH == 64) r += r > 0 && r < last && even > 1;
+            t0 = split * even + min(split, r);
+            share = split == last ? nt - t0 : even + (split < r);
+        } else if (last == 0) {
+            t0 = 0;
+            share = nt;
+        } else {
+            const int longest = (int)divide(nt + a.tree_cost + last, a.nsplit, a.mul_nsplit);
+            const int tree = max(min(longest - a.tree_cost, even), min(even, (a.N + 2 * kKeyTile - 2) / kKeyTile));
+            const int end = nt - max(max(tree, nt - last * longest), 1);   // the last split's first tile
+            const int q = (int)divide(end, last, a.mul_last), r = end - q * last;
+            t0 = split == last ? end : split * q + min(split, r);
+            share = split == last ? nt - end : q + (split < r);
+        }
         k0 = t0 * kKeyTile;
-        k1 = split == last ? Tk : min(Tk, (t0 + q + (split < r)) * kKeyTile);
+        k1 = min(Tk, (t0 + share) * kKeyTile);
     } else {
         const int t0 = max(run_lo, tiles_before) - tiles_before, t1 = min(run_hi, tiles_before + nt) - tiles_before;
         const int s_first = slot_of_tile(tiles_before), s_last = slot_of_tile(tiles_before + nt - 1);
@@ -552,28 +570,36 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         for (int v = 1; v < 16; ++v) m = fmaxf(m, x[v]);
         return m;
     };
-    // blk0 = first key of the 32-key block; clean = the block's tile lies wholly inside the prefix
-    auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], int blk0, bool clean) {
+    // Keys of the 32-key block from blk0 on that this lane's row sees, of the 16 in the lane: bit 8*(v/4) + v%4 for its key v.  clean:
+    // the block's tile lies wholly inside the prefix.
+    auto visible = [&](int blk0, bool clean) __attribute__((always_inline)) -> uint32_t {
+        uint32_t ok = 0xffffffffu;      // bit u: key u of the block
+        if (__builtin_expect(!clean, 0)) {
+            const int bt = blk0 - L;    // tree-node index of the block's first key (negative inside the prefix)
+            const uint32_t* w = anc_s + (node_of[0] - i_first) * aw;
+            if (bt >= 0) {
+                const int wi = bt >> 5;
+                const uint64_t w0 = wi < aw ? w[wi] : 0u;
+                const uint64_t w1 = wi + 1 < aw ? w[wi + 1] : 0u;
+                ok = (uint32_t)(((w1 << 32) | w0) >> (bt & 31));
+            } else if (bt > -32) {      // block straddles the end of the prefix
+                ok = (0xffffffffu >> (32 + bt)) | (w[0] << (-bt));
+            }
+            const int left = k1 - blk0; // keys of this block inside the split
+            if (left < 32) ok &= left <= 0 ? 0u : (0xffffffffu >> (32 - left));
+            ok >>= 4 * g2;
+        }
+        return ok;
+    };
+    auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], uint32_t ok, bool clean) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             if (__builtin_expect(!clean, 0)) {
-                uint32_t okmask = 0xffffffffu;  // bit u: key u of this block is visible to this lane's row
-                const int bt = blk0 - L;        // tree-node index of the block's first key (negative inside the prefix)
-                const uint32_t* w = anc_s + (node_of[rb] - i_first) * aw;
-                if (bt >= 0) {
-                    const int wi = bt >> 5;
-                    const uint64_t w0 = wi < aw ? w[wi] : 0u;
-                    const uint64_t w1 = wi + 1 < aw ? w[wi + 1] : 0u;
-                    okmask = (uint32_t)(((w1 << 32) | w0) >> (bt & 31));
-                } else if (bt > -32) {          // block straddles the end of the prefix
-                    okmask = (0xffffffffu >> (32 + bt)) | (w[0] << (-bt));
-                }
-                const int left = k1 - blk0;     // keys of this block inside the split
-                if (left < 32) okmask &= left <= 0 ? 0u : (0xffffffffu >> (32 - left));
-                okmask >>= 4 * g2;  // this half-lane's keys are now bits 8*(v/4) + v%4
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    if (!((okmask >> (8 * (v >> 2) + (v & 3))) & 1u)) st[rb][v] = -INFINITY;
+                for (int v = 0; v < 16; ++v) {   // (two instructions a key)
+                    const uint32_t see = (uint32_t)__builtin_amdgcn_sbfe((int)ok, 8 * (v >> 2) + (v & 3), 1);
+                    st[rb][v] = __uint_as_float((see & __float_as_uint(st[rb][v])) | (~see & 0xff800000u));
+                }
             }
             // weights of this lane's 16 keys relative to the reference ms, packed for the P.V product; returns their sum
             auto weights = [&](float ms) __attribute__((always_inline)) {
@@ -758,8 +784,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // Wavefronts 0 to 4 always work, so that one SIMD keeps its pair and the workgroup keeps the pace of the other row
     // tiles of its K/V stream: a workgroup that runs ahead of them fetches every tile from HBM a second time (1284 rows x
     // 32768 keys with all seven idle wavefronts of the last row tile skipping: 221 MB fetched per launch instead of 149).
-    // Only the 256-row shape takes the branch: the six-wavefront shape measured 1.5 % slower with it.
-    constexpr bool kSkipIdle = NW == 8 && KS == 1;
+    // The six-wavefront shape measured 1.5 % slower with the branch.
+    // (With opposite phases it takes the branch as well: without a condition in the loop the compiler moves every buffer's addresses in
+    // front of it and spills 464 registers.)
+    constexpr bool kSkipIdle = (NW == 8 && KS == 1) || PING;
     const bool has_rows = !kSkipIdle || wave <= 4 || __builtin_amdgcn_readfirstlane((int)(row_base + wrow * RB * 32 < R)) != 0;
     // PING: matrix and vector instructions of different wavefronts run side by side, but two wavefronts that want the same
     // pipe get it one after the other, the older one first even if the younger is half through its phase: a pair that meets
@@ -767,7 +795,8 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // which the matrix pipe is busy 2262).  So the pair of a SIMD (wavefronts w and w + 4) is held in opposite phases: a
     // barrier between any two phases, the later wavefront one phase behind.  2755 cycles per tile that way, 2660 with the
     // conditions of the first and last tiles out of the loop (1284 rows x 32768 keys on 8 kv heads: 197 -> 182 us).  The
-    // shapes of four and six wavefronts keep one barrier per tile: most of their wavefronts are alone on their SIMD.
+    // shape of four wavefronts keeps one barrier per tile, as each is alone on its SIMD; that of six, where two SIMDs have a pair and
+    // set the pace, takes the phases too (516 rows x 8192 keys on 8 kv heads 33.0 -> 31.3 us per call, 129 x 4096 on 40 31.7 -> 29.9).
     const bool late = PING && wave >= 4;
     auto interleave_reads = [&]() {   // two LDS reads behind each of the NS matrix instructions
         static_for<0, NS>([&](auto) {
@@ -798,9 +827,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         if constexpr (PING) {
             const int buf_p2 = (buf + 2) % NBUF, buf_p3 = (buf + 3) % NBUF;   // buffers of tiles t+2 and t+3
             // Vector phase of block 0: the K operand of block 1 is requested, then the softmax.
+            const uint32_t ok0 = visible(tile_base, clean);
             read_k(buf, 1, ka);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, tile_base, clean);
+            softmax(st, pb, ok0, clean);
             __builtin_amdgcn_sched_barrier(0);
             if (late) await_tile(t, true, STEADY);
             step();
@@ -816,9 +846,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             // block 1 of the tile; the next tile is visible before its first operand is read
             if (!late) await_tile(t, false, STEADY);
             step();
+            const uint32_t ok1 = visible(tile_base + 32, clean);
             if (STEADY || t + 1 < ntiles) read_k(buf_next, 0, ka);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, tile_base + 32, clean);
+            softmax(st, pb, ok1, clean);
             __builtin_amdgcn_sched_barrier(0);
             step();
             pv(va, pb);
@@ -834,22 +865,25 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             return;
         } else if constexpr (KS == 1) {
             // block 0 of the tile
+            const uint32_t ok0 = visible(tile_base, clean);
             read_v(buf, 0, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, tile_base, clean);
+            softmax(st, pb, ok0, clean);
             read_k(buf, 1, ka);
             __builtin_amdgcn_sched_barrier(0);
             pv(va, pb);
             qk(ka, st);
             __builtin_amdgcn_sched_barrier(0);
             // block 1 of the tile; the next tile becomes visible before its first K operand is read
+            const uint32_t ok1 = visible(tile_base + 32, clean);
             read_v(buf, 1, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, tile_base + 32, clean);
+            softmax(st, pb, ok1, clean);
         } else {
+            const uint32_t ok = visible(tile_base + 32 * kh, clean);
             read_v(buf, kh, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, tile_base + 32 * kh, clean);
+            softmax(st, pb, ok, clean);
         }
         turn(t, buf, tile_base);
         if (t + 1 < ntiles) read_k(buf_next, kh, ka);
@@ -1063,6 +1097,9 @@ hipError_t launch_cfg(const AttnArgs& a, const AttnPlan& p, hipStream_t st) {
             return p.row_tiles == 1 ? launch_variant<NW, RB, KT, KS, false, true, BAL, DHT, PING>(a, p, st)
                                     : launch_variant<NW, RB, KT, KS, false, false, BAL, DHT, PING>(a, p, st);
         };
+        if constexpr (KS == 1 && NW == 6 && DHT == 128) {
+            if (p.phases && a.slots == 0) return go(std::false_type{}, std::true_type{});
+        }
         if constexpr (KS == 1 && NW == 8) {
             if (p.phases) return a.slots > 0 ? go(std::true_type{}, std::true_type{}) : go(std::false_type{}, std::true_type{});
         }
@@ -1104,6 +1141,10 @@ hipError_t raise_shapes() {
     constexpr std::false_type no;
     both(IntC<4>{}, IntC<1>{}, no); both(IntC<6>{}, IntC<1>{}, no); both(IntC<8>{}, IntC<1>{}, no);
     both(IntC<8>{}, IntC<1>{}, std::true_type{});
+    if constexpr (DHT == 128) {
+        if (e == hipSuccess) e = raise_variant<6, 1, 64, 1, false, false, false, DHT, true>();
+        if (e == hipSuccess) e = raise_variant<6, 1, 64, 1, false, true, false, DHT, true>();
+    }
     both(IntC<2>{}, IntC<2>{}, no); both(IntC<4>{}, IntC<2>{}, no); both(IntC<8>{}, IntC<2>{}, no);
     return e;
 }
@@ -1117,7 +1158,7 @@ size_t attn_mfma_smem(int waves, int kshares, int head_dim, int group, int nodes
     const size_t tile = (size_t)64 * 2 * head_dim;
     const int rw = waves / kshares * 32;
     const int nodes_local = rw % group == 0 ? rw / group : (rw + group - 1) / group + 1;
-    const int nbuf = 3, q_outside = q_apart(waves, kshares, head_dim) ? waves / kshares : waves - 4 * (nbuf - 2);
+    const int nbuf = 3, q_outside = q_apart(waves, kshares, head_dim) ? waves / kshares : std::max(waves - 4 * (nbuf - 2), waves >= 6 ? 4 : 0);
     return 2 * nbuf * tile + (q_outside > 0 ? q_outside * tile / 2 : 0) +
            (size_t)nodes_local * ((nodes + 31) / 32) * 4 + (size_t)((nodes + 63) / 64) * 256;
 }

@@ -85,7 +85,7 @@ static int64_t equal_splits(const ygg_shape& s, int row_tiles, int64_t tiles) {
 // At least this many key tiles to a workgroup of the longest sequence: a batch is cut into equal runs instead (plan_attention).
 static constexpr int64_t kTilesForRuns = 8;
 // At least this many tiles of one sequence to a workgroup: opposite phases (plan_attention).
-static constexpr int64_t kTilesForPhases128 = 20, kTilesForPhases64 = 64;
+static constexpr int64_t kTilesForPhases128 = 10, kTilesForPhases64 = 24;
 
 // The padded rows decide where a workgroup streams many key tiles.  Where its share of them is short, a workgroup of fewer rows
 // is the better one: it starts sooner (fewer rows of Q, fewer wavefronts to meet) and its tiles take less time, so with the
@@ -196,11 +196,21 @@ AttnPlan plan_attention(const ygg_shape& s) {
         }
         // Opposite phases of the two wavefronts of a SIMD pay where a workgroup streams many tiles of one sequence: the first tile and
         // the last four go through a body with conditions, and a tile takes four barriers instead of one.  One sequence on 8 kv heads,
-        // us per call without -> with them, by tiles to a workgroup: head_dim 128, 7 tiles (1284 rows x 2048 tokens) 29.6 -> 32.2, 13
-        // 40.8 -> 43.5, 26 61.6 -> 62.8, 52 106.5 -> 104.3, 22 (1032 rows x 8192) 49.9 -> 48.7, 16 (772 rows) 42.4 -> 42.7, 32 69.7 ->
-        // 67.1; head_dim 64, 13 tiles 28.5 -> 33.3, 52 66.9 -> 70.0, runs of 64 (4 x 8192, 776 rows) 82.7 -> 82.2, of 128 149 -> 145.
+        // us per call without -> with them, by tiles to a workgroup, both with shares after tree_cost: 256 rows, head_dim 128, 7 tiles
+        // (516 rows x 4096 tokens) 23.5 -> 23.2, 9 (1284 x 2600) 29.7 -> 30.1, 11 33.4 -> 32.3, 13 38.8 -> 36.9 and (516 x 8192) 34.8 ->
+        // 32.8; head_dim 64, 13 tiles 27.4 -> 26.9, 16 (392 rows) 26.9 -> 27.4, 26 40.7 -> 39.4, 52 68.5 -> 65.9; 192 rows, head_dim 128, 4
+        // tiles (516 x 2000) 19.2 -> 20.0, 7 23.1 -> 23.0, 9 (161 x 4096 on 32 kv heads) 29.9 -> 30.0, 11 (129 x 4096 on 40) 31.7 -> 29.9, 13
+        // 33.0 -> 31.3.
         const int64_t segment = p.slots > 0 ? std::min(s.batch * tiles / p.slots, tiles) : tiles / std::clamp(ns, (int64_t)1, (int64_t)64);
-        p.phases = p.waves == 8 && p.kshares == 1 && segment >= (s.head_dim == 128 ? kTilesForPhases128 : kTilesForPhases64);
+        p.phases = p.kshares == 1 && segment >= (s.head_dim == 128 ? kTilesForPhases128 : kTilesForPhases64) &&
+                   (p.waves == 8 || (p.waves == 6 && s.head_dim == 128 && p.slots == 0));
+        // What the tree's keys and their masks cost the workgroup of a sequence's last split beside their tiles, in tiles: the masks'
+        // chain, and per tile of tree keys the masking, which with opposite phases lengthens both wavefronts' phases.  Such a workgroup
+        // with an equal share ended 5.9 us after the others (1284 rows x 2048 tokens), 7.5 at 8192.  us per call with equal shares ->
+        // these: 1284 rows x 4096 tokens on 8 kv heads 42.1 -> 36.5, x 8192 59.8 -> 55.0, x 32768 178 -> 174, 516 rows x 4096 in
+        // tiles of 256 26.0 -> 24.2, 392 x 16384 41.1 -> 40.6; without opposite phases 1284 x 2048 27.6 -> 27.1.
+        const int32_t tree_tiles = (s.n_nodes + kKeyTile - 1) / kKeyTile;
+        p.tree_cost = p.phases ? 1 + 6 * tree_tiles / 5 : 1 + tree_tiles / 4;
     } else {
         // vector path: one wavefront per (row, split); aim for ~4096 wavefronts
         ns = (4096 + rows - 1) / rows;
@@ -334,10 +344,12 @@ static int32_t tree_attention_impl(const ygg_shape* s, const void* q, const void
     a.nsplit = p.nsplit; a.max_seq_len = s->max_seq_len; a.cap = s->kv_capacity; a.scale = s->softmax_scale;
     a.slots = p.slots;
     a.lead = kSegmentLead;
+    a.tree_cost = p.tree_cost;
     a.seq_runs = p.slots > 0 && p.slots % s->batch == 0 ? p.slots / s->batch : 0;
     a.S = p.slots > 0 ? a.Hkv * p.slots : a.B * a.Hkv * p.nsplit;
     a.rows_total = a.B * a.N * a.Hq;
     a.mul_nsplit = 0xffffffffu / (uint32_t)a.nsplit;
+    a.mul_last = a.nsplit > 1 ? 0xffffffffu / (uint32_t)(a.nsplit - 1) : 0;   // the last split apart
     a.mul_hkv = 0xffffffffu / (uint32_t)a.Hkv;
     a.mul_g = 0xffffffffu / (uint32_t)a.G;
     a.row_tiles = p.row_tiles > 0 ? p.row_tiles : 1;

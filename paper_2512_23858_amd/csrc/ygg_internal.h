@@ -37,12 +37,13 @@ struct AttnArgs {
     int32_t B, N, Hq, Hkv, G, Dh;
     int32_t nsplit, max_seq_len;
     int32_t slots;    // matrix-core kernel, batches: > 0 = workgroups take equal runs of the concatenated key tiles (nsplit = slots)
+    int32_t tree_cost; // matrix-core kernel, key splits: what the tree's keys and masks cost the last one beside their tiles, in tiles
     int32_t lead;     // slots > 0: what a segment costs beside its key tiles, in tiles
     int32_t seq_runs; // slots > 0: runs to a sequence where that is a whole number, else 0
     int32_t S;        // matrix-core kernel: K/V streams, slots * Hkv or B * Hkv * nsplit
     int32_t rows_total;                        // B * N * Hq
     int32_t row_tiles;                         // matrix-core kernel: workgroups along the query rows
-    uint32_t mul_nsplit, mul_hkv, mul_g, mul_rt;   // (2^32 - 1) / d: reciprocals for the kernels' divisions
+    uint32_t mul_nsplit, mul_last, mul_hkv, mul_g, mul_rt;   // (2^32 - 1) / d: reciprocals for the kernels' divisions
     int64_t cap;
     float scale;
 };
@@ -56,6 +57,7 @@ struct AttnPlan {
     int32_t row_tiles;      // MFMA kernel: workgroups along the N*G query rows of one kv head
     int32_t slots;          // MFMA kernel, batches: equal runs of key tiles per (kv head, row tile); 0 = one sequence per workgroup
     int32_t phases;         // MFMA kernel, 8 wavefronts: the two of a SIMD in opposite phases
+    int32_t tree_cost;      // MFMA kernel: key tiles by which the last split's share is smaller
     size_t part_o_bytes, part_rec_bytes, seq_splits_bytes;
 };
 

@@ -131,3 +131,9 @@ def test_attach_tree_feeds_attention_and_acceptance():
     from test_gpu_expand_accept import _accept_both
     logits = wl.acceptance_inputs(cfg, parent, token)
     _accept_both(cfg, parent, token, 2, lens, logits=logits)
+
+
+# places counted or sorted, by the number of entries for the threads there are: both sides of the line, and widths that fill no wavefront
+@pytest.mark.parametrize("D,W", [(9, 14), (11, 15), (7, 13), (4, 3), (12, 3), (2, 31)])
+def test_places_counted_and_sorted(D, W):
+    attach_both(_cfg(2, D, W, 3001, seed=61), check_margin=False)

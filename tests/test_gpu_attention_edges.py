@@ -184,3 +184,14 @@ def test_partial_rows_of_pairs_that_cancel(plan, waves, Dh):
     out, _ = run_attention(shape, host, parent)
     bound = 2 * 192 * 2.0 ** -12 / 120 + 2.0 ** -8 * np.abs(ref)     # (120 to 123 keys to a row)
     assert (np.abs(out - ref) <= 1.001 * bound).all(), (np.abs(out - ref) / bound).max()
+
+
+# The last split's share is smaller by what the tree's keys cost it, down to one tile, and the others' differ by one: trees of one, two
+# and four tiles over prefixes that leave splits empty, leave them one tile, and give them enough for opposite phases (the longest).
+@pytest.mark.parametrize("waves,Dh", [(8, 128), (6, 128), (4, 128), (8, 64), (6, 64)])
+@pytest.mark.parametrize("D,W,nsplit", [(5, 8, 3), (6, 16, 5), (10, 20, 5), (10, 20, 16)])
+def test_shares_of_the_last_split(plan, waves, Dh, D, W, nsplit):
+    plan(waves=waves, rblocks=1, kshares=1, nsplit=nsplit)
+    for L in (0, 63, 200, 64 * nsplit - 1 - D * W % 64, 640, 1111, 64 * 11 * nsplit if nsplit < 10 else 700):
+        cfg, host, parent = _inputs(_cfg(1, 4, 1, D, W, Dh=Dh, seed=47), [L], max(L, 64 * nsplit), tree_gain=2.0)
+        _check(cfg, host, parent, max(L, 64 * nsplit))

@@ -320,7 +320,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             int r = nt - even * a.nsplit;
             if constexpr (DH == 64) r += r > 0 && r < last && even > 1;
             t0 = split * even + min(split, r);
-            share = split == last ? nt - t0 : even + (split < r);
+            share = DH == 64 && split == last ? nt - t0 : even + (split < r);
         } else if (last == 0) {
             t0 = 0;
             share = nt;
@@ -593,10 +593,13 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         }
         return ok;
     };
-    auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], uint32_t ok, bool clean) {
+    // seen(): visible() of the block, formed in front of the operand reads where these would be waited for first (pairs have time for
+    // it behind them: 392 rows x 2000 tokens on 8 kv heads 15.9 -> 15.7 us per call)
+    auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], auto seen, bool clean) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             if (__builtin_expect(!clean, 0)) {
+                const uint32_t ok = seen();
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {   // (two instructions a key)
                     const uint32_t see = (uint32_t)__builtin_amdgcn_sbfe((int)ok, 8 * (v >> 2) + (v & 3), 1);
@@ -832,7 +835,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             const uint32_t ok0 = visible(tile_base, clean);
             read_k(buf, 1, ka);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, ok0, clean);
+            softmax(st, pb, [&] { return ok0; }, clean);
             __builtin_amdgcn_sched_barrier(0);
             if (late) await_tile(t, true, STEADY);
             step();
@@ -851,7 +854,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             const uint32_t ok1 = visible(tile_base + 32, clean);
             if (STEADY || t + 1 < ntiles) read_k(buf_next, 0, ka);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, ok1, clean);
+            softmax(st, pb, [&] { return ok1; }, clean);
             __builtin_amdgcn_sched_barrier(0);
             step();
             pv(va, pb);
@@ -870,7 +873,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             const uint32_t ok0 = visible(tile_base, clean);
             read_v(buf, 0, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, ok0, clean);
+            softmax(st, pb, [&] { return ok0; }, clean);
             read_k(buf, 1, ka);
             __builtin_amdgcn_sched_barrier(0);
             pv(va, pb);
@@ -880,12 +883,11 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             const uint32_t ok1 = visible(tile_base + 32, clean);
             read_v(buf, 1, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, ok1, clean);
+            softmax(st, pb, [&] { return ok1; }, clean);
         } else {
-            const uint32_t ok = visible(tile_base + 32 * kh, clean);
             read_v(buf, kh, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, ok, clean);
+            softmax(st, pb, [&] { return visible(tile_base + 32 * kh, false); }, clean);
         }
         turn(t, buf, tile_base);
         if (t + 1 < ntiles) read_k(buf_next, kh, ka);

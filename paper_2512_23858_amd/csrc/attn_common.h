@@ -40,27 +40,28 @@ __device__ __forceinline__ i16x4 lds_read_tr16(const unsigned char* p) {
 // (lds_base is wave-uniform and goes through M0).  Written as inline assembly so that the compiler
 // does not treat every later LDS read as dependent on it (it would wait for the whole prefetch
 // before each operand read); completion is awaited explicitly with dma_wait_keep() before the barrier
-// that publishes the tile.  The compiler keeps nothing live in M0 on this target.
+// that publishes the tile.  The compiler keeps nothing live in M0 on this target.  A direct-to-LDS load must not follow the
+// scalar write of M0 directly (one wait state, which the compiler puts in for its own builtin but not inside an asm block): s_nop.
 // NT adds the streaming hint: used when the stream is read by one workgroup only (one row tile), so that
 // nothing would ever hit the lines in L2 again.
 template <bool NT>
 __device__ __forceinline__ void dma_load16(const void* base /* wave-uniform */, uint32_t byte_off, uint32_t lds_base) {
     if constexpr (NT)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(byte_off), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(byte_off), "s"(base) : "memory");
     else
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(byte_off), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(byte_off), "s"(base) : "memory");
 }
 // Same with a per-lane 64-bit address.
 template <bool NT>
 __device__ __forceinline__ void dma_load16_flat(const void* gptr, uint32_t lds_base) {
     if constexpr (NT)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds_base), "v"(gptr) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds_base), "v"(gptr) : "memory");
     else
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
 }
 // Same, 4 bytes per lane: lane l's data lands at lds_base + 4*l.
 __device__ __forceinline__ void dma_load4(const void* gptr, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
 }
 // n / d for n < 2^31 with mul = (2^32 - 1) / d from the host: the product is the quotient or one less.
 __device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint32_t mul) {

@@ -294,6 +294,13 @@ int32_t ygg_debug_validate(const ygg_shape *shape, const int32_t *parent_idx, co
 int32_t ygg_debug_attention_plan(const ygg_shape *shape, int32_t *plan /* [5], host */);
 
 /*
+ * More of the same plan, for tests: launch[0] = 1 if the two wavefronts of a SIMD run in opposite phases, launch[1] = key tiles
+ * by which the last key split's share is smaller than an equal one where that shortens the longest, launch[2] = bytes of shared
+ * memory of a workgroup (all 0 for the vector kernel).
+ */
+int32_t ygg_debug_attention_launch(const ygg_shape *shape, int32_t *launch /* [3], host */);
+
+/*
  * Tuning hook: forces the workgroup shape (wavefronts, 32-row blocks per wavefront, key shares) and/or the number
  * of key splits of every later ygg_tree_attention call of this process; a field left 0 keeps the library's own
  * choice, an unknown shape is ignored, and (0, 0, 0, 0) removes the override.  The workspace must be sized

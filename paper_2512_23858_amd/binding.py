@@ -96,6 +96,8 @@ def load_library() -> ctypes.CDLL:
         lib.ygg_debug_set_attention_plan.argtypes = [i32, i32, i32, i32]
         lib.ygg_debug_attention_plan.restype = i32
         lib.ygg_debug_attention_plan.argtypes = [shp, ctypes.POINTER(i32)]
+        lib.ygg_debug_attention_launch.restype = i32
+        lib.ygg_debug_attention_launch.argtypes = [shp, ctypes.POINTER(i32)]
         lib.ygg_debug_tree_attention_main.restype = i32
         lib.ygg_debug_tree_attention_main.argtypes = [shp] + [vp] * 9 + [vp, sz, vp]
         _lib = lib
@@ -280,6 +282,14 @@ def attention_plan(shape: Shape) -> dict:
     out = (ctypes.c_int32 * 5)()
     _check(load_library().ygg_debug_attention_plan(ctypes.byref(cs), out), "ygg_debug_attention_plan")
     return dict(matrix_cores=bool(out[0]), waves=out[1], key_shares=out[2], row_tiles=out[3], key_splits=out[4])
+
+
+def attention_launch(shape: Shape) -> dict:
+    """ygg_debug_attention_launch: more of the launch plan of tree_attention for this shape (host only)."""
+    cs = shape.c()
+    out = (ctypes.c_int32 * 3)()
+    _check(load_library().ygg_debug_attention_launch(ctypes.byref(cs), out), "ygg_debug_attention_launch")
+    return dict(opposite_phases=bool(out[0]), tree_cost=out[1], lds_bytes=out[2])
 
 
 def init():

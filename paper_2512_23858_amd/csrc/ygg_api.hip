@@ -86,6 +86,7 @@ static int64_t equal_splits(const ygg_shape& s, int row_tiles, int64_t tiles) {
 static constexpr int64_t kTilesForRuns = 8;
 // At least this many tiles of one sequence to a workgroup: opposite phases (plan_attention).
 static constexpr int64_t kTilesForPhases128 = 10, kTilesForPhases64 = 24;
+static constexpr int64_t kTilesForPhasesInRuns128 = 20, kTilesForPhasesInRuns64 = 64;
 
 // The padded rows decide where a workgroup streams many key tiles.  Where its share of them is short, a workgroup of fewer rows
 // is the better one: it starts sooner (fewer rows of Q, fewer wavefronts to meet) and its tiles take less time, so with the
@@ -200,9 +201,16 @@ AttnPlan plan_attention(const ygg_shape& s) {
         // (516 rows x 4096 tokens) 23.5 -> 23.2, 9 (1284 x 2600) 29.7 -> 30.1, 11 33.4 -> 32.3, 13 38.8 -> 36.9 and (516 x 8192) 34.8 ->
         // 32.8; head_dim 64, 13 tiles 27.4 -> 26.9, 16 (392 rows) 26.9 -> 27.4, 26 40.7 -> 39.4, 52 68.5 -> 65.9; 192 rows, head_dim 128, 4
         // tiles (516 x 2000) 19.2 -> 20.0, 7 23.1 -> 23.0, 9 (161 x 4096 on 32 kv heads) 29.9 -> 30.0, 11 (129 x 4096 on 40) 31.7 -> 29.9, 13
-        // 33.0 -> 31.3.
+        // 33.0 -> 31.3.  Runs start a pipeline for every sequence they touch, their shares are not shorter for the tree's keys, and the
+        // lengths may lie far below the bound that the tiles are counted from, so their line lies higher.  us per call without -> with
+        // them, by tiles of the bound to a run: head_dim 128, 12 (24 sequences of 63 tokens, 208 rows on 40 kv heads) 93.5 -> 98.8, (23 of
+        // 84, 776 rows on 8) 53.8 -> 56.6, 14 (7 of 203 to 407, 788 rows on 8) 35.7 -> 37.8, 10 (2 of 3000, 1284 rows on 8) 54.8 -> 55.4, 15
+        // (3 of 5000, 392 rows on 8) 42.0 -> 40.6; head_dim 64, 27 (4 of 6000, 388 rows on 8) 39.8 -> 41.2, 33 (of 8192) 47.3 -> 48.2, 39 (2
+        // of 6000, 1284 rows) 58.7 -> 61.4, 36 (8 of 2048, 804 rows) 51.1 -> 52.8.
         const int64_t segment = p.slots > 0 ? std::min(s.batch * tiles / p.slots, tiles) : tiles / std::clamp(ns, (int64_t)1, (int64_t)64);
-        p.phases = p.kshares == 1 && segment >= (s.head_dim == 128 ? kTilesForPhases128 : kTilesForPhases64) &&
+        const int64_t phases_from = p.slots > 0 ? (s.head_dim == 128 ? kTilesForPhasesInRuns128 : kTilesForPhasesInRuns64)
+                                                : (s.head_dim == 128 ? kTilesForPhases128 : kTilesForPhases64);
+        p.phases = p.kshares == 1 && segment >= phases_from &&
                    (p.waves == 8 || (p.waves == 6 && s.head_dim == 128 && p.slots == 0));
         // What the tree's keys and their masks cost the workgroup of a sequence's last split beside their tiles, in tiles: the masks'
         // chain, and per tile of tree keys the masking, which with opposite phases lengthens both wavefronts' phases.  Such a workgroup
@@ -280,6 +288,15 @@ int32_t ygg_debug_attention_plan(const ygg_shape* s, int32_t* plan) {
     if (!plan) return YGG_ERR_NULL;
     const AttnPlan p = plan_attention(*s);
     plan[0] = p.use_mfma; plan[1] = p.waves; plan[2] = p.kshares; plan[3] = p.row_tiles; plan[4] = p.nsplit;
+    return YGG_OK;
+}
+
+int32_t ygg_debug_attention_launch(const ygg_shape* s, int32_t* launch) {
+    if (int32_t rc = check_shape(s, true, false)) return rc;
+    if (!launch) return YGG_ERR_NULL;
+    const AttnPlan p = plan_attention(*s);
+    launch[0] = p.phases; launch[1] = p.tree_cost;
+    launch[2] = p.use_mfma ? (int32_t)attn_mfma_smem(p.waves, p.kshares, s->head_dim, s->n_q_heads / s->n_kv_heads, s->n_nodes) : 0;
     return YGG_OK;
 }
 

@@ -314,6 +314,27 @@ def test_split_launches_run_in_one_round(kv_dtype, head_dim):
                     assert streams * B <= most or (B > 1 and p["key_shares"] == 1 and streams <= most), (heads, n, B, L, p)
 
 
+def test_opposite_phases_by_tiles_to_a_workgroup():
+    """From 10 tiles of one sequence on, 24 at head_dim 64; batches in runs from 20 and 64 tiles of the longest length on."""
+    seen = set()
+    for head_dim, one, runs in ((128, 10, 20), (64, 24, 64)):
+        for heads in ((32, 8), (64, 8), (40, 40), (32, 4), (12, 12)):
+            for n in (49, 129, 193, 321):
+                for B in (1, 2, 3, 7, 16, 40):
+                    for L in (60, 500, 1500, 2500, 6000, 12000, 30000):
+                        s = _shape(batch=B, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=head_dim, n_nodes=n, max_seq_len=L, kv_capacity=L + 8)
+                        p, got = ygg.attention_plan(s), ygg.attention_launch(s)["opposite_phases"]
+                        tiles = -(-(L + n) // 64)
+                        # (runs: more splits than one sequence's compute units allow)
+                        in_runs = p["key_shares"] == 1 and B > 1 and p["key_splits"] * B * heads[1] * p["row_tiles"] > 256 and p["key_splits"] > 1
+                        tiles = min(B * tiles // p["key_splits"], tiles) if in_runs else tiles // p["key_splits"]
+                        shapes = (8,) if in_runs or head_dim == 64 else (8, 6)
+                        want = p["key_shares"] == 1 and p["waves"] in shapes and tiles >= (runs if in_runs else one)
+                        assert got == want, (s, p, got)
+                        seen.add((head_dim, in_runs, got))
+    assert len(seen) == 8
+
+
 def test_plan_override_is_explicit_and_removable():
     """The tuning override is a call, not an environment variable, and leaves no trace once removed."""
     import os

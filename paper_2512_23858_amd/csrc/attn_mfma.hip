@@ -24,7 +24,6 @@
 // wavefronts widen the codes to bf16 while filling the LDS tiles, everything else is shared.
 #include "attn_common.h"
 
-#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -53,9 +52,6 @@ __device__ __forceinline__ void e4m3x16_to_bf16(const u32x4& raw, uint4& first8,
     first8 = make_uint4(o[0], o[1], o[2], o[3]);
     last8 = make_uint4(o[4], o[5], o[6], o[7]);
 }
-
-// Workgroup shapes whose rows of Q have space of their own in LDS.
-constexpr bool q_apart(int waves, int kshares, int head_dim) { return kshares == 2 || (head_dim == 64 && waves <= 6); }
 
 // NW wavefronts, RB 32-row blocks per wavefront, KT keys per tile, KS key shares: with KS = 2 the
 // wavefronts pair up on the same rows and each takes one of the two 32-key blocks of every tile (a
@@ -107,28 +103,25 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* k_s = smem;                                   // [NBUF][KT][ROWB]
     unsigned char* v_s = smem + NBUF * TILEB;                    // [NBUF][KT][ROWB]
-    // Q passes through LDS.  QAPART: through space of its own behind the tile buffers, where the wavefronts of a pair share their
-    // rows (49 rows on 32 kv heads: 14 KB fetched by a workgroup instead of 32); else through the tile buffers from the third on (tile
-    // 2 is requested once Q is read) and what space they lack.
+    // Q passes through the tile buffers from the third on (tile 2 is requested once it is read) and, where these
+    // do not hold it, through space behind them.  In space of its own, shared by the wavefronts of a pair and with a third tile
+    // requested at once, it leaves room for two workgroups of four wavefronts of head_dim 64 to a compute unit instead of three: 48
+    // sequences of 300 tokens, 49 rows on 12 kv heads 16.9 -> 18.8 us per call; and where one is enough it gains nothing: 22 of 192 with
+    // 5 rows 8.3 -> 8.7, one of 2048 with 65 rows 10.2 either way, of 1024 with 49 rows on 32 kv heads of 128 12.7 -> 12.8.
     constexpr int QW = 32 * RB * ROWB;           // a wavefront's rows
-    constexpr bool QAPART = !KV8 && q_apart(NW, KS, DH);
-    constexpr int QB = QAPART ? 0 : 2 * (NBUF - 2);   // wavefronts whose rows fit the spare K (or V) buffers
-    constexpr int QX = KV8 ? 0 : QAPART ? NRW * QW : NW > 2 * QB ? (NW - 2 * QB) * QW : 0;
-    // Tiles requested before the loop is reached.  About 64 KB is what a compute unit has in flight: at head_dim 128 a third tile
-    // stands in the way of the first (49 rows x 1024 tokens on 32 kv heads 12.9 -> 13.2 us per call).
-    constexpr int AHEAD = QAPART && DH == 64 ? 3 : 2;
+    constexpr int QB = 2 * (NBUF - 2);           // wavefronts whose rows fit the spare K (or V) buffers
+    constexpr int QX = NW > 2 * QB ? (NW - 2 * QB) * QW : 0;
     static_assert(RB == 1 && QW * 2 == TILEB, "two wavefronts' rows to a tile buffer");
-    static_assert(KS == 1 || KV8 || QAPART, "a pair's rows of Q are shared");
     uint32_t* anc_s = reinterpret_cast<uint32_t*>(smem + 2 * NBUF * TILEB + QX);  // [local node][aw], then parent[N]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
     const int n = lane & 31, g2 = lane >> 5;
+    unsigned char* q_s = (wave < QB ? k_s + 2 * TILEB + wave * QW
+                                    : wave < 2 * QB ? v_s + 2 * TILEB + (wave - QB) * QW : smem + 2 * NBUF * TILEB + (wave - 2 * QB) * QW);
     const bool is_loader = KV8 && wave >= NW;      // wave-uniform
     const int wrow = KS == 1 ? wave : wave % NRW;  // position along the rows (computing wavefronts)
     const int kh = KS == 1 ? 0 : wave / NRW;       // which block of every tile (KS = 2)
-    unsigned char* q_s = (wrow < QB ? k_s + 2 * TILEB + wrow * QW
-                                    : wrow < 2 * QB ? v_s + 2 * TILEB + (wrow - QB) * QW : smem + 2 * NBUF * TILEB + (wrow - 2 * QB) * QW);
 
     // All arguments at once: left to itself the compiler fetches each where it is first needed, one scalar-cache miss after
     // the other in front of the first tile fill (32 layers of a 516-row verify pass: 923 -> 887 us).  The paired shapes'
@@ -259,9 +252,6 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // are never stored.  As plain register loads they would hold up the first block until every tile in flight has landed:
     // the compiler's wait for them does not know of the tile fills behind them and awaits those as well.
     bf16x8 qreg[RB][NS];
-    // Pairs: rows of the block from q_last on are not fetched, they repeat it.  (Without pairs the wavefronts that have no rows
-    // would run ahead: 16 sequences of 512 to 8192 tokens with 392 rows 137.4 -> 138.7 us per call.)
-    const int q_last = KS == 2 ? min(max(R - 1 - row_base - wrow * 32, 0), 31) : 31;
     if constexpr (KV8) {   // (the computing wavefronts have nothing else in flight: plain loads)
         if (!is_loader) {
 #pragma unroll
@@ -275,9 +265,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     } else {
         const uint32_t q_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)q_s;
 #pragma unroll
-        for (int i0 = 0; i0 < 32 * RB / RPI; i0 += KS) {
-            const int it = i0 + kh;            // (the wavefronts of a pair take turns)
-            if (RPI * it > q_last) break;      // wave-uniform
+        for (int it = 0; it < 32 * RB / RPI; ++it) {
             const int lrow = RPI * it + lane / SLOTS;
             const int rc = min(row_base + wrow * RB * 32 + lrow, R - 1);
             const int i = (int)divide(rc, a.G, a.mul_g);
@@ -718,21 +706,16 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     if constexpr (!KV8) {
         fill_tile(0, k0);
         if (ntiles > 1) fill_tile(1, k0 + KT);
-        if (AHEAD > 2 && ntiles > 2) fill_tile(2, k0 + 2 * KT);
     }
-    auto wait_tiles_out = [&](int tiles) {   // until at most so many tiles are out, of those requested so far
-        if (tiles <= 0 || KV8 || (FILLERS < NW && wave >= FILLERS)) dma_wait_keep<0>();
-        else if (tiles == 1) dma_wait_keep<PT>();
-        else if (AHEAD == 2 || tiles == 2) dma_wait_keep<2 * PT>();
-        else dma_wait_keep<3 * PT>();
+    auto wait_tiles_out = [&](bool both) {   // until at most the last one or both of the two tiles are out
+        if (KV8 || (FILLERS < NW && wave >= FILLERS)) dma_wait_keep<0>();
+        else if (both) dma_wait_keep<2 * PT>();
+        else dma_wait_keep<PT>();
     };
-    const int out_first = min(ntiles, AHEAD);
     if constexpr (!KV8) {
-        wait_tiles_out(out_first);
-        if constexpr (KS == 2) lds_barrier();   // the pair's rows of Q, and the parents
-        const int nq = min(n, q_last);
-        const unsigned char* qp = q_s + nq * ROWB + 16 * (g2 ^ (nq & 1));
-        const int pair_xor = ((nq & (SLOTS - 1)) >> 1) << 5;
+        wait_tiles_out(ntiles > 1);
+        const unsigned char* qp = q_s + n * ROWB + 16 * (g2 ^ (n & 1));
+        const int pair_xor = ((n & (SLOTS - 1)) >> 1) << 5;
 #pragma unroll
         for (int s = 0; s < NS; ++s) qreg[0][s] = *reinterpret_cast<const bf16x8*>(qp + ((32 * s) ^ pair_xor));
     }
@@ -740,12 +723,14 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // 10258 tokens 14.3 -> 14.9 us per call.)
     if (has_tree_keys) {
         if constexpr (KV8) dma_wait_keep<0>();
-        if constexpr (KV8 || KS == 1) lds_barrier();
+        lds_barrier();
         build_masks();
     }
-    if constexpr (!KV8) wait_tiles_out(out_first - 1);
+    if constexpr (!KV8) {
+        if (ntiles > 1) wait_tiles_out(false); else dma_wait_keep<0>();
+    }
     lds_barrier();  // tile 0 has landed for everybody, anc_s is published, Q is read
-    if constexpr (!KV8 && AHEAD == 2) {
+    if constexpr (!KV8) {
         if (ntiles > 2) fill_tile(2, k0 + 2 * KT);
     }
 
@@ -1155,14 +1140,14 @@ hipError_t raise_shapes() {
 
 }  // namespace
 
-// Dynamic shared memory of a workgroup: three K and V tile buffers of 64 keys, space for Q (q_apart) or for what the spare buffers do not hold of it
-// (in the 256-row shape as much as the fourth buffer of its opposite phases, which then holds Q), the ancestor bitmasks of the
-// nodes the rows belong to, and the parent table.
+// Dynamic shared memory of a workgroup: three K and V tile buffers of 64 keys, space for the rows of Q that the spare buffers do not
+// hold (as much as the fourth buffer of opposite phases, which then holds Q, in the shapes that may take them), the ancestor
+// bitmasks of the nodes the rows belong to, and the parent table.
 size_t attn_mfma_smem(int waves, int kshares, int head_dim, int group, int nodes) {
     const size_t tile = (size_t)64 * 2 * head_dim;
     const int rw = waves / kshares * 32;
     const int nodes_local = rw % group == 0 ? rw / group : (rw + group - 1) / group + 1;
-    const int nbuf = 3, q_outside = q_apart(waves, kshares, head_dim) ? waves / kshares : std::max(waves - 4 * (nbuf - 2), waves >= 6 ? 4 : 0);
+    const int nbuf = 3, q_outside = waves == 6 && head_dim == 128 ? 4 : waves - 4 * (nbuf - 2);
     return 2 * nbuf * tile + (q_outside > 0 ? q_outside * tile / 2 : 0) +
            (size_t)nodes_local * ((nodes + 31) / 32) * 4 + (size_t)((nodes + 63) / 64) * 256;
 }

@@ -335,6 +335,15 @@ def test_opposite_phases_by_tiles_to_a_workgroup():
     assert len(seen) == 8
 
 
+def test_small_workgroups_of_head_dim_64_share_a_compute_unit():
+    """Three workgroups of four wavefronts fit the 160 KB of shared memory: a launch of up to 768 of them is one round."""
+    for heads in ((12, 12), (32, 32), (32, 8), (8, 2)):
+        for n in (5, 9, 16, 33, 49, 65):
+            s = _shape(batch=40, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=64, n_nodes=n, max_seq_len=300, kv_capacity=308)
+            if ygg.attention_plan(s)["waves"] <= 4:
+                assert 3 * ygg.attention_launch(s)["lds_bytes"] <= 160 << 10, (heads, n)
+
+
 def test_plan_override_is_explicit_and_removable():
     """The tuning override is a call, not an environment variable, and leaves no trace once removed."""
     import os

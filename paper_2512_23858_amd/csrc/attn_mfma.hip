@@ -169,10 +169,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         hk = (int)divide(sigma, a.slots, a.mul_nsplit);   // (nsplit == slots)
         slot = sigma - hk * a.slots;
         constexpr int CH = 4;   // 64 sequences at a time: batches of up to 256
-        int tl[CH];
+        int tl[CH] = {};        // (all of them: the sum below takes those beyond the batch too)
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            tl[c] = 0;
             if (64 * c >= a.B) break;
             const int bb = 64 * c + lane;
             int Lb = bb < a.B ? a.seq_lens[bb] : 0;
@@ -289,7 +288,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
 
     L = L < 0 ? 0 : (L > a.max_seq_len ? a.max_seq_len : L);
     const int Tk = L + a.N;
-    int k0, k1, split;
+    int k0, k1, split = 0;
     bool direct = a.nsplit == 1;   // this segment is the whole sequence: final rows are written here
     const int nt = (Tk + kKeyTile - 1) / kKeyTile;
     if constexpr (!balanced) {

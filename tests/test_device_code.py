@@ -1,4 +1,6 @@
-"""Wait states that the compiler does not supply inside inline assembly, looked for in the built library's device code."""
+"""What the device code's own tests cannot show because it depends on the compiler's choices: wait states that it does not supply inside
+inline assembly, looked for in the built library, and values that are read before they are set, looked for in a compilation that
+gives these a pattern."""
 import os
 import re
 import shutil
@@ -73,3 +75,19 @@ def test_loads_keep_their_distance_from_scalars_that_the_vector_unit_writes(kern
         return m and _scalars(m[1]) & _scalars(load)
     for name, code in kernels.items():
         assert not _too_close(code, DIRECT_TO_LDS, writes, 5), name
+
+
+def test_no_count_or_index_is_read_before_it_is_set(tmp_path):
+    """Local variables start as 0xAA bytes here; where these survive optimisation in whole numbers, a path reads them.  (The operand
+    registers of wavefronts without rows, which nothing reads, are vectors of floats and of 16-bit halves.)"""
+    from paper_2512_23858_amd import build
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("hipcc is not installed")
+    flags = [x for x in build.FLAGS if x not in ("-O3", "-Wall", "-fPIC")]
+    ir = tmp_path / "attention.ll"
+    subprocess.run([build.HIPCC, *flags, "-w", "-O1", "--cuda-device-only", "-S", "-emit-llvm", "-ftrivial-auto-var-init=pattern",
+                    os.path.join(os.path.dirname(build.__file__), "csrc", "attn_mfma.hip"), "-o", str(ir)], check=True)
+    text = ir.read_text()
+    assert text.count("define ") >= 20
+    found = [line.strip()[:200] for line in text.splitlines() if "-1431655766" in line or "-6148914691236517206" in line]
+    assert not found, found[:5]

@@ -559,37 +559,31 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         for (int v = 1; v < 16; ++v) m = fmaxf(m, x[v]);
         return m;
     };
-    // Keys of the 32-key block from blk0 on that this lane's row sees, of the 16 in the lane: bit 8*(v/4) + v%4 for its key v.  clean:
-    // the block's tile lies wholly inside the prefix.
-    auto visible = [&](int blk0, bool clean) __attribute__((always_inline)) -> uint32_t {
-        uint32_t ok = 0xffffffffu;      // bit u: key u of the block
-        if (__builtin_expect(!clean, 0)) {
-            const int bt = blk0 - L;    // tree-node index of the block's first key (negative inside the prefix)
-            const uint32_t* w = anc_s + (node_of[0] - i_first) * aw;
-            if (bt >= 0) {
-                const int wi = bt >> 5;
-                const uint64_t w0 = wi < aw ? w[wi] : 0u;
-                const uint64_t w1 = wi + 1 < aw ? w[wi + 1] : 0u;
-                ok = (uint32_t)(((w1 << 32) | w0) >> (bt & 31));
-            } else if (bt > -32) {      // block straddles the end of the prefix
-                ok = (0xffffffffu >> (32 + bt)) | (w[0] << (-bt));
-            }
-            const int left = k1 - blk0; // keys of this block inside the split
-            if (left < 32) ok &= left <= 0 ? 0u : (0xffffffffu >> (32 - left));
-            ok >>= 4 * g2;
-        }
-        return ok;
-    };
-    // seen(): visible() of the block, formed in front of the operand reads where these would be waited for first (pairs have time for
-    // it behind them: 392 rows x 2000 tokens on 8 kv heads 15.9 -> 15.7 us per call)
-    auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], auto seen, bool clean) {
+    // blk0 = first key of the 32-key block; clean = the block's tile lies wholly inside the prefix.  (The mask's words read in front of
+    // the operands, so that the wait for them does not await these, with the mask formed there: us per call in the shapes without
+    // pairs, 24 sequences of 63 tokens, 208 rows on 40 kv heads 91.1 -> 93.6, 8 of 500 to 4096, 804 rows on 8 of head_dim 64 67.8 -> 68.7,
+    // two of 3000, 1284 rows on 8 55.5 -> 56.4, three of up to 1531, 144 rows on 8 16.1 -> 16.2.)
+    auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], int blk0, bool clean) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             if (__builtin_expect(!clean, 0)) {
-                const uint32_t ok = seen();
+                uint32_t okmask = 0xffffffffu;  // bit u: key u of this block is visible to this lane's row
+                const int bt = blk0 - L;        // tree-node index of the block's first key (negative inside the prefix)
+                const uint32_t* w = anc_s + (node_of[rb] - i_first) * aw;
+                if (bt >= 0) {
+                    const int wi = bt >> 5;
+                    const uint64_t w0 = wi < aw ? w[wi] : 0u;
+                    const uint64_t w1 = wi + 1 < aw ? w[wi + 1] : 0u;
+                    okmask = (uint32_t)(((w1 << 32) | w0) >> (bt & 31));
+                } else if (bt > -32) {          // block straddles the end of the prefix
+                    okmask = (0xffffffffu >> (32 + bt)) | (w[0] << (-bt));
+                }
+                const int left = k1 - blk0;     // keys of this block inside the split
+                if (left < 32) okmask &= left <= 0 ? 0u : (0xffffffffu >> (32 - left));
+                okmask >>= 4 * g2;  // this half-lane's keys are now bits 8*(v/4) + v%4
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {   // (two instructions a key)
-                    const uint32_t see = (uint32_t)__builtin_amdgcn_sbfe((int)ok, 8 * (v >> 2) + (v & 3), 1);
+                    const uint32_t see = (uint32_t)__builtin_amdgcn_sbfe((int)okmask, 8 * (v >> 2) + (v & 3), 1);
                     st[rb][v] = __uint_as_float((see & __float_as_uint(st[rb][v])) | (~see & 0xff800000u));
                 }
             }
@@ -816,10 +810,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         if constexpr (PING) {
             const int buf_p2 = (buf + 2) % NBUF, buf_p3 = (buf + 3) % NBUF;   // buffers of tiles t+2 and t+3
             // Vector phase of block 0: the K operand of block 1 is requested, then the softmax.
-            const uint32_t ok0 = visible(tile_base, clean);
             read_k(buf, 1, ka);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, [&] { return ok0; }, clean);
+            softmax(st, pb, tile_base, clean);
             __builtin_amdgcn_sched_barrier(0);
             if (late) await_tile(t, true, STEADY);
             step();
@@ -835,10 +828,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             // block 1 of the tile; the next tile is visible before its first operand is read
             if (!late) await_tile(t, false, STEADY);
             step();
-            const uint32_t ok1 = visible(tile_base + 32, clean);
             if (STEADY || t + 1 < ntiles) read_k(buf_next, 0, ka);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, [&] { return ok1; }, clean);
+            softmax(st, pb, tile_base + 32, clean);
             __builtin_amdgcn_sched_barrier(0);
             step();
             pv(va, pb);
@@ -854,24 +846,22 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
             return;
         } else if constexpr (KS == 1) {
             // block 0 of the tile
-            const uint32_t ok0 = visible(tile_base, clean);
             read_v(buf, 0, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, [&] { return ok0; }, clean);
+            softmax(st, pb, tile_base, clean);
             read_k(buf, 1, ka);
             __builtin_amdgcn_sched_barrier(0);
             pv(va, pb);
             qk(ka, st);
             __builtin_amdgcn_sched_barrier(0);
             // block 1 of the tile; the next tile becomes visible before its first K operand is read
-            const uint32_t ok1 = visible(tile_base + 32, clean);
             read_v(buf, 1, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, [&] { return ok1; }, clean);
+            softmax(st, pb, tile_base + 32, clean);
         } else {
             read_v(buf, kh, va);
             __builtin_amdgcn_sched_barrier(0);
-            softmax(st, pb, [&] { return visible(tile_base + 32 * kh, false); }, clean);
+            softmax(st, pb, tile_base + 32 * kh, clean);
         }
         turn(t, buf, tile_base);
         if (t + 1 < ntiles) read_k(buf_next, kh, ka);

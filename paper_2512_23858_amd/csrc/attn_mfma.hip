@@ -296,16 +296,17 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         // masks to do as well, which takes about tree_cost tiles more (plan_attention): as many fewer are its share, as far as that
         // shortens the longest split and leaves it the tree's keys.  The others get equal shares, the first of them one tile more.
         // Pairs: few tiles to a workgroup and no time for the arithmetic in front of the first (49 rows x 1024 tokens on 32 kv heads
-        // 12.8 -> 13.1 us per call).  The last split takes the smaller share; at head_dim 64, where a workgroup's tiles are all in flight
-        // at once, it gives a tile away if that leaves the longest split no longer (12 heads, 65 rows x 2048 tokens 10.8 -> 10.3; at
-        // head_dim 128 a third tile starts when the first has landed, and 3 sequences of up to 1531 tokens lost: 16.5 -> 16.9).
+        // 12.8 -> 13.1 us per call).  The last split takes the smaller share; at head_dim 64 it gives a tile away if that leaves the
+        // longest split no longer and the tree's keys in the last one (12 heads, 65 rows x 2048 tokens 10.7 -> 10.3 us per call; with the
+        // tree cut in two, 524 rows x 277 tokens on 8 kv heads 10.3 -> 10.8).  At head_dim 128 three sequences of up to 1531 tokens, 144 rows
+        // on 8 lost: 16.5 -> 16.9.
         const int hb = (int)divide(sigma, a.nsplit, a.mul_nsplit), last = a.nsplit - 1;
         split = sigma - hb * a.nsplit;
         const int even = (int)divide(nt, a.nsplit, a.mul_nsplit);
         int t0, share;
         if constexpr (KS == 2) {
             int r = nt - even * a.nsplit;
-            if constexpr (DH == 64) r += r > 0 && r < last && even > 1;
+            if constexpr (DH == 64) r += r > 0 && r < last && even > 1 && (last * even + r + 1) * kKeyTile <= L;
             t0 = split * even + min(split, r);
             share = DH == 64 && split == last ? nt - t0 : even + (split < r);
         } else if (last == 0) {
@@ -561,8 +562,8 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     };
     // blk0 = first key of the 32-key block; clean = the block's tile lies wholly inside the prefix.  (The mask's words read in front of
     // the operands, so that the wait for them does not await these, with the mask formed there: us per call in the shapes without
-    // pairs, 24 sequences of 63 tokens, 208 rows on 40 kv heads 91.1 -> 93.6, 8 of 500 to 4096, 804 rows on 8 of head_dim 64 67.8 -> 68.7,
-    // two of 3000, 1284 rows on 8 55.5 -> 56.4, three of up to 1531, 144 rows on 8 16.1 -> 16.2.)
+    // pairs, 24 sequences of 63 tokens, 208 rows on 40 kv heads 90.6 -> 92.4, 8 of 500 to 4096, 804 rows on 8 of head_dim 64 67.8 -> 68.3,
+    // two of 3000, 1284 rows on 8 55.2 -> 56.1, three of up to 1531, 144 rows on 8 16.1 -> 16.2.)
     auto softmax = [&](f32x16 (&st)[RB], i16x8 (&pb)[RB][2], int blk0, bool clean) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {

@@ -195,3 +195,18 @@ def test_shares_of_the_last_split(plan, waves, Dh, D, W, nsplit):
     for L in (0, 63, 200, 64 * nsplit - 1 - D * W % 64, 640, 1111, 64 * 11 * nsplit if nsplit < 10 else 700):
         cfg, host, parent = _inputs(_cfg(1, 4, 1, D, W, Dh=Dh, seed=47), [L], max(L, 64 * nsplit), tree_gain=2.0)
         _check(cfg, host, parent, max(L, 64 * nsplit))
+
+
+# Pairs of head_dim 64: the last split gives a tile away where the tree's keys then still lie in it alone.  Prefixes around that, with one
+# to three tiles of tree.
+@pytest.mark.parametrize("waves", [8, 4, 2])
+@pytest.mark.parametrize("D,W,nsplit", [(2, 4, 3), (5, 8, 4), (10, 13, 3), (10, 13, 10)])
+def test_tiles_given_away_by_pairs(plan, waves, D, W, nsplit):
+    plan(waves=waves, rblocks=1, kshares=2, nsplit=nsplit)
+    tree = 1 + D * W
+    for tiles in (2 * nsplit, 2 * nsplit + 1, 3 * nsplit - 2, 3 * nsplit - 1):
+        for keys in (64 * tiles, 64 * tiles - 1, 64 * tiles - 63):
+            L = keys - tree
+            cfg, host, parent = _inputs(_cfg(1, 2, 1, D, W, Dh=64, seed=67), [L], L, tree_gain=2.0)
+            assert ygg.attention_plan(shape_of(cfg, max_seq_len=L))["key_splits"] == nsplit
+            _check(cfg, host, parent, L)

@@ -637,14 +637,14 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         for (int t = tid; t <= i_last - i_first; t += THREADS) {
             uint32_t* w = anc_s + t * aw;
             for (int x = 0; x < aw; ++x) w[x] = 0;
-            // (three steps to a check; behind the root a lane goes on reading the root's entry and sets no bit)
+            // (three steps to a check; behind the root, as behind a parent that is no node, a lane goes on and sets no bit)
             int c = i_first + t;
             for (int guard = 0; guard < a.N && __any(c >= 0); guard += 3)
 #pragma unroll
                 for (int u = 0; u < 3; ++u) {
                     const int at = min(max(c, 0), a.N - 1);
                     const uint32_t bit = (uint32_t)c < (uint32_t)a.N ? 1u << (at & 31) : 0u;
-                    c = c < 0 ? -1 : parent_s[at];
+                    c = bit ? parent_s[at] : -1;
                     __hip_atomic_fetch_or(w + (at >> 5), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
         }

@@ -402,12 +402,13 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
         const uint32_t dst0 = buf * TILEB + wave * 1024;
         if (known_clean || tile_base + KT <= clean_end) {  // a whole tile of cache rows: the tile's base joins the scalar
             // pointer, the per-lane offsets are constants of the kernel (no vector arithmetic per load)
+            const uint32_t dst = __builtin_amdgcn_readfirstlane(k_lds + dst0);
             static_for<FROM, TO>([&](auto i) {
                 constexpr int it = decltype(i)::value / 2;
                 constexpr bool is_v = decltype(i)::value % 2 != 0;
                 const size_t off = (size_t)((uint32_t)(tile_base + it / NPAT * NPAT * STEP) * tok_bytes);
-                dma_load16<NT>(uniform_ptr((is_v ? vc : kc) + off), is_v ? fill_v[it % NPAT] : fill_k[it % NPAT],
-                               __builtin_amdgcn_readfirstlane((is_v ? v_lds : k_lds) + dst0 + it * FILLERS * 1024));
+                dma_load16<NT, (is_v ? NBUF * TILEB : 0) + it * FILLERS * 1024>(uniform_ptr((is_v ? vc : kc) + off),
+                                                                                is_v ? fill_v[it % NPAT] : fill_k[it % NPAT], dst);
             });
         } else if (tile_base < k1) {
             static_for<FROM, TO>([&](auto i) {

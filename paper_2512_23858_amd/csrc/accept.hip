@@ -15,6 +15,8 @@
 //                   snapshot: seq_lens itself may already have moved), for its share of the layers.
 #include "ygg_internal.h"
 
+#include <algorithm>
+
 namespace ygg {
 namespace {
 
@@ -205,6 +207,15 @@ AcceptPlan plan_accept(const ygg_shape& s) {
     p.part_bytes = ((size_t)rows * (size_t)p.nchunk * sizeof(ArgPart) + 255) / 256 * 256;
     p.oldlen_bytes = ((size_t)s.batch * sizeof(int32_t) + 255) / 256 * 256;
     return p;
+}
+
+// Scratch for this shape and every smaller batch, tree or vocabulary: fewer rows may have more chunks each, up to one for every 4096 logits
+// and, the shorter last ones included, 1900 and one to a row; or as many as the longest chunk leaves.
+size_t accept_scratch_bytes(const ygg_shape& s) {
+    const int64_t rows = (int64_t)s.batch * s.n_nodes;
+    auto chunks = [&](int64_t chunk) { return rows * ((s.vocab + chunk - 1) / chunk); };
+    const int64_t most = std::min(chunks(4096), std::max(1900 + rows, chunks(32768)));
+    return ((size_t)most * sizeof(ArgPart) + 255) / 256 * 256 + plan_accept(s).oldlen_bytes;
 }
 
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {

@@ -327,8 +327,7 @@ size_t ygg_workspace_bytes(const ygg_shape* s, int32_t op, int32_t n_layers) {
         }
         case YGG_OP_ACCEPT: {
             if (check_shape(s, false, true) != YGG_OK) return 0;
-            const AcceptPlan p = plan_accept(*s);
-            return p.part_bytes + p.oldlen_bytes;
+            return accept_scratch_bytes(*s);
         }
         default: return 0;
     }

@@ -153,6 +153,7 @@ struct AcceptArgs {
     int64_t cap;
 };
 AcceptPlan plan_accept(const ygg_shape& s);
+size_t accept_scratch_bytes(const ygg_shape& s);
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st);
 
 }  // namespace ygg

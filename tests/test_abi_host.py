@@ -199,6 +199,22 @@ def test_growth_scratch_of_the_largest_shape_serves_the_smaller_ones(W, op):
         assert sizes == sorted(sizes), B
 
 
+def test_acceptance_scratch_of_the_largest_shape_serves_the_smaller_ones():
+    """A decoder allocates once, for its largest batch, tree and vocabulary."""
+    size = lambda B, N, V: ygg.workspace_bytes(_shape(batch=B, n_nodes=N, vocab=V), ygg.OP_ACCEPT)
+    for N in (1, 9, 49, 65, 129, 1000):
+        for V in (100, 4096, 4097, 32000, 50257, 128256, 300000):
+            sizes = [size(B, N, V) for B in range(1, 70)]
+            assert sizes == sorted(sizes), (N, V)
+    for B in (1, 2, 13, 15, 60):
+        for V in (4097, 32000, 128256):
+            sizes = [size(B, N, V) for N in range(1, 1025, 7)]
+            assert sizes == sorted(sizes), (B, V)
+        for N in (1, 49, 129):
+            sizes = [size(B, N, V) for V in range(64, 400000, 997)]
+            assert sizes == sorted(sizes), (B, N)
+
+
 def test_prune_rejects_bad_arguments_on_the_host():
     lib = ygg.load_library()
 

@@ -195,9 +195,12 @@ __global__ __launch_bounds__(256) void match_compact_kernel(AcceptArgs a) {
 AcceptPlan plan_accept(const ygg_shape& s) {
     AcceptPlan p;
     // Chunks are multiples of 1024 logits (one float4 per thread).  2048 workgroups run at once, eight to a compute unit; a few more
-    // are a round of their own, as long as the first: with 2064 the chunk is made longer.  Aimed at 1900, rounding included; rows end
-    // in a shorter chunk, and these go last.  us per call, aimed at 2048 -> 1900: 129 rows of 128256 22.0 -> 19.5 (16 chunks to a
-    // row -> 14), 16 x 49 of 32000 29.8 -> 28.2, 321 of 128256 41.6 -> 40.8, 49 of 32000 11.5 either way; aimed at 1024 16 x 49 take 31.3.
+    // are a round of their own, as long as the first.  The chunk is what 1900 workgroups would take, rounded up; rows end in a
+    // shorter chunk, so that up to one workgroup to a row comes on top: most shapes stay below 2048, some do not (784 rows of 32000: three
+    // chunks, 2352).  us per call, aimed at 2048 -> 1900: 129 rows of 128256 23.0 -> 21.2 (16 chunks to a row -> 14), 257 of them 40.4 ->
+    // 34.5, 513 of 50257 35.3 -> 32.4, 784 of 32000 32.1 -> 30.7, 321 of 128256 41.3 -> 40.6, 49 of 32000 11.6 either way.  As many equal
+    // chunks to a row as keep all within 2048 instead: 513 of 50257 31.0 and 435 of 107874 44.3 -> 43.0, but 784 of 32000 31.5, 321 of
+    // 128256 41.2, 631 of 119474 69.9 -> 72.6: two long chunks to a row leave compute units idle at the end.
     const int64_t rows = (int64_t)s.batch * s.n_nodes;
     int64_t chunk = ((int64_t)s.vocab * rows / 1900 + 1023) / 1024 * 1024;
     if (chunk < 4096) chunk = 4096;

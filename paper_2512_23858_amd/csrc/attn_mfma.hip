@@ -139,8 +139,8 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     const int row_base = rt * RW;
 
     // Which (sequence, key range) segments does this workgroup serve?
-    //   classic   one segment: sigma = (sequence, kv head, split); the split is one of nsplit equal chunks of that
-    //             sequence's own key range.
+    //   classic   one segment: sigma = (sequence, kv head, split); the split is one of nsplit shares of that
+    //             sequence's own key tiles (below).
     //   balanced  (a.slots > 0, batches) sigma = (kv head, slot).  The sequences' 64-key tiles are laid end to end and
     //             cut into a.slots runs of equal length; the workgroup serves its run, i.e. the tail of one sequence,
     //             whole short sequences, the head of another, one segment after the other.  Every workgroup then has the

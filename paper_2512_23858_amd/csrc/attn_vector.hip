@@ -296,11 +296,16 @@ hipError_t launch_combine_t(const AttnArgs& a, hipStream_t st) {
     auto go = [&](auto dh) {
         constexpr int DH = decltype(dh)::value, TPR = DH / (HALF ? 8 : 4);
         auto grid = [&](int lanes) { return dim3((unsigned)((a.N * a.Hq + 256 / lanes - 1) / (256 / lanes)), (unsigned)a.B); };
-        // One trip to memory instead of two for nine to sixteen splits: 4128 rows of ten splits, us per attention call with G = 1 -> 2,
-        // head_dim 128 23.1 -> 22.7, 64 37.0 -> 36.3.  Up to eight splits two groups only add an exchange: 10272 rows of five 40.6 -> 42.5.
-        const bool two = HALF && !few && a.nsplit > 8 && !a.seq_splits && a.rows_total <= 16384;
-        if (two) hipLaunchKernelGGL((attn_combine_kernel<T, DH, HALF, 2>), grid(2 * TPR), dim3(256), 0, st, a);
-        else if (few) hipLaunchKernelGGL((attn_combine_kernel<T, DH, HALF, 64 / TPR>), grid(64), dim3(256), 0, st, a);
+        // One trip to memory instead of two for nine to sixteen splits (the plan has no more for so many rows): 4128 rows of ten splits, us
+        // per attention call with G = 1 -> 2, head_dim 128 23.1 -> 22.7, 64 37.0 -> 36.3.  Up to eight splits two groups only add an
+        // exchange: 10272 rows of five 40.6 -> 42.5.
+        if constexpr (HALF) {
+            if (!few && a.nsplit > 8 && !a.seq_splits && a.rows_total <= 16384) {
+                hipLaunchKernelGGL((attn_combine_kernel<T, DH, HALF, 2>), grid(2 * TPR), dim3(256), 0, st, a);
+                return;
+            }
+        }
+        if (few) hipLaunchKernelGGL((attn_combine_kernel<T, DH, HALF, 64 / TPR>), grid(64), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((attn_combine_kernel<T, DH, HALF, 1>), grid(TPR), dim3(256), 0, st, a);
     };
     if (a.Dh == 128) go(std::integral_constant<int, 128>{});

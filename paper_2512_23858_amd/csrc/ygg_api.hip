@@ -94,8 +94,9 @@ static constexpr int64_t kTilesForPhasesInRuns128 = 20, kTilesForPhasesInRuns64 
 // start and a time per tile of 64 keys for each shape, in us, fitted per head_dim on calls of 129 to 516 rows, plus the merge.  On 252
 // calls per head_dim (65 to 1284 rows on 4, 8, 12, 32 and 40 kv heads over 256 to 16384 tokens) its mean error is 7 % (head_dim 64:
 // 11 %); the plan's shape is 1.4 % (1.7 %) slower than the best of the five on average and at most 32 % (36 %), that of fewest padded
-// rows 8.9 % (8.8 %) and 43 % (54 %).  The shape of fewest padded rows stays unless another promises 4 % less.  Measured, us per call with the shape of fewest padded rows -> with this rule's, 8 kv heads: 196 rows
-// x 633 tokens 17.4 -> 12.7 (tiles of 256 rows -> 64), x 4096 20.4 -> 16.6, 176 x 2078 17.8 -> 14.7 (192 -> 64), 516 x 1024
+// rows 8.9 % (8.8 %) and 43 % (54 %).  (Fitted and counted with the kernels before the last split's share and opposite phases in
+// short streams, which made the first two shapes up to 10 % faster.)  The shape of fewest padded rows stays unless another promises 4 %
+// less.  Measured then, us per call with the shape of fewest padded rows -> with this rule's, 8 kv heads: 196 rows x 633 tokens 17.4 -> 12.7 (tiles of 256 rows -> 64), x 4096 20.4 -> 16.6, 176 x 2078 17.8 -> 14.7 (192 -> 64), 516 x 1024
 // 17.8 -> 16.7 (192 -> 64), 392 x 4096 21.7 -> 20.9 (256 -> 128); 32 kv heads: 321 rows x 4096 48.1 -> 43.2 (128 -> 192).  At
 // 16384 tokens tiles of 256 lead again (392 rows: 39.0, of 128 44.3).
 static void short_run_shape(const ygg_shape& s, int R, int64_t tiles, AttnPlan& p) {
@@ -216,7 +217,9 @@ AttnPlan plan_attention(const ygg_shape& s) {
         // chain, and per tile of tree keys the masking, which with opposite phases lengthens both wavefronts' phases.  Such a workgroup
         // with an equal share ended 5.9 us after the others (1284 rows x 2048 tokens), 7.5 at 8192.  us per call with equal shares ->
         // these: 1284 rows x 4096 tokens on 8 kv heads 42.1 -> 36.5, x 8192 59.8 -> 55.0, x 32768 178 -> 174, 516 rows x 4096 in
-        // tiles of 256 26.0 -> 24.2, 392 x 16384 41.1 -> 40.6; without opposite phases 1284 x 2048 27.6 -> 27.1.
+        // tiles of 256 26.0 -> 24.2, 392 x 16384 41.1 -> 40.6; without opposite phases 1284 x 2048 27.6 -> 27.1.  8-bit K/V: 1284 x 4096
+        // 49.6 -> 48.3, 516 x 4096 23.7 either way; where the shares stay the same the arithmetic for them shows, 140 rows x 522 on 4
+        // 10.85 -> 10.95.
         const int32_t tree_tiles = (s.n_nodes + kKeyTile - 1) / kKeyTile;
         p.tree_cost = p.phases ? 1 + 6 * tree_tiles / 5 : 1 + tree_tiles / 4;
     } else {

@@ -56,8 +56,8 @@ struct AttnPlan {
     int32_t kshares;        // MFMA kernel: 1, or 2 = pairs of wavefronts split every key tile
     int32_t row_tiles;      // MFMA kernel: workgroups along the N*G query rows of one kv head
     int32_t slots;          // MFMA kernel, batches: equal runs of key tiles per (kv head, row tile); 0 = one sequence per workgroup
-    int32_t phases;         // MFMA kernel, 8 wavefronts: the two of a SIMD in opposite phases
-    int32_t tree_cost;      // MFMA kernel: key tiles by which the last split's share is smaller
+    int32_t phases;         // MFMA kernel, 8 wavefronts, or 6 without runs at head_dim 128: the two of a SIMD in opposite phases
+    int32_t tree_cost;      // MFMA kernel, wavefronts on rows of their own: what the tree costs a sequence's last split, in key tiles
     size_t part_o_bytes, part_rec_bytes, seq_splits_bytes;
 };
 

@@ -19,9 +19,10 @@ def plan():
     ygg.set_attention_plan()
 
 
-# query heads on one kv head and a tree of 41 nodes: 246 rows, or 41 with one query head.  The 256-row shape runs its wavefronts in
-# opposite phases where the longest prefix leaves a workgroup many tiles, whatever the lengths then are.
+# query heads on one kv head and a tree of 41 nodes: 246 rows, or 41 with one query head.  The 256-row shape, and at head_dim 128 that of
+# 192 rows, run their wavefronts in opposite phases where the longest prefix leaves a workgroup many tiles, whatever the lengths then are.
 @pytest.mark.parametrize("waves,kshares,Hq,longest", [(8, 1, 6, 0), (8, 1, 4, 0), (8, 1, 6, 8300), (8, 1, 4, 8300), (6, 1, 6, 0),
+                                                      (6, 1, 6, 8300), (6, 1, 4, 8300),
                                                       (4, 1, 6, 0), (8, 2, 6, 0), (4, 2, 2, 0), (2, 2, 1, 0)])
 @pytest.mark.parametrize("Dh", [128, 64])
 @pytest.mark.parametrize("nsplit", [1, 2])
@@ -30,8 +31,12 @@ def test_every_workgroup_shape_from_one_tile_upwards(plan, waves, kshares, Hq, l
     for keys in (41, 63, 64, 65, 100, 129, 192, 200, 257, 320, 330, 385, 450, 513, 640, 705, 1000):
         L = keys - 41
         cfg, host, parent = _inputs(_cfg(1, Hq, 1, 5, 8, Dh=Dh, seed=31), [L], max(L, longest, 1), tree_gain=2.0)
-        got = ygg.attention_plan(shape_of(cfg, max_seq_len=max(L, longest, 1)))
+        shape = shape_of(cfg, max_seq_len=max(L, longest, 1))
+        got = ygg.attention_plan(shape)
         assert (got["waves"], got["key_shares"]) == (waves, kshares)
+        tiles = (keys + 63) // 64 // got["key_splits"]
+        phases = longest > 0 or tiles >= (10 if Dh == 128 else 24)
+        assert ygg.attention_launch(shape)["opposite_phases"] == (phases and kshares == 1 and (waves == 8 or (waves == 6 and Dh == 128)))
         _check(cfg, host, parent, max(L, longest, 1))
 
 
@@ -52,7 +57,7 @@ def test_the_widest_tree_under_a_forced_shape(plan, waves):
     (16, 32, 4, 6, 8, [0] * 9 + [5000] + [3] * 6, 128, 32),         # many sequences of one tile: runs without a tile of their own
     (2, 32, 4, 6, 8, [9000, 0], 128, 32),                           # exactly eight tiles, an empty prefix at the end
     (6, 48, 8, 5, 8, [7500, 0, 64, 1500, 15, 333], 128, 32),        # runs of up to 22 tiles: opposite phases
-    (6, 48, 8, 5, 8, [23000, 0, 64, 1500, 15, 333], 64, 32),        # up to 67, as head_dim 64 asks for
+    (6, 48, 8, 5, 8, [23000, 0, 64, 1500, 15, 333], 64, 32),        # up to 67: opposite phases at head_dim 64
     (2, 28, 4, 5, 8, [3000, 0], 128, 0),
 ])
 def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh, runs):
@@ -60,6 +65,7 @@ def test_batches_in_runs(B, Hq, Hkv, D, W, lens, Dh, runs):
     got = ygg.attention_plan(shape_of(cfg, max_seq_len=max(lens)))
     equal_splits = 256 // (B * Hkv * got["row_tiles"])
     assert got["key_splits"] == (runs or equal_splits) and equal_splits != runs
+    assert ygg.attention_launch(shape_of(cfg, max_seq_len=max(lens)))["opposite_phases"] == (B == 6 or (B, Dh) == (16, 128))
     _check(cfg, host, parent, max(lens))
 
 
@@ -187,14 +193,20 @@ def test_partial_rows_of_pairs_that_cancel(plan, waves, Dh):
 
 
 # The last split's share is smaller by what the tree's keys cost it, down to one tile, and the others' differ by one: trees of one, two
-# and four tiles over prefixes that leave splits empty, leave them one tile, and give them enough for opposite phases (the longest).
+# and four tiles over prefixes that leave splits empty, leave them one tile, and (the longest, where the splits are few) give them
+# enough for opposite phases.
 @pytest.mark.parametrize("waves,Dh", [(8, 128), (6, 128), (4, 128), (8, 64), (6, 64)])
 @pytest.mark.parametrize("D,W,nsplit", [(5, 8, 3), (6, 16, 5), (10, 20, 5), (10, 20, 16)])
 def test_shares_of_the_last_split(plan, waves, Dh, D, W, nsplit):
     plan(waves=waves, rblocks=1, kshares=1, nsplit=nsplit)
-    for L in (0, 63, 200, 64 * nsplit - 1 - D * W % 64, 640, 1111, 64 * 11 * nsplit if nsplit < 10 else 700):
+    longest = 64 * (11 if Dh == 128 else 25) * nsplit if nsplit < 10 else 700
+    for L in (0, 63, 200, 64 * nsplit - 1 - D * W % 64, 640, 1111, longest):
         cfg, host, parent = _inputs(_cfg(1, 4, 1, D, W, Dh=Dh, seed=47), [L], max(L, 64 * nsplit), tree_gain=2.0)
         _check(cfg, host, parent, max(L, 64 * nsplit))
+    got = ygg.attention_launch(shape_of(cfg, max_seq_len=longest))
+    assert got["opposite_phases"] == (nsplit < 10 and (waves == 8 or (waves == 6 and Dh == 128)))
+    tiles = (1 + D * W + 63) // 64
+    assert got["tree_cost"] == (1 + 6 * tiles // 5 if got["opposite_phases"] else 1 + tiles // 4)
 
 
 # Pairs of head_dim 64: the last split gives a tile away where the tree's keys then still lie in it alone.  Prefixes around that, with one

@@ -78,7 +78,7 @@ def test_expand_is_deterministic():
     assert all(np.array_equal(x.view(np.int32), y.view(np.int32)) for x, y in zip(a, b))
 
 
-def _accept_both(cfg, parent, token, layers, lens, logits=None, tstar=None, depth=None, codes=False):
+def _accept_both(cfg, parent, token, layers, lens, logits=None, tstar=None, depth=None, codes=False, scratch=None):
     B, N = parent.shape
     D = cfg.depth if depth is None else depth
     max_len = int(lens.max())
@@ -100,7 +100,7 @@ def _accept_both(cfg, parent, token, layers, lens, logits=None, tstar=None, dept
     ygg.accept_and_compact(shape, layers, to_dev(parent), to_dev(token), g[0], g[1], g[2], g[3], g[4], alen, apath, bonus,
                            target_logits=None if logits is None else to_dev(logits),
                            target_tokens=None if tstar is None else to_dev(tstar),
-                           workspace=workspace(shape, ygg.OP_ACCEPT))
+                           workspace=workspace(shape, ygg.OP_ACCEPT) if scratch is None else scratch)
     torch.cuda.synchronize()
     assert np.array_equal(alen.cpu().numpy(), ref["accept_len"])
     assert np.array_equal(apath.cpu().numpy(), ref["accept_path"])
@@ -121,6 +121,17 @@ def test_accept_shapes(B, D, W, V, dtype, layers):
     lens = wl.rng(cfg.seed, 50).integers(0, 40, size=B)
     ref = _accept_both(cfg, parent, token, layers, lens, logits=logits)
     assert ref["accept_len"].max() > 1
+
+
+def test_accept_in_the_scratch_of_a_larger_batch():
+    """49 nodes of 32000 logits: eight chunks to a row for batches of 1 to 5, fewer chunks and more rows up to 13."""
+    make = lambda B: _cfg(B, 6, 8, 32000)
+    scratch = workspace(shape_of(make(13), max_seq_len=40, kv_capacity=64), ygg.OP_ACCEPT)
+    for B in (5, 9, 12, 13):
+        cfg = make(B)
+        parent = wl.trees(cfg); token = wl.tokens(cfg, parent)
+        logits = wl.acceptance_inputs(wl.scaled(cfg, agree=(0.8,)), parent, token)
+        _accept_both(cfg, parent, token, 1, wl.rng(cfg.seed, 50).integers(0, 40, size=B), logits=logits, scratch=scratch)
 
 
 def test_accept_compacts_8bit_caches():

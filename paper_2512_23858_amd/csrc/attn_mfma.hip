@@ -108,20 +108,26 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // requested at once, it leaves room for two workgroups of four wavefronts of head_dim 64 to a compute unit instead of three: 48
     // sequences of 300 tokens, 49 rows on 12 kv heads 16.9 -> 18.8 us per call; and where one is enough it gains nothing: 22 of 192 with
     // 5 rows 8.3 -> 8.7, one of 2048 with 65 rows 10.2 either way, of 1024 with 49 rows on 32 kv heads of 128 12.7 -> 12.8.
+    // QSHARED: the two wavefronts of the 32-row shape fetch the rows that there are once between them, instead of 32 each: on 32 kv heads 2
+    // rows x 62 tokens 8.80 -> 8.52 us per call, 5 x 267 9.10 -> 8.85, 16 x 46 9.20 -> 9.00, 25 x 488 10.33 -> 10.27; on 8, 12 rows x 113 8.61
+    // -> 8.35.  At head_dim 64, where 32 rows are half as many bytes, 8.20 either way (32 x 214 on 8).  Skipped rows alone, without sharing:
+    // half of the gain, and wider pairs lose 1 %.
     constexpr int QW = 32 * RB * ROWB;           // a wavefront's rows
     constexpr int QB = 2 * (NBUF - 2);           // wavefronts whose rows fit the spare K (or V) buffers
     constexpr int QX = NW > 2 * QB ? (NW - 2 * QB) * QW : 0;
+    constexpr bool QSHARED = !KV8 && KS == 2 && NW == 2 && DH == 128;
     static_assert(RB == 1 && QW * 2 == TILEB, "two wavefronts' rows to a tile buffer");
     uint32_t* anc_s = reinterpret_cast<uint32_t*>(smem + 2 * NBUF * TILEB + QX);  // [local node][aw], then parent[N]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
     const int n = lane & 31, g2 = lane >> 5;
-    unsigned char* q_s = (wave < QB ? k_s + 2 * TILEB + wave * QW
-                                    : wave < 2 * QB ? v_s + 2 * TILEB + (wave - QB) * QW : smem + 2 * NBUF * TILEB + (wave - 2 * QB) * QW);
     const bool is_loader = KV8 && wave >= NW;      // wave-uniform
     const int wrow = KS == 1 ? wave : wave % NRW;  // position along the rows (computing wavefronts)
     const int kh = KS == 1 ? 0 : wave / NRW;       // which block of every tile (KS = 2)
+    const int wq = QSHARED ? wrow : wave;
+    unsigned char* q_s = (wq < QB ? k_s + 2 * TILEB + wq * QW
+                                  : wq < 2 * QB ? v_s + 2 * TILEB + (wq - QB) * QW : smem + 2 * NBUF * TILEB + (wq - 2 * QB) * QW);
 
     // All arguments at once: left to itself the compiler fetches each where it is first needed, one scalar-cache miss after
     // the other in front of the first tile fill (32 layers of a 516-row verify pass: 923 -> 887 us).  The paired shapes'
@@ -251,6 +257,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // are never stored.  As plain register loads they would hold up the first block until every tile in flight has landed:
     // the compiler's wait for them does not know of the tile fills behind them and awaits those as well.
     bf16x8 qreg[RB][NS];
+    const int q_last = QSHARED ? min(R - 1 - row_base, 31) : 31;   // the last row of the block that is fetched; those behind repeat it
     if constexpr (KV8) {   // (the computing wavefronts have nothing else in flight: plain loads)
         if (!is_loader) {
 #pragma unroll
@@ -264,7 +271,9 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     } else {
         const uint32_t q_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)q_s;
 #pragma unroll
-        for (int it = 0; it < 32 * RB / RPI; ++it) {
+        for (int i0 = 0; i0 < 32 * RB / RPI; i0 += QSHARED ? KS : 1) {
+            const int it = i0 + (QSHARED ? kh : 0);   // (the two take turns)
+            if (RPI * it > q_last) break;             // wave-uniform
             const int lrow = RPI * it + lane / SLOTS;
             const int rc = min(row_base + wrow * RB * 32 + lrow, R - 1);
             const int i = (int)divide(rc, a.G, a.mul_g);
@@ -709,8 +718,10 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     };
     if constexpr (!KV8) {
         wait_tiles_out(ntiles > 1);
-        const unsigned char* qp = q_s + n * ROWB + 16 * (g2 ^ (n & 1));
-        const int pair_xor = ((n & (SLOTS - 1)) >> 1) << 5;
+        if constexpr (QSHARED) lds_barrier();   // the other wavefront's rows of Q, and the parents
+        const int nq = min(n, q_last);
+        const unsigned char* qp = q_s + nq * ROWB + 16 * (g2 ^ (nq & 1));
+        const int pair_xor = ((nq & (SLOTS - 1)) >> 1) << 5;
 #pragma unroll
         for (int s = 0; s < NS; ++s) qreg[0][s] = *reinterpret_cast<const bf16x8*>(qp + ((32 * s) ^ pair_xor));
     }
@@ -718,7 +729,7 @@ __global__ __launch_bounds__((NW + (KV8 ? 4 : 0)) * 64, (RB == 1 && !KV8 ? 2 : 1
     // 10258 tokens 14.3 -> 14.9 us per call.)
     if (has_tree_keys) {
         if constexpr (KV8) dma_wait_keep<0>();
-        lds_barrier();
+        if constexpr (!QSHARED) lds_barrier();
         build_masks();
     }
     if constexpr (!KV8) {

@@ -40,6 +40,19 @@ def test_every_workgroup_shape_from_one_tile_upwards(plan, waves, kshares, Hq, l
         _check(cfg, host, parent, max(L, longest, 1))
 
 
+# two wavefronts fetch the rows of up to 32 in turns of four: 2, 3, 4, 5, 8, 9, 12, 13, 28, 31 and 32 rows to a kv head
+@pytest.mark.parametrize("group,D,W", [(1, 1, 1), (1, 1, 2), (2, 1, 1), (1, 1, 4), (4, 1, 1), (3, 1, 2), (4, 1, 2), (1, 3, 4), (4, 2, 3), (1, 5, 6),
+                                       (2, 3, 5)])
+@pytest.mark.parametrize("nsplit", [1, 3])
+def test_rows_of_two_wavefronts(plan, group, D, W, nsplit):
+    plan(nsplit=nsplit)
+    for L in (0, 50, 257):
+        cfg, host, parent = _inputs(_cfg(2, 2 * group, 2, D, W, seed=33), [L, L // 2], max(L, 1), tree_gain=2.0)
+        got = ygg.attention_plan(shape_of(cfg, max_seq_len=max(L, 1)))
+        assert (got["waves"], got["key_shares"]) == (2, 2)
+        _check(cfg, host, parent, max(L, 1))
+
+
 @pytest.mark.parametrize("waves", [8, 6, 4])
 def test_the_widest_tree_under_a_forced_shape(plan, waves):
     plan(waves=waves, rblocks=1, kshares=1)

@@ -38,7 +38,7 @@ DEFAULT_LAYERS = {1: 1, 2: 32, 3: 32, 4: 32, 5: 4}
 # (a benchmark run cannot collect counters itself) by the commands in TRAFFIC_SOURCE, for the kernel as it stands in
 # the commit that file names.  Reported only together with that source.
 TRAFFIC_SOURCE = "profiles/attn_mfma_hbm_traffic.md"
-MEASURED_TRAFFIC_BYTES = {2: 23444841, 3: 38190642, 4: 164277645, 5: 381202662}
+MEASURED_TRAFFIC_BYTES = {2: 23492403, 3: 38072013, 4: 163841843, 5: 387984282}
 
 
 def attention_work(cfg, lens, kv_bytes=None):
